@@ -80,6 +80,15 @@ bool f32mfma(int D, int p, int causal, int dt, int N)
     return fm::f32mfma_applies(D, p, dt == FASTMAX_BF16);
 }
 
+// Whether the moment path's launch grids for a forward fit the dispatch
+// limits: a call beyond them is refused whichever kernels would serve it.
+bool fwd_grids_fit(int BH, int N, int D, int p, int causal, int dt)
+{
+    if (mfma_causal(D, p, causal, dt)) return fm::mfma_causal_fwd_grids_fit(BH, N);
+    if (mfma_noncausal(N, D, p, causal, dt)) return fm::mfma_nc_grids_fit(BH, N);
+    return fm::f32mfma_fwd_grids_fit(BH, N, D, p);
+}
+
 size_t fwd_ws(int B, int H, int N, int D, int p, int causal, int dt)
 {
     if (mfma_causal(D, p, causal, dt)) return fm::mfma_causal_fwd_workspace(B * H, N);
@@ -146,7 +155,12 @@ int fwd_run(const void *q, const void *k, const void *v, void *out, float *g, in
             int D, int p, int causal, float qk_scale, int dt, void *workspace, hipStream_t stream)
 {
     hipError_t e;
-    if (mfma_causal(D, p, causal, dt))
+    const int bf = dt == FASTMAX_BF16;
+    // Short sequences: explicit pairs (the plan's tables hold both sides).
+    const int shape = pairs_fwd_plan(B * H, N, D, p, causal, bf, fwd_ws(B, H, N, D, p, causal, dt));
+    if (shape >= 0 && fwd_grids_fit(B * H, N, D, p, causal, dt))
+        e = pairs_fwd(q, k, v, out, g, B * H, N, D, causal, bf, qk_scale, shape, workspace, stream);
+    else if (mfma_causal(D, p, causal, dt))
         e = mfma_causal_fwd(q, k, v, out, g, B * H, N, qk_scale, workspace, stream);
     else if (mfma_noncausal(N, D, p, causal, dt))
         e = mfma_nc_fwd(q, k, v, out, g, B * H, N, qk_scale, workspace, stream);

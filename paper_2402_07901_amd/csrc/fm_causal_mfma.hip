@@ -107,6 +107,16 @@ size_t mfma_causal_fwd_workspace(int BH, int N)
 
 size_t mfma_causal_smem_bytes() { return sizeof(mfma_causal::Smem); }
 
+bool mfma_causal_fwd_grids_fit(int BH, int N)
+{
+    using namespace mfma_causal;
+    const size_t rows = (size_t)BH * N;
+    const int items = BH * NSL;
+    const ScanSplit plan = causal_scan_split(items, (N + C - 1) / C, true);
+    return grid_fits((long long)((rows + 31) / 32), 256) &&
+           grid_fits((long long)items * (1 + plan.split), NTH);
+}
+
 hipError_t mfma_causal_fwd(const void *q, const void *k, const void *v, void *out, float *g,
                            int BH, int N, float qs, void *ws, hipStream_t st)
 {
@@ -116,9 +126,7 @@ hipError_t mfma_causal_fwd(const void *q, const void *k, const void *v, void *ou
     const size_t rows = (size_t)BH * N;
     const int items = BH * NSL, nch = (N + C - 1) / C;
     const ScanSplit plan = causal_scan_split(items, nch, true);
-    if (!grid_fits((long long)((rows + 31) / 32), 256) ||
-        !grid_fits((long long)items * (1 + plan.split), NTH))
-        return hipErrorInvalidConfiguration;
+    if (!mfma_causal_fwd_grids_fit(BH, N)) return hipErrorInvalidConfiguration;
     unsigned char *p = (unsigned char *)ws;
     _Float16 *qh = (_Float16 *)p;
     p += a256(rows * D * 2);

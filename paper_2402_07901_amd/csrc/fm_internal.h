@@ -25,6 +25,7 @@ inline bool grid_fits(long long blocks, long long threads)
 // the segmented non-causal MFMA path's grids fit.
 bool f32mfma_fwd_grids_fit(int BH, int N, int D, int p);
 bool mfma_nc_grids_fit(int BH, int N);
+bool mfma_causal_fwd_grids_fit(int BH, int N);
 
 // FASTMAX_OK if stream is 0 or belongs to the current device, FASTMAX_EINVAL
 // if it belongs to another one, FASTMAX_EHIP if HIP cannot tell.
@@ -82,6 +83,16 @@ int set_scan_segment_mode(int mode);
 // Summaries and flags of a split scan of `items` (head, slice) items of nch
 // chunks (reserved whenever nch >= 2, whatever the mode).
 size_t causal_scan_seg_workspace(int items, int nch);
+
+// Pair kernels (p = 2, every D and dtype): the forward over explicit (query,
+// key) pairs, faster than the moments while sequences are short.
+// pairs_fwd_plan picks a workgroup shape (>= 0) or the moments (-1); ws_bytes
+// is the size of the workspace the call will bring.  A shape's ws needs at
+// most 128 bytes per row, within what the moment path asks for.
+int pairs_fwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t ws_bytes);
+hipError_t pairs_fwd(const void *q, const void *k, const void *v, void *out, float *g, int BH,
+                     int N, int D, int causal, int is_bf16, float qs, int shape, void *ws,
+                     hipStream_t st);
 
 // Float32 MFMA kernels (v_mfma_f32_16x16x4_f32): p in {1, 2}, D in {16, 32,
 // 64, 128}, float32 or bf16 I/O, causal and non-causal (dispatch sends bf16

@@ -1,0 +1,198 @@
+// Shared pieces of the pair kernels (fm_pairs_fwd.hip, fm_pairs_bwd.hip):
+// Fastmax evaluated over explicit (query, key) pairs, 32 x 32 at a time in
+// registers, for sequences short enough that a pair costs less than its share
+// of the moments (Sec. 2.4's factorisation pays once N exceeds about D^2; the
+// rules at each launcher state the measured lines).  The weights
+// f_p(q^.k^) never leave the registers.
+//
+// v_mfma_f32_32x32x16_f16 lane layout (lane = 32h + r): A holds row r, K
+// indices 8h..8h+7; B holds column r, the same K indices; accumulator element
+// i holds column r, row 8(i/4) + 4h + i%4.  Scores are formed as
+// S^T = K^ Q^T (rows keys, columns queries), so the weights of a 32-key tile
+// are, element for element, the B operands of two 16-key contraction steps
+// once the keys of a step are numbered K index 8h + r <-> key
+// 8(r/4) + 4h + r%4: nothing moves between lanes.  The A operand of that
+// contraction (16 keys of a value column) is read from the row-major tile by
+// ds_read_b64_tr_b16, which hands lane i of 16 the column i of a 4 x 16 block.
+//
+// float32-grade operands.  A float32 x is held as two fp16 numbers hi + lo
+// (22 bits and more); a product takes three MFMAs (hi hi, lo hi, hi lo).  The
+// values carry a power-of-two scale per 8-column group.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "fm_common.h"
+#include "fm_f32_mfma.h"
+#include "fm_mfma.h"
+
+namespace fm {
+namespace pr {
+
+using m32::RawRow;
+using mx::cat;
+using mx::h2;
+using mx::h4;
+using mx::h8;
+using mx::ld8;
+using mx::static_for;
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef short s4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f16v mma(h8 a, h8 b, f16v c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+// Two floats to two halves, round to nearest even.
+__device__ __forceinline__ h2 cvt2(float a, float b)
+{
+    return __builtin_convertvector((f2{a, b}), h2);
+}
+
+// x - (float)h
+__device__ __forceinline__ float rest(float x, _Float16 h) { return fmaf((float)h, -1.0f, x); }
+
+// Row strides (halves) of the staged tiles.  Rows read 16 bytes per lane,
+// one row per lane (scores): D + 8, which puts 16 consecutive rows on 16
+// distinct groups of four banks.  Rows read through the transposing load
+// (values): a stride of 16 banks modulo 32, so that the four rows of a block
+// fall on distinct banks.
+template <int D> constexpr int row_stride() { return D + 8; }
+template <int D> constexpr int tr_stride() { return D <= 32 ? 32 : D + 32; }
+
+// The A operand of a 16-key contraction step: keys key0 + {0..15} (numbered
+// as above) of columns col0..col0+31 of a row-major tile of row stride S.
+template <int S>
+__device__ __forceinline__ h8 ld_tr(const _Float16 *tile, int key0, int col0)
+{
+    typedef s4v __attribute__((address_space(3))) *lp;
+    const int lane = threadIdx.x & 63, h = lane >> 5, g = (lane >> 4) & 1, j = (lane >> 2) & 3, c = lane & 3;
+    const _Float16 *p = tile + (key0 + 4 * h + j) * S + col0 + 16 * g + 4 * c;
+    const s4v a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)p);
+    const s4v b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + 8 * S));
+    return cat(__builtin_bit_cast(h4, a), __builtin_bit_cast(h4, b));
+}
+
+// Sum over an aligned group of L = 2, 4, 8 or 16 lanes, in every lane, with
+// DPP moves.
+template <int L>
+__device__ __forceinline__ float group_sum(float x)
+{
+    static_assert(L == 2 || L == 4 || L == 8 || L == 16, "lanes per token");
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true));
+    if constexpr (L >= 4)
+        x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, true));
+    if constexpr (L >= 8)
+        x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xF, 0xF, true));
+    if constexpr (L >= 16)
+        x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x140, 0xF, 0xF, true));
+    return x;
+}
+
+// Sum of a lane's and its partner's (lane ^ 32) values, in both.
+__device__ __forceinline__ float half_sum(float x)
+{
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// Eight floats as fp16 hi and (SPL) lo parts.
+template <bool SPL>
+__device__ __forceinline__ void split8(const float *x, h8 &hi, h8 &lo)
+{
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        const h2 a = cvt2(x[i], x[i + 1]);
+        hi[i] = a[0];
+        hi[i + 1] = a[1];
+        if constexpr (SPL) {
+            const h2 b = cvt2(rest(x[i], a[0]), rest(x[i + 1], a[1]));
+            lo[i] = b[0];
+            lo[i + 1] = b[1];
+        }
+    }
+}
+
+// 1 / sqrt(v): the hardware's approximation (1 ulp) with one Newton step, so
+// that a row's scale is no larger an error than its elements' rounding.
+__device__ __forceinline__ float rsqrt1(float v)
+{
+    const float r = __builtin_amdgcn_rsqf(v);
+    return fmaf(0.5f * r, fmaf(-v * r, r, 1.0f), r);
+}
+
+// Standardises the 8 channels a lane holds of a token (Sec. 2.2, Eqs. 6-7:
+// population std, no epsilon; the token's D/8 lanes are an aligned group) in
+// place.  Every lane of the wave takes part.
+template <int D>
+__device__ __forceinline__ void standardise_group(float (&x)[8], bool valid)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s += x[i];
+    const float mu = group_sum<D / 8>(s) * (1.0f / D);
+    float v = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        x[i] -= mu;
+        v = fmaf(x[i], x[i], v);
+    }
+    const float r = valid ? rsqrt1(group_sum<D / 8>(v) * (1.0f / D)) : 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] *= r;
+}
+
+// The B operands of a row-major matrix whose rows are this wave's 32 columns
+// (queries or keys): lane (r, h) loads channels 16 ks + 8h .. + 7 of row r.
+template <typename T, int D>
+__device__ __forceinline__ void load_cols(const T *rows, int n, int N, float (&x)[D / 2])
+{
+    const int h = (threadIdx.x >> 5) & 1;
+    const bool valid = n < N;
+    RawRow<T, 8> raw[D / 16];
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks)
+        raw[ks].load(rows + (size_t)(valid ? n : 0) * D + 16 * ks + 8 * h, valid);
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[8 * ks + i] = raw[ks].get(i);
+}
+
+// Standardises such rows (the two half lanes of a column hold its channels)
+// and scales them.
+template <int D>
+__device__ __forceinline__ void standardise_cols(float (&x)[D / 2], bool valid, float scale)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < D / 2; ++i) s += x[i];
+    const float mu = half_sum(s) * (1.0f / D);
+    float v = 0.f;
+#pragma unroll
+    for (int i = 0; i < D / 2; ++i) {
+        x[i] -= mu;
+        v = fmaf(x[i], x[i], v);
+    }
+    const float r = valid ? rsqrt1(half_sum(v) * (1.0f / D)) * scale : 0.0f;
+#pragma unroll
+    for (int i = 0; i < D / 2; ++i) x[i] *= r;
+}
+
+// Power of two 2^(top - e), 2^e the least power of two above m (m finite,
+// >= 0): values up to m scaled by it stay below 2^top.  The result and its
+// inverse are normal numbers.
+__device__ __forceinline__ float pow2_scale(float m, int top)
+{
+    if (m == 0.0f) return 1.0f;
+    int e = (int)(__float_as_uint(m) >> 23) - 126;   // m < 2^e
+    int x = top - e + 127;
+    x = x < 1 ? 1 : (x > 253 ? 253 : x);
+    return __uint_as_float((uint32_t)x << 23);
+}
+
+}  // namespace pr
+}  // namespace fm

@@ -1,0 +1,582 @@
+// Pair forward (see fm_pairs.h): O_i = sum_n w_in v_n / sum_n w_in with the
+// weights formed 32 keys x 32 queries at a time, one launch, no workspace.
+//
+// A workgroup of NWQ x NWK waves takes NWQ 32-query columns tiles (NQ per
+// wave); NWK waves share a query tile and split the keys.  Per step it stages
+// BK keys (standardised on the way, Sec. 2.2) and their values in LDS, the
+// next step's rows already on their way into registers.
+//
+// Value scale.  fp16 values need a power-of-two scale per 8-column group.  It
+// is taken from the first staged tile with 8 binary digits of headroom; each
+// thread keeps the largest magnitude that it stages, and only if that
+// overflowed the headroom (a later token more than 2^8 times the first tile's
+// largest) the workgroup finds the true maximum and runs its keys again.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
+
+#include "fm_internal.h"
+#include "fm_pairs.h"
+
+namespace fm {
+namespace pr {
+
+template <typename T_, int D_, int P_, bool CAUSAL_, bool SPL_, bool KP_, int NQ_, int NWQ_, int NWK_, int BK_>
+struct FwdCfg {
+    typedef T_ T;
+    static constexpr int D = D_, P = P_, NQ = NQ_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
+    static constexpr bool CAUSAL = CAUSAL_, SPL = SPL_, KP = KP_;
+    static constexpr bool VSPL = SPL && sizeof(T) == 4;   // bf16 values need no lo part
+    // the products with a lo part have a sum of their own where registers
+    // allow: the main sum then rounds once per contraction step, not three times
+    static constexpr bool LOACC = VSPL && D <= 64;
+    static constexpr int NTH = 64 * NWQ * NWK;
+    static constexpr int QB = 32 * NQ * NWQ;              // queries per workgroup
+    static constexpr int KS = D / 16;                     // contraction steps of a score
+    static constexpr int CT = D < 32 ? 1 : D / 32;        // 32-column value tiles
+    static constexpr int LPT = D / 8;                     // staging lanes per token
+    static constexpr int TPP = NTH / LPT;                 // tokens per staging pass
+    static constexpr int NP = (BK + TPP - 1) / TPP;       // passes
+    static constexpr int RS = row_stride<D>(), VS = tr_stride<D>();
+    static constexpr int KH = BK * RS, VH = BK * VS;      // halves per plane
+    static constexpr int TILE_BYTES = 2 * ((SPL ? 2 : 1) * KH + (VSPL ? 2 : 1) * VH);
+    // the waves' partial numerators meet in LDS when they split the keys
+    static constexpr int RED_BYTES = NWK > 1 ? 4 * NWQ * NWK * 32 * (32 * CT + 1) : 0;
+    // at D = 128 the queries' lo parts wait in LDS: the registers go to the
+    // prefetch
+    static constexpr bool QLDS = SPL && D >= 128;
+    static constexpr int LOOP_BYTES = TILE_BYTES + (QLDS ? 2 * QB * RS : 0);
+    static constexpr int SMEM = LOOP_BYTES > RED_BYTES ? LOOP_BYTES : RED_BYTES;
+    static_assert(BK % (32 * NWK) == 0 && D % 16 == 0 && (NWK == 1 || NQ == 1), "shape");
+};
+
+template <typename C>
+__global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
+    const typename C::T *__restrict__ q, const typename C::T *__restrict__ k,
+    const typename C::T *__restrict__ v, const _Float16 *__restrict__ khat, size_t klo_off,
+    typename C::T *__restrict__ out, float *__restrict__ g, int N, int BH, int nqb, int hgrp, float qs)
+{
+    typedef typename C::T T;
+    constexpr int D = C::D, NQ = C::NQ, KS = C::KS, CT = C::CT, LPT = C::LPT, RS = C::RS, VS = C::VS;
+    constexpr bool SPL = C::SPL, VSPL = C::VSPL;
+    __shared__ alignas(16) unsigned char smem[C::SMEM];
+    __shared__ unsigned int smax[LPT];
+    __shared__ float sscale[LPT];
+    _Float16 *const khi = (_Float16 *)smem, *const klo = khi + C::KH;
+    _Float16 *const vhi = khi + (SPL ? 2 : 1) * C::KH, *const vlo = vhi + C::VH;
+    _Float16 *const qlo = (_Float16 *)(smem + C::TILE_BYTES);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r32 = lane & 31, h = lane >> 5;
+    const int wq = wave / C::NWK, wk = wave % C::NWK;
+
+    // Block order: heads in groups of hgrp (a multiple of 8 where there are
+    // as many, so that a head's blocks share an XCD's L2), within a group the
+    // blocks with the most keys first.
+    int head, qb;
+    {
+        const int b = blockIdx.x, per = hgrp * nqb, grp = b / per, r = b - grp * per;
+        const int gs = min(hgrp, BH - grp * hgrp);
+        head = grp * hgrp + r % gs;
+        qb = nqb - 1 - r / gs;
+    }
+    const size_t hb = (size_t)head * N * D;
+    q += hb;
+    k += hb;
+    v += hb;
+    khat += hb;
+    out += hb;
+    const int q0 = qb * C::QB + 32 * NQ * wq;      // this wave's first query
+    const int kend = C::CAUSAL ? min(N, (qb + 1) * C::QB) : N;
+    const int nt = (kend + C::BK - 1) / C::BK;
+
+    // the wave's queries, standardised, as B operands
+    h8 qh[NQ][KS], ql[NQ][SPL && !C::QLDS ? KS : 1];
+    _Float16 *const qlw = qlo + (32 * NQ * wq + r32) * RS + 8 * h;
+#pragma unroll
+    for (int t = 0; t < NQ; ++t) {
+        float x[D / 2];
+        const int n = q0 + 32 * t + r32;
+        load_cols<T, D>(q, n, N, x);
+        standardise_cols<D>(x, n < N, qs);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            h8 lo;
+            split8<SPL>(x + 8 * ks, qh[t][ks], lo);
+            if constexpr (C::QLDS) {
+                if (wk == 0) *(h8 *)(qlw + 32 * t * RS + 16 * ks) = lo;
+            } else {
+                ql[t][SPL ? ks : 0] = lo;
+            }
+        }
+    }
+
+    // staging: this thread's 8 channels and first token
+    const int sc = tid % LPT, st0 = tid / LPT;
+    RawRow<T, 8> kr[C::KP ? 1 : C::NP], vr[C::NP];
+    RawRow<bf16_t, 8> kph[C::KP ? C::NP : 1], kpl[C::KP && SPL ? C::NP : 1];   // fp16 words
+    auto load_tile = [&](int t) {
+#pragma unroll
+        for (int p = 0; p < C::NP; ++p) {
+            const int row = st0 + C::TPP * p, n = t * C::BK + row;
+            const bool ok = row < C::BK && n < N;
+            if constexpr (C::KP) {
+                kph[p].load((const bf16_t *)khat + (size_t)(ok ? n : 0) * D + 8 * sc, ok);
+                if constexpr (SPL)
+                    kpl[p].load((const bf16_t *)khat + klo_off + (size_t)(ok ? n : 0) * D + 8 * sc, ok);
+            } else {
+                kr[p].load(k + (size_t)(ok ? n : 0) * D + 8 * sc, ok);
+            }
+            vr[p].load(v + (size_t)(ok ? n : 0) * D + 8 * sc, ok);
+        }
+    };
+    float vmax = 0.f;
+    auto raw_max = [&]() {
+#pragma unroll
+        for (int p = 0; p < C::NP; ++p)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) vmax = fmaxf(vmax, fabsf(vr[p].get(i)));
+    };
+    // per column group: the scale that puts the largest m below 2^top
+    auto set_scale = [&](float m, int top) {
+        if (tid < LPT) smax[tid] = 0u;
+        __syncthreads();
+        atomicMax(&smax[sc], __float_as_uint(m));
+        __syncthreads();
+        const float s = pow2_scale(__uint_as_float(smax[sc]), top);
+        if (tid < LPT) sscale[tid] = s;
+        return s;
+    };
+
+    load_tile(0);
+    raw_max();
+    float vscale = set_scale(vmax <= 3e38f ? vmax : 0.f, 7);
+
+    f16v acc[NQ][CT], acl[NQ][C::LOACC ? CT : 1];
+    float rs[NQ];
+    for (int attempt = 0;; ++attempt) {
+#pragma unroll
+        for (int t = 0; t < NQ; ++t) {
+            rs[t] = 0.f;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) acc[t][c] = f16v{};
+            if constexpr (C::LOACC)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) acl[t][c] = f16v{};
+        }
+        for (int t = 0; t < nt; ++t) {
+            __syncthreads();
+#pragma unroll
+            for (int p = 0; p < C::NP; ++p) {
+                const int row = st0 + C::TPP * p;
+                float y[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    y[i] = vr[p].get(i);
+                    vmax = fmaxf(vmax, fabsf(y[i]));
+                    y[i] *= vscale;
+                }
+                h8 hi, lo;
+                split8<VSPL>(y, hi, lo);
+                const bool ok = C::BK % C::TPP == 0 || row < C::BK;
+                if (ok) {
+                    *(h8 *)(vhi + row * VS + 8 * sc) = hi;
+                    if constexpr (VSPL) *(h8 *)(vlo + row * VS + 8 * sc) = lo;
+                }
+                if constexpr (C::KP) {
+                    if (ok) {
+                        *(uint4 *)(khi + row * RS + 8 * sc) = *(uint4 *)kph[p].w;
+                        if constexpr (SPL) *(uint4 *)(klo + row * RS + 8 * sc) = *(uint4 *)kpl[p].w;
+                    }
+                } else {
+                    float x[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) x[i] = kr[p].get(i);
+                    standardise_group<D>(x, t * C::BK + row < N);
+                    split8<SPL>(x, hi, lo);
+                    if (ok) {
+                        *(h8 *)(khi + row * RS + 8 * sc) = hi;
+                        if constexpr (SPL) *(h8 *)(klo + row * RS + 8 * sc) = lo;
+                    }
+                }
+            }
+            if (t + 1 < nt) load_tile(t + 1);
+            __syncthreads();
+#pragma unroll 1
+            for (int j = wk; j < C::BK / 32; j += C::NWK) {
+                const int kb = t * C::BK + 32 * j;
+                if (kb >= N || (C::CAUSAL && kb > q0 + 32 * NQ - 1)) break;
+                f16v s[NQ];
+#pragma unroll
+                for (int u = 0; u < NQ; ++u)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) s[u][i] = 1.0f;
+                const _Float16 *kp = khi + (32 * j + r32) * RS + 8 * h;
+                // the products with a lo part first, while the sum is small (at
+                // D = 128 side by side with the main ones: fewer live operands)
+                if constexpr (SPL && D < 128) {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        const h8 a = ld8(kp + 16 * ks), b = ld8(kp + C::KH + 16 * ks);
+#pragma unroll
+                        for (int u = 0; u < NQ; ++u) {
+                            s[u] = mma(a, ql[u][C::QLDS ? 0 : ks], s[u]);
+                            s[u] = mma(b, qh[u][ks], s[u]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const h8 a = ld8(kp + 16 * ks);
+                    if constexpr (SPL && D >= 128) {
+                        const h8 b = ld8(kp + C::KH + 16 * ks);
+#pragma unroll
+                        for (int u = 0; u < NQ; ++u) {
+                            s[u] = mma(a, ld8(qlw + 32 * u * RS + 16 * ks), s[u]);
+                            s[u] = mma(b, qh[u][ks], s[u]);
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < NQ; ++u) s[u] = mma(a, qh[u][ks], s[u]);
+                }
+                // weights: s holds 1 + s; p = 2 takes 2 f_2 = (1 + s)^2 + 1 (the
+                // factor 2 cancels in F / G and is taken out of G)
+                h8 wh[NQ][2], wl[NQ][SPL ? 2 : 1];
+#pragma unroll
+                for (int u = 0; u < NQ; ++u) {
+                    const int qb0 = q0 + 32 * u;
+                    float w[16];
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) w[i] = C::P == 2 ? fmaf(s[u][i], s[u][i], 1.0f) : s[u][i];
+                    if ((C::CAUSAL && kb + 31 > qb0) || kb + 32 > N) {
+                        const int last = C::CAUSAL ? qb0 + r32 : N - 1;
+#pragma unroll
+                        for (int i = 0; i < 16; ++i)
+                            if (kb + 8 * (i / 4) + 4 * h + i % 4 > last) w[i] = 0.f;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        split8<SPL>(w + 8 * e, wh[u][e], wl[u][SPL ? e : 0]);
+                    }
+                    if constexpr (SPL) {
+#pragma unroll
+                        for (int d = 8; d; d /= 2)
+#pragma unroll
+                            for (int i = 0; i < d; ++i) w[i] += w[i + d];
+                        rs[u] += w[0];
+                    } else {
+                        // the sum of the rounded weights, as the numerator takes them
+                        const h2 one = {(_Float16)1.0f, (_Float16)1.0f};
+#pragma unroll
+                        for (int i = 0; i < 16; i += 2)
+                            rs[u] = __builtin_amdgcn_fdot2(h2{wh[u][i / 8][i % 8], wh[u][i / 8][i % 8 + 1]},
+                                                           one, rs[u], false);
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) {
+                        const h8 a = ld_tr<VS>(vhi, 32 * j + 16 * e, 32 * c);
+#pragma unroll
+                        for (int u = 0; u < NQ; ++u) acc[u][c] = mma(a, wh[u][e], acc[u][c]);
+                        if constexpr (SPL) {
+#pragma unroll
+                            for (int u = 0; u < NQ; ++u) {
+                                f16v &z = C::LOACC ? acl[u][C::LOACC ? c : 0] : acc[u][c];
+                                z = mma(a, wl[u][SPL ? e : 0], z);
+                            }
+                        }
+                        if constexpr (VSPL) {
+                            const h8 b = ld_tr<VS>(vlo, 32 * j + 16 * e, 32 * c);
+#pragma unroll
+                            for (int u = 0; u < NQ; ++u) {
+                                f16v &z = C::LOACC ? acl[u][C::LOACC ? c : 0] : acc[u][c];
+                                z = mma(b, wh[u][e], z);
+                            }
+                        }
+                    }
+            }
+        }
+        if (attempt || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
+        // the largest finite magnitude of the column group over the keys read
+        float m = 0.f;
+        for (int n = st0; n < kend; n += C::TPP) {
+            RawRow<T, 8> x;
+            x.load(v + (size_t)n * D + 8 * sc, true);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float y = fabsf(x.get(i));
+                if (y <= 3.4028235e38f) m = fmaxf(m, y);
+            }
+        }
+        vscale = set_scale(m, 14);
+        load_tile(0);
+    }
+
+    if constexpr (C::LOACC)
+#pragma unroll
+        for (int t = 0; t < NQ; ++t)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) acc[t][c] += acl[t][c];
+
+    // O = F / G.  Where waves split the keys their partial sums meet in LDS
+    // first, [wave][column][query], and each wave finishes a share of the
+    // columns.
+    if constexpr (C::NWK == 1) {
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) {
+            const int n = q0 + 32 * u + r32;
+            const float G = half_sum(rs[u]);
+            if (n < N) {
+                if (g && h == 0) g[(size_t)head * N + n] = C::P == 2 ? 0.5f * G : G;
+                const float r = 1.0f / G;
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        const int d = 32 * c + 8 * b + 4 * h;
+                        if (D % 32 == 0 || d < D) {
+                            const float f = r / sscale[d / 8];
+                            T *o = out + (size_t)n * D + d;
+                            if constexpr (sizeof(T) == 2) {
+                                *(uint2 *)o = make_uint2(
+                                    mx::pack_bf16x2(acc[u][c][4 * b] * f, acc[u][c][4 * b + 1] * f),
+                                    mx::pack_bf16x2(acc[u][c][4 * b + 2] * f, acc[u][c][4 * b + 3] * f));
+                            } else {
+                                *(float4 *)o = make_float4(acc[u][c][4 * b] * f, acc[u][c][4 * b + 1] * f,
+                                                           acc[u][c][4 * b + 2] * f, acc[u][c][4 * b + 3] * f);
+                            }
+                        }
+                    }
+            }
+        }
+    } else {
+        constexpr int W = 32 * CT + 1;   // columns and the row sum, 32 floats each
+        float *red = (float *)smem;
+        __syncthreads();
+        float *mine = red + wave * 32 * W;
+        const float G0 = half_sum(rs[0]);
+        if (h == 0) mine[32 * 32 * CT + r32] = G0;
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                mine[32 * (32 * c + 8 * (i / 4) + 4 * h + i % 4) + r32] = acc[0][c][i];
+        __syncthreads();
+        const float *part = red + wq * C::NWK * 32 * W;
+        float G = 0.f;
+#pragma unroll
+        for (int w = 0; w < C::NWK; ++w) G += part[w * 32 * W + 32 * 32 * CT + r32];
+        const int n = q0 + r32;
+        if (n < N) {
+            if (g && h == 0 && wk == 0) g[(size_t)head * N + n] = C::P == 2 ? 0.5f * G : G;
+            const float r = 1.0f / G;
+            // columns of this wave and half wave, 4 at a time
+#pragma unroll
+            for (int d = 4 * (2 * wk + h); d < D; d += 8 * C::NWK) {
+                const float f = r / sscale[d / 8];
+                float x[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    x[i] = 0.f;
+#pragma unroll
+                    for (int w = 0; w < C::NWK; ++w) x[i] += part[w * 32 * W + 32 * (d + i) + r32];
+                    x[i] *= f;
+                }
+                T *o = out + (size_t)n * D + d;
+                if constexpr (sizeof(T) == 2)
+                    *(uint2 *)o = make_uint2(mx::pack_bf16x2(x[0], x[1]), mx::pack_bf16x2(x[2], x[3]));
+                else *(float4 *)o = make_float4(x[0], x[1], x[2], x[3]);
+            }
+        }
+    }
+}
+
+// k^ in fp16 (and its lo part, SPL) for the kernels that read each key from
+// many workgroups: one thread per 8 channels.
+template <typename T, int D, bool SPL>
+__global__ __launch_bounds__(256) void khat_kernel(const T *__restrict__ k, _Float16 *__restrict__ khat,
+                                                   size_t klo_off, long long rows)
+{
+    const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / (D / 8);
+    const int c = threadIdx.x % (D / 8);
+    const bool ok = row < rows;
+    RawRow<T, 8> raw;
+    raw.load(k + (size_t)(ok ? row : 0) * D + 8 * c, ok);
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = raw.get(i);
+    standardise_group<D>(x, ok);
+    h8 hi, lo;
+    split8<SPL>(x, hi, lo);
+    if (ok) {
+        *(h8 *)(khat + (size_t)row * D + 8 * c) = hi;
+        if constexpr (SPL) *(h8 *)(khat + klo_off + (size_t)row * D + 8 * c) = lo;
+    }
+}
+
+// The workgroup shapes (queries per wave / 32, query columns, key columns of
+// waves, keys per step; KP: k^ from khat_kernel) and what each measured on an
+// MI355X: t = t0 + |(a N, b pairs)|_2 us, a (ns per key) one workgroup's pace
+// down its keys, b (ps per pair) the chip's when full, fitted to calls of 1 to
+// 96 heads of 256 to 8192 tokens, causal (pairs = heads N (N + queries per
+// workgroup) / 2; without the mask b is 0.85 to 0.95 of it).  Waves that split
+// the keys shorten a, waves that share a staged tile lower b.
+struct Shape {
+    int qb;
+    float t0, a, b;
+};
+// fp16 operands: bf16, D = 64
+constexpr Shape SH64[] = {{32, 5.f, 7.6f, 1.13f}, {64, 4.f, 9.6f, .68f}, {128, 5.f, 13.f, .455f},
+                          {128, 4.f, 20.5f, .375f}, {256, 7.f, 17.f, .31f}, {512, 6.f, 31.f, .275f}};
+// float32-grade operands
+constexpr Shape SS16[] = {{32, 4.f, 4.6f, .70f}, {64, 4.f, 7.2f, .53f}, {256, 4.f, 18.6f, .32f}};
+constexpr Shape SS32[] = {{32, 4.f, 6.7f, 1.02f}, {64, 4.f, 9.f, .66f}, {256, 4.f, 21.5f, .40f}};
+constexpr Shape SS64[] = {{64, 6.f, 15.4f, 1.14f}, {128, 6.f, 21.2f, .82f}, {256, 6.f, 36.5f, .71f}};
+constexpr Shape SS128[] = {{64, 7.f, 25.f, 1.67f}, {128, 7.f, 36.f, 1.27f}, {256, 7.f, 57.f, 1.05f}};
+constexpr Shape SF128[] = {{32, 7.f, 36.f, 4.9f}, {128, 7.f, 42.5f, 1.7f}, {256, 7.f, 69.f, 1.43f}};
+
+// The moment kernels' forward, t = t0 + h heads + max(a N, b heads N)
+// (a and b in ns per token).
+struct Moments {
+    float t0, h, a, b;
+};
+Moments moments_fwd(int N, int D, int causal, int is_bf16)
+{
+    if (is_bf16 && D == 64 && causal) return {12.f, 0.f, 50.f, .95f};
+    if (is_bf16 && D == 64 && N >= 128) return {25.f, .5f, 5.5f, .87f};
+    switch (D) {
+    case 16: return {13.f, 0.f, 2.4f, causal ? .425f : .28f};
+    case 32: return {15.f, 0.f, 4.5f, causal ? 1.65f : 1.15f};
+    case 64: return {30.f, 0.f, 10.f, 6.5f};
+    default: return {15.f, 0.f, 81.f, 50.f};
+    }
+}
+
+template <typename C>
+hipError_t launch_fwd(const void *q, const void *k, const void *v, void *out, float *g, int BH,
+                      int N, float qs, void *ws, hipStream_t st)
+{
+    typedef typename C::T T;
+    const int nqb = (N + C::QB - 1) / C::QB;
+    const int hgrp = BH < 32 ? BH : 32;
+    const long long rows = (long long)BH * N, pb = (rows * (C::D / 8) + 255) / 256;
+    if (!grid_fits((long long)BH * nqb, C::NTH) || (C::KP && !grid_fits(pb, 256)))
+        return hipErrorInvalidConfiguration;
+    _Float16 *khat = (_Float16 *)ws;
+    const size_t lo = (size_t)rows * C::D;
+    if (C::KP)
+        hipLaunchKernelGGL((khat_kernel<T, C::D, C::SPL>), dim3((unsigned)pb), dim3(256), 0, st,
+                           (const T *)k, khat, lo, rows);
+    hipLaunchKernelGGL((fwd_kernel<C>), dim3((unsigned)((long long)BH * nqb)), dim3(C::NTH), 0, st,
+                       (const T *)q, (const T *)k, (const T *)v, khat, lo, (T *)out, g, N, BH, nqb,
+                       hgrp, qs);
+    return hipGetLastError();
+}
+
+template <typename T, int D, bool CAUSAL, bool SPL>
+hipError_t launch_shape(const void *q, const void *k, const void *v, void *out, float *g, int BH,
+                        int N, float qs, int shape, void *ws, hipStream_t st)
+{
+#define L(KP, NQ, NWQ, NWK, BK)                                                                    \
+    do {                                                                                           \
+        typedef FwdCfg<T, D, 2, CAUSAL, SPL, KP, NQ, NWQ, NWK, BK> C;                              \
+        static_assert(C::QB == S.qb, "table");                                                     \
+        return launch_fwd<C>(q, k, v, out, g, BH, N, qs, ws, st);                                  \
+    } while (0)
+    if constexpr (D <= 32) {
+        if (shape == 0) { constexpr Shape S = (D == 16 ? SS16 : SS32)[0]; L(false, 1, 1, 8, 256); }
+        if (shape == 1) { constexpr Shape S = (D == 16 ? SS16 : SS32)[1]; L(false, 1, 2, 4, 128); }
+        if (shape == 2) { constexpr Shape S = (D == 16 ? SS16 : SS32)[2]; L(false, 1, 8, 1, 128); }
+    } else if constexpr (D == 64 && !SPL) {
+        if (shape == 0) { constexpr Shape S = SH64[0]; L(false, 1, 1, 8, 256); }
+        if (shape == 1) { constexpr Shape S = SH64[1]; L(false, 1, 2, 4, 128); }
+        if (shape == 2) { constexpr Shape S = SH64[2]; L(false, 1, 4, 2, 128); }
+        if (shape == 3) { constexpr Shape S = SH64[3]; L(false, 1, 4, 1, 64); }
+        if (shape == 4) { constexpr Shape S = SH64[4]; L(true, 1, 8, 1, 128); }
+        if (shape == 5) { constexpr Shape S = SH64[5]; L(false, 2, 8, 1, 128); }
+    } else if constexpr (D == 64) {
+        if (shape == 0) { constexpr Shape S = SS64[0]; L(false, 1, 2, 4, 128); }
+        if (shape == 1) { constexpr Shape S = SS64[1]; L(false, 1, 4, 2, 64); }
+        if (shape == 2) { constexpr Shape S = SS64[2]; L(false, 1, 8, 1, 64); }
+    } else if constexpr (sizeof(T) == 2) {
+        if (shape == 0) { constexpr Shape S = SS128[0]; L(false, 1, 2, 4, 128); }
+        if (shape == 1) { constexpr Shape S = SS128[1]; L(false, 1, 4, 2, 64); }
+        if (shape == 2) { constexpr Shape S = SS128[2]; L(false, 1, 8, 1, 64); }
+    } else {
+        if (shape == 0) { constexpr Shape S = SF128[0]; L(false, 1, 1, 4, 128); }
+        if (shape == 1) { constexpr Shape S = SF128[1]; L(false, 1, 4, 2, 64); }
+        if (shape == 2) { constexpr Shape S = SF128[2]; L(false, 1, 8, 1, 64); }
+    }
+#undef L
+    return hipErrorInvalidValue;
+}
+
+}  // namespace pr
+
+// The fastest shape by the tables above, or -1 where the moment kernels are
+// faster (by 3% at least: near the line the rule stays with them).  ws_bytes
+// bounds the shape that keeps k^ there.
+int pairs_fwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t ws_bytes)
+{
+    using namespace pr;
+    if (p != 2) return -1;
+    const Shape *s = SS16;
+    int n = 3;
+    switch (D) {
+    case 16: break;
+    case 32: s = SS32; break;
+    case 64:
+        s = is_bf16 ? SH64 : SS64;
+        n = is_bf16 ? 6 : 3;
+        break;
+    case 128: s = is_bf16 ? SS128 : SF128; break;
+    default: return -1;
+    }
+    const double tok = (double)N;
+    const Moments m = moments_fwd(N, D, causal, is_bf16);
+    double best = m.t0 + m.h * BH + 1e-3 * std::max(m.a * tok, m.b * tok * BH);
+    best *= 0.97;
+    int shape = -1;
+    for (int i = 0; i < n; ++i) {
+        if (s == SH64 && i == 4 && ws_bytes < (size_t)BH * N * 64 * 2) continue;
+        const double pairs = causal ? 0.5 * BH * tok * (tok + s[i].qb) : 0.95 * BH * tok * tok;
+        const double t = s[i].t0 + std::hypot(1e-3 * s[i].a * tok, 1e-6 * s[i].b * pairs);
+        if (t < best) {
+            best = t;
+            shape = i;
+        }
+    }
+    return shape;
+}
+
+hipError_t pairs_fwd(const void *q, const void *k, const void *v, void *out, float *g, int BH,
+                     int N, int D, int causal, int is_bf16, float qs, int shape, void *ws,
+                     hipStream_t st)
+{
+#define GO(T, DD, SPL)                                                                            \
+    return causal ? pr::launch_shape<T, DD, true, SPL>(q, k, v, out, g, BH, N, qs, shape, ws, st) \
+                  : pr::launch_shape<T, DD, false, SPL>(q, k, v, out, g, BH, N, qs, shape, ws, st)
+    if (is_bf16) {
+        switch (D) {
+        case 16: GO(bf16_t, 16, true);
+        case 32: GO(bf16_t, 32, true);
+        case 64: GO(bf16_t, 64, false);
+        case 128: GO(bf16_t, 128, true);
+        }
+    } else {
+        switch (D) {
+        case 16: GO(float, 16, true);
+        case 32: GO(float, 32, true);
+        case 64: GO(float, 64, true);
+        case 128: GO(float, 128, true);
+        }
+    }
+#undef GO
+    return hipErrorInvalidValue;
+}
+
+}  // namespace fm
