@@ -89,6 +89,13 @@ bool fwd_grids_fit(int BH, int N, int D, int p, int causal, int dt)
     return fm::f32mfma_fwd_grids_fit(BH, N, D, p);
 }
 
+bool bwd_grids_fit(int BH, int N, int D, int p, int causal, int dt)
+{
+    if (mfma_causal(D, p, causal, dt) || mfma_noncausal(N, D, p, causal, dt))
+        return fm::mfma_bwd_grids_fit(BH, N, causal);
+    return fm::f32mfma_bwd_grids_fit(BH, N, D, p);
+}
+
 size_t fwd_ws(int B, int H, int N, int D, int p, int causal, int dt)
 {
     if (mfma_causal(D, p, causal, dt)) return fm::mfma_causal_fwd_workspace(B * H, N);
@@ -207,7 +214,12 @@ int bwd_impl(const void *q, const void *k, const void *v, const void *out, const
     if (workspace && !aligned16(workspace)) return FASTMAX_EALIGN;
     if ((rc = fm::check_stream(stream)) != FASTMAX_OK) return rc;
     hipError_t e;
-    if (mfma_causal(D, p, causal, dt))
+    const int bf = dt == FASTMAX_BF16;
+    const int shape = fm::pairs_bwd_plan(B * H, N, D, p, causal, bf, need);
+    if (shape >= 0 && bwd_grids_fit(B * H, N, D, p, causal, dt))
+        e = fm::pairs_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, causal, bf, qk_scale,
+                          shape, workspace, stream);
+    else if (mfma_causal(D, p, causal, dt))
         e = fm::mfma_causal_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, qk_scale, workspace,
                                 stream);
     else if (mfma_noncausal(N, D, p, causal, dt))

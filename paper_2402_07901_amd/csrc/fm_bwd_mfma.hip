@@ -795,6 +795,18 @@ size_t base_workspace(int BH, int N)
            2 * a256(rows * mx::D * 2) + causal_scan_seg_workspace(4 * BH, (int)nch);
 }
 
+// All the grids of a call fit the dispatch limits.
+template <bool CAUSAL>
+bool bwd_grids_fit(int BH, int N, const ScanSplit &plan)
+{
+    const size_t rows = (size_t)BH * N;
+    const int nch = (N + C - 1) / C;
+    return grid_fits((long long)BH * nch, 256) &&
+           (!CAUSAL || grid_fits((long long)BH * (4 * (1 + plan.split) + nch), 512)) &&
+           grid_fits((long long)BH * 8, MG_NTH) && grid_fits((long long)((rows + 31) / 32), 256) &&
+           (CAUSAL || mfma_nc_grids_fit(BH, N));
+}
+
 // Causal: dv by the reverse scan with the in-chunk blocks, then the
 // moment-gradient scans over earlier chunks.  Non-causal: dv by the
 // non-causal forward kernels (queries and keys exchanged, no divide; their
@@ -814,11 +826,7 @@ hipError_t run(const void *q, const void *k, const void *v, const void *o, const
     const ScanSplit plan = CAUSAL ? causal_scan_split(4 * BH, nch, false) : ScanSplit{0, 0, 1};
     // prep, dv with the in-chunk blocks, the moment-gradient scans, finish;
     // non-causal: the dv launches
-    if (!grid_fits((long long)BH * nch, 256) ||
-        (CAUSAL && !grid_fits((long long)BH * (4 * (1 + plan.split) + nch), 512)) ||
-        !grid_fits((long long)BH * 8, MG_NTH) || !grid_fits((long long)((rows + 31) / 32), 256) ||
-        (!CAUSAL && !mfma_nc_grids_fit(BH, N)))
-        return hipErrorInvalidConfiguration;
+    if (!bwd_grids_fit<CAUSAL>(BH, N, plan)) return hipErrorInvalidConfiguration;
     auto a256 = [](size_t x) { return (x + 255) & ~(size_t)255; };
     unsigned char *p = (unsigned char *)ws;
     float *rg = (float *)p;
@@ -878,6 +886,14 @@ hipError_t run(const void *q, const void *k, const void *v, const void *o, const
 }  // namespace mfma_bwd
 
 size_t mfma_causal_bwd_workspace(int BH, int N) { return mfma_bwd::base_workspace(BH, N); }
+
+bool mfma_bwd_grids_fit(int BH, int N, int causal)
+{
+    using namespace mfma_bwd;
+    const int nch = (N + C - 1) / C;
+    return causal ? bwd_grids_fit<true>(BH, N, causal_scan_split(4 * BH, nch, false))
+                  : bwd_grids_fit<false>(BH, N, ScanSplit{0, 0, 1});
+}
 
 hipError_t mfma_causal_bwd(const void *q, const void *k, const void *v, const void *o,
                            const void *dout, const float *g, void *dq, void *dk, void *dv, int BH,

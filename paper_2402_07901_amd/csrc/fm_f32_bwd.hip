@@ -585,6 +585,15 @@ struct BwdPlan {
     size_t bytes() const { return 2 * vec_bytes + 2 * grad_bytes + scan_bytes; }
 };
 
+template <int D, int P>
+bool bwd_grids_fit(int BH, int N)
+{
+    const BwdPlan<D, P> pl(BH, N);
+    const long long rb = ((long long)BH * N + 15) / 16;
+    return grid_fits(rb, 256) && grid_fits((long long)pl.items * pl.nseg, Pat<D, P>::NTH) &&
+           f32mfma_fwd_grids_fit(BH, N, D, P);
+}
+
 template <int D, typename T, bool REV, int P>
 hipError_t grad_launch(const BwdPlan<D, P> &pl, const T *X, const T *Z, const T *VS, const T *UC,
                        const float *vsm, const float *ucm, const float *wv, const float *zv,
@@ -635,10 +644,7 @@ hipError_t bwd_run(const void *q, const void *k, const void *v, const void *o, c
     void *scan = p + 2 * pl.vec_bytes + 2 * pl.grad_bytes;
     const size_t rb = (rows + 15) / 16;
     // every grid of the sequence checked before the first launch
-    if (!grid_fits((long long)rb, 256) ||
-        !grid_fits((long long)pl.items * pl.nseg, Pat<D, P>::NTH) ||
-        !f32mfma_fwd_grids_fit(BH, N, D, P))
-        return hipErrorInvalidConfiguration;
+    if (!bwd_grids_fit<D, P>(BH, N)) return hipErrorInvalidConfiguration;
     const T *Q = (const T *)q, *K = (const T *)k, *V = (const T *)v, *DO = (const T *)dout;
     hipLaunchKernelGGL((bwd_prep_kernel<D, T>), dim3((unsigned)rb), dim3(256), 0, st, (const T *)o,
                        DO, g, rg, cvec, dqh, dkh, rows);
@@ -673,6 +679,18 @@ hipError_t bwd_dt(const void *q, const void *k, const void *v, const void *o, co
 }
 
 }  // namespace m32
+
+bool f32mfma_bwd_grids_fit(int BH, int N, int D, int p)
+{
+    using namespace m32;
+    switch (D) {
+    case 16: return p == 1 ? bwd_grids_fit<16, 1>(BH, N) : bwd_grids_fit<16, 2>(BH, N);
+    case 32: return p == 1 ? bwd_grids_fit<32, 1>(BH, N) : bwd_grids_fit<32, 2>(BH, N);
+    case 64: return p == 1 ? bwd_grids_fit<64, 1>(BH, N) : bwd_grids_fit<64, 2>(BH, N);
+    case 128: return p == 1 ? bwd_grids_fit<128, 1>(BH, N) : bwd_grids_fit<128, 2>(BH, N);
+    }
+    return false;
+}
 
 size_t f32mfma_bwd_workspace(int BH, int N, int D, int p)
 {

@@ -26,6 +26,8 @@ inline bool grid_fits(long long blocks, long long threads)
 bool f32mfma_fwd_grids_fit(int BH, int N, int D, int p);
 bool mfma_nc_grids_fit(int BH, int N);
 bool mfma_causal_fwd_grids_fit(int BH, int N);
+bool f32mfma_bwd_grids_fit(int BH, int N, int D, int p);
+bool mfma_bwd_grids_fit(int BH, int N, int causal);
 
 // FASTMAX_OK if stream is 0 or belongs to the current device, FASTMAX_EINVAL
 // if it belongs to another one, FASTMAX_EHIP if HIP cannot tell.
@@ -93,6 +95,12 @@ int pairs_fwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t 
 hipError_t pairs_fwd(const void *q, const void *k, const void *v, void *out, float *g, int BH,
                      int N, int D, int causal, int is_bf16, float qs, int shape, void *ws,
                      hipStream_t st);
+// The backward likewise: at most 8 D + 8 bytes of ws per row (bf16, D = 64:
+// 656), which the plan holds against ws_bytes.
+int pairs_bwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t ws_bytes);
+hipError_t pairs_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
+                     const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
+                     int is_bf16, float qs, int shape, void *ws, hipStream_t st);
 
 // Float32 MFMA kernels (v_mfma_f32_16x16x4_f32): p in {1, 2}, D in {16, 32,
 // 64, 128}, float32 or bf16 I/O, causal and non-causal (dispatch sends bf16

@@ -23,6 +23,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
+
 #include "fm_common.h"
 #include "fm_f32_mfma.h"
 #include "fm_mfma.h"
@@ -194,5 +197,45 @@ __device__ __forceinline__ float pow2_scale(float m, int top)
     return __uint_as_float((uint32_t)x << 23);
 }
 
+// A workgroup shape: queries (keys) per workgroup and its paces, and the
+// moment kernels' t = t0 + h heads + max(a N, b heads N) us (a and b in ns per
+// token).
+struct Shape {
+    int qb;
+    float t0, a, b;
+};
+struct Moments {
+    float t0, h, a, b;
+};
+
+// The fastest shape, or -1 where the moment kernels are faster (by 3% at
+// least: near the line the rule stays with them).  skip: a shape left out.
+inline int pick(const Shape *s, int n, const Moments &m, int BH, int N, int causal, int skip = -1)
+{
+    const double tok = (double)N;
+    const double mtok = std::max(tok, 128.0);   // their chunk
+    double best = 0.97 * (m.t0 + m.h * BH + 1e-3 * std::max(m.a * mtok, m.b * mtok * BH));
+    int shape = -1;
+    for (int i = 0; i < n; ++i) {
+        if (i == skip) continue;
+        const double pairs = causal ? 0.5 * BH * tok * (tok + s[i].qb) : 0.95 * BH * tok * tok;
+        const double t = s[i].t0 + std::hypot(1e-3 * s[i].a * tok, 1e-6 * s[i].b * pairs);
+        if (t < best) {
+            best = t;
+            shape = i;
+        }
+    }
+    return shape;
+}
+
 }  // namespace pr
+
+// float32-grade operands, as the float32 moment kernels have, wherever the
+// fp16 ones do not serve a call: they take bf16 at D = 64, without the mask
+// from 128 keys up (with fewer, rounding the operands shows in G).
+inline bool pairs_grade32(int N, int D, int causal, int is_bf16)
+{
+    return !(is_bf16 && D == 64 && (causal || N >= 128));
+}
+
 }  // namespace fm

@@ -1,0 +1,855 @@
+// Pair backward (see fm_pairs.h; p = 2): the custom gradient of Sec. 2.5 (only
+// O and G saved) over explicit (query, key) pairs.  With q~ = tau q^,
+// u = 1 / G, delta_i = dO_i.O_i and t = 1 + q~_i.k^_n = f_2'(tau s),
+//   dv_n  = sum_i f_2 u_i dO_i,               f_2 = (t^2 + 1) / 2,
+//   dq~_i = sum_n T_in k^_n,  dk^_n = sum_i T_in q~_i,
+//   T_in  = t u_i (dO_i.v_n - delta_i)
+// (Sec. 2.3, Eq. "bound"), then the standardisation backward (Eqs. 6-7) of the
+// finished rows.  bwd_prep writes q~ and k^ as fp16 planes (and their lo
+// parts) and one word pair per row; bwd_kernel holds three kinds of workgroups
+// in one launch, each with 32 columns per wave in registers and the other side
+// staged in steps of BK rows: role Q (columns queries, out dq), role K (columns
+// keys, out dk) and role V (columns keys, out dv).  No atomics: every output
+// row has one owner, results repeat bit for bit.
+//
+// Scales.  1/G falls from about 1 to 1/(tens of N) along a causal sequence, so
+// a row's power of two goes to the contraction's A operand and its pairs fill
+// the fp16 range.  Role K: with G_i = 2^k / rho (1/2 < rho <= 1) and
+// 2^h > |dO_i.v_n|, |delta_i| for the workgroup's keys n, the pairs carry
+// rho t (dO_i.v_n - delta_i) 2^-h and row i's A operand 2^(h - k - M) <= 1, M
+// the largest h - k of the rows read; role V: dO_i / G_i 2^-M; role Q: 1/G_i
+// stays out of the sum.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
+#include "fm_internal.h"
+#include "fm_pairs.h"
+
+namespace fm {
+namespace pr {
+
+enum Role { ROLE_Q = 0, ROLE_K = 1, ROLE_V = 2 };
+
+// Exponents of zero and non-finite rows: they take no part in a maximum.
+constexpr int NO_EXP = -1000;
+
+// Least e with m < 2^e for finite m > 0.
+__device__ __forceinline__ int exp_above(float m)
+{
+    const int x = (int)(__float_as_uint(m) >> 23);
+    return m > 0.f && x < 255 ? x - 126 : NO_EXP;
+}
+
+__device__ __forceinline__ float exp2i(int n)
+{
+    n = n < -126 ? -126 : (n > 127 ? 127 : n);
+    return __uint_as_float((uint32_t)(n + 127) << 23);
+}
+
+__device__ __forceinline__ int g_exp(float G) { return (int)((__float_as_uint(G) >> 23) & 255) - 127; }
+
+template <int L>
+__device__ __forceinline__ float group_max(float x)
+{
+    auto mv = [](float y, auto ctl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), decltype(ctl)::value, 0xF, 0xF, true));
+    };
+    x = fmaxf(x, mv(x, std::integral_constant<int, 0xB1>{}));
+    if constexpr (L >= 4) x = fmaxf(x, mv(x, std::integral_constant<int, 0x4E>{}));
+    if constexpr (L >= 8) x = fmaxf(x, mv(x, std::integral_constant<int, 0x141>{}));
+    if constexpr (L >= 16) x = fmaxf(x, mv(x, std::integral_constant<int, 0x140>{}));
+    return x;
+}
+
+// The per-row words.  float32-grade calls keep delta = dO.O and the exponents
+// of dO and v.  The fp16 ones also keep v, dO and dO rho as fp16 planes, each row scaled by
+// a power of two to below 2^10, so that a step stages them with one packed
+// multiply per pair: delta in dO's scale, rho, and the exponents of dO, v and
+// dO / G.
+struct RowInfo {
+    float delta;
+    short e_do, e_v;
+};
+struct RowInfoH {
+    float delta, rho;
+    short e_do, e_v;
+    int eg;
+};
+static_assert(sizeof(RowInfo) == 8 && sizeof(RowInfoH) == 16, "bytes per row");
+
+// 2^n as a half, flushed to zero below its range (n at most 15).
+__device__ __forceinline__ _Float16 half2i(int n) { return n < -24 ? (_Float16)0.0f : (_Float16)exp2i(n); }
+
+// One thread per 8 channels of a row of the whole call.
+template <typename T, int D, bool SPL>
+__global__ __launch_bounds__(256) void bwd_prep_kernel(
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
+    const T *__restrict__ o, const T *__restrict__ dout, const float *__restrict__ g,
+    _Float16 *__restrict__ planes, void *__restrict__ info, long long rows, float qn)
+{
+    constexpr int L = D / 8;
+    const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / L;
+    const int c = threadIdx.x % L;
+    const bool ok = row < rows;
+    const size_t off = (size_t)(ok ? row : 0) * D + 8 * c, np = (size_t)rows * D;
+    RawRow<T, 8> rq, rk, rv, ro, rd;
+    rq.load(q + off, ok);
+    rk.load(k + off, ok);
+    rv.load(v + off, ok);
+    ro.load(o + off, ok);
+    rd.load(dout + off, ok);
+    float x[8];
+    h8 hi, lo;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = rq.get(i);
+    standardise_group<D>(x, ok);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] *= qn;
+    split8<SPL>(x, hi, lo);
+    if (ok) {
+        *(h8 *)(planes + off) = hi;
+        if constexpr (SPL) *(h8 *)(planes + np + off) = lo;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = rk.get(i);
+    standardise_group<D>(x, ok);
+    split8<SPL>(x, hi, lo);
+    if (ok) {
+        *(h8 *)(planes + (SPL ? 2 : 1) * np + off) = hi;
+        if constexpr (SPL) *(h8 *)(planes + 3 * np + off) = lo;
+    }
+    float d = 0.f, md = 0.f, mv = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        d = fmaf(rd.get(i), ro.get(i), d);
+        md = fmaxf(md, fabsf(rd.get(i)));
+        mv = fmaxf(mv, fabsf(rv.get(i)));
+    }
+    d = group_sum<L>(d);
+    md = group_max<L>(md);
+    mv = group_max<L>(mv);
+    const int ed = exp_above(md), ev = exp_above(mv);
+    if constexpr (SPL) {
+        if (ok && c == 0) ((RowInfo *)info)[row] = RowInfo{d, (short)ed, (short)ev};
+    } else {
+        const int e = ed == NO_EXP ? 0 : ed;
+        const float G = g[ok ? row : 0];
+        const int kx = g_exp(G);
+        const float rho = exp2i(kx) / G, fd = exp2i(10 - e), fv = exp2i(10 - (ev == NO_EXP ? 0 : ev));
+        float y[8], z[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            x[i] = rv.get(i) * fv;
+            y[i] = rd.get(i) * fd;
+            z[i] = y[i] * rho;
+        }
+        if (ok) {
+            split8<false>(x, hi, lo);
+            *(h8 *)(planes + 2 * np + off) = hi;
+            split8<false>(y, hi, lo);
+            *(h8 *)(planes + 3 * np + off) = hi;
+            split8<false>(z, hi, lo);
+            *(h8 *)(planes + 4 * np + off) = hi;
+            if (c == 0)
+                ((RowInfoH *)info)[row] = RowInfoH{d * fd, rho, (short)ed, (short)ev, ed == NO_EXP ? NO_EXP : ed - kx};
+        }
+    }
+}
+
+template <typename T_, int D_, bool CAUSAL_, bool SPL_, int NQ_, int NWQ_, int NWK_, int BK_>
+struct BwdCfg {
+    typedef T_ T;
+    static constexpr int D = D_, NQ = NQ_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
+    static constexpr bool CAUSAL = CAUSAL_, SPL = SPL_;
+    static constexpr bool VSPL = SPL && sizeof(T) == 4;
+    static constexpr bool LOACC = VSPL && D <= 32;
+    static constexpr int NTH = 64 * NWQ * NWK;
+    static constexpr int QB = 32 * NQ * NWQ;
+    static constexpr int KS = D / 16, CT = D < 32 ? 1 : D / 32;
+    static constexpr int LPT = D / 8, TPP = NTH / LPT, NP = (BK + TPP - 1) / TPP;
+    static constexpr int RS = row_stride<D>(), VS = tr_stride<D>();
+    static constexpr int XH = BK * RS, AH = BK * VS;
+    static constexpr int NX = SPL ? 2 : 1, NV = VSPL ? 2 : 1;
+    // planes of a step: x (scores), val (dO.v), and the contraction's A
+    // operand where it is not x itself (role K: scaled q~; role V: scaled dO u)
+    static constexpr int TILE_Q = 2 * (NX * XH + NV * XH);
+    static constexpr int TILE_K = 2 * (NX * XH + NV * XH + NX * AH) + 8 * BK;
+    static constexpr int TILE = TILE_K;   // role V: NX (x) + NX (u) planes, fewer
+    static constexpr bool QLDS = SPL && D >= 128;
+    // two steps' tiles in turn where LDS has room beside the other workgroups
+    // of the CU (eight waves in all): one barrier a step instead of two
+    static constexpr bool DB = 2 * TILE + (QLDS ? 2 * QB * RS : 0) <= 160 * 1024 * NWQ * NWK / 8 - 256;
+    static constexpr int NB = DB ? 2 : 1;
+    static constexpr int LOOP_BYTES = NB * TILE + (QLDS ? 2 * QB * RS : 0);
+    static constexpr int RED_BYTES = NWK > 1 ? 4 * NWQ * NWK * 32 * 32 * CT : 0;
+    static constexpr int SMEM = LOOP_BYTES > RED_BYTES ? LOOP_BYTES : RED_BYTES;
+    static_assert(BK % (32 * NWK) == 0 && (NWK == 1 || NQ == 1) && TILE_K >= TILE_Q, "shape");
+};
+
+struct BwdArgs {
+    const void *q, *k, *v, *dout;
+    const float *g;
+    const _Float16 *planes;
+    const void *info;
+    void *dq, *dk, *dv;
+    int N, BH;
+    float qs, sc;   // tau, and the power of two the planes of q~ lack
+};
+
+template <typename C, int ROLE>
+__device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const BwdArgs &a, int head,
+                                          int qb)
+{
+    typedef typename C::T T;
+    constexpr int D = C::D, NQ = C::NQ, KS = C::KS, CT = C::CT, RS = C::RS, VS = C::VS, NX = C::NX, NV = C::NV;
+    constexpr bool SPL = C::SPL, VSPL = C::VSPL;
+    const int N = a.N;
+    // a step's planes (a buffer of them), in halves from its start: x, the
+    // staged values (roles Q, K), the contraction's A operand (K, V), and
+    // role K's row factors
+    constexpr int OV = NX * C::XH, OA = ROLE == ROLE_V ? OV : OV + NV * C::XH, OB = OA + NX * C::AH;
+    static_assert(C::TILE % 16 == 0, "alignment");
+    _Float16 *const olo = (_Float16 *)(smem + C::NB * C::TILE);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r32 = lane & 31, h = lane >> 5;
+    const int wq = wave / C::NWK, wk = wave % C::NWK;
+    const size_t hb = (size_t)head * N * D, np = (size_t)a.BH * N * D;
+    // own columns and staged rows
+    const _Float16 *const qpl = a.planes + hb, *const kpl = a.planes + (size_t)NX * np + hb;
+    const _Float16 *const own = ROLE == ROLE_Q ? qpl : kpl, *const stg = ROLE == ROLE_Q ? kpl : qpl;
+    const T *const val = (const T *)(ROLE == ROLE_Q ? a.v : a.dout) + hb;   // staged
+    typedef typename std::conditional<SPL, RowInfo, RowInfoH>::type Info;
+    const Info *const info = (const Info *)a.info + (size_t)head * N;
+    // fp16 planes of v, dO and dO rho (unsplit operands only)
+    const _Float16 *const hpl = a.planes + (ROLE == ROLE_Q ? 2 : ROLE == ROLE_K ? 3 : 4) * np + hb;
+    const float *const g = a.g + (size_t)head * N;
+    const int q0 = qb * C::QB + 32 * NQ * wq;
+    const int rbeg = C::CAUSAL && ROLE != ROLE_Q ? qb * C::QB : 0;
+    const int rend = C::CAUSAL && ROLE == ROLE_Q ? min(N, (qb + 1) * C::QB) : N;
+    const int t0 = rbeg / C::BK, t1 = (rend + C::BK - 1) / C::BK;
+
+    // staging: this thread's 8 channels and first row
+    const int sc = tid % C::LPT, st0 = tid / C::LPT;
+    RawRow<bf16_t, 8> xr[C::NP], xl[SPL ? C::NP : 1];   // fp16 words
+    RawRow<T, 8> vr[SPL ? C::NP : 1];
+    RawRow<bf16_t, 8> hr[SPL ? 1 : C::NP];              // fp16 words
+    Info ri[C::NP];
+    float gr[C::NP];
+    // rows past the end repeat the last one: masked (role Q) or given weight 0
+    auto load_tile = [&](int t) {
+#pragma unroll
+        for (int p = 0; p < C::NP; ++p) {
+            const unsigned n = (unsigned)min(t * C::BK + st0 + C::TPP * p, N - 1);
+            const unsigned off = n * (unsigned)D + 8u * sc;
+            xr[p].load((const bf16_t *)stg + off, true);
+            if constexpr (SPL) {
+                xl[p].load((const bf16_t *)stg + np + off, true);
+                vr[p].load(val + off, true);
+                if constexpr (ROLE != ROLE_Q) {
+                    ri[p] = info[n];
+                    gr[p] = g[n];
+                }
+            } else {
+                hr[p].load((const bf16_t *)hpl + off, true);
+                ri[p] = info[n];
+            }
+        }
+    };
+    load_tile(t0);
+
+    // Q: the largest exponent of the staged v; V: of dO / G; K: of the own v
+    // (MO), then of h - k
+    constexpr int LD = D == 16 ? 4 : D == 32 ? 5 : D == 64 ? 6 : 7;
+    if (tid < 2) sred[tid] = NO_EXP;
+    __syncthreads();
+    int MO = 0;
+    if constexpr (ROLE == ROLE_K) {
+        const int n = qb * C::QB + tid;
+        if (tid < C::QB && n < N && info[n].e_v > NO_EXP) atomicMax(&sred[1], (int)info[n].e_v);
+        __syncthreads();
+        MO = sred[1] == NO_EXP ? 0 : sred[1];
+    }
+    // h - e of a row of dO
+    auto row_h = [&](const Info &x) {
+        if constexpr (SPL) return max(LD + MO, exp_above(fabsf(x.delta)) - x.e_do);
+        else return max(LD + MO, exp_above(fabsf(x.delta)) - 10);
+    };
+    {
+        int m = NO_EXP;
+        for (int n = rbeg + tid; n < rend; n += C::NTH) {
+            const Info x = info[n];
+            if constexpr (ROLE == ROLE_Q) {
+                m = max(m, (int)x.e_v);
+            } else if (x.e_do != NO_EXP) {
+                int e;
+                if constexpr (SPL) e = x.e_do - g_exp(g[n]);
+                else e = x.eg;
+                m = max(m, ROLE == ROLE_K ? e + row_h(x) : e);
+            }
+        }
+        if (m > NO_EXP) atomicMax(&sred[0], m);
+    }
+    __syncthreads();
+    const int M = sred[0] == NO_EXP ? 0 : sred[0];
+    // role Q: T = t (dP - delta) with |dP| < D 2^24 (values below 2^14 and 2^10)
+    constexpr int X = -10 - 2 * LD;
+
+    // own columns as B operands: x, and (roles Q, K) dO or v scaled
+    h8 oh[NQ][KS], ol[NQ][SPL && !C::QLDS ? KS : 1];
+    h8 vo[ROLE != ROLE_V ? NQ : 1][KS], vol[ROLE != ROLE_V && VSPL ? NQ : 1][KS];
+    float dcol[NQ];
+    int ecol[NQ];
+    _Float16 *const olw = olo + (32 * NQ * wq + r32) * RS + 8 * h;
+#pragma unroll
+    for (int t = 0; t < NQ; ++t) {
+        const int n = q0 + 32 * t + r32;
+        const bool ok = n < N;
+        const size_t off = (size_t)(ok ? n : 0) * D + 8 * h;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            h8 x = *(const h8 *)(own + off + 16 * ks);
+            oh[t][ks] = ok ? x : h8{};
+            if constexpr (SPL) {
+                x = *(const h8 *)(own + np + off + 16 * ks);
+                x = ok ? x : h8{};
+                if constexpr (C::QLDS) {
+                    if (wk == 0) *(h8 *)(olw + 32 * t * RS + 16 * ks) = x;
+                } else {
+                    ol[t][ks] = x;
+                }
+            }
+        }
+        if constexpr (ROLE != ROLE_V) {
+            const Info w = info[ok ? n : 0];
+            ecol[t] = ROLE == ROLE_Q ? (w.e_do == NO_EXP ? 0 : w.e_do) : MO;
+            if constexpr (SPL) {
+                float x[D / 2];
+                load_cols<T, D>((const T *)(ROLE == ROLE_Q ? a.dout : a.v) + hb, n, N, x);
+                const float s = exp2i(10 - ecol[t]);
+                // role Q: delta in the scale of dP, times the scale of T
+                dcol[t] = ROLE == ROLE_Q ? (ok ? w.delta : 0.f) * s * exp2i(14 - M) * exp2i(X) : 0.f;
+#pragma unroll
+                for (int i = 0; i < D / 2; ++i) x[i] *= s;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) split8<VSPL>(x + 8 * ks, vo[t][ks], vol[VSPL ? t : 0][ks]);
+            } else {
+                const _Float16 *const pl = a.planes + (ROLE == ROLE_Q ? 3 : 2) * np + hb;
+                const _Float16 s = ROLE == ROLE_Q ? (_Float16)1.0f : half2i((w.e_v == NO_EXP ? 0 : w.e_v) - MO);
+                dcol[t] = ROLE == ROLE_Q ? w.delta * exp2i(14 - M) * exp2i(X) : 0.f;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) vo[t][ks] = *(const h8 *)(pl + off + 16 * ks) * s;
+            }
+        }
+    }
+
+    f16v acc[NQ][CT], acl[NQ][C::LOACC ? CT : 1];
+#pragma unroll
+    for (int t = 0; t < NQ; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            acc[t][c] = f16v{};
+            if constexpr (C::LOACC) acl[t][c] = f16v{};
+        }
+
+    // One 32-row tile j of the staged step against the wave's columns; masked:
+    // some of its pairs lie beyond the diagonal.
+    auto tile = [&](const _Float16 *xhi, int j, int kb, bool masked) {
+        const _Float16 *const vhi = xhi + OV, *const ahi = xhi + OA;
+        const float *const rowB = (const float *)(xhi + OB), *const rowD = rowB + C::BK;
+        f16v s[NQ], d[ROLE != ROLE_V ? NQ : 1];
+#pragma unroll
+        for (int u = 0; u < NQ; ++u)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                s[u][i] = SPL ? 0.0f : 1.0f;
+                if constexpr (ROLE != ROLE_V) d[u][i] = 0.0f;
+            }
+        const _Float16 *xp = xhi + (32 * j + r32) * RS + 8 * h;
+        if constexpr (SPL && D < 128) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const h8 x = ld8(xp + 16 * ks), w = ld8(xp + C::XH + 16 * ks);
+#pragma unroll
+                for (int u = 0; u < NQ; ++u) {
+                    s[u] = mma(x, ol[u][C::QLDS ? 0 : ks], s[u]);
+                    s[u] = mma(w, oh[u][ks], s[u]);
+                }
+            }
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const h8 x = ld8(xp + 16 * ks);
+            if constexpr (SPL && D >= 128) {
+                const h8 w = ld8(xp + C::XH + 16 * ks);
+#pragma unroll
+                for (int u = 0; u < NQ; ++u) {
+                    s[u] = mma(x, ld8(olw + 32 * u * RS + 16 * ks), s[u]);
+                    s[u] = mma(w, oh[u][ks], s[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) s[u] = mma(x, oh[u][ks], s[u]);
+        }
+        if constexpr (ROLE != ROLE_V) {
+            const _Float16 *vp = vhi + (32 * j + r32) * RS + 8 * h;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const h8 x = ld8(vp + 16 * ks);
+#pragma unroll
+                for (int u = 0; u < NQ; ++u) d[u] = mma(x, vo[u][ks], d[u]);
+                if constexpr (VSPL) {
+                    const h8 w = ld8(vp + C::XH + 16 * ks);
+#pragma unroll
+                    for (int u = 0; u < NQ; ++u) {
+                        d[u] = mma(x, vol[u][ks], d[u]);
+                        d[u] = mma(w, vo[u][ks], d[u]);
+                    }
+                }
+            }
+        }
+        h8 th[NQ][2], tl[NQ][SPL ? 2 : 1];
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) {
+            const int col = q0 + 32 * u + r32, last = C::CAUSAL ? min(col, N - 1) : N - 1;
+            float w[16];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                float4 B, E;
+                if constexpr (ROLE == ROLE_K) {
+                    B = *(const float4 *)(rowB + 32 * j + 8 * b + 4 * h);
+                    E = *(const float4 *)(rowD + 32 * j + 8 * b + 4 * h);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float st = SPL ? fmaf(s[u][4 * b + i], a.sc, 1.0f) : s[u][4 * b + i];   // 1 + tau s
+                    if constexpr (ROLE == ROLE_V) w[4 * b + i] = fmaf(st, st, 1.0f);
+                    else if constexpr (ROLE == ROLE_Q)
+                        w[4 * b + i] = st * fmaf(d[u][4 * b + i], exp2i(X), -dcol[u]);
+                    else
+                        w[4 * b + i] = st * fmaf(d[u][4 * b + i], ((const float *)&B)[i], -((const float *)&E)[i]);
+                }
+            }
+            if (masked) {
+                asm volatile("");   // a branch, not a compare and select per element of every tile
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int row = kb + 8 * (i / 4) + 4 * h + i % 4;
+                    if (ROLE == ROLE_Q ? row > last : row < col) w[i] = 0.f;
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) split8<SPL>(w + 8 * e, th[u][e], tl[u][SPL ? e : 0]);
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                constexpr int AS = ROLE == ROLE_Q ? RS : VS;
+                constexpr int APL = ROLE == ROLE_Q ? C::XH : C::AH;
+                const _Float16 *ap = ROLE == ROLE_Q ? xhi : ahi;
+                const h8 x = ld_tr<AS>(ap, 32 * j + 16 * e, 32 * c);
+#pragma unroll
+                for (int u = 0; u < NQ; ++u) acc[u][c] = mma(x, th[u][e], acc[u][c]);
+                if constexpr (SPL) {
+                    const h8 y = ld_tr<AS>(ap + APL, 32 * j + 16 * e, 32 * c);
+#pragma unroll
+                    for (int u = 0; u < NQ; ++u) {
+                        f16v &z = C::LOACC ? acl[u][C::LOACC ? c : 0] : acc[u][c];
+                        z = mma(x, tl[u][SPL ? e : 0], z);
+                        z = mma(y, th[u][e], z);
+                    }
+                }
+            }
+    };
+
+    // writes the loaded step t to a buffer
+    auto stage = [&](_Float16 *xhi, int t) {
+        _Float16 *const vhi = xhi + OV, *const ahi = xhi + OA;
+        float *const rowB = (float *)(xhi + OB), *const rowD = rowB + C::BK;
+#pragma unroll
+        for (int p = 0; p < C::NP; ++p) {
+            const int row = st0 + C::TPP * p;
+            const bool ok = C::BK % C::TPP == 0 || row < C::BK;
+            const int n = t * C::BK + row;
+            const bool in = n < N && n >= rbeg;   // the others weigh nothing
+            const h8 x0 = __builtin_bit_cast(h8, *(uint4 *)xr[p].w);
+            if (ok) *(h8 *)(xhi + row * RS + 8 * sc) = x0;
+            if constexpr (!SPL) {
+                const h8 z = __builtin_bit_cast(h8, *(uint4 *)hr[p].w);
+                if constexpr (ROLE == ROLE_Q) {
+                    if (ok) *(h8 *)(vhi + row * RS + 8 * sc) = z * half2i(4 + ri[p].e_v - M);
+                } else if constexpr (ROLE == ROLE_V) {
+                    if (ok) *(h8 *)(ahi + row * VS + 8 * sc) = z * (in ? half2i(4 + ri[p].eg - M) : (_Float16)0.0f);
+                } else {
+                    const int hm = row_h(ri[p]), y = in ? min(max(ri[p].eg + hm - M, -40), 0) : -40;
+                    if (ok) {
+                        *(h8 *)(vhi + row * RS + 8 * sc) = z;
+                        *(h8 *)(ahi + row * VS + 8 * sc) = x0 * half2i(11 + y);
+                        if (sc == 0) {
+                            // the scales of dO.v (values below 2^10) and delta in T
+                            const float B = in ? ri[p].rho * exp2i(MO - 8 - LD - hm) : 0.f;
+                            rowB[row] = B;
+                            rowD[row] = in ? ri[p].rho * exp2i(2 - LD - hm) * ri[p].delta : 0.f;
+                        }
+                    }
+                }
+            } else {
+                float f;            // the staged values' scale
+                int y = 0;          // role K: the row's share of the scale of q~
+                if constexpr (ROLE == ROLE_Q) {
+                    f = exp2i(14 - M);
+                } else {
+                    const int kx = g_exp(gr[p]), e = ri[p].e_do == NO_EXP ? 0 : ri[p].e_do;
+                    if constexpr (ROLE == ROLE_K) {
+                        const int hm = row_h(ri[p]);
+                        const bool live = in && ri[p].e_do != NO_EXP;
+                        y = live ? min(max(e + hm - kx - M, -40), 0) : -40;
+                        f = exp2i(14 - e);
+                        if (ok && sc == 0) {
+                            // the scales of dO.v (below 2^14, 2^10) and delta in T
+                            const float rho = live ? exp2i(kx) / gr[p] : 0.f;
+                            rowB[row] = rho * exp2i(MO - 12 - LD - hm);
+                            rowD[row] = live ? rho * exp2i(12 - LD - hm - e) * ri[p].delta : 0.f;
+                        }
+                    } else {
+                        f = in ? exp2i(14 - M) / gr[p] : 0.f;
+                    }
+                }
+                float z[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) z[i] = vr[p].get(i) * f;
+                h8 hi, lo;
+                const h8 x1 = __builtin_bit_cast(h8, *(uint4 *)xl[p].w);
+                if (ok) *(h8 *)(xhi + C::XH + row * RS + 8 * sc) = x1;
+                if constexpr (ROLE == ROLE_V) {
+                    split8<true>(z, hi, lo);
+                    if (ok) {
+                        *(h8 *)(ahi + row * VS + 8 * sc) = hi;
+                        *(h8 *)(ahi + C::AH + row * VS + 8 * sc) = lo;
+                    }
+                } else {
+                    split8<VSPL>(z, hi, lo);
+                    if (ok) {
+                        *(h8 *)(vhi + row * RS + 8 * sc) = hi;
+                        if constexpr (VSPL) *(h8 *)(vhi + C::XH + row * RS + 8 * sc) = lo;
+                    }
+                }
+                if constexpr (ROLE == ROLE_K) {
+                    const _Float16 w = half2i(y + 11);
+                    if (ok) {
+                        *(h8 *)(ahi + row * VS + 8 * sc) = x0 * w;
+                        *(h8 *)(ahi + C::AH + row * VS + 8 * sc) = x1 * w;
+                    }
+                }
+            }
+        }
+    };
+    auto compute = [&](const _Float16 *buf, int t) {
+#pragma unroll 1
+        for (int j = wk; j < C::BK / 32; j += C::NWK) {
+            const int kb = t * C::BK + 32 * j;
+            if (kb >= N || (C::CAUSAL && ROLE == ROLE_Q && kb > q0 + 32 * NQ - 1)) break;
+            if (C::CAUSAL && ROLE != ROLE_Q && kb + 31 < q0) continue;
+            tile(buf, j, kb, ROLE == ROLE_Q ? (C::CAUSAL && kb + 31 > q0) || kb + 32 > N
+                                       : C::CAUSAL && kb < q0 + 32 * NQ - 1);
+        }
+    };
+
+    if constexpr (C::DB) {
+        constexpr int BH2 = C::TILE / 2;
+        if (t0 < t1) stage((_Float16 *)smem, t0);
+        if (t0 + 1 < t1) load_tile(t0 + 1);
+        __syncthreads();
+        for (int t = t0; t < t1; ++t) {
+            _Float16 *const buf = (_Float16 *)smem + ((t - t0) & 1) * BH2;
+            compute(buf, t);
+            if (t + 1 < t1) {
+                stage((_Float16 *)smem + ((t + 1 - t0) & 1) * BH2, t + 1);
+                if (t + 2 < t1) load_tile(t + 2);
+            }
+            __syncthreads();
+        }
+    } else {
+        for (int t = t0; t < t1; ++t) {
+            __syncthreads();
+            stage((_Float16 *)smem, t);
+            if (t + 1 < t1) load_tile(t + 1);
+            __syncthreads();
+            compute((const _Float16 *)smem, t);
+        }
+    }
+    if constexpr (C::LOACC)
+#pragma unroll
+        for (int t = 0; t < NQ; ++t)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) acc[t][c] += acl[t][c];
+
+    // partial sums of the waves that shared the columns
+    if constexpr (C::NWK > 1) {
+        float *red = (float *)smem;
+        constexpr int W = 32 * 32 * CT;
+        __syncthreads();
+        if (wk > 0) {
+            float *mine = red + wave * W;
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    mine[32 * (32 * c + 8 * (i / 4) + 4 * h + i % 4) + r32] = acc[0][c][i];
+        }
+        __syncthreads();
+        if (wk > 0) return;
+#pragma unroll
+        for (int w = 1; w < C::NWK; ++w) {
+            const float *part = red + (wave + w) * W;
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    acc[0][c][i] += part[32 * (32 * c + 8 * (i / 4) + 4 * h + i % 4) + r32];
+        }
+    }
+
+    const float tau = a.qs;
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+        const int n = q0 + 32 * u + r32;
+        const bool ok = n < N;
+        T *const out = (T *)(ROLE == ROLE_Q ? a.dq : ROLE == ROLE_K ? a.dk : a.dv) + hb + (size_t)(ok ? n : 0) * D;
+        // out of the scales (in two factors: each a normal number)
+        float f0, f1;
+        if constexpr (ROLE == ROLE_V) {
+            f0 = 0.5f * exp2i(-14);
+            f1 = exp2i(M);
+        } else if constexpr (ROLE == ROLE_K) {
+            f0 = exp2i(LD - 23) * a.sc;
+            f1 = exp2i(M);
+        } else {
+            f0 = tau / g[ok ? n : 0] * exp2i(-X - 24);
+            f1 = exp2i(ecol[u]) * exp2i(M);
+        }
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[u][c][i] = acc[u][c][i] * f0 * f1;
+        if constexpr (ROLE != ROLE_V) {
+            // dx = (dx^ - mean dx^ - x^ mean(dx^ x^)) / sigma
+            const T *const xrow = (const T *)(ROLE == ROLE_Q ? a.q : a.k) + hb + (size_t)(ok ? n : 0) * D;
+            float x[CT][16], sum = 0.f;
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int dd = 32 * c + 8 * b + 4 * h;
+                    const bool in = D % 32 == 0 || dd < D;
+                    RawRow<T, 4> raw;
+                    raw.load(xrow + (in ? dd : 0), in);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        x[c][4 * b + i] = raw.get(i);
+                        sum += x[c][4 * b + i];
+                    }
+                }
+            const float mu = half_sum(sum) * (1.0f / D);
+            float var = 0.f, m1 = 0.f, m2 = 0.f;
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    if (D % 32 == 0 || 32 * c + 8 * (i / 4) + 4 * h < D) {
+                        x[c][i] -= mu;
+                        var = fmaf(x[c][i], x[c][i], var);
+                        m1 += acc[u][c][i];
+                        m2 = fmaf(acc[u][c][i], x[c][i], m2);
+                    }
+                }
+            const float r = rsqrt1(half_sum(var) * (1.0f / D));
+            m1 = half_sum(m1) * (1.0f / D);
+            m2 = half_sum(m2) * (1.0f / D) * r * r;
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[u][c][i] = (acc[u][c][i] - m1 - x[c][i] * m2) * r;
+        }
+        if (ok) {
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int dd = 32 * c + 8 * b + 4 * h;
+                    if (D % 32 == 0 || dd < D) {
+                        if constexpr (sizeof(T) == 2)
+                            *(uint2 *)(out + dd) = make_uint2(
+                                mx::pack_bf16x2(acc[u][c][4 * b], acc[u][c][4 * b + 1]),
+                                mx::pack_bf16x2(acc[u][c][4 * b + 2], acc[u][c][4 * b + 3]));
+                        else
+                            *(float4 *)(out + dd) = make_float4(acc[u][c][4 * b], acc[u][c][4 * b + 1],
+                                                                acc[u][c][4 * b + 2], acc[u][c][4 * b + 3]);
+                    }
+                }
+        }
+    }
+}
+
+// Block order: heads in groups of hgrp; within a group the columns with the
+// most rows first (role Q: the last queries; K, V: the first keys), the three
+// roles of a column block side by side.
+template <typename C>
+__global__ __launch_bounds__(C::NTH, 2) void bwd_kernel(BwdArgs a, int nqb, int hgrp)
+{
+    __shared__ alignas(16) unsigned char smem[C::SMEM];
+    __shared__ int sred[2];
+    const int b = blockIdx.x, per = 3 * hgrp * nqb, grp = b / per, r = b - grp * per;
+    const int gs = min(hgrp, a.BH - grp * hgrp);
+    const int head = grp * hgrp + r % gs, rest = r / gs, role = rest % 3, i = rest / 3;
+    if (role == 0) bwd_block<C, ROLE_Q>(smem, sred, a, head, nqb - 1 - i);
+    else if (role == 1) bwd_block<C, ROLE_K>(smem, sred, a, head, i);
+    else bwd_block<C, ROLE_V>(smem, sred, a, head, i);
+}
+
+template <typename C>
+hipError_t launch_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
+                      const float *g, void *dq, void *dk, void *dv, int BH, int N, float qs,
+                      void *ws, hipStream_t st)
+{
+    typedef typename C::T T;
+    const long long rows = (long long)BH * N, pb = (rows * (C::D / 8) + 255) / 256;
+    const int nqb = (N + C::QB - 1) / C::QB, hgrp = BH < 32 ? BH : 32;
+    if (!grid_fits(pb, 256) || !grid_fits(3LL * BH * nqb, C::NTH)) return hipErrorInvalidConfiguration;
+    // the planes hold q^ scaled by tau's mantissa: a small tau would push their
+    // lo parts below fp16's range
+    int e = 0;
+    if (C::SPL) frexpf(qs, &e);
+    const float sc = C::SPL ? ldexpf(1.0f, e - 1) : 1.0f;
+    _Float16 *planes = (_Float16 *)ws;
+    void *info = planes + (C::SPL ? 4 : 5) * (size_t)rows * C::D;
+    hipLaunchKernelGGL((bwd_prep_kernel<T, C::D, C::SPL>), dim3((unsigned)pb), dim3(256), 0, st,
+                       (const T *)q, (const T *)k, (const T *)v, (const T *)o, (const T *)dout, g,
+                       planes, info, rows, qs / sc);
+    const BwdArgs a{q, k, v, dout, g, planes, info, dq, dk, dv, N, BH, qs, sc};
+    hipLaunchKernelGGL((bwd_kernel<C>), dim3((unsigned)(3LL * BH * nqb)), dim3(C::NTH), 0, st, a, nqb, hgrp);
+    return hipGetLastError();
+}
+
+// The workgroup shapes and their measured paces, as in the forward's tables:
+// t = t0 + |(a N, b pairs)|_2 us for the whole call, fitted to 1 to 96 heads
+// of 128 to 4096 tokens.
+constexpr Shape BH64[] = {{64, 13.5f, 10.f, 2.15f}, {128, 13.5f, 14.f, 1.5f}, {256, 13.f, 23.f, 1.22f},
+                          {256, 15.f, 36.f, 1.1f}};
+constexpr Shape BS16[] = {{32, 11.f, 5.9f, 2.6f}, {32, 10.5f, 8.5f, 1.6f}, {256, 13.f, 25.f, 1.25f}};
+constexpr Shape BS32[] = {{32, 13.f, 8.7f, 3.8f}, {64, 14.5f, 11.f, 2.4f}, {256, 15.f, 31.f, 1.65f}};
+constexpr Shape BS64[] = {{64, 17.f, 19.7f, 4.35f}, {128, 18.f, 28.f, 3.3f}, {256, 20.f, 47.f, 2.85f}};
+constexpr Shape BS128[] = {{128, 20.f, 45.f, 5.4f}, {256, 22.f, 70.f, 4.3f}};
+constexpr Shape BF128[] = {{128, 20.f, 82.f, 7.5f}, {256, 22.f, 90.f, 5.3f}};
+
+Moments moments_bwd(int D, int causal, int is_bf16, bool grade32)
+{
+    if (!grade32 && causal) return {12.f, 0.f, 113.f, 3.6f};
+    if (!grade32) return {40.f, .5f, 68.f, 3.25f};
+    switch (D) {
+    case 16: return {42.f, 0.f, 7.f, causal ? 1.75f : 1.25f};
+    case 32: return {60.f, 0.f, 13.f, causal ? 6.f : 4.4f};
+    case 64: return {110.f, 0.f, 30.f, 20.5f};
+    default: return {110.f, 0.f, 236.f, 162.f};
+    }
+}
+
+template <typename T, int D, bool CAUSAL, bool SPL>
+hipError_t launch_bwd_shape(const void *q, const void *k, const void *v, const void *o,
+                            const void *dout, const float *g, void *dq, void *dk, void *dv, int BH,
+                            int N, float qs, int shape, void *ws, hipStream_t st)
+{
+#define L(S, ...)                                                                                  \
+    do {                                                                                           \
+        typedef BwdCfg<T, D, CAUSAL, SPL, __VA_ARGS__> C;                                          \
+        static_assert(C::QB == (S).qb, "table");                                                   \
+        return launch_bwd<C>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st);                  \
+    } while (0)
+    if constexpr (D == 16) {
+        if (shape == 0) L(BS16[0], 1, 1, 8, 256);
+        if (shape == 1) L(BS16[1], 1, 1, 4, 128);
+        if (shape == 2) L(BS16[2], 1, 8, 1, 64);
+    } else if constexpr (D == 32) {
+        if (shape == 0) L(BS32[0], 1, 1, 8, 256);
+        if (shape == 1) L(BS32[1], 1, 2, 4, 128);
+        if (shape == 2) L(BS32[2], 1, 8, 1, 64);
+    } else if constexpr (D == 64 && !SPL) {
+        if (shape == 0) L(BH64[0], 1, 2, 4, 128);
+        if (shape == 1) L(BH64[1], 1, 4, 2, 128);
+        if (shape == 2) L(BH64[2], 1, 8, 1, 64);
+        if (shape == 3) L(BH64[3], 2, 4, 1, 32);
+    } else if constexpr (D == 64) {
+        if (shape == 0) L(BS64[0], 1, 2, 4, 128);
+        if (shape == 1) L(BS64[1], 1, 4, 2, 64);
+        if (shape == 2) L(BS64[2], 1, 8, 1, 64);
+    } else if constexpr (sizeof(T) == 2) {
+        if (shape == 0) L(BS128[0], 1, 4, 2, 64);
+        if (shape == 1) L(BS128[1], 1, 8, 1, 32);
+    } else {
+        if (shape == 0) L(BF128[0], 1, 4, 1, 32);
+        if (shape == 1) L(BF128[1], 1, 8, 1, 32);
+    }
+#undef L
+    return hipErrorInvalidValue;
+}
+
+}  // namespace pr
+
+int pairs_bwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t ws_bytes)
+{
+    using namespace pr;
+    if (p != 2) return -1;
+    const bool grade32 = pairs_grade32(N, D, causal, is_bf16);
+    const size_t rows = (size_t)BH * N;
+    if (ws_bytes < rows * (grade32 ? 8 * (size_t)D + sizeof(RowInfo) : 10 * (size_t)D + sizeof(RowInfoH))) return -1;
+    const Moments m = moments_bwd(D, causal, is_bf16, grade32);
+    switch (D) {
+    case 16: return pick(BS16, 3, m, BH, N, causal);
+    case 32: return pick(BS32, 3, m, BH, N, causal);
+    case 64: return grade32 ? pick(BS64, 3, m, BH, N, causal) : pick(BH64, 4, m, BH, N, causal);
+    case 128: return is_bf16 ? pick(BS128, 2, m, BH, N, causal) : pick(BF128, 2, m, BH, N, causal);
+    }
+    return -1;
+}
+
+hipError_t pairs_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
+                     const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
+                     int is_bf16, float qs, int shape, void *ws, hipStream_t st)
+{
+#define GO(T, DD, CA, SPL)                                                                         \
+    return pr::launch_bwd_shape<T, DD, CA, SPL>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, shape, \
+                                                ws, st)
+#define GO2(T, DD)                                                                                 \
+    do {                                                                                           \
+        if (causal) GO(T, DD, true, true);                                                         \
+        GO(T, DD, false, true);                                                                    \
+    } while (0)
+    if (is_bf16) {
+        switch (D) {
+        case 16: GO2(bf16_t, 16);
+        case 32: GO2(bf16_t, 32);
+        case 64:
+            if (causal) GO(bf16_t, 64, true, false);
+            if (pairs_grade32(N, D, causal, is_bf16)) GO(bf16_t, 64, false, true);
+            GO(bf16_t, 64, false, false);
+        case 128: GO2(bf16_t, 128);
+        }
+    } else {
+        switch (D) {
+        case 16: GO2(float, 16);
+        case 32: GO2(float, 32);
+        case 64: GO2(float, 64);
+        case 128: GO2(float, 128);
+        }
+    }
+#undef GO2
+#undef GO
+    return hipErrorInvalidValue;
+}
+
+}  // namespace fm

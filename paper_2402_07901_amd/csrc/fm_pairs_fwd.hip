@@ -14,8 +14,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <algorithm>
-#include <cmath>
 
 #include "fm_internal.h"
 #include "fm_pairs.h"
@@ -68,7 +66,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
     _Float16 *const vhi = khi + (SPL ? 2 : 1) * C::KH, *const vlo = vhi + C::VH;
     _Float16 *const qlo = (_Float16 *)(smem + C::TILE_BYTES);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, h = lane >> 5;
     const int wq = wave / C::NWK, wk = wave % C::NWK;
 
@@ -120,16 +118,16 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
     auto load_tile = [&](int t) {
 #pragma unroll
         for (int p = 0; p < C::NP; ++p) {
-            const int row = st0 + C::TPP * p, n = t * C::BK + row;
-            const bool ok = row < C::BK && n < N;
+            // rows past the end repeat the last one: their weights are masked
+            const unsigned n = (unsigned)min(t * C::BK + st0 + C::TPP * p, N - 1);
+            const unsigned off = n * (unsigned)D + 8u * sc;
             if constexpr (C::KP) {
-                kph[p].load((const bf16_t *)khat + (size_t)(ok ? n : 0) * D + 8 * sc, ok);
-                if constexpr (SPL)
-                    kpl[p].load((const bf16_t *)khat + klo_off + (size_t)(ok ? n : 0) * D + 8 * sc, ok);
+                kph[p].load((const bf16_t *)khat + off, true);
+                if constexpr (SPL) kpl[p].load((const bf16_t *)khat + klo_off + off, true);
             } else {
-                kr[p].load(k + (size_t)(ok ? n : 0) * D + 8 * sc, ok);
+                kr[p].load(k + off, true);
             }
-            vr[p].load(v + (size_t)(ok ? n : 0) * D + 8 * sc, ok);
+            vr[p].load(v + off, true);
         }
     };
     float vmax = 0.f;
@@ -156,6 +154,102 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
 
     f16v acc[NQ][CT], acl[NQ][C::LOACC ? CT : 1];
     float rs[NQ];
+    // One 32-key tile j of the staged step against the wave's queries; masked:
+    // some of its pairs lie beyond the diagonal or the last key.
+    auto tile = [&](int j, int kb, bool masked) {
+        f16v s[NQ];
+#pragma unroll
+        for (int u = 0; u < NQ; ++u)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[u][i] = 1.0f;
+        const _Float16 *kp = khi + (32 * j + r32) * RS + 8 * h;
+        // the products with a lo part first, while the sum is small (at
+        // D = 128 side by side with the main ones: fewer live operands)
+        if constexpr (SPL && D < 128) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const h8 a = ld8(kp + 16 * ks), b = ld8(kp + C::KH + 16 * ks);
+#pragma unroll
+                for (int u = 0; u < NQ; ++u) {
+                    s[u] = mma(a, ql[u][C::QLDS ? 0 : ks], s[u]);
+                    s[u] = mma(b, qh[u][ks], s[u]);
+                }
+            }
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const h8 a = ld8(kp + 16 * ks);
+            if constexpr (SPL && D >= 128) {
+                const h8 b = ld8(kp + C::KH + 16 * ks);
+#pragma unroll
+                for (int u = 0; u < NQ; ++u) {
+                    s[u] = mma(a, ld8(qlw + 32 * u * RS + 16 * ks), s[u]);
+                    s[u] = mma(b, qh[u][ks], s[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) s[u] = mma(a, qh[u][ks], s[u]);
+        }
+        // weights: s holds 1 + s; p = 2 takes 2 f_2 = (1 + s)^2 + 1 (the
+        // factor 2 cancels in F / G and is taken out of G)
+        h8 wh[NQ][2], wl[NQ][SPL ? 2 : 1];
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) {
+            const int qb0 = q0 + 32 * u;
+            float w[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) w[i] = C::P == 2 ? fmaf(s[u][i], s[u][i], 1.0f) : s[u][i];
+            if (masked) {
+                asm volatile("");   // a branch, not a compare and select per element of every tile
+                const int last = C::CAUSAL ? qb0 + r32 : N - 1;
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (kb + 8 * (i / 4) + 4 * h + i % 4 > last) w[i] = 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                split8<SPL>(w + 8 * e, wh[u][e], wl[u][SPL ? e : 0]);
+            }
+            if constexpr (SPL) {
+#pragma unroll
+                for (int d = 8; d; d /= 2)
+#pragma unroll
+                    for (int i = 0; i < d; ++i) w[i] += w[i + d];
+                rs[u] += w[0];
+            } else {
+                // the sum of the rounded weights, as the numerator takes them
+                const h2 one = {(_Float16)1.0f, (_Float16)1.0f};
+#pragma unroll
+                for (int i = 0; i < 16; i += 2)
+                    rs[u] = __builtin_amdgcn_fdot2(h2{wh[u][i / 8][i % 8], wh[u][i / 8][i % 8 + 1]},
+                                                   one, rs[u], false);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const h8 a = ld_tr<VS>(vhi, 32 * j + 16 * e, 32 * c);
+#pragma unroll
+                for (int u = 0; u < NQ; ++u) acc[u][c] = mma(a, wh[u][e], acc[u][c]);
+                if constexpr (SPL) {
+#pragma unroll
+                    for (int u = 0; u < NQ; ++u) {
+                        f16v &z = C::LOACC ? acl[u][C::LOACC ? c : 0] : acc[u][c];
+                        z = mma(a, wl[u][SPL ? e : 0], z);
+                    }
+                }
+                if constexpr (VSPL) {
+                    const h8 b = ld_tr<VS>(vlo, 32 * j + 16 * e, 32 * c);
+#pragma unroll
+                    for (int u = 0; u < NQ; ++u) {
+                        f16v &z = C::LOACC ? acl[u][C::LOACC ? c : 0] : acc[u][c];
+                        z = mma(b, wh[u][e], z);
+                    }
+                }
+            }
+    };
+
     for (int attempt = 0;; ++attempt) {
 #pragma unroll
         for (int t = 0; t < NQ; ++t) {
@@ -194,7 +288,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
                     float x[8];
 #pragma unroll
                     for (int i = 0; i < 8; ++i) x[i] = kr[p].get(i);
-                    standardise_group<D>(x, t * C::BK + row < N);
+                    standardise_group<D>(x, true);
                     split8<SPL>(x, hi, lo);
                     if (ok) {
                         *(h8 *)(khi + row * RS + 8 * sc) = hi;
@@ -208,96 +302,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
             for (int j = wk; j < C::BK / 32; j += C::NWK) {
                 const int kb = t * C::BK + 32 * j;
                 if (kb >= N || (C::CAUSAL && kb > q0 + 32 * NQ - 1)) break;
-                f16v s[NQ];
-#pragma unroll
-                for (int u = 0; u < NQ; ++u)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) s[u][i] = 1.0f;
-                const _Float16 *kp = khi + (32 * j + r32) * RS + 8 * h;
-                // the products with a lo part first, while the sum is small (at
-                // D = 128 side by side with the main ones: fewer live operands)
-                if constexpr (SPL && D < 128) {
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) {
-                        const h8 a = ld8(kp + 16 * ks), b = ld8(kp + C::KH + 16 * ks);
-#pragma unroll
-                        for (int u = 0; u < NQ; ++u) {
-                            s[u] = mma(a, ql[u][C::QLDS ? 0 : ks], s[u]);
-                            s[u] = mma(b, qh[u][ks], s[u]);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    const h8 a = ld8(kp + 16 * ks);
-                    if constexpr (SPL && D >= 128) {
-                        const h8 b = ld8(kp + C::KH + 16 * ks);
-#pragma unroll
-                        for (int u = 0; u < NQ; ++u) {
-                            s[u] = mma(a, ld8(qlw + 32 * u * RS + 16 * ks), s[u]);
-                            s[u] = mma(b, qh[u][ks], s[u]);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < NQ; ++u) s[u] = mma(a, qh[u][ks], s[u]);
-                }
-                // weights: s holds 1 + s; p = 2 takes 2 f_2 = (1 + s)^2 + 1 (the
-                // factor 2 cancels in F / G and is taken out of G)
-                h8 wh[NQ][2], wl[NQ][SPL ? 2 : 1];
-#pragma unroll
-                for (int u = 0; u < NQ; ++u) {
-                    const int qb0 = q0 + 32 * u;
-                    float w[16];
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) w[i] = C::P == 2 ? fmaf(s[u][i], s[u][i], 1.0f) : s[u][i];
-                    if ((C::CAUSAL && kb + 31 > qb0) || kb + 32 > N) {
-                        const int last = C::CAUSAL ? qb0 + r32 : N - 1;
-#pragma unroll
-                        for (int i = 0; i < 16; ++i)
-                            if (kb + 8 * (i / 4) + 4 * h + i % 4 > last) w[i] = 0.f;
-                    }
-#pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        split8<SPL>(w + 8 * e, wh[u][e], wl[u][SPL ? e : 0]);
-                    }
-                    if constexpr (SPL) {
-#pragma unroll
-                        for (int d = 8; d; d /= 2)
-#pragma unroll
-                            for (int i = 0; i < d; ++i) w[i] += w[i + d];
-                        rs[u] += w[0];
-                    } else {
-                        // the sum of the rounded weights, as the numerator takes them
-                        const h2 one = {(_Float16)1.0f, (_Float16)1.0f};
-#pragma unroll
-                        for (int i = 0; i < 16; i += 2)
-                            rs[u] = __builtin_amdgcn_fdot2(h2{wh[u][i / 8][i % 8], wh[u][i / 8][i % 8 + 1]},
-                                                           one, rs[u], false);
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 2; ++e)
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) {
-                        const h8 a = ld_tr<VS>(vhi, 32 * j + 16 * e, 32 * c);
-#pragma unroll
-                        for (int u = 0; u < NQ; ++u) acc[u][c] = mma(a, wh[u][e], acc[u][c]);
-                        if constexpr (SPL) {
-#pragma unroll
-                            for (int u = 0; u < NQ; ++u) {
-                                f16v &z = C::LOACC ? acl[u][C::LOACC ? c : 0] : acc[u][c];
-                                z = mma(a, wl[u][SPL ? e : 0], z);
-                            }
-                        }
-                        if constexpr (VSPL) {
-                            const h8 b = ld_tr<VS>(vlo, 32 * j + 16 * e, 32 * c);
-#pragma unroll
-                            for (int u = 0; u < NQ; ++u) {
-                                f16v &z = C::LOACC ? acl[u][C::LOACC ? c : 0] : acc[u][c];
-                                z = mma(b, wh[u][e], z);
-                            }
-                        }
-                    }
+                tile(j, kb, (C::CAUSAL && kb + 31 > q0) || kb + 32 > N);
             }
         }
         if (attempt || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
@@ -425,10 +430,6 @@ __global__ __launch_bounds__(256) void khat_kernel(const T *__restrict__ k, _Flo
 // 96 heads of 256 to 8192 tokens, causal (pairs = heads N (N + queries per
 // workgroup) / 2; without the mask b is 0.85 to 0.95 of it).  Waves that split
 // the keys shorten a, waves that share a staged tile lower b.
-struct Shape {
-    int qb;
-    float t0, a, b;
-};
 // fp16 operands: bf16, D = 64
 constexpr Shape SH64[] = {{32, 5.f, 7.6f, 1.13f}, {64, 4.f, 9.6f, .68f}, {128, 5.f, 13.f, .455f},
                           {128, 4.f, 20.5f, .375f}, {256, 7.f, 17.f, .31f}, {512, 6.f, 31.f, .275f}};
@@ -439,15 +440,10 @@ constexpr Shape SS64[] = {{64, 6.f, 15.4f, 1.14f}, {128, 6.f, 21.2f, .82f}, {256
 constexpr Shape SS128[] = {{64, 7.f, 25.f, 1.67f}, {128, 7.f, 36.f, 1.27f}, {256, 7.f, 57.f, 1.05f}};
 constexpr Shape SF128[] = {{32, 7.f, 36.f, 4.9f}, {128, 7.f, 42.5f, 1.7f}, {256, 7.f, 69.f, 1.43f}};
 
-// The moment kernels' forward, t = t0 + h heads + max(a N, b heads N)
-// (a and b in ns per token).
-struct Moments {
-    float t0, h, a, b;
-};
-Moments moments_fwd(int N, int D, int causal, int is_bf16)
+Moments moments_fwd(int D, int causal, bool grade32)
 {
-    if (is_bf16 && D == 64 && causal) return {12.f, 0.f, 50.f, .95f};
-    if (is_bf16 && D == 64 && N >= 128) return {25.f, .5f, 5.5f, .87f};
+    if (!grade32 && causal) return {12.f, 0.f, 50.f, .95f};
+    if (!grade32) return {25.f, .5f, 5.5f, .87f};
     switch (D) {
     case 16: return {13.f, 0.f, 2.4f, causal ? .425f : .28f};
     case 32: return {15.f, 0.f, 4.5f, causal ? 1.65f : 1.15f};
@@ -517,64 +513,53 @@ hipError_t launch_shape(const void *q, const void *k, const void *v, void *out, 
 
 }  // namespace pr
 
-// The fastest shape by the tables above, or -1 where the moment kernels are
-// faster (by 3% at least: near the line the rule stays with them).  ws_bytes
-// bounds the shape that keeps k^ there.
 int pairs_fwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t ws_bytes)
 {
     using namespace pr;
     if (p != 2) return -1;
-    const Shape *s = SS16;
-    int n = 3;
+    const bool grade32 = pairs_grade32(N, D, causal, is_bf16);
+    const Moments m = moments_fwd(D, causal, grade32);
     switch (D) {
-    case 16: break;
-    case 32: s = SS32; break;
+    case 16: return pick(SS16, 3, m, BH, N, causal);
+    case 32: return pick(SS32, 3, m, BH, N, causal);
     case 64:
-        s = is_bf16 ? SH64 : SS64;
-        n = is_bf16 ? 6 : 3;
-        break;
-    case 128: s = is_bf16 ? SS128 : SF128; break;
-    default: return -1;
+        if (grade32) return pick(SS64, 3, m, BH, N, causal);
+        // shape 4 keeps k^ in the workspace
+        return pick(SH64, 6, m, BH, N, causal, ws_bytes < (size_t)BH * N * 128 ? 4 : -1);
+    case 128: return is_bf16 ? pick(SS128, 3, m, BH, N, causal) : pick(SF128, 3, m, BH, N, causal);
     }
-    const double tok = (double)N;
-    const Moments m = moments_fwd(N, D, causal, is_bf16);
-    double best = m.t0 + m.h * BH + 1e-3 * std::max(m.a * tok, m.b * tok * BH);
-    best *= 0.97;
-    int shape = -1;
-    for (int i = 0; i < n; ++i) {
-        if (s == SH64 && i == 4 && ws_bytes < (size_t)BH * N * 64 * 2) continue;
-        const double pairs = causal ? 0.5 * BH * tok * (tok + s[i].qb) : 0.95 * BH * tok * tok;
-        const double t = s[i].t0 + std::hypot(1e-3 * s[i].a * tok, 1e-6 * s[i].b * pairs);
-        if (t < best) {
-            best = t;
-            shape = i;
-        }
-    }
-    return shape;
+    return -1;
 }
 
 hipError_t pairs_fwd(const void *q, const void *k, const void *v, void *out, float *g, int BH,
                      int N, int D, int causal, int is_bf16, float qs, int shape, void *ws,
                      hipStream_t st)
 {
-#define GO(T, DD, SPL)                                                                            \
-    return causal ? pr::launch_shape<T, DD, true, SPL>(q, k, v, out, g, BH, N, qs, shape, ws, st) \
-                  : pr::launch_shape<T, DD, false, SPL>(q, k, v, out, g, BH, N, qs, shape, ws, st)
+#define GO(T, DD, CA, SPL) return pr::launch_shape<T, DD, CA, SPL>(q, k, v, out, g, BH, N, qs, shape, ws, st)
+#define GO2(T, DD)                                                                                 \
+    do {                                                                                           \
+        if (causal) GO(T, DD, true, true);                                                         \
+        GO(T, DD, false, true);                                                                    \
+    } while (0)
     if (is_bf16) {
         switch (D) {
-        case 16: GO(bf16_t, 16, true);
-        case 32: GO(bf16_t, 32, true);
-        case 64: GO(bf16_t, 64, false);
-        case 128: GO(bf16_t, 128, true);
+        case 16: GO2(bf16_t, 16);
+        case 32: GO2(bf16_t, 32);
+        case 64:
+            if (causal) GO(bf16_t, 64, true, false);
+            if (pairs_grade32(N, D, causal, is_bf16)) GO(bf16_t, 64, false, true);
+            GO(bf16_t, 64, false, false);
+        case 128: GO2(bf16_t, 128);
         }
     } else {
         switch (D) {
-        case 16: GO(float, 16, true);
-        case 32: GO(float, 32, true);
-        case 64: GO(float, 64, true);
-        case 128: GO(float, 128, true);
+        case 16: GO2(float, 16);
+        case 32: GO2(float, 32);
+        case 64: GO2(float, 64);
+        case 128: GO2(float, 128);
         }
     }
+#undef GO2
 #undef GO
     return hipErrorInvalidValue;
 }

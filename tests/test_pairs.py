@@ -1,5 +1,5 @@
-"""The pair kernels (fm_pairs_fwd.hip): explicit 32 x 32 weight tiles for short
-sequences.
+"""The pair kernels (fm_pairs_fwd.hip, fm_pairs_bwd.hip): explicit 32 x 32
+weight tiles for short sequences.
 
 Every workgroup shape of the plan, at sizes that straddle its tiles (32 keys,
 32 queries, the keys staged per step, the queries of a workgroup), against the
@@ -21,12 +21,12 @@ from paper_2402_07901_amd.inputs import bf16_bits_to_f64, f32_to_bf16_bits, make
 from gpu_util import TOL, max_rel, say, to_dev, to_f64
 
 
-def plan(BH, N, D, causal, dt):
+def plan(BH, N, D, causal, dt, backward=False):
     """The shape the library picks (-1: the moment kernels)."""
-    f = getattr(fm.lib(), "_ZN2fm14pairs_fwd_planEiiiiiim")
+    f = getattr(fm.lib(), f"_ZN2fm14pairs_{'bwd' if backward else 'fwd'}_planEiiiiiim")
     f.restype = ctypes.c_int
     code = fm.BF16 if dt == "bf16" else fm.F32
-    ws = fm.workspace_bytes(1, BH, N, D, 2, causal, code)
+    ws = fm.workspace_bytes(1, BH, N, D, 2, causal, code, backward)
     return f(BH, N, D, 2, int(causal), int(dt == "bf16"), ctypes.c_size_t(ws))
 
 
@@ -38,13 +38,30 @@ CASES = [
     (24, 700, 64, "f32"), (64, 1025, 64, "f32"), (64, 2049, 64, "f32"), (2, 32, 128, "f32"), (16, 513, 128, "f32"),
     (64, 1025, 128, "f32"), (1, 127, 128, "bf16"), (16, 1025, 128, "bf16"),
     (64, 1023, 128, "bf16"),
-    (1, 1, 64, "bf16"), (2, 64, 64, "bf16"), (1, 700, 64, "bf16"), (16, 515, 64, "bf16"),
-    (24, 1300, 64, "bf16"), (48, 1025, 64, "bf16"), (96, 2305, 64, "bf16"),
+    (1, 1, 64, "bf16"), (2, 64, 64, "bf16"), (5, 127, 64, "bf16"), (1, 700, 64, "bf16"),
+    (16, 515, 64, "bf16"), (24, 1300, 64, "bf16"), (48, 1025, 64, "bf16"), (96, 2305, 64, "bf16"),
     (200, 512, 64, "bf16"), (96, 4700, 64, "bf16"),
 ]
 
 
+BWD_CASES = [
+    (1, 1, 16, "f32"), (2, 257, 16, "f32"), (16, 300, 16, "f32"), (64, 801, 16, "f32"),
+    (3, 33, 16, "bf16"), (1, 255, 32, "f32"), (1, 2047, 32, "f32"), (8, 1030, 32, "f32"),
+    (64, 700, 32, "f32"), (5, 129, 32, "bf16"), (3, 65, 64, "f32"), (24, 700, 64, "f32"),
+    (64, 900, 64, "f32"), (2, 32, 128, "f32"), (16, 513, 128, "f32"), (64, 1025, 128, "f32"),
+    (1, 127, 128, "bf16"), (64, 1023, 128, "bf16"), (1, 1, 64, "bf16"), (2, 64, 64, "bf16"),
+    (1, 700, 64, "bf16"), (16, 515, 64, "bf16"), (24, 1300, 64, "bf16"), (96, 1025, 64, "bf16"),
+    (96, 2305, 64, "bf16"),
+]
+
+
 def test_every_shape_is_reached():
+    want = {(16, "f32"): 3, (32, "f32"): 3, (64, "f32"): 3, (128, "f32"): 2, (128, "bf16"): 2,
+            (64, "bf16"): 4}
+    for (D, dt), n in want.items():
+        got = {plan(BH, N, D, c, dt, True) for BH, N, d, t in BWD_CASES if (d, t) == (D, dt)
+               for c in (True, False)}
+        assert set(range(n)) <= got, ("backward", D, dt, got)
     want = {(16, "f32"): 3, (32, "f32"): 3, (64, "f32"): 3, (128, "f32"): 3, (128, "bf16"): 3,
             (64, "bf16"): 6}
     for (D, dt), n in want.items():
@@ -58,8 +75,27 @@ def test_plan_keeps_the_moments_for_long_sequences():
     assert plan(64, 8192, 64, True, "bf16") == -1
     assert plan(8, 131072, 64, False, "bf16") == -1
     assert plan(8, 65536, 64, True, "bf16") == -1
+    assert plan(64, 8192, 64, True, "bf16", True) == -1
     for D in (16, 32, 64, 128):
-        assert plan(4, 1 << 20, D, True, "f32") == -1
+        for back in (False, True):
+            assert plan(4, 1 << 20, D, True, "f32", back) == -1
+
+
+def test_plan_stays_within_the_workspace():
+    """The scratch a shape takes never exceeds what the call asks for, whose
+    size is the moment path's."""
+    for D in (16, 32, 64, 128):
+        for dt in ("f32", "bf16"):
+            for causal in (True, False):
+                for BH, N in ((1, 1), (1, 127), (7, 100), (96, 64), (96, 127), (300, 33), (96, 777)):
+                    code = fm.BF16 if dt == "bf16" else fm.F32
+                    have = fm.workspace_bytes(1, BH, N, D, 2, causal, code, True)
+                    half = dt == "bf16" and D == 64 and (causal or N >= 128)
+                    if plan(BH, N, D, causal, dt, True) >= 0:
+                        assert have >= BH * N * (656 if half else 8 * D + 8)
+                    have = fm.workspace_bytes(1, BH, N, D, 2, causal, code, False)
+                    if half and plan(BH, N, D, causal, dt) == 4:
+                        assert have >= BH * N * 128
 
 
 def heads_of(inp, sel):
@@ -79,6 +115,13 @@ def check(inp, dt, causal, label):
         eg = float((np.abs(g[h] - rg[0, 0]) / np.abs(rg[0, 0])).max())
         say(f"{label} head {h}: E_O={eo:.2e} E_G={eg:.2e}")
         assert eo <= TOL[dt] and eg <= TOL[dt], (label, h, eo, eg)
+        if "D64 bf16 cFalse" in label and N_of(inp) < 128:
+            # float32-grade operands: 2^-22 a product, G of at most 127 keys
+            assert eg <= 1e-5, (label, h, eg)
+
+
+def N_of(inp):
+    return inp["q"].shape[2]
 
 
 @pytest.mark.gpu
@@ -89,16 +132,70 @@ def test_shapes_against_explicit_matrix(BH, N, D, dt, causal):
     check(inp, dt, causal, f"BH{BH} N{N} D{D} {dt} c{causal} shape {plan(BH, N, D, causal, dt)}")
 
 
-def scale_values(inp, dt, factor):
-    """v rows times factor [N] (a power of two: exact)."""
-    v = inp["v64"] * factor[None, None, :, None]
+def check_bwd(inp, dt, causal, scale, label):
+    BH, N, D = inp["q64"].shape[1:]
+    q, k, v, do = (to_dev(inp[n], dt) for n in ("q", "k", "v", "dout"))
+    o, g = fm.fastmax_fwd(q, k, v, p=2, causal=causal, scale=scale)
+    grads = fm.fastmax_bwd(q, k, v, o, do, g, p=2, causal=causal, scale=scale)
+    again = fm.fastmax_bwd(q, k, v, o, do, g, p=2, causal=causal, scale=scale)
+    if plan(BH, N, D, causal, dt, True) >= 0:
+        # one owner per output row: the same bits every time
+        assert all(torch.equal(a, b) for a, b in zip(grads, again)), label
+    grads = [to_f64(x).reshape(BH, N, D) for x in grads]
+    for h in sorted({0, BH // 2, BH - 1}):
+        q64, k64, v64 = heads_of(inp, h)
+        d64 = inp["dout64"].reshape(BH, N, D)[h]
+        ref = oracle.bwd_brute(*(x[None, None] for x in (q64, k64, v64, d64)), 2, causal,
+                               scale=scale)
+        # entries are held to the largest of the head's gradient, or of
+        # |dO| |v| sqrt(D) where the exact gradient vanishes (one key: dq = dk = 0)
+        floor = np.abs(d64).max() * np.abs(v64).max() * np.sqrt(D) if N == 1 else 0.0
+        for name, x, r in zip(("dq", "dk", "dv"), grads, ref):
+            den = max(np.abs(r).max(), floor if name != "dv" else 0.0)
+            e = float(np.abs(x[h] - r[0, 0]).max() / den)
+            say(f"{label} head {h} {name}: {e:.2e}")
+            assert e <= TOL[dt], (label, h, name, e)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("BH,N,D,dt", BWD_CASES)
+def test_backward_shapes_against_explicit_gradient(BH, N, D, dt, causal):
+    inp = make_inputs(1, BH, N, D, 7400 + N, dt, with_dout=True)
+    check_bwd(inp, dt, causal, 1.0, f"bwd BH{BH} N{N} D{D} {dt} c{causal} shape "
+              f"{plan(BH, N, D, causal, dt, True)}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("D,dt", [(64, "bf16"), (128, "bf16"), (32, "f32"), (64, "f32")])
+@pytest.mark.parametrize("kind", ["late", "zeros", "tau", "huge", "tiny"])
+def test_backward_scales(D, dt, causal, kind):
+    """Rows of v and dO that differ by large powers of two, rows of zeros, a
+    small score scale, and values near the ends of the range."""
+    N = 300
+    f = np.ones(N)
+    if kind == "late":
+        f[200:] = 2.0 ** 12
+    elif kind == "zeros":
+        f[:150] = 0.0
+    elif kind != "tau":
+        f[:] = 2.0 ** (55 if kind == "huge" else -55)
+    inp = scale_values(make_inputs(1, 3, N, D, 7500, dt, with_dout=True), dt, f)
+    inp = scale_values(inp, dt, f[::-1] if kind == "late" else f, "dout")
+    check_bwd(inp, dt, causal, 1.0 / D if kind == "tau" else 1.0, f"bwd {kind} D{D} {dt} c{causal}")
+
+
+def scale_values(inp, dt, factor, name="v"):
+    """Rows of v (or dout) times factor [N] (powers of two: exact)."""
+    v = inp[name + "64"] * factor[None, None, :, None]
     out = dict(inp)
     if dt == "bf16":
-        out["v"] = f32_to_bf16_bits(v.astype(np.float32))
-        out["v64"] = bf16_bits_to_f64(out["v"])
+        out[name] = f32_to_bf16_bits(v.astype(np.float32))
+        out[name + "64"] = bf16_bits_to_f64(out[name])
     else:
-        out["v"] = v.astype(np.float32)
-        out["v64"] = out["v"].astype(np.float64)
+        out[name] = v.astype(np.float32)
+        out[name + "64"] = out[name].astype(np.float64)
     return out
 
 
