@@ -40,6 +40,16 @@
 // and perform the same operations in the same order as one workgroup over
 // all chunks: split and unsplit scans give bit-identical results.
 //
+// Many segments (few heads, long sequences: B H x 4 workgroups would leave
+// most of the chip idle).  Three launches: every segment but the last sums its
+// own chunks (MULTI = 1: the build-only loop, its sums stored as the summary
+// of the next segment), seg_prefix_kernel turns them into prefixes, and every
+// segment scans its chunks from its prefix (MULTI = 2).  The build costs about
+// half a scan of the same chunks, so it pays from three segments up.  q is
+// standardised while it is staged (its fp16 copy's place in the workspace
+// holds the summaries), and max |v| comes from block maxima instead of a pass
+// over the slice in each of the segments.
+//
 // State numerics.  The state lives in fp16 (v is pre-scaled by a power of two
 // 2^-e per workgroup so that no entry, bounded by N * 63 * max|v|, can exceed
 // 2^15).  A tile's accumulator layout holds exactly the elements of its half of
@@ -136,6 +146,12 @@ struct SegArgs {
     int split;              // 0: one workgroup per (head, slice); 1: two
     int csplit;             // first chunk of segment 1
     int wait;               // 1: segment 1 waits for segment 0's summary; 0: rebuilds it
+    // Many segments (see "Many segments"): nseg of cseg chunks (cseg even),
+    // summaries [item][segment], the block maxima of |v| ([head][nvb][slice],
+    // 32 tokens a block), and the score scale of the raw q.
+    int nseg, cseg, nvb;
+    const float *vmax;
+    float qs;
 };
 // summary layout: fp16 state [wave][pair][lane] (h8), Y3 accumulators
 // [helper][tile][lane] (f4), y2, y2 scaled, x1 (fp32)
@@ -205,7 +221,7 @@ __device__ __forceinline__ h8 set_half(h8 x, h4 r)
 // id must be a multiple of 8 for the XCD mapping below).  Blocks
 // [0, nitems) are the (head, slice) items (their first segments when the
 // scan is split), blocks [nitems, 2 nitems) their second segments.
-template <bool DV>
+template <bool DV, int MULTI = 0>
 __device__ __forceinline__ void scan_block(Smem &sm, const _Float16 *__restrict__ q,
                                            const _Float16 *__restrict__ k,
                                            const bf16_t *__restrict__ v, bf16_t *__restrict__ out,
@@ -213,7 +229,10 @@ __device__ __forceinline__ void scan_block(Smem &sm, const _Float16 *__restrict_
                                            int N, int BH, int b, int nitems, const SegArgs &sa)
 {
     int seg = 0;
-    if (sa.split && b >= nitems) {
+    if constexpr (MULTI != 0) {
+        seg = b / nitems;
+        b -= seg * nitems;
+    } else if (sa.split && b >= nitems) {
         seg = 1;
         b -= nitems;
     }
@@ -244,28 +263,33 @@ __device__ __forceinline__ void scan_block(Smem &sm, const _Float16 *__restrict_
     {
         const int tid = threadIdx.x;
         float vmax = 0.f;
-        constexpr int U = 8;
-        for (int p0 = tid; p0 < 2 * N; p0 += U * NTH) {
-            uint4 raw[U];
-            float rr[U];
+        if constexpr (MULTI != 0) {
+            const float *mv = sa.vmax + (size_t)head * sa.nvb * NSL + sl;
+            for (int i = tid; i < sa.nvb; i += NTH) vmax = fmaxf(vmax, mv[(size_t)i * NSL]);
+        } else {
+            constexpr int U = 8;
+            for (int p0 = tid; p0 < 2 * N; p0 += U * NTH) {
+                uint4 raw[U];
+                float rr[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int p = p0 + u * NTH, n = p >> 1, hh = p & 1;
-                raw[u] = uint4{0u, 0u, 0u, 0u};
-                rr[u] = 0.0f;
-                if (p < 2 * N) {
-                    raw[u] = *(const uint4 *)(v + (size_t)n * D + SL * sl + 8 * hh);
-                    // raw: no arithmetic on a loaded value before all U are issued
-                    rr[u] = DV ? rg[n] : 1.0f;
+                for (int u = 0; u < U; ++u) {
+                    const int p = p0 + u * NTH, n = p >> 1, hh = p & 1;
+                    raw[u] = uint4{0u, 0u, 0u, 0u};
+                    rr[u] = 0.0f;
+                    if (p < 2 * N) {
+                        raw[u] = *(const uint4 *)(v + (size_t)n * D + SL * sl + 8 * hh);
+                        // raw: no arithmetic on a loaded value before all U are issued
+                        rr[u] = DV ? rg[n] : 1.0f;
+                    }
                 }
-            }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                float x[8];
-                bf16x8_to_f32(raw[u], x);
-                const float ar = fabsf(rr[u]);
+                for (int u = 0; u < U; ++u) {
+                    float x[8];
+                    bf16x8_to_f32(raw[u], x);
+                    const float ar = fabsf(rr[u]);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) vmax = fmaxf(vmax, fabsf(x[i]) * ar);
+                    for (int i = 0; i < 8; ++i) vmax = fmaxf(vmax, fabsf(x[i]) * ar);
+                }
             }
         }
 #pragma unroll
@@ -286,12 +310,16 @@ __device__ __forceinline__ void scan_block(Smem &sm, const _Float16 *__restrict_
 
     // chunk range of this workgroup; [cstart, cbeg) are build-only chunks
     // (a second segment rebuilding its prefix)
-    const int cbeg = seg ? sa.csplit : 0;
-    const int cend = (sa.split && seg == 0) ? sa.csplit : nch;
-    int cstart = cbeg;
-    bool loaded = false;
-    unsigned char *sum = sa.split ? sa.sum + (size_t)item * SUM_BYTES : nullptr;
-    if (seg == 1) {
+    const int cbeg = MULTI == 1 ? (seg + 1) * sa.cseg : MULTI == 2 ? seg * sa.cseg : seg ? sa.csplit : 0;
+    const int cend = MULTI == 1 ? cbeg
+                   : MULTI == 2 ? min(nch, cbeg + sa.cseg)
+                   : (sa.split && seg == 0) ? sa.csplit : nch;
+    int cstart = MULTI == 1 ? seg * sa.cseg : cbeg;
+    bool loaded = MULTI == 2 && seg > 0;
+    unsigned char *sum = MULTI != 0 ? sa.sum + ((size_t)item * sa.nseg + seg + (MULTI == 1)) * SUM_BYTES
+                       : sa.split ? sa.sum + (size_t)item * SUM_BYTES : nullptr;
+    const bool emit = MULTI != 0 ? MULTI == 1 : sum && seg == 0;
+    if (MULTI == 0 && seg == 1) {
         if (sa.wait) {
             // one thread polls; the summary loads (sum_get) come after the
             // barrier that follows
@@ -453,7 +481,7 @@ __device__ __forceinline__ void scan_block(Smem &sm, const _Float16 *__restrict_
             });
             __syncthreads();
         }
-        if (sum && seg == 0) {
+        if (emit) {
 #pragma unroll
             for (int p = 0; p < NKS; ++p)
                 sum_put_lane(sum_ast + (w * NKS + p) * 128, threadIdx.x & 63, Ast[p]);
@@ -501,7 +529,7 @@ __device__ __forceinline__ void scan_block(Smem &sm, const _Float16 *__restrict_
                 const _Float16 *qp = q + p0 * D + 8 * cg, *kp = k + p0 * D + 8 * cg;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    pq[j] = *(const uint4 *)(qp + j * step);
+                    pq[j] = MULTI == 1 ? z : *(const uint4 *)(qp + j * step);
                     pk[j] = *(const uint4 *)(kp + j * step);
                 }
             } else {
@@ -511,7 +539,7 @@ __device__ __forceinline__ void scan_block(Smem &sm, const _Float16 *__restrict_
                     pq[j] = pk[j] = z;
                     if (n < N) {
                         const size_t pn = DV ? (size_t)(N - 1 - n) : (size_t)n;
-                        pq[j] = *(const uint4 *)(q + pn * D + 8 * cg);
+                        if (MULTI != 1) pq[j] = *(const uint4 *)(q + pn * D + 8 * cg);
                         pk[j] = *(const uint4 *)(k + pn * D + 8 * cg);
                     }
                 }
@@ -537,7 +565,12 @@ __device__ __forceinline__ void scan_block(Smem &sm, const _Float16 *__restrict_
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int row = 4 * tg + j;
-                const h8 hq = __builtin_bit_cast(h8, pq[j]);
+                h8 hq = __builtin_bit_cast(h8, pq[j]);
+                if constexpr (MULTI == 2) {
+                    float xq[8];
+                    bf16x8_to_f32(pq[j], xq);
+                    hq = standardise8(xq, c * C + row < N, sa.qs);
+                }
                 *(h8 *)(sm.qrow + sw64(row, 8 * cg)) = hq;
                 hk[j] = __builtin_bit_cast(h8, pk[j]);
                 *(h8 *)(sm.krow + sw64(row, 8 * cg)) = hk[j];
@@ -731,7 +764,7 @@ __device__ __forceinline__ void scan_block(Smem &sm, const _Float16 *__restrict_
             if (more) stage(c + 1);
             __syncthreads();
         }
-        if (sum && seg == 0) {
+        if (emit) {
             // the summary: Y3 accumulators and the prefix sums after the last chunk
             const int ln = threadIdx.x & 63, ht = threadIdx.x - NSW * 64, cb = cend & 1;
 #pragma unroll
@@ -743,7 +776,7 @@ __device__ __forceinline__ void scan_block(Smem &sm, const _Float16 *__restrict_
             if (ht < SL) sum_put_f(sum_misc + 2 * D + ht, sm.x1[cb][ht]);
         }
     }
-    if (sum && seg == 0) {
+    if (MULTI == 0 && emit) {
         // publish: every thread's summary stores have completed (waitcnt on
         // all counters) before the barrier, the flag goes up after it
         __builtin_amdgcn_s_waitcnt(0);

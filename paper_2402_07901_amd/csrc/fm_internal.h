@@ -130,6 +130,9 @@ hipError_t f32mfma_bwd(const void *q, const void *k, const void *v, const void *
 hipError_t mfma_causal_fwd(const void *q, const void *k, const void *v, void *out, float *g,
                            int BH, int N, float qs, void *ws, hipStream_t st);
 size_t mfma_causal_fwd_workspace(int BH, int N);
+// Segments of the forward scan of few heads over a long sequence (0: not cut
+// into many).
+int causal_multi_segments(int BH, int N);
 size_t mfma_causal_smem_bytes();
 
 // MFMA causal backward: D = 64, p = 2, bf16 I/O.  ws holds

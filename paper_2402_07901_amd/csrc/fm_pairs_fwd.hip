@@ -440,8 +440,11 @@ constexpr Shape SS64[] = {{64, 6.f, 15.4f, 1.14f}, {128, 6.f, 21.2f, .82f}, {256
 constexpr Shape SS128[] = {{64, 7.f, 25.f, 1.67f}, {128, 7.f, 36.f, 1.27f}, {256, 7.f, 57.f, 1.05f}};
 constexpr Shape SF128[] = {{32, 7.f, 36.f, 4.9f}, {128, 7.f, 42.5f, 1.7f}, {256, 7.f, 69.f, 1.43f}};
 
-Moments moments_fwd(int D, int causal, bool grade32)
+Moments moments_fwd(int BH, int N, int D, int causal, bool grade32)
 {
+    // the causal scan cut into many segments
+    if (!grade32 && causal)
+        if (const int S = causal_multi_segments(BH, N)) return {40.f, 0.f, 83.f / S, 0.f};
     if (!grade32 && causal) return {12.f, 0.f, 50.f, .95f};
     if (!grade32) return {25.f, .5f, 5.5f, .87f};
     switch (D) {
@@ -518,7 +521,7 @@ int pairs_fwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t 
     using namespace pr;
     if (p != 2) return -1;
     const bool grade32 = pairs_grade32(N, D, causal, is_bf16);
-    const Moments m = moments_fwd(D, causal, grade32);
+    const Moments m = moments_fwd(BH, N, D, causal, grade32);
     switch (D) {
     case 16: return pick(SS16, 3, m, BH, N, causal);
     case 32: return pick(SS32, 3, m, BH, N, causal);

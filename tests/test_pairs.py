@@ -237,6 +237,31 @@ def test_constant_row_and_infinite_value_stay_in_their_rows(D, dt):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("BH,N", [(1, 40000), (5, 24577), (16, 26111), (21, 24700)])
+def test_many_segment_scan(BH, N):
+    """Few heads over a long sequence: the causal scan cut into many segments
+    (a ragged last one among them) against the oracle's sampled rows, every
+    segment's edge rows included."""
+    f = getattr(fm.lib(), "_ZN2fm21causal_multi_segmentsEii")
+    S = f(BH, N)
+    assert S >= 3 and plan(BH, N, 64, True, "bf16") == -1
+    inp = make_inputs(1, BH, N, 64, 7600 + BH, "bf16")
+    q, k, v = (to_dev(inp[n], "bf16") for n in ("q", "k", "v"))
+    o, g = fm.fastmax_fwd(q, k, v, p=2, causal=True, scale=0.125)
+    o, g = to_f64(o).reshape(-1, 64), g.cpu().numpy().astype(np.float64).reshape(-1)
+    nch = (N + 127) // 128
+    cseg = (-(-nch // S) + 1) & ~1
+    edges = [e for s in range(1, S) for e in (s * cseg * 128 - 1, s * cseg * 128)]
+    local = sorted({0, 127, 128, N - 1, *edges, *np.random.default_rng(1).integers(0, N, 12).tolist()})
+    rows = [h * N + i for h in {0, BH - 1} for i in local if i < N]
+    ro, rg = oracle.fwd_rows(inp["q64"], inp["k64"], inp["v64"], 2, True, rows, scale=0.125)
+    eo = float((np.abs(o[rows] - ro).max(-1) / np.abs(ro).max()).max())
+    eg = float((np.abs(g[rows] - rg) / rg).max())
+    say(f"BH{BH} N{N} S{S}: E_O={eo:.2e} E_G={eg:.2e}")
+    assert eo <= TOL["bf16"] and eg <= TOL["bf16"]
+
+
+@pytest.mark.gpu
 def test_scan_modes_agree_where_the_scan_serves():
     """The segment modes of the causal scan give the same bits at a size that
     the plan leaves to it."""
