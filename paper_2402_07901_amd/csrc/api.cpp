@@ -165,7 +165,9 @@ int fwd_run(const void *q, const void *k, const void *v, void *out, float *g, in
     const int bf = dt == FASTMAX_BF16;
     // Short sequences: explicit pairs (the plan's tables hold both sides).
     const int shape = pairs_fwd_plan(B * H, N, D, p, causal, bf, fwd_ws(B, H, N, D, p, causal, dt));
-    if (shape >= 0 && fwd_grids_fit(B * H, N, D, p, causal, dt))
+    if (linear_plan(B * H, N, D, p, causal, bf, qk_scale, 0, 0) && fwd_grids_fit(B * H, N, D, p, causal, dt))
+        e = linear_fwd(q, k, v, out, g, B * H, N, D, causal, qk_scale, stream);
+    else if (shape >= 0 && fwd_grids_fit(B * H, N, D, p, causal, dt))
         e = pairs_fwd(q, k, v, out, g, B * H, N, D, causal, bf, qk_scale, shape, workspace, stream);
     else if (mfma_causal(D, p, causal, dt))
         e = mfma_causal_fwd(q, k, v, out, g, B * H, N, qk_scale, workspace, stream);
@@ -216,7 +218,11 @@ int bwd_impl(const void *q, const void *k, const void *v, const void *out, const
     hipError_t e;
     const int bf = dt == FASTMAX_BF16;
     const int shape = fm::pairs_bwd_plan(B * H, N, D, p, causal, bf, need);
-    if (shape >= 0 && bwd_grids_fit(B * H, N, D, p, causal, dt))
+    if (fm::linear_plan(B * H, N, D, p, causal, bf, qk_scale, 1, need) &&
+        bwd_grids_fit(B * H, N, D, p, causal, dt))
+        e = fm::linear_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, causal, qk_scale, workspace,
+                           stream);
+    else if (shape >= 0 && bwd_grids_fit(B * H, N, D, p, causal, dt))
         e = fm::pairs_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, causal, bf, qk_scale,
                           shape, workspace, stream);
     else if (mfma_causal(D, p, causal, dt))

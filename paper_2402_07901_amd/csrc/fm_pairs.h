@@ -185,6 +185,72 @@ __device__ __forceinline__ void standardise_cols(float (&x)[D / 2], bool valid, 
     for (int i = 0; i < D / 2; ++i) x[i] *= r;
 }
 
+// A column's D values as a wave holds them: tile c, element i is channel
+// 32 c + 8 (i / 4) + 4 h + i % 4, both halves of the wave together all D.
+// The standardisation backward in place: dx = (dx^ - mean dx^ - x^ mean(dx^ x^))
+// / sigma (Eqs. 6-7), x the raw row.
+template <typename T, int D, int CT>
+__device__ __forceinline__ void standardise_back(const T *__restrict__ xrow, f16v (&acc)[CT])
+{
+    const int h = (threadIdx.x >> 5) & 1;
+    float x[CT][16], sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int dd = 32 * c + 8 * b + 4 * h;
+            const bool in = D % 32 == 0 || dd < D;
+            RawRow<T, 4> raw;
+            raw.load(xrow + (in ? dd : 0), in);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                x[c][4 * b + i] = raw.get(i);
+                sum += x[c][4 * b + i];
+            }
+        }
+    const float mu = half_sum(sum) * (1.0f / D);
+    float var = 0.f, m1 = 0.f, m2 = 0.f;
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            if (D % 32 == 0 || 32 * c + 8 * (i / 4) + 4 * h < D) {
+                x[c][i] -= mu;
+                var = fmaf(x[c][i], x[c][i], var);
+                m1 += acc[c][i];
+                m2 = fmaf(acc[c][i], x[c][i], m2);
+            }
+        }
+    const float r = rsqrt1(half_sum(var) * (1.0f / D));
+    m1 = half_sum(m1) * (1.0f / D);
+    m2 = half_sum(m2) * (1.0f / D) * r * r;
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[c][i] = (acc[c][i] - m1 - x[c][i] * m2) * r;
+}
+
+// Stores such a column as a row of D channels.
+template <typename T, int D, int CT>
+__device__ __forceinline__ void store_col(T *__restrict__ out, const f16v (&acc)[CT])
+{
+    const int h = (threadIdx.x >> 5) & 1;
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int dd = 32 * c + 8 * b + 4 * h;
+            if (D % 32 == 0 || dd < D) {
+                if constexpr (sizeof(T) == 2)
+                    *(uint2 *)(out + dd) = make_uint2(mx::pack_bf16x2(acc[c][4 * b], acc[c][4 * b + 1]),
+                                                      mx::pack_bf16x2(acc[c][4 * b + 2], acc[c][4 * b + 3]));
+                else
+                    *(float4 *)(out + dd) =
+                        make_float4(acc[c][4 * b], acc[c][4 * b + 1], acc[c][4 * b + 2], acc[c][4 * b + 3]);
+            }
+        }
+}
+
 // Power of two 2^(top - e), 2^e the least power of two above m (m finite,
 // >= 0): values up to m scaled by it stay below 2^top.  The result and its
 // inverse are normal numbers.

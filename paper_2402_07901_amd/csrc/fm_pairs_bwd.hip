@@ -28,137 +28,12 @@
 
 #include "fm_internal.h"
 #include "fm_pairs.h"
+#include "fm_pairs_rows.h"
 
 namespace fm {
 namespace pr {
 
 enum Role { ROLE_Q = 0, ROLE_K = 1, ROLE_V = 2 };
-
-// Exponents of zero and non-finite rows: they take no part in a maximum.
-constexpr int NO_EXP = -1000;
-
-// Least e with m < 2^e for finite m > 0.
-__device__ __forceinline__ int exp_above(float m)
-{
-    const int x = (int)(__float_as_uint(m) >> 23);
-    return m > 0.f && x < 255 ? x - 126 : NO_EXP;
-}
-
-__device__ __forceinline__ float exp2i(int n)
-{
-    n = n < -126 ? -126 : (n > 127 ? 127 : n);
-    return __uint_as_float((uint32_t)(n + 127) << 23);
-}
-
-__device__ __forceinline__ int g_exp(float G) { return (int)((__float_as_uint(G) >> 23) & 255) - 127; }
-
-template <int L>
-__device__ __forceinline__ float group_max(float x)
-{
-    auto mv = [](float y, auto ctl) {
-        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), decltype(ctl)::value, 0xF, 0xF, true));
-    };
-    x = fmaxf(x, mv(x, std::integral_constant<int, 0xB1>{}));
-    if constexpr (L >= 4) x = fmaxf(x, mv(x, std::integral_constant<int, 0x4E>{}));
-    if constexpr (L >= 8) x = fmaxf(x, mv(x, std::integral_constant<int, 0x141>{}));
-    if constexpr (L >= 16) x = fmaxf(x, mv(x, std::integral_constant<int, 0x140>{}));
-    return x;
-}
-
-// The per-row words.  float32-grade calls keep delta = dO.O and the exponents
-// of dO and v.  The fp16 ones also keep v, dO and dO rho as fp16 planes, each row scaled by
-// a power of two to below 2^10, so that a step stages them with one packed
-// multiply per pair: delta in dO's scale, rho, and the exponents of dO, v and
-// dO / G.
-struct RowInfo {
-    float delta;
-    short e_do, e_v;
-};
-struct RowInfoH {
-    float delta, rho;
-    short e_do, e_v;
-    int eg;
-};
-static_assert(sizeof(RowInfo) == 8 && sizeof(RowInfoH) == 16, "bytes per row");
-
-// 2^n as a half, flushed to zero below its range (n at most 15).
-__device__ __forceinline__ _Float16 half2i(int n) { return n < -24 ? (_Float16)0.0f : (_Float16)exp2i(n); }
-
-// One thread per 8 channels of a row of the whole call.
-template <typename T, int D, bool SPL>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(
-    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
-    const T *__restrict__ o, const T *__restrict__ dout, const float *__restrict__ g,
-    _Float16 *__restrict__ planes, void *__restrict__ info, long long rows, float qn)
-{
-    constexpr int L = D / 8;
-    const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / L;
-    const int c = threadIdx.x % L;
-    const bool ok = row < rows;
-    const size_t off = (size_t)(ok ? row : 0) * D + 8 * c, np = (size_t)rows * D;
-    RawRow<T, 8> rq, rk, rv, ro, rd;
-    rq.load(q + off, ok);
-    rk.load(k + off, ok);
-    rv.load(v + off, ok);
-    ro.load(o + off, ok);
-    rd.load(dout + off, ok);
-    float x[8];
-    h8 hi, lo;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = rq.get(i);
-    standardise_group<D>(x, ok);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] *= qn;
-    split8<SPL>(x, hi, lo);
-    if (ok) {
-        *(h8 *)(planes + off) = hi;
-        if constexpr (SPL) *(h8 *)(planes + np + off) = lo;
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = rk.get(i);
-    standardise_group<D>(x, ok);
-    split8<SPL>(x, hi, lo);
-    if (ok) {
-        *(h8 *)(planes + (SPL ? 2 : 1) * np + off) = hi;
-        if constexpr (SPL) *(h8 *)(planes + 3 * np + off) = lo;
-    }
-    float d = 0.f, md = 0.f, mv = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        d = fmaf(rd.get(i), ro.get(i), d);
-        md = fmaxf(md, fabsf(rd.get(i)));
-        mv = fmaxf(mv, fabsf(rv.get(i)));
-    }
-    d = group_sum<L>(d);
-    md = group_max<L>(md);
-    mv = group_max<L>(mv);
-    const int ed = exp_above(md), ev = exp_above(mv);
-    if constexpr (SPL) {
-        if (ok && c == 0) ((RowInfo *)info)[row] = RowInfo{d, (short)ed, (short)ev};
-    } else {
-        const int e = ed == NO_EXP ? 0 : ed;
-        const float G = g[ok ? row : 0];
-        const int kx = g_exp(G);
-        const float rho = exp2i(kx) / G, fd = exp2i(10 - e), fv = exp2i(10 - (ev == NO_EXP ? 0 : ev));
-        float y[8], z[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            x[i] = rv.get(i) * fv;
-            y[i] = rd.get(i) * fd;
-            z[i] = y[i] * rho;
-        }
-        if (ok) {
-            split8<false>(x, hi, lo);
-            *(h8 *)(planes + 2 * np + off) = hi;
-            split8<false>(y, hi, lo);
-            *(h8 *)(planes + 3 * np + off) = hi;
-            split8<false>(z, hi, lo);
-            *(h8 *)(planes + 4 * np + off) = hi;
-            if (c == 0)
-                ((RowInfoH *)info)[row] = RowInfoH{d * fd, rho, (short)ed, (short)ev, ed == NO_EXP ? NO_EXP : ed - kx};
-        }
-    }
-}
 
 template <typename T_, int D_, bool CAUSAL_, bool SPL_, int NQ_, int NWQ_, int NWK_, int BK_>
 struct BwdCfg {
@@ -637,62 +512,9 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
         for (int c = 0; c < CT; ++c)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[u][c][i] = acc[u][c][i] * f0 * f1;
-        if constexpr (ROLE != ROLE_V) {
-            // dx = (dx^ - mean dx^ - x^ mean(dx^ x^)) / sigma
-            const T *const xrow = (const T *)(ROLE == ROLE_Q ? a.q : a.k) + hb + (size_t)(ok ? n : 0) * D;
-            float x[CT][16], sum = 0.f;
-#pragma unroll
-            for (int c = 0; c < CT; ++c)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int dd = 32 * c + 8 * b + 4 * h;
-                    const bool in = D % 32 == 0 || dd < D;
-                    RawRow<T, 4> raw;
-                    raw.load(xrow + (in ? dd : 0), in);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        x[c][4 * b + i] = raw.get(i);
-                        sum += x[c][4 * b + i];
-                    }
-                }
-            const float mu = half_sum(sum) * (1.0f / D);
-            float var = 0.f, m1 = 0.f, m2 = 0.f;
-#pragma unroll
-            for (int c = 0; c < CT; ++c)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    if (D % 32 == 0 || 32 * c + 8 * (i / 4) + 4 * h < D) {
-                        x[c][i] -= mu;
-                        var = fmaf(x[c][i], x[c][i], var);
-                        m1 += acc[u][c][i];
-                        m2 = fmaf(acc[u][c][i], x[c][i], m2);
-                    }
-                }
-            const float r = rsqrt1(half_sum(var) * (1.0f / D));
-            m1 = half_sum(m1) * (1.0f / D);
-            m2 = half_sum(m2) * (1.0f / D) * r * r;
-#pragma unroll
-            for (int c = 0; c < CT; ++c)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[u][c][i] = (acc[u][c][i] - m1 - x[c][i] * m2) * r;
-        }
-        if (ok) {
-#pragma unroll
-            for (int c = 0; c < CT; ++c)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int dd = 32 * c + 8 * b + 4 * h;
-                    if (D % 32 == 0 || dd < D) {
-                        if constexpr (sizeof(T) == 2)
-                            *(uint2 *)(out + dd) = make_uint2(
-                                mx::pack_bf16x2(acc[u][c][4 * b], acc[u][c][4 * b + 1]),
-                                mx::pack_bf16x2(acc[u][c][4 * b + 2], acc[u][c][4 * b + 3]));
-                        else
-                            *(float4 *)(out + dd) = make_float4(acc[u][c][4 * b], acc[u][c][4 * b + 1],
-                                                                acc[u][c][4 * b + 2], acc[u][c][4 * b + 3]);
-                    }
-                }
-        }
+        if constexpr (ROLE != ROLE_V)
+            standardise_back<T, D>((const T *)(ROLE == ROLE_Q ? a.q : a.k) + hb + (size_t)(ok ? n : 0) * D, acc[u]);
+        if (ok) store_col<T, D>(out, acc[u]);
     }
 }
 

@@ -279,3 +279,73 @@ def test_scan_modes_agree_where_the_scan_serves():
             assert torch.equal(o, ref[0]) and torch.equal(g, ref[1]), mode
     finally:
         fm.set_scan_segments(old)
+
+
+# ---------------------------------------------------------------------------
+# First order over blocks with linear states (fm_linear.hip): bf16, tau D <= 1
+# ---------------------------------------------------------------------------
+def linear_plan(BH, N, D, causal, scale, backward, dt="bf16", p=1):
+    f = getattr(fm.lib(), "_ZN2fm11linear_planEiiiiiifim")
+    f.restype = ctypes.c_bool
+    ws = fm.workspace_bytes(1, BH, N, D, p, causal, fm.BF16 if dt == "bf16" else fm.F32, backward)
+    return f(BH, N, D, p, int(causal), int(dt == "bf16"), ctypes.c_float(scale), int(backward),
+             ctypes.c_size_t(ws))
+
+
+LINEAR_CASES = [(64, 1, 64), (48, 255, 64), (32, 257, 64), (24, 1281, 64), (64, 900, 32),
+                (64, 511, 16), (64, 300, 128), (3, 700, 128)]
+
+
+def test_linear_plan():
+    """Float32 rows, signed weights and second order stay with the other
+    kernels, as do few heads of many tokens; every head size has a case."""
+    assert not linear_plan(64, 1024, 64, True, 1.0, True)
+    assert not linear_plan(64, 1024, 64, True, 1.0 / 64, True, dt="f32")
+    assert not linear_plan(64, 1024, 64, True, 1.0 / 64, True, p=2)
+    assert not linear_plan(1, 65536, 64, True, 1.0 / 64, False)
+    for back in (False, True):
+        for D in (16, 32, 64, 128):
+            assert any(linear_plan(BH, N, D, c, 1.0 / D, back) for BH, N, d in LINEAR_CASES if d == D
+                       for c in (True, False)) or (D == 16 and not back)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("BH,N,D", LINEAR_CASES)
+@pytest.mark.parametrize("kind", ["plain", "late", "zeros"])
+def test_linear_against_explicit_gradient(BH, N, D, causal, kind):
+    """O, G and the gradients against the oracle (bf16 bars; G, whose weights
+    are non-negative sums of operands good to 2^-22, to 1e-5), with rows of v
+    and dO that jump by 2^12 and rows of zeros."""
+    scale = 1.0 / D
+    inp = make_inputs(1, BH, N, D, 7700 + N, "bf16", with_dout=True)
+    if kind != "plain":
+        if N < 200:
+            pytest.skip("one step of rows")
+        f = np.ones(N)
+        f[2 * N // 3:] = 2.0 ** 12 if kind == "late" else 1.0
+        if kind == "zeros":
+            f[:N // 3] = 0.0
+        inp = scale_values(scale_values(inp, "bf16", f), "bf16", f[::-1] if kind == "late" else f, "dout")
+    q, k, v, do = (to_dev(inp[n], "bf16") for n in ("q", "k", "v", "dout"))
+    o, g = fm.fastmax_fwd(q, k, v, p=1, causal=causal, scale=scale)
+    grads = fm.fastmax_bwd(q, k, v, o, do, g, p=1, causal=causal, scale=scale)
+    if linear_plan(BH, N, D, causal, scale, True):
+        again = fm.fastmax_bwd(q, k, v, o, do, g, p=1, causal=causal, scale=scale)
+        assert all(torch.equal(a, b) for a, b in zip(grads, again))
+    for h in sorted({0, BH // 2, BH - 1}):
+        q64, k64, v64 = heads_of(inp, h)
+        d64 = inp["dout64"].reshape(BH, N, D)[h]
+        four = [x[None, None] for x in (q64, k64, v64)]
+        ro, rg = oracle.fwd_brute(*four, 1, causal, scale=scale)
+        eo = max_rel(to_f64(o).reshape(BH, N, D)[h], ro[0, 0])
+        gg = g.cpu().numpy().astype(np.float64).reshape(BH, N)[h]
+        eg = float((np.abs(gg - rg[0, 0]) / np.abs(rg[0, 0]).max()).max())
+        assert eo <= TOL["bf16"] and eg <= 1e-5, (h, eo, eg)
+        ref = oracle.bwd_brute(*four, d64[None, None], 1, causal, scale=scale)
+        floor = np.abs(d64).max() * np.abs(v64).max() * np.sqrt(D) if N == 1 else 0.0
+        for name, x, r in zip(("dq", "dk", "dv"), grads, ref):
+            den = max(np.abs(r).max(), floor if name != "dv" else 0.0)
+            e = float(np.abs(to_f64(x).reshape(BH, N, D)[h] - r[0, 0]).max() / den)
+            say(f"linear {kind} BH{BH} N{N} D{D} c{causal} head {h} {name}: {e:.2e}")
+            assert e <= TOL["bf16"], (h, name, e)
