@@ -41,7 +41,7 @@ struct BwdCfg {
     static constexpr int D = D_, NQ = NQ_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
     static constexpr bool CAUSAL = CAUSAL_, SPL = SPL_;
     static constexpr bool VSPL = SPL && sizeof(T) == 4;
-    static constexpr bool LOACC = VSPL && D <= 32;
+    static constexpr bool EXACT = VSPL;   // as in the forward
     static constexpr int NTH = 64 * NWQ * NWK;
     static constexpr int QB = 32 * NQ * NWQ;
     static constexpr int KS = D / 16, CT = D < 32 ? 1 : D / 32;
@@ -222,13 +222,12 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
         }
     }
 
-    f16v acc[NQ][CT], acl[NQ][C::LOACC ? CT : 1];
+    f16v acc[NQ][CT];
 #pragma unroll
     for (int t = 0; t < NQ; ++t)
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             acc[t][c] = f16v{};
-            if constexpr (C::LOACC) acl[t][c] = f16v{};
         }
 
     // One 32-row tile j of the staged step against the wave's columns; masked:
@@ -320,26 +319,42 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
 #pragma unroll
             for (int e = 0; e < 2; ++e) split8<SPL>(w + 8 * e, th[u][e], tl[u][SPL ? e : 0]);
         }
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
+        constexpr int AS = ROLE == ROLE_Q ? RS : VS;
+        constexpr int APL = ROLE == ROLE_Q ? C::XH : C::AH;
+        const _Float16 *const ap = ROLE == ROLE_Q ? xhi : ahi;
+        if constexpr (C::EXACT) {
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
-                constexpr int AS = ROLE == ROLE_Q ? RS : VS;
-                constexpr int APL = ROLE == ROLE_Q ? C::XH : C::AH;
-                const _Float16 *ap = ROLE == ROLE_Q ? xhi : ahi;
-                const h8 x = ld_tr<AS>(ap, 32 * j + 16 * e, 32 * c);
+                const h8 x0 = ld_tr<AS>(ap, 32 * j, 32 * c), x1 = ld_tr<AS>(ap, 32 * j + 16, 32 * c);
+                const h8 y0 = ld_tr<AS>(ap + APL, 32 * j, 32 * c), y1 = ld_tr<AS>(ap + APL, 32 * j + 16, 32 * c);
 #pragma unroll
-                for (int u = 0; u < NQ; ++u) acc[u][c] = mma(x, th[u][e], acc[u][c]);
-                if constexpr (SPL) {
-                    const h8 y = ld_tr<AS>(ap + APL, 32 * j + 16 * e, 32 * c);
-#pragma unroll
-                    for (int u = 0; u < NQ; ++u) {
-                        f16v &z = C::LOACC ? acl[u][C::LOACC ? c : 0] : acc[u][c];
-                        z = mma(x, tl[u][SPL ? e : 0], z);
-                        z = mma(y, th[u][e], z);
-                    }
+                for (int u = 0; u < NQ; ++u) {
+                    f16v z = mma(y0, th[u][0], f16v{});
+                    z = mma(y1, th[u][1], z);
+                    z = mma(x0, tl[u][0], z);
+                    z = mma(x1, tl[u][1], z);
+                    z = mma(x0, th[u][0], z);
+                    acc[u][c] += mma(x1, th[u][1], z);
                 }
             }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    const h8 x = ld_tr<AS>(ap, 32 * j + 16 * e, 32 * c);
+#pragma unroll
+                    for (int u = 0; u < NQ; ++u) acc[u][c] = mma(x, th[u][e], acc[u][c]);
+                    if constexpr (SPL) {
+                        const h8 y = ld_tr<AS>(ap + APL, 32 * j + 16 * e, 32 * c);
+#pragma unroll
+                        for (int u = 0; u < NQ; ++u) {
+                            acc[u][c] = mma(x, tl[u][SPL ? e : 0], acc[u][c]);
+                            acc[u][c] = mma(y, th[u][e], acc[u][c]);
+                        }
+                    }
+                }
+        }
     };
 
     // writes the loaded step t to a buffer
@@ -458,12 +473,6 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
             compute((const _Float16 *)smem, t);
         }
     }
-    if constexpr (C::LOACC)
-#pragma unroll
-        for (int t = 0; t < NQ; ++t)
-#pragma unroll
-            for (int c = 0; c < CT; ++c) acc[t][c] += acl[t][c];
-
     // partial sums of the waves that shared the columns
     if constexpr (C::NWK > 1) {
         float *red = (float *)smem;

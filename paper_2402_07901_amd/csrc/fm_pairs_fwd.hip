@@ -27,9 +27,11 @@ struct FwdCfg {
     static constexpr int D = D_, P = P_, NQ = NQ_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
     static constexpr bool CAUSAL = CAUSAL_, SPL = SPL_, KP = KP_;
     static constexpr bool VSPL = SPL && sizeof(T) == 4;   // bf16 values need no lo part
-    // the products with a lo part have a sum of their own where registers
-    // allow: the main sum then rounds once per contraction step, not three times
-    static constexpr bool LOACC = VSPL && D <= 64;
+    // float32 rows: a tile's contribution is summed on its own, the products
+    // with a lo part first, and added with a rounded float32 add.  The matrix
+    // pipe's own chained sums round toward zero: at N = 1000 the error of O is
+    // 1.2e-7 this way and 2.1e-7 (keys split four ways) to 4.5e-7 chained.
+    static constexpr bool EXACT = VSPL;
     static constexpr int NTH = 64 * NWQ * NWK;
     static constexpr int QB = 32 * NQ * NWQ;              // queries per workgroup
     static constexpr int KS = D / 16;                     // contraction steps of a score
@@ -54,7 +56,7 @@ template <typename C>
 __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
     const typename C::T *__restrict__ q, const typename C::T *__restrict__ k,
     const typename C::T *__restrict__ v, const _Float16 *__restrict__ khat, size_t klo_off,
-    typename C::T *__restrict__ out, float *__restrict__ g, int N, int BH, int nqb, int hgrp, float qs)
+    typename C::T *__restrict__ out, float *__restrict__ g, int N, int BH, int nqb, int hgrp, float qs, float sc2)
 {
     typedef typename C::T T;
     constexpr int D = C::D, NQ = C::NQ, KS = C::KS, CT = C::CT, LPT = C::LPT, RS = C::RS, VS = C::VS;
@@ -152,7 +154,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
     raw_max();
     float vscale = set_scale(vmax <= 3e38f ? vmax : 0.f, 7);
 
-    f16v acc[NQ][CT], acl[NQ][C::LOACC ? CT : 1];
+    f16v acc[NQ][CT];
     float rs[NQ];
     // One 32-key tile j of the staged step against the wave's queries; masked:
     // some of its pairs lie beyond the diagonal or the last key.
@@ -161,7 +163,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
 #pragma unroll
         for (int u = 0; u < NQ; ++u)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[u][i] = 1.0f;
+            for (int i = 0; i < 16; ++i) s[u][i] = SPL ? 0.0f : 1.0f;
         const _Float16 *kp = khi + (32 * j + r32) * RS + 8 * h;
         // the products with a lo part first, while the sum is small (at
         // D = 128 side by side with the main ones: fewer live operands)
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
 #pragma unroll
             for (int u = 0; u < NQ; ++u) s[u] = mma(a, qh[u][ks], s[u]);
         }
-        // weights: s holds 1 + s; p = 2 takes 2 f_2 = (1 + s)^2 + 1 (the
+        // weights: t = 1 + s; p = 2 takes 2 f_2 = (1 + s)^2 + 1 (the
         // factor 2 cancels in F / G and is taken out of G)
         h8 wh[NQ][2], wl[NQ][SPL ? 2 : 1];
 #pragma unroll
@@ -198,7 +200,10 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
             const int qb0 = q0 + 32 * u;
             float w[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) w[i] = C::P == 2 ? fmaf(s[u][i], s[u][i], 1.0f) : s[u][i];
+            for (int i = 0; i < 16; ++i) {
+                const float t = SPL ? fmaf(s[u][i], sc2, 1.0f) : s[u][i];
+                w[i] = C::P == 2 ? fmaf(t, t, 1.0f) : t;
+            }
             if (masked) {
                 asm volatile("");   // a branch, not a compare and select per element of every tile
                 const int last = C::CAUSAL ? qb0 + r32 : N - 1;
@@ -225,29 +230,35 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
                                                    one, rs[u], false);
             }
         }
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
+        if constexpr (C::EXACT) {
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
-                const h8 a = ld_tr<VS>(vhi, 32 * j + 16 * e, 32 * c);
+                const h8 a0 = ld_tr<VS>(vhi, 32 * j, 32 * c), a1 = ld_tr<VS>(vhi, 32 * j + 16, 32 * c);
+                const h8 b0 = ld_tr<VS>(vlo, 32 * j, 32 * c), b1 = ld_tr<VS>(vlo, 32 * j + 16, 32 * c);
 #pragma unroll
-                for (int u = 0; u < NQ; ++u) acc[u][c] = mma(a, wh[u][e], acc[u][c]);
-                if constexpr (SPL) {
-#pragma unroll
-                    for (int u = 0; u < NQ; ++u) {
-                        f16v &z = C::LOACC ? acl[u][C::LOACC ? c : 0] : acc[u][c];
-                        z = mma(a, wl[u][SPL ? e : 0], z);
-                    }
-                }
-                if constexpr (VSPL) {
-                    const h8 b = ld_tr<VS>(vlo, 32 * j + 16 * e, 32 * c);
-#pragma unroll
-                    for (int u = 0; u < NQ; ++u) {
-                        f16v &z = C::LOACC ? acl[u][C::LOACC ? c : 0] : acc[u][c];
-                        z = mma(b, wh[u][e], z);
-                    }
+                for (int u = 0; u < NQ; ++u) {
+                    f16v z = mma(b0, wh[u][0], f16v{});
+                    z = mma(b1, wh[u][1], z);
+                    z = mma(a0, wl[u][0], z);
+                    z = mma(a1, wl[u][1], z);
+                    z = mma(a0, wh[u][0], z);
+                    acc[u][c] += mma(a1, wh[u][1], z);
                 }
             }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    const h8 a = ld_tr<VS>(vhi, 32 * j + 16 * e, 32 * c);
+#pragma unroll
+                    for (int u = 0; u < NQ; ++u) acc[u][c] = mma(a, wh[u][e], acc[u][c]);
+                    if constexpr (SPL) {
+#pragma unroll
+                        for (int u = 0; u < NQ; ++u) acc[u][c] = mma(a, wl[u][SPL ? e : 0], acc[u][c]);
+                    }
+                }
+        }
     };
 
     for (int attempt = 0;; ++attempt) {
@@ -256,9 +267,6 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
             rs[t] = 0.f;
 #pragma unroll
             for (int c = 0; c < CT; ++c) acc[t][c] = f16v{};
-            if constexpr (C::LOACC)
-#pragma unroll
-                for (int c = 0; c < CT; ++c) acl[t][c] = f16v{};
         }
         for (int t = 0; t < nt; ++t) {
             __syncthreads();
@@ -320,12 +328,6 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
         vscale = set_scale(m, 14);
         load_tile(0);
     }
-
-    if constexpr (C::LOACC)
-#pragma unroll
-        for (int t = 0; t < NQ; ++t)
-#pragma unroll
-            for (int c = 0; c < CT; ++c) acc[t][c] += acl[t][c];
 
     // O = F / G.  Where waves split the keys their partial sums meet in LDS
     // first, [wave][column][query], and each wave finishes a share of the
@@ -465,6 +467,11 @@ hipError_t launch_fwd(const void *q, const void *k, const void *v, void *out, fl
     const long long rows = (long long)BH * N, pb = (rows * (C::D / 8) + 255) / 256;
     if (!grid_fits((long long)BH * nqb, C::NTH) || (C::KP && !grid_fits(pb, 256)))
         return hipErrorInvalidConfiguration;
+    // float32-grade scores: q^ carries tau's mantissa, its power of two
+    // follows the sum (a small tau would push the lo parts below fp16's range)
+    int e = 0;
+    if (C::SPL) frexpf(qs, &e);
+    const float sc2 = C::SPL ? ldexpf(1.0f, e - 1) : 1.0f;
     _Float16 *khat = (_Float16 *)ws;
     const size_t lo = (size_t)rows * C::D;
     if (C::KP)
@@ -472,7 +479,7 @@ hipError_t launch_fwd(const void *q, const void *k, const void *v, void *out, fl
                            (const T *)k, khat, lo, rows);
     hipLaunchKernelGGL((fwd_kernel<C>), dim3((unsigned)((long long)BH * nqb)), dim3(C::NTH), 0, st,
                        (const T *)q, (const T *)k, (const T *)v, khat, lo, (T *)out, g, N, BH, nqb,
-                       hgrp, qs);
+                       hgrp, qs / sc2, sc2);
     return hipGetLastError();
 }
 
