@@ -220,8 +220,8 @@ int bwd_impl(const void *q, const void *k, const void *v, const void *out, const
     const int shape = fm::pairs_bwd_plan(B * H, N, D, p, causal, bf, need);
     if (fm::linear_plan(B * H, N, D, p, causal, bf, qk_scale, 1, need) &&
         bwd_grids_fit(B * H, N, D, p, causal, dt))
-        e = fm::linear_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, causal, qk_scale, workspace,
-                           stream);
+        e = fm::linear_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, causal, bf, qk_scale,
+                           workspace, stream);
     else if (shape >= 0 && bwd_grids_fit(B * H, N, D, p, causal, dt))
         e = fm::pairs_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, causal, bf, qk_scale,
                           shape, workspace, stream);

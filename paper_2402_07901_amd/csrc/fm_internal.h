@@ -102,15 +102,16 @@ hipError_t pairs_bwd(const void *q, const void *k, const void *v, const void *o,
                      const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
                      int is_bf16, float qs, int shape, void *ws, hipStream_t st);
 
-// First order over blocks with linear states (bf16 I/O, tau D <= 1): whether a
-// call runs there, and the calls (the backward's ws: 8 D + 8 bytes per row).
+// First order over blocks with linear states (tau D <= 1; forward: bf16 I/O):
+// whether a call runs there, and the calls (the backward's ws: 8 D + 8 bytes
+// per row).
 bool linear_plan(int BH, int N, int D, int p, int causal, int is_bf16, float qs, int backward,
                  size_t ws_bytes);
 hipError_t linear_fwd(const void *q, const void *k, const void *v, void *out, float *g, int BH,
                       int N, int D, int causal, float qs, hipStream_t st);
 hipError_t linear_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
                       const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
-                      float qs, void *ws, hipStream_t st);
+                      int is_bf16, float qs, void *ws, hipStream_t st);
 
 // Float32 MFMA kernels (v_mfma_f32_16x16x4_f32): p in {1, 2}, D in {16, 32,
 // 64, 128}, float32 or bf16 I/O, causal and non-causal (dispatch sends bf16

@@ -312,14 +312,33 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
 #pragma unroll
                 for (int i = 0; i < C::TPW; ++i) {
                     const int yc = (tile0 + i) / CT, xc = (tile0 + i) % CT;
+                    if constexpr (C::VSPL) {
+                        // the step's products on their own, the ones with a lo part
+                        // first, then one rounded add (the matrix pipe's chained
+                        // sums round toward zero)
+                        f16v z = f16v{};
+                        h8 ya[(C::STEPS + C::GW - 1) / C::GW], xb[(C::STEPS + C::GW - 1) / C::GW];
 #pragma unroll
-                    for (int e0 = 0; e0 < C::STEPS; e0 += C::GW) {
-                        const int e = e0 + part;
-                        if (C::STEPS % C::GW != 0 && e >= C::STEPS) break;
-                        const h8 ya = ld_tr<VS>(yp, 16 * e, 32 * yc), xb = ld_tr<RS>(xp, 16 * e, 32 * xc);
-                        sh[i] = mma(ya, xb, sh[i]);
-                        if constexpr (XSPL) sl[i] = mma(ya, ld_tr<RS>(xp + C::XH, 16 * e, 32 * xc), sl[i]);
-                        if constexpr (YSPL) sl[i] = mma(ld_tr<VS>(yp + C::YH, 16 * e, 32 * yc), xb, sl[i]);
+                        for (int e0 = 0; e0 < C::STEPS; e0 += C::GW) {
+                            const int e = min(e0 + part, C::STEPS - 1);
+                            ya[e0 / C::GW] = ld_tr<VS>(yp, 16 * e, 32 * yc);
+                            xb[e0 / C::GW] = ld_tr<RS>(xp, 16 * e, 32 * xc);
+                            if constexpr (XSPL) z = mma(ya[e0 / C::GW], ld_tr<RS>(xp + C::XH, 16 * e, 32 * xc), z);
+                            if constexpr (YSPL) z = mma(ld_tr<VS>(yp + C::YH, 16 * e, 32 * yc), xb[e0 / C::GW], z);
+                        }
+#pragma unroll
+                        for (int e0 = 0; e0 < C::STEPS; e0 += C::GW) z = mma(ya[e0 / C::GW], xb[e0 / C::GW], z);
+                        if (C::STEPS % C::GW == 0 || part < C::STEPS) sh[i] += z;
+                    } else {
+#pragma unroll
+                        for (int e0 = 0; e0 < C::STEPS; e0 += C::GW) {
+                            const int e = e0 + part;
+                            if (C::STEPS % C::GW != 0 && e >= C::STEPS) break;
+                            const h8 ya = ld_tr<VS>(yp, 16 * e, 32 * yc), xb = ld_tr<RS>(xp, 16 * e, 32 * xc);
+                            sh[i] = mma(ya, xb, sh[i]);
+                            if constexpr (XSPL) sl[i] = mma(ya, ld_tr<RS>(xp + C::XH, 16 * e, 32 * xc), sl[i]);
+                            if constexpr (YSPL) sl[i] = mma(ld_tr<VS>(yp + C::YH, 16 * e, 32 * yc), xb, sl[i]);
+                        }
                     }
                 }
             }
@@ -459,14 +478,19 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
                     rs += w[0];
                 }
 #pragma unroll
-                for (int e = 0; e < 2; ++e)
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) {
-                        const h8 A = ld_tr<VS>(yp, 32 * j + 16 * e, 32 * c);
-                        acc[c] = mma(A, wl[e], acc[c]);
-                        if constexpr (YSPL) acc[c] = mma(ld_tr<VS>(yp + C::YH, 32 * j + 16 * e, 32 * c), wh[e], acc[c]);
-                        acc[c] = mma(A, wh[e], acc[c]);
+                for (int c = 0; c < CT; ++c) {
+                    const h8 A0 = ld_tr<VS>(yp, 32 * j, 32 * c), A1 = ld_tr<VS>(yp, 32 * j + 16, 32 * c);
+                    f16v z = C::VSPL ? f16v{} : acc[c];
+                    z = mma(A0, wl[0], z);
+                    z = mma(A1, wl[1], z);
+                    if constexpr (YSPL) {
+                        z = mma(ld_tr<VS>(yp + C::YH, 32 * j, 32 * c), wh[0], z);
+                        z = mma(ld_tr<VS>(yp + C::YH, 32 * j + 16, 32 * c), wh[1], z);
                     }
+                    z = mma(A0, wh[0], z);
+                    z = mma(A1, wh[1], z);
+                    acc[c] = C::VSPL ? acc[c] + z : z;
+                }
             }
         }
         if constexpr (PASS != FWD) break;
@@ -578,16 +602,20 @@ hipError_t run_bwd(const void *q, const void *k, const void *v, const void *o, c
     return hipGetLastError();
 }
 
-// First-order calls that run here: bf16 I/O whose scores satisfy |tau s| <= 1
-// (tau D <= 1: every weight is non-negative).  The operands' 22 bits show
-// neither in bf16 rows nor, without cancellation, in G; float32 rows and
-// weights that change sign (G may nearly cancel) keep the float32 scans.
+// First-order calls that run here: scores with |tau s| <= 1 (tau D <= 1), so
+// that every weight is non-negative: G cannot nearly cancel, which would show
+// the operands' 22 bits (at tau = 1 the error of O was ten times the float32
+// scans', whose 24 bits those calls keep).  Float32 I/O: the backward only,
+// whose errors are the scans' (O 1.1e-7, dq, dk 1.8e-7, dv 1.3e-7); a float32
+// forward's G would go from 3.2e-8 to 4.6e-8.
 //
 // Paces, us: a workgroup takes w + a N rows / 1000 (half the rows under the
-// causal mask, on average), 256 run at once; the scans take s + o heads N / 1000.
-// Measured, scans -> here (D = 64, causal, tau = 1/64): 64 heads of 3001
-// tokens 226 -> 116 forward, 976 -> 371 backward; 8 of 3001 51 -> 49 and
-// 197 -> 73; 64 of 256 21 -> 17 and 91 -> 29; 1 of 8192 26 -> 103 (stays).
+// causal mask, on average), 256 run at once, float32 rows 1.25 times as long;
+// the scans take s + o heads N / 1000.  Measured, scans -> here (D = 64,
+// causal, tau = 1/64): 64 heads of 3001 tokens bf16 226 -> 118 forward,
+// 976 -> 313 backward, float32 backward 990 -> 440; 8 of 3001 51 -> 49
+// and 197 -> 73; 64 of 256 21 -> 17 and 91 -> 29; 1 of 8192 26 -> 103 (stays).
+// Float32 backward of 8 heads of 2048 tokens, D = 32: 71 -> 48.
 struct Pace {
     float w, a, s, o;
 };
@@ -599,13 +627,13 @@ constexpr Pace BP[] = {{13.f, 8.f, 37.f, 1.f}, {15.f, 11.f, 38.f, 2.2f}, {18.f, 
 bool linear_plan(int BH, int N, int D, int p, int causal, int is_bf16, float qs, int backward, size_t ws_bytes)
 {
     using namespace lin;
-    if (p != 1 || !is_bf16 || qs * (float)D > 1.0f) return false;
+    if (p != 1 || qs * (float)D > 1.0f || (!is_bf16 && !backward)) return false;
     const size_t rows = (size_t)BH * N;
     if (backward && ws_bytes < rows * (8 * (size_t)D + sizeof(RowInfo))) return false;
     const Pace &x = (backward ? BP : FP)[D == 16 ? 0 : D == 32 ? 1 : D == 64 ? 2 : 3];
     const double n = 1e-3 * N, blocks = (double)BH * ((N + 255) / 256) * (backward ? 3 : 1) / 256;
     const double t = 5 + std::hypot(x.w + x.a * n, blocks * (x.w + x.a * n * (causal ? .5 : 1)));
-    return t < 0.9 * (x.s + x.o * BH * n);
+    return (is_bf16 ? t : 1.25 * t) < 0.9 * (x.s + x.o * BH * n);
 }
 
 hipError_t linear_fwd(const void *q, const void *k, const void *v, void *out, float *g, int BH,
@@ -626,11 +654,12 @@ hipError_t linear_fwd(const void *q, const void *k, const void *v, void *out, fl
 
 hipError_t linear_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
                       const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
-                      float qs, void *ws, hipStream_t st)
+                      int is_bf16, float qs, void *ws, hipStream_t st)
 {
-#define GO(DD)                                                                                     \
-    return causal ? lin::run_bwd<bf16_t, DD, true>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st) \
-                  : lin::run_bwd<bf16_t, DD, false>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st)
+#define GO2(T, DD)                                                                                 \
+    (causal ? lin::run_bwd<T, DD, true>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st)        \
+            : lin::run_bwd<T, DD, false>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st))
+#define GO(DD) return is_bf16 ? GO2(bf16_t, DD) : GO2(float, DD)
     switch (D) {
     case 16: GO(16);
     case 32: GO(32);
@@ -638,6 +667,7 @@ hipError_t linear_bwd(const void *q, const void *k, const void *v, const void *o
     case 128: GO(128);
     }
 #undef GO
+#undef GO2
     return hipErrorInvalidValue;
 }
 
