@@ -13,15 +13,18 @@
  *                                      Sec. 2.4 Eq. "bigo")
  *
  * with n running over all N tokens, or over n <= i when causal (Sec. 2.1
- * tril mask; Sec. 2.4 causal F and G).  The library evaluates it exactly
+ * tril mask; Sec. 2.4 causal F and G).  The library evaluates it exactly,
  * through the factorisation of Sec. 2.4 (moments of k^ and v contracted
- * against powers of q^), never forming the N x N matrix.
+ * against powers of q^) or, where a sequence is short enough for that to be
+ * less work, over the pairs (i, n) themselves, 32 x 32 weights at a time in
+ * registers; the N x N matrix is never stored.
  *
  * Conventions shared by every entry point
  *  - Layout: q, k, v, out, dout, dq, dk, dv are [B, H, N, D] contiguous
  *    (D fastest) in the I/O dtype `dt`; g is [B, H, N] float32.
- *    Statistics (standardisation, G) are float32 whatever `dt` is; moment
- *    contractions accumulate in float32.  The causal bf16, D = 64, p = 2
+ *    Statistics (standardisation, G) are float32 whatever `dt` is;
+ *    contractions accumulate in float32, and float32 rows enter them as fp16
+ *    pairs (22 bits) or in float32.  The causal bf16, D = 64, p = 2
  *    MFMA path carries its moment state between 128-token chunks in fp16
  *    (each chunk's float32 contribution is rounded and added); its error
  *    stays within the bf16 tolerance on every row of 65536-token causal
@@ -41,9 +44,12 @@
  *    HIP calls before it ask which device is current and which device the
  *    stream belongs to): on any error nothing is enqueued and nothing is
  *    written.
- *  - Supported: D in {16, 32, 64, 128} (fp16 MFMA kernels serve D = 64,
- *    p = 2, bf16, except non-causal below 128 tokens; every other case runs
- *    on float32 MFMA kernels, and the dropout calls on float32 VALU kernels);
+ *  - Supported: D in {16, 32, 64, 128} (p = 2 below a length that depends on
+ *    the shape: pair kernels on fp16 MFMA; longer: factorised fp16 MFMA
+ *    kernels for D = 64, bf16, float32 MFMA kernels otherwise; p = 1: block
+ *    kernels on fp16 MFMA where qk_scale D <= 1 and heads fill the GPU
+ *    (float32: the backward only), float32 MFMA kernels otherwise; the dropout
+ *    calls: float32 VALU kernels);
  *    p in {1, 2}; causal in {0, 1};
  *    dt in {FASTMAX_F32, FASTMAX_BF16}; B, H, N >= 1, B*H <= 2^20 heads,
  *    N <= 2^30 tokens per head and B*H*N*D < 2^62.
@@ -98,7 +104,10 @@ enum {
  * for about 256 workgroups).  The causal bf16, D = 64, p = 2 forward keeps
  * the standardised q and k in fp16 (256 bytes per row) and, for N > 128,
  * room for the summaries of split scans (99072 bytes per head and 16-column
- * slice, see fastmax_set_scan_segments).  The backward always
+ * slice, see fastmax_set_scan_segments).  The sizes are those of the
+ * factorised kernels; the pair and block kernels work within them, and a call
+ * whose workspace is too small for them stays with the factorised ones.  The
+ * backward always
  * needs one: per token 1/G, c = dO.O/G, the fp32
  * gradient accumulators of q^ and k^ and (causal bf16, D = 64, p = 2) the
  * standardised q^, k^ in fp16, the dv scan's segment summaries, plus
@@ -249,8 +258,13 @@ const char *fastmax_strerror(int code);
  *     the first's summary itself (state updates over the earlier chunks)
  *     instead of waiting for it -- the path a second workgroup also takes
  *     if the summary has not arrived within about 0.3 s.
- * Every mode gives bit-identical results; the workspace sizes do not depend
- * on the mode.  The mode is process-wide and applies to calls made after
+ * The modes choose between one workgroup and two per scan.  Where the scans
+ * of a few long heads would leave most CUs idle (at most 21 heads; e.g. 8
+ * heads of 65536 tokens), the forward cuts each into 3 or more segments
+ * whatever the mode, with the segments' summaries built in parallel first (in
+ * the workspace's room for q^), and sequences that the pair kernels take have
+ * no scan.  Every mode gives bit-identical results; the workspace sizes do not
+ * depend on the mode.  The mode is process-wide and applies to calls made after
  * this returns.  Returns the previous mode, or FASTMAX_EINVAL for any other
  * value.
  */

@@ -11,9 +11,10 @@
 namespace {
 
 // Head sizes served: 16, 32, 64 and 128 (the last the head size of Sec. 3.1's
-// Llama-2 remark).  bf16 D = 64, p = 2 runs on the fp16 MFMA kernels where they
-// apply, every other plain call on the float32 MFMA kernels, the dropout
-// calls on the generic float32 kernels.
+// Llama-2 remark).  In order of preference: the first-order block kernels
+// (linear_plan), the pair kernels (pairs_*_plan), the factorised fp16 MFMA
+// kernels (bf16 D = 64, p = 2), the float32 MFMA kernels; the dropout calls run
+// on the generic float32 kernels.
 bool supported_d(int D) { return D == 16 || D == 32 || D == 64 || D == 128; }
 
 int check_common(int B, int H, int N, int D, int p, int causal, int dt)
@@ -71,8 +72,8 @@ bool mfma_causal(int D, int p, int causal, int dt)
     return D == 64 && p == 2 && causal && dt == FASTMAX_BF16;
 }
 
-// The float32 MFMA kernels (forward and backward) serve every case the fp16
-// MFMA kernels do not (p = 1; p = 2 with float32 I/O, with D != 64, or
+// The float32 MFMA kernels (forward and backward) serve every case that no
+// plan and none of the factorised fp16 MFMA kernels takes (p = 1; p = 2 with float32 I/O, with D != 64, or
 // non-causal below 128 tokens).
 bool f32mfma(int D, int p, int causal, int dt, int N)
 {

@@ -1,5 +1,6 @@
 // Pair forward (see fm_pairs.h): O_i = sum_n w_in v_n / sum_n w_in with the
-// weights formed 32 keys x 32 queries at a time, one launch, no workspace.
+// weights formed 32 keys x 32 queries at a time, one launch and no workspace
+// (shapes with KP: k^ once as fp16 planes in the workspace, a launch before).
 //
 // A workgroup of NWQ x NWK waves takes NWQ 32-query columns tiles (NQ per
 // wave); NWK waves share a query tile and split the keys.  Per step it stages
