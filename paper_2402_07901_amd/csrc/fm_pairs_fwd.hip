@@ -11,7 +11,10 @@
 // is taken from the first staged tile with 8 binary digits of headroom; each
 // thread keeps the largest magnitude that it stages, and only if that
 // overflowed the headroom (a later token more than 2^8 times the first tile's
-// largest) the workgroup finds the true maximum and runs its keys again.
+// largest) the workgroup finds the true maximum and runs its keys again.  A
+// group that is zero over the whole first tile (a padded or zeroed prefix)
+// says nothing about the later values, however small: the workgroup finds the
+// true maximum first.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -154,6 +157,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
     load_tile(0);
     raw_max();
     float vscale = set_scale(vmax <= 3e38f ? vmax : 0.f, 7);
+    bool rescan = __syncthreads_or(smax[sc] == 0u) && nt > 1;
 
     f16v acc[NQ][CT];
     float rs[NQ];
@@ -262,7 +266,22 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
         }
     };
 
-    for (int attempt = 0;; ++attempt) {
+    for (;;) {
+        if (rescan) {
+            // the largest finite magnitude of the column group over the keys read
+            float m = 0.f;
+            for (int n = st0; n < kend; n += C::TPP) {
+                RawRow<T, 8> x;
+                x.load(v + (size_t)n * D + 8 * sc, true);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float y = fabsf(x.get(i));
+                    if (y <= 3.4028235e38f) m = fmaxf(m, y);
+                }
+            }
+            vscale = set_scale(m, 14);
+            load_tile(0);
+        }
 #pragma unroll
         for (int t = 0; t < NQ; ++t) {
             rs[t] = 0.f;
@@ -314,20 +333,8 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
                 tile(j, kb, (C::CAUSAL && kb + 31 > q0) || kb + 32 > N);
             }
         }
-        if (attempt || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
-        // the largest finite magnitude of the column group over the keys read
-        float m = 0.f;
-        for (int n = st0; n < kend; n += C::TPP) {
-            RawRow<T, 8> x;
-            x.load(v + (size_t)n * D + 8 * sc, true);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float y = fabsf(x.get(i));
-                if (y <= 3.4028235e38f) m = fmaxf(m, y);
-            }
-        }
-        vscale = set_scale(m, 14);
-        load_tile(0);
+        if (rescan || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
+        rescan = true;
     }
 
     // O = F / G.  Where waves split the keys their partial sums meet in LDS

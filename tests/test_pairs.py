@@ -202,16 +202,18 @@ def scale_values(inp, dt, factor, name="v"):
 @pytest.mark.gpu
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("D,dt", [(64, "bf16"), (128, "bf16"), (32, "f32"), (64, "f32")])
-@pytest.mark.parametrize("kind", ["late", "zeros", "huge", "tiny"])
+@pytest.mark.parametrize("kind", ["late", "zeros", "prefix", "huge", "tiny"])
 def test_value_scale(D, dt, causal, kind):
     """Values that outgrow the first tile's scale (a second attempt), a first
-    tile of zeros, and values near the ends of the float range."""
+    tile of zeros before values of 1 and (prefix) of 2^-24, and values near the
+    ends of the float range."""
     N = 420
     f = np.ones(N)
     if kind == "late":
         f[300:] = 2.0 ** 14
-    elif kind == "zeros":
+    elif kind in ("zeros", "prefix"):
         f[:280] = 0.0
+        f[280:] = 1.0 if kind == "zeros" else 2.0 ** -24
     else:
         f[:] = 2.0 ** (110 if kind == "huge" else -110)
     inp = scale_values(make_inputs(1, 3, N, D, 7200, dt), dt, f)
@@ -315,11 +317,13 @@ def test_linear_plan():
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("BH,N,D", LINEAR_CASES)
 @pytest.mark.parametrize("kind,dt", [("plain", "bf16"), ("late", "bf16"), ("zeros", "bf16"),
-                                     ("plain", "f32"), ("late", "f32")])
+                                     ("prefix", "bf16"), ("plain", "f32"), ("late", "f32"),
+                                     ("prefix", "f32")])
 def test_linear_against_explicit_gradient(BH, N, D, causal, kind, dt):
     """O, G and the gradients against the oracle (the suite's bars; G, whose weights
     are non-negative sums of operands good to 2^-22, to 1e-5), with rows of v
-    and dO that jump by 2^12 and rows of zeros."""
+    and dO that jump by 2^12, and rows of zeros before values of 1 and (prefix)
+    of 2^-24."""
     scale = 1.0 / D
     inp = make_inputs(1, BH, N, D, 7700 + N, dt, with_dout=True)
     if kind != "plain":
@@ -327,8 +331,9 @@ def test_linear_against_explicit_gradient(BH, N, D, causal, kind, dt):
             pytest.skip("one step of rows")
         f = np.ones(N)
         f[2 * N // 3:] = 2.0 ** 12 if kind == "late" else 1.0
-        if kind == "zeros":
+        if kind in ("zeros", "prefix"):
             f[:N // 3] = 0.0
+            f[N // 3:] *= 1.0 if kind == "zeros" else 2.0 ** -24
         inp = scale_values(scale_values(inp, dt, f), dt, f[::-1] if kind == "late" else f, "dout")
     q, k, v, do = (to_dev(inp[n], dt) for n in ("q", "k", "v", "dout"))
     o, g = fm.fastmax_fwd(q, k, v, p=1, causal=causal, scale=scale)
