@@ -15,9 +15,18 @@
 // contraction (16 keys of a value column) is read from the row-major tile by
 // ds_read_b64_tr_b16, which hands lane i of 16 the column i of a 4 x 16 block.
 //
-// float32-grade operands.  A float32 x is held as two fp16 numbers hi + lo
-// (22 bits and more); a product takes three MFMAs (hi hi, lo hi, hi lo).  The
-// values carry a power-of-two scale per 8-column group.
+// float32-grade operands.  The standardised q^ and k^ and the weights, whose
+// range is known, are held as two fp16 numbers hi + lo, a product takes three
+// MFMAs (hi hi, lo hi, hi lo); q^ and k^ are multiplied by 2^8 each, which
+// keeps lo out of fp16's subnormals (24 bits, not 22; the scores' 2^16 goes
+// into the factor that they are read with).  bf16 values have one fp16 plane
+// with a power-of-two scale per 8-column group.  float32 values have no known
+// range: an fp16 pair under a shared scale loses what lies far below the
+// scale's largest value, even if a row or column never meets that value.  They
+// are held as three bf16 numbers, which take a float32 apart into 8 + 8 + 8
+// bits: every bit of every exponent, no scale; the weights meet them in the
+// same form and a product takes six MFMAs (the three smallest of nine are
+// below 2^-24).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -47,6 +56,13 @@ typedef short s4v __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f16v mma(h8 a, h8 b, f16v c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+// Operands that hold bf16 numbers (words of the same h8).
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ f16v mma_b(h8 a, h8 b, f16v c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0);
 }
 
 // Two floats to two halves, round to nearest even.
@@ -119,6 +135,45 @@ __device__ __forceinline__ void split8(const float *x, h8 &hi, h8 &lo)
     }
 }
 
+// Eight floats as three bf16 parts, cut (not rounded) so that the parts of a
+// finite number add up to it and none overflows.
+__device__ __forceinline__ void split3(const float *x, h8 (&p)[3])
+{
+    uint4 w[3];
+    uint32_t *const o[3] = {(uint32_t *)&w[0], (uint32_t *)&w[1], (uint32_t *)&w[2]};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = x[2 * i], b = x[2 * i + 1];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+            o[j][i] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+            if (j < 2) {
+                a -= __uint_as_float(ua & 0xffff0000u);
+                b -= __uint_as_float(ub & 0xffff0000u);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) p[j] = __builtin_bit_cast(h8, w[j]);
+}
+
+// The products of two such operands over 32 rows (two K steps e).  The matrix
+// pipe cuts its sums toward zero: the leading products, 16 bits each, are summed
+// on their own, where little is cut, the others (2^-8 of them and less) apart,
+// and the two meet in a rounded add.
+__device__ __forceinline__ f16v mma33(const h8 (&a)[3][2], const h8 (&b)[2][3])
+{
+    f16v y = f16v{}, z = f16v{};
+#pragma unroll
+    for (int o = 2; o >= 0; --o)
+#pragma unroll
+        for (int i = 0; i <= o; ++i)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) (o ? y : z) = mma_b(a[i][e], b[e][o - i], o ? y : z);
+    return y + z;
+}
+
 // 1 / sqrt(v): the hardware's approximation (1 ulp) with one Newton step, so
 // that a row's scale is no larger an error than its elements' rounding.
 __device__ __forceinline__ float rsqrt1(float v)
@@ -129,9 +184,9 @@ __device__ __forceinline__ float rsqrt1(float v)
 
 // Standardises the 8 channels a lane holds of a token (Sec. 2.2, Eqs. 6-7:
 // population std, no epsilon; the token's D/8 lanes are an aligned group) in
-// place.  Every lane of the wave takes part.
+// place, times scale.  Every lane of the wave takes part.
 template <int D>
-__device__ __forceinline__ void standardise_group(float (&x)[8], bool valid)
+__device__ __forceinline__ void standardise_group(float (&x)[8], bool valid, float scale = 1.0f)
 {
     float s = 0.f;
 #pragma unroll
@@ -143,7 +198,7 @@ __device__ __forceinline__ void standardise_group(float (&x)[8], bool valid)
         x[i] -= mu;
         v = fmaf(x[i], x[i], v);
     }
-    const float r = valid ? rsqrt1(group_sum<D / 8>(v) * (1.0f / D)) : 0.0f;
+    const float r = valid ? rsqrt1(group_sum<D / 8>(v) * (1.0f / D)) * scale : 0.0f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i] *= r;
 }

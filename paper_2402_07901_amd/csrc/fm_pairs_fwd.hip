@@ -1,13 +1,14 @@
 // Pair forward (see fm_pairs.h): O_i = sum_n w_in v_n / sum_n w_in with the
 // weights formed 32 keys x 32 queries at a time, one launch and no workspace
-// (shapes with KP: k^ once as fp16 planes in the workspace, a launch before).
+// (the shape with KP: k^ once as an fp16 plane in the workspace, a launch before).
 //
 // A workgroup of NWQ x NWK waves takes NWQ 32-query columns tiles (NQ per
 // wave); NWK waves share a query tile and split the keys.  Per step it stages
 // BK keys (standardised on the way, Sec. 2.2) and their values in LDS, the
 // next step's rows already on their way into registers.
 //
-// Value scale.  fp16 values need a power-of-two scale per 8-column group.  It
+// Value scale.  bf16 values go to fp16 under a power-of-two scale per 8-column
+// group (float32 values are bf16 triples and need none).  It
 // is taken from the first staged tile with 8 binary digits of headroom; each
 // thread keeps the largest magnitude that it stages, and only if that
 // overflowed the headroom (a later token more than 2^8 times the first tile's
@@ -25,17 +26,17 @@
 namespace fm {
 namespace pr {
 
-template <typename T_, int D_, int P_, bool CAUSAL_, bool SPL_, bool KP_, int NQ_, int NWQ_, int NWK_, int BK_>
+template <typename T_, int D_, bool CAUSAL_, bool SPL_, bool KP_, int NQ_, int NWQ_, int NWK_, int BK_>
 struct FwdCfg {
     typedef T_ T;
-    static constexpr int D = D_, P = P_, NQ = NQ_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
+    static constexpr int D = D_, NQ = NQ_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
     static constexpr bool CAUSAL = CAUSAL_, SPL = SPL_, KP = KP_;
-    static constexpr bool VSPL = SPL && sizeof(T) == 4;   // bf16 values need no lo part
-    // float32 rows: a tile's contribution is summed on its own, the products
-    // with a lo part first, and added with a rounded float32 add.  The matrix
-    // pipe's own chained sums round toward zero: at N = 1000 the error of O is
-    // 1.2e-7 this way and 2.1e-7 (keys split four ways) to 4.5e-7 chained.
-    static constexpr bool EXACT = VSPL;
+    // float32 values: three bf16 parts.  A tile's contribution is summed on its
+    // own, the small products first, and added with a rounded float32 add (the
+    // matrix pipe's own chained sums round toward zero).
+    static constexpr bool V3 = SPL && sizeof(T) == 4;
+    static constexpr int VP = V3 ? 3 : 1;
+    static constexpr float QKS = SPL ? 256.0f : 1.0f;      // of q^ and of k^
     static constexpr int NTH = 64 * NWQ * NWK;
     static constexpr int QB = 32 * NQ * NWQ;              // queries per workgroup
     static constexpr int KS = D / 16;                     // contraction steps of a score
@@ -45,7 +46,7 @@ struct FwdCfg {
     static constexpr int NP = (BK + TPP - 1) / TPP;       // passes
     static constexpr int RS = row_stride<D>(), VS = tr_stride<D>();
     static constexpr int KH = BK * RS, VH = BK * VS;      // halves per plane
-    static constexpr int TILE_BYTES = 2 * ((SPL ? 2 : 1) * KH + (VSPL ? 2 : 1) * VH);
+    static constexpr int TILE_BYTES = 2 * ((SPL ? 2 : 1) * KH + VP * VH);
     // the waves' partial numerators meet in LDS when they split the keys
     static constexpr int RED_BYTES = NWK > 1 ? 4 * NWQ * NWK * 32 * (32 * CT + 1) : 0;
     // at D = 128 the queries' lo parts wait in LDS: the registers go to the
@@ -53,23 +54,26 @@ struct FwdCfg {
     static constexpr bool QLDS = SPL && D >= 128;
     static constexpr int LOOP_BYTES = TILE_BYTES + (QLDS ? 2 * QB * RS : 0);
     static constexpr int SMEM = LOOP_BYTES > RED_BYTES ? LOOP_BYTES : RED_BYTES;
-    static_assert(BK % (32 * NWK) == 0 && D % 16 == 0 && (NWK == 1 || NQ == 1), "shape");
+    static_assert(BK % (32 * NWK) == 0 && D % 16 == 0 && (NWK == 1 || NQ == 1) && !(KP && SPL), "shape");
+    static_assert(SMEM <= 160 * 1024 - 256, "LDS");
+    // waves per SIMD: four waves that fill a CU's LDS are alone on it
+    static constexpr int WPS = NTH <= 256 && SMEM > 80 * 1024 ? 1 : 2;
 };
 
 template <typename C>
-__global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
+__global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
     const typename C::T *__restrict__ q, const typename C::T *__restrict__ k,
-    const typename C::T *__restrict__ v, const _Float16 *__restrict__ khat, size_t klo_off,
+    const typename C::T *__restrict__ v, const _Float16 *__restrict__ khat,
     typename C::T *__restrict__ out, float *__restrict__ g, int N, int BH, int nqb, int hgrp, float qs, float sc2)
 {
     typedef typename C::T T;
     constexpr int D = C::D, NQ = C::NQ, KS = C::KS, CT = C::CT, LPT = C::LPT, RS = C::RS, VS = C::VS;
-    constexpr bool SPL = C::SPL, VSPL = C::VSPL;
+    constexpr bool SPL = C::SPL, V3 = C::V3;
     __shared__ alignas(16) unsigned char smem[C::SMEM];
     __shared__ unsigned int smax[LPT];
     __shared__ float sscale[LPT];
     _Float16 *const khi = (_Float16 *)smem, *const klo = khi + C::KH;
-    _Float16 *const vhi = khi + (SPL ? 2 : 1) * C::KH, *const vlo = vhi + C::VH;
+    _Float16 *const vhi = khi + (SPL ? 2 : 1) * C::KH;
     _Float16 *const qlo = (_Float16 *)(smem + C::TILE_BYTES);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -104,7 +108,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
         float x[D / 2];
         const int n = q0 + 32 * t + r32;
         load_cols<T, D>(q, n, N, x);
-        standardise_cols<D>(x, n < N, qs);
+        standardise_cols<D>(x, n < N, qs * C::QKS);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             h8 lo;
@@ -120,7 +124,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
     // staging: this thread's 8 channels and first token
     const int sc = tid % LPT, st0 = tid / LPT;
     RawRow<T, 8> kr[C::KP ? 1 : C::NP], vr[C::NP];
-    RawRow<bf16_t, 8> kph[C::KP ? C::NP : 1], kpl[C::KP && SPL ? C::NP : 1];   // fp16 words
+    RawRow<bf16_t, 8> kph[C::KP ? C::NP : 1];   // fp16 words
     auto load_tile = [&](int t) {
 #pragma unroll
         for (int p = 0; p < C::NP; ++p) {
@@ -129,7 +133,6 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
             const unsigned off = n * (unsigned)D + 8u * sc;
             if constexpr (C::KP) {
                 kph[p].load((const bf16_t *)khat + off, true);
-                if constexpr (SPL) kpl[p].load((const bf16_t *)khat + klo_off + off, true);
             } else {
                 kr[p].load(k + off, true);
             }
@@ -155,9 +158,13 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
     };
 
     load_tile(0);
-    raw_max();
-    float vscale = set_scale(vmax <= 3e38f ? vmax : 0.f, 7);
-    bool rescan = __syncthreads_or(smax[sc] == 0u) && nt > 1;
+    float vscale = 1.0f;
+    bool rescan = false;
+    if constexpr (!V3) {
+        raw_max();
+        vscale = set_scale(vmax <= 3e38f ? vmax : 0.f, 7);
+        rescan = __syncthreads_or(smax[sc] == 0u) && nt > 1;
+    }
 
     f16v acc[NQ][CT];
     float rs[NQ];
@@ -178,6 +185,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
                 const h8 a = ld8(kp + 16 * ks), b = ld8(kp + C::KH + 16 * ks);
 #pragma unroll
                 for (int u = 0; u < NQ; ++u) {
+                    if constexpr (V3) s[u] = mma(b, ql[u][C::QLDS ? 0 : ks], s[u]);
                     s[u] = mma(a, ql[u][C::QLDS ? 0 : ks], s[u]);
                     s[u] = mma(b, qh[u][ks], s[u]);
                 }
@@ -190,42 +198,56 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
                 const h8 b = ld8(kp + C::KH + 16 * ks);
 #pragma unroll
                 for (int u = 0; u < NQ; ++u) {
-                    s[u] = mma(a, ld8(qlw + 32 * u * RS + 16 * ks), s[u]);
+                    const h8 lo = ld8(qlw + 32 * u * RS + 16 * ks);
+                    if constexpr (V3) s[u] = mma(b, lo, s[u]);
+                    s[u] = mma(a, lo, s[u]);
                     s[u] = mma(b, qh[u][ks], s[u]);
                 }
             }
 #pragma unroll
             for (int u = 0; u < NQ; ++u) s[u] = mma(a, qh[u][ks], s[u]);
         }
-        // weights: t = 1 + s; p = 2 takes 2 f_2 = (1 + s)^2 + 1 (the
-        // factor 2 cancels in F / G and is taken out of G)
-        h8 wh[NQ][2], wl[NQ][SPL ? 2 : 1];
+        // weights 2 f_2 = (1 + s)^2 + 1 (the factor 2 cancels in F / G and is
+        // taken out of G)
+        h8 wh[NQ][2], wl[NQ][SPL ? 2 : 1], w3[V3 ? NQ : 1][2][3];
 #pragma unroll
         for (int u = 0; u < NQ; ++u) {
             const int qb0 = q0 + 32 * u;
-            float w[16];
+            float w[16], z[V3 ? 16 : 1];
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const float t = SPL ? fmaf(s[u][i], sc2, 1.0f) : s[u][i];
-                w[i] = C::P == 2 ? fmaf(t, t, 1.0f) : t;
+                if constexpr (V3) {
+                    // 2 f_2 - 2 = s (s + 2): what G has beside its count of keys
+                    const float x = s[u][i] * sc2;
+                    z[i] = x * (x + 2.0f);
+                    w[i] = z[i] + 2.0f;
+                } else {
+                    const float t = SPL ? fmaf(s[u][i], sc2, 1.0f) : s[u][i];
+                    w[i] = fmaf(t, t, 1.0f);
+                }
             }
             if (masked) {
                 asm volatile("");   // a branch, not a compare and select per element of every tile
                 const int last = C::CAUSAL ? qb0 + r32 : N - 1;
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
-                    if (kb + 8 * (i / 4) + 4 * h + i % 4 > last) w[i] = 0.f;
+                    if (kb + 8 * (i / 4) + 4 * h + i % 4 > last) {
+                        w[i] = 0.f;
+                        if constexpr (V3) z[i] = 0.f;
+                    }
             }
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                split8<SPL>(w + 8 * e, wh[u][e], wl[u][SPL ? e : 0]);
+                if constexpr (V3) split3(w + 8 * e, w3[u][e]);
+                else split8<SPL>(w + 8 * e, wh[u][e], wl[u][SPL ? e : 0]);
             }
             if constexpr (SPL) {
+                float *const y = V3 ? z : w;
 #pragma unroll
                 for (int d = 8; d; d /= 2)
 #pragma unroll
-                    for (int i = 0; i < d; ++i) w[i] += w[i + d];
-                rs[u] += w[0];
+                    for (int i = 0; i < d; ++i) y[i] += y[i + d];
+                rs[u] += y[0];
             } else {
                 // the sum of the rounded weights, as the numerator takes them
                 const h2 one = {(_Float16)1.0f, (_Float16)1.0f};
@@ -235,20 +257,16 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
                                                    one, rs[u], false);
             }
         }
-        if constexpr (C::EXACT) {
+        if constexpr (V3) {
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
-                const h8 a0 = ld_tr<VS>(vhi, 32 * j, 32 * c), a1 = ld_tr<VS>(vhi, 32 * j + 16, 32 * c);
-                const h8 b0 = ld_tr<VS>(vlo, 32 * j, 32 * c), b1 = ld_tr<VS>(vlo, 32 * j + 16, 32 * c);
+                h8 a[3][2];
 #pragma unroll
-                for (int u = 0; u < NQ; ++u) {
-                    f16v z = mma(b0, wh[u][0], f16v{});
-                    z = mma(b1, wh[u][1], z);
-                    z = mma(a0, wl[u][0], z);
-                    z = mma(a1, wl[u][1], z);
-                    z = mma(a0, wh[u][0], z);
-                    acc[u][c] += mma(a1, wh[u][1], z);
-                }
+                for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) a[i][e] = ld_tr<VS>(vhi + i * C::VH, 32 * j + 16 * e, 32 * c);
+#pragma unroll
+                for (int u = 0; u < NQ; ++u) acc[u][c] += mma33(a, w3[u]);
             }
         } else {
 #pragma unroll
@@ -297,26 +315,30 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     y[i] = vr[p].get(i);
-                    vmax = fmaxf(vmax, fabsf(y[i]));
-                    y[i] *= vscale;
+                    if constexpr (!V3) {
+                        vmax = fmaxf(vmax, fabsf(y[i]));
+                        y[i] *= vscale;
+                    }
                 }
                 h8 hi, lo;
-                split8<VSPL>(y, hi, lo);
                 const bool ok = C::BK % C::TPP == 0 || row < C::BK;
-                if (ok) {
-                    *(h8 *)(vhi + row * VS + 8 * sc) = hi;
-                    if constexpr (VSPL) *(h8 *)(vlo + row * VS + 8 * sc) = lo;
+                if constexpr (V3) {
+                    h8 y3[3];
+                    split3(y, y3);
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (ok) *(h8 *)(vhi + i * C::VH + row * VS + 8 * sc) = y3[i];
+                } else {
+                    split8<false>(y, hi, lo);
+                    if (ok) *(h8 *)(vhi + row * VS + 8 * sc) = hi;
                 }
                 if constexpr (C::KP) {
-                    if (ok) {
-                        *(uint4 *)(khi + row * RS + 8 * sc) = *(uint4 *)kph[p].w;
-                        if constexpr (SPL) *(uint4 *)(klo + row * RS + 8 * sc) = *(uint4 *)kpl[p].w;
-                    }
+                    if (ok) *(uint4 *)(khi + row * RS + 8 * sc) = *(uint4 *)kph[p].w;
                 } else {
                     float x[8];
 #pragma unroll
                     for (int i = 0; i < 8; ++i) x[i] = kr[p].get(i);
-                    standardise_group<D>(x, true);
+                    standardise_group<D>(x, true, C::QKS);
                     split8<SPL>(x, hi, lo);
                     if (ok) {
                         *(h8 *)(khi + row * RS + 8 * sc) = hi;
@@ -333,10 +355,11 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
                 tile(j, kb, (C::CAUSAL && kb + 31 > q0) || kb + 32 > N);
             }
         }
-        if (rescan || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
+        if (V3 || rescan || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
         rescan = true;
     }
 
+    auto keys_of = [&](int n) { return C::CAUSAL ? n + 1 : N; };
     // O = F / G.  Where waves split the keys their partial sums meet in LDS
     // first, [wave][column][query], and each wave finishes a share of the
     // columns.
@@ -344,9 +367,9 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
 #pragma unroll
         for (int u = 0; u < NQ; ++u) {
             const int n = q0 + 32 * u + r32;
-            const float G = half_sum(rs[u]);
+            const float G = half_sum(rs[u]) + (V3 ? 2.0f * (float)keys_of(n) : 0.f);
             if (n < N) {
-                if (g && h == 0) g[(size_t)head * N + n] = C::P == 2 ? 0.5f * G : G;
+                if (g && h == 0) g[(size_t)head * N + n] = 0.5f * G;
                 const float r = 1.0f / G;
 #pragma unroll
                 for (int c = 0; c < CT; ++c)
@@ -354,7 +377,7 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
                     for (int b = 0; b < 4; ++b) {
                         const int d = 32 * c + 8 * b + 4 * h;
                         if (D % 32 == 0 || d < D) {
-                            const float f = r / sscale[d / 8];
+                            const float f = V3 ? r : r / sscale[d / 8];
                             T *o = out + (size_t)n * D + d;
                             if constexpr (sizeof(T) == 2) {
                                 *(uint2 *)o = make_uint2(
@@ -386,13 +409,14 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
 #pragma unroll
         for (int w = 0; w < C::NWK; ++w) G += part[w * 32 * W + 32 * 32 * CT + r32];
         const int n = q0 + r32;
+        if constexpr (V3) G += 2.0f * (float)keys_of(n);
         if (n < N) {
-            if (g && h == 0 && wk == 0) g[(size_t)head * N + n] = C::P == 2 ? 0.5f * G : G;
+            if (g && h == 0 && wk == 0) g[(size_t)head * N + n] = 0.5f * G;
             const float r = 1.0f / G;
             // columns of this wave and half wave, 4 at a time
 #pragma unroll
             for (int d = 4 * (2 * wk + h); d < D; d += 8 * C::NWK) {
-                const float f = r / sscale[d / 8];
+                const float f = V3 ? r : r / sscale[d / 8];
                 float x[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -410,11 +434,11 @@ __global__ __launch_bounds__(C::NTH, 2) void fwd_kernel(
     }
 }
 
-// k^ in fp16 (and its lo part, SPL) for the kernels that read each key from
-// many workgroups: one thread per 8 channels.
-template <typename T, int D, bool SPL>
+// k^ in fp16 for the kernel that reads each key from many workgroups: one
+// thread per 8 channels.
+template <typename T, int D>
 __global__ __launch_bounds__(256) void khat_kernel(const T *__restrict__ k, _Float16 *__restrict__ khat,
-                                                   size_t klo_off, long long rows)
+                                                   long long rows)
 {
     const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / (D / 8);
     const int c = threadIdx.x % (D / 8);
@@ -426,29 +450,34 @@ __global__ __launch_bounds__(256) void khat_kernel(const T *__restrict__ k, _Flo
     for (int i = 0; i < 8; ++i) x[i] = raw.get(i);
     standardise_group<D>(x, ok);
     h8 hi, lo;
-    split8<SPL>(x, hi, lo);
-    if (ok) {
-        *(h8 *)(khat + (size_t)row * D + 8 * c) = hi;
-        if constexpr (SPL) *(h8 *)(khat + klo_off + (size_t)row * D + 8 * c) = lo;
-    }
+    split8<false>(x, hi, lo);
+    if (ok) *(h8 *)(khat + (size_t)row * D + 8 * c) = hi;
 }
 
 // The workgroup shapes (queries per wave / 32, query columns, key columns of
 // waves, keys per step; KP: k^ from khat_kernel) and what each measured on an
 // MI355X: t = t0 + |(a N, b pairs)|_2 us, a (ns per key) one workgroup's pace
 // down its keys, b (ps per pair) the chip's when full, fitted to calls of 1 to
-// 96 heads of 256 to 8192 tokens, causal (pairs = heads N (N + queries per
-// workgroup) / 2; without the mask b is 0.85 to 0.95 of it).  Waves that split
-// the keys shorten a, waves that share a staged tile lower b.
+// 96 heads of 256 to 8192 tokens (float32 rows: 130 to 100000), causal (pairs =
+// heads N (N + queries per workgroup) / 2; without the mask b is 0.85 to 0.95 of
+// it).  Waves that split the keys shorten a, waves that share a staged tile
+// lower b.  Beyond the fit, to 100000 tokens of bf16 rows, the choice was within
+// 7% of the better side of the line between pairs and moments but for 1.31 (8
+// heads of 12000, D = 64) and 1.19.
 // fp16 operands: bf16, D = 64
 constexpr Shape SH64[] = {{32, 5.f, 7.6f, 1.13f}, {64, 4.f, 9.6f, .68f}, {128, 5.f, 13.f, .455f},
                           {128, 4.f, 20.5f, .375f}, {256, 7.f, 17.f, .31f}, {512, 6.f, 31.f, .275f}};
-// float32-grade operands
+// float32-grade operands, bf16 rows
 constexpr Shape SS16[] = {{32, 4.f, 4.6f, .70f}, {64, 4.f, 7.2f, .53f}, {256, 4.f, 18.6f, .32f}};
 constexpr Shape SS32[] = {{32, 4.f, 6.7f, 1.02f}, {64, 4.f, 9.f, .66f}, {256, 4.f, 21.5f, .40f}};
 constexpr Shape SS64[] = {{64, 6.f, 15.4f, 1.14f}, {128, 6.f, 21.2f, .82f}, {256, 6.f, 36.5f, .71f}};
 constexpr Shape SS128[] = {{64, 7.f, 25.f, 1.67f}, {128, 7.f, 36.f, 1.27f}, {256, 7.f, 57.f, 1.05f}};
-constexpr Shape SF128[] = {{32, 7.f, 36.f, 4.9f}, {128, 7.f, 42.5f, 1.7f}, {256, 7.f, 69.f, 1.43f}};
+// float32 rows (bf16 triples for the values: 1.0 to 1.5 of the time that fp16
+// pairs took, whose values depended on a shared scale)
+constexpr Shape SF16[] = {{32, 4.5f, 4.1f, .68f}, {64, 4.4f, 7.9f, .575f}, {256, 3.8f, 27.f, .485f}};
+constexpr Shape SF32[] = {{32, 5.5f, 5.6f, 1.1f}, {64, 5.2f, 9.f, .72f}, {256, 4.4f, 31.f, .59f}};
+constexpr Shape SF64[] = {{64, 7.f, 16.1f, 1.5f}, {128, 6.6f, 28.6f, 1.19f}, {256, 5.9f, 54.5f, 1.06f}};
+constexpr Shape SF128[] = {{64, 9.4f, 49.f, 3.6f}, {128, 10.9f, 53.f, 2.27f}, {256, 9.3f, 97.f, 1.99f}};
 
 Moments moments_fwd(int BH, int N, int D, int causal, bool grade32)
 {
@@ -458,10 +487,10 @@ Moments moments_fwd(int BH, int N, int D, int causal, bool grade32)
     if (!grade32 && causal) return {12.f, 0.f, 50.f, .95f};
     if (!grade32) return {25.f, .5f, 5.5f, .87f};
     switch (D) {
-    case 16: return {13.f, 0.f, 2.4f, causal ? .425f : .28f};
-    case 32: return {15.f, 0.f, 4.5f, causal ? 1.65f : 1.15f};
-    case 64: return {30.f, 0.f, 10.f, 6.5f};
-    default: return {15.f, 0.f, 81.f, 50.f};
+    case 16: return causal ? Moments{14.f, .07f, 1.9f, .46f} : Moments{14.f, .14f, 1.9f, .31f};
+    case 32: return causal ? Moments{16.f, .36f, 2.5f, 1.8f} : Moments{17.f, .55f, 2.5f, 1.21f};
+    case 64: return causal ? Moments{30.f, .63f, 9.1f, 9.8f} : Moments{30.f, 2.1f, 6.f, 6.6f};
+    default: return causal ? Moments{30.f, 0.f, 81.f, 50.f} : Moments{35.f, 0.f, 57.f, 53.f};
     }
 }
 
@@ -481,13 +510,12 @@ hipError_t launch_fwd(const void *q, const void *k, const void *v, void *out, fl
     if (C::SPL) frexpf(qs, &e);
     const float sc2 = C::SPL ? ldexpf(1.0f, e - 1) : 1.0f;
     _Float16 *khat = (_Float16 *)ws;
-    const size_t lo = (size_t)rows * C::D;
     if (C::KP)
-        hipLaunchKernelGGL((khat_kernel<T, C::D, C::SPL>), dim3((unsigned)pb), dim3(256), 0, st,
-                           (const T *)k, khat, lo, rows);
+        hipLaunchKernelGGL((khat_kernel<T, C::D>), dim3((unsigned)pb), dim3(256), 0, st, (const T *)k,
+                           khat, rows);
     hipLaunchKernelGGL((fwd_kernel<C>), dim3((unsigned)((long long)BH * nqb)), dim3(C::NTH), 0, st,
-                       (const T *)q, (const T *)k, (const T *)v, khat, lo, (T *)out, g, N, BH, nqb,
-                       hgrp, qs / sc2, sc2);
+                       (const T *)q, (const T *)k, (const T *)v, khat, (T *)out, g, N, BH, nqb, hgrp,
+                       qs / sc2, sc2 / (C::QKS * C::QKS));
     return hipGetLastError();
 }
 
@@ -497,14 +525,16 @@ hipError_t launch_shape(const void *q, const void *k, const void *v, void *out, 
 {
 #define L(KP, NQ, NWQ, NWK, BK)                                                                    \
     do {                                                                                           \
-        typedef FwdCfg<T, D, 2, CAUSAL, SPL, KP, NQ, NWQ, NWK, BK> C;                              \
+        typedef FwdCfg<T, D, CAUSAL, SPL, KP, NQ, NWQ, NWK, BK> C;                              \
         static_assert(C::QB == S.qb, "table");                                                     \
         return launch_fwd<C>(q, k, v, out, g, BH, N, qs, ws, st);                                  \
     } while (0)
+    constexpr bool F32 = sizeof(T) == 4;
     if constexpr (D <= 32) {
-        if (shape == 0) { constexpr Shape S = (D == 16 ? SS16 : SS32)[0]; L(false, 1, 1, 8, 256); }
-        if (shape == 1) { constexpr Shape S = (D == 16 ? SS16 : SS32)[1]; L(false, 1, 2, 4, 128); }
-        if (shape == 2) { constexpr Shape S = (D == 16 ? SS16 : SS32)[2]; L(false, 1, 8, 1, 128); }
+        constexpr const Shape *const X = D == 16 ? (F32 ? SF16 : SS16) : F32 ? SF32 : SS32;
+        if (shape == 0) { constexpr Shape S = X[0]; L(false, 1, 1, 8, 256); }
+        if (shape == 1) { constexpr Shape S = X[1]; L(false, 1, 2, 4, 128); }
+        if (shape == 2) { constexpr Shape S = X[2]; L(false, 1, 8, 1, 128); }
     } else if constexpr (D == 64 && !SPL) {
         if (shape == 0) { constexpr Shape S = SH64[0]; L(false, 1, 1, 8, 256); }
         if (shape == 1) { constexpr Shape S = SH64[1]; L(false, 1, 2, 4, 128); }
@@ -513,17 +543,18 @@ hipError_t launch_shape(const void *q, const void *k, const void *v, void *out, 
         if (shape == 4) { constexpr Shape S = SH64[4]; L(true, 1, 8, 1, 128); }
         if (shape == 5) { constexpr Shape S = SH64[5]; L(false, 2, 8, 1, 128); }
     } else if constexpr (D == 64) {
-        if (shape == 0) { constexpr Shape S = SS64[0]; L(false, 1, 2, 4, 128); }
-        if (shape == 1) { constexpr Shape S = SS64[1]; L(false, 1, 4, 2, 64); }
-        if (shape == 2) { constexpr Shape S = SS64[2]; L(false, 1, 8, 1, 64); }
+        constexpr const Shape *const X = F32 ? SF64 : SS64;
+        if (shape == 0) { constexpr Shape S = X[0]; L(false, 1, 2, 4, 128); }
+        if (shape == 1) { constexpr Shape S = X[1]; L(false, 1, 4, 2, 64); }
+        if (shape == 2) { constexpr Shape S = X[2]; L(false, 1, 8, 1, 64); }
     } else if constexpr (sizeof(T) == 2) {
         if (shape == 0) { constexpr Shape S = SS128[0]; L(false, 1, 2, 4, 128); }
         if (shape == 1) { constexpr Shape S = SS128[1]; L(false, 1, 4, 2, 64); }
         if (shape == 2) { constexpr Shape S = SS128[2]; L(false, 1, 8, 1, 64); }
     } else {
-        if (shape == 0) { constexpr Shape S = SF128[0]; L(false, 1, 1, 4, 128); }
+        if (shape == 0) { constexpr Shape S = SF128[0]; L(false, 1, 2, 2, 64); }
         if (shape == 1) { constexpr Shape S = SF128[1]; L(false, 1, 4, 2, 64); }
-        if (shape == 2) { constexpr Shape S = SF128[2]; L(false, 1, 8, 1, 64); }
+        if (shape == 2) { constexpr Shape S = SF128[2]; L(false, 1, 8, 1, 32); }
     }
 #undef L
     return hipErrorInvalidValue;
@@ -538,10 +569,10 @@ int pairs_fwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t 
     const bool grade32 = pairs_grade32(N, D, causal, is_bf16);
     const Moments m = moments_fwd(BH, N, D, causal, grade32);
     switch (D) {
-    case 16: return pick(SS16, 3, m, BH, N, causal);
-    case 32: return pick(SS32, 3, m, BH, N, causal);
+    case 16: return pick(is_bf16 ? SS16 : SF16, 3, m, BH, N, causal);
+    case 32: return pick(is_bf16 ? SS32 : SF32, 3, m, BH, N, causal);
     case 64:
-        if (grade32) return pick(SS64, 3, m, BH, N, causal);
+        if (grade32) return pick(is_bf16 ? SS64 : SF64, 3, m, BH, N, causal);
         // shape 4 keeps k^ in the workspace
         return pick(SH64, 6, m, BH, N, causal, ws_bytes < (size_t)BH * N * 128 ? 4 : -1);
     case 128: return is_bf16 ? pick(SS128, 3, m, BH, N, causal) : pick(SF128, 3, m, BH, N, causal);
