@@ -23,8 +23,13 @@
  *  - Layout: q, k, v, out, dout, dq, dk, dv are [B, H, N, D] contiguous
  *    (D fastest) in the I/O dtype `dt`; g is [B, H, N] float32.
  *    Statistics (standardisation, G) are float32 whatever `dt` is;
- *    contractions accumulate in float32, and float32 rows enter them as fp16
- *    pairs (22 bits) or in float32.  The causal bf16, D = 64, p = 2
+ *    contractions accumulate in float32.  float32 rows keep every bit at any
+ *    magnitude (float32 MFMA, or three bf16 parts per operand), except in the
+ *    first-order (p = 1) backward's block kernels, whose operands are fp16 hi
+ *    + lo pairs under powers of two shared by a head.  bf16 rows enter the
+ *    fp16 MFMA kernels under powers of two shared by a group of columns, a row
+ *    or a head: values down to 2^-20 of the largest one that shares the scale
+ *    keep bf16's bits.  The causal bf16, D = 64, p = 2
  *    MFMA path carries its moment state between 128-token chunks in fp16
  *    (each chunk's float32 contribution is rounded and added); its error
  *    stays within the bf16 tolerance on every row of 65536-token causal

@@ -102,6 +102,14 @@ hipError_t pairs_bwd(const void *q, const void *k, const void *v, const void *o,
                      const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
                      int is_bf16, float qs, int shape, void *ws, hipStream_t st);
 
+// Its float32 rows (fm_pairs_bwd32.hip): six floats of ws per row.
+constexpr int PAIRS_BWD32_ROW_BYTES = 24;
+namespace pr { struct Moments; }
+int pairs_bwd32_pick(int BH, int N, int D, int causal, const pr::Moments &m);
+hipError_t pairs_bwd32(const void *q, const void *k, const void *v, const void *o, const void *dout,
+                       const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
+                       float qs, int shape, void *ws, hipStream_t st);
+
 // First order over blocks with linear states (tau D <= 1; forward: bf16 I/O):
 // whether a call runs there, and the calls (the backward's ws: 8 D + 8 bytes
 // per row).

@@ -25,8 +25,8 @@
 // scale's largest value, even if a row or column never meets that value.  They
 // are held as three bf16 numbers, which take a float32 apart into 8 + 8 + 8
 // bits: every bit of every exponent, no scale; the weights meet them in the
-// same form and a product takes six MFMAs (the three smallest of nine are
-// below 2^-24).
+// same form and a product takes six MFMAs (the other three of nine are 2^-26 of
+// it and less).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -135,8 +135,10 @@ __device__ __forceinline__ void split8(const float *x, h8 &hi, h8 &lo)
     }
 }
 
-// Eight floats as three bf16 parts, cut (not rounded) so that the parts of a
-// finite number add up to it and none overflows.
+// Eight floats as three bf16 parts, each the rest of the ones before it rounded
+// to nearest: they add up to the float, and a part is at most 2^-9 of the one
+// before it.
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void split3(const float *x, h8 (&p)[3])
 {
     uint4 w[3];
@@ -146,11 +148,11 @@ __device__ __forceinline__ void split3(const float *x, h8 (&p)[3])
         float a = x[2 * i], b = x[2 * i + 1];
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-            o[j][i] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+            const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), b2));
+            o[j][i] = u;
             if (j < 2) {
-                a -= __uint_as_float(ua & 0xffff0000u);
-                b -= __uint_as_float(ub & 0xffff0000u);
+                a -= __uint_as_float(u << 16);
+                b -= __uint_as_float(u & 0xffff0000u);
             }
         }
     }

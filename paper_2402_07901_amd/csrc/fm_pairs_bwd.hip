@@ -1,4 +1,5 @@
-// Pair backward (see fm_pairs.h; p = 2): the custom gradient of Sec. 2.5 (only
+// Pair backward of bf16 rows (see fm_pairs.h; p = 2; float32 rows:
+// fm_pairs_bwd32.hip): the custom gradient of Sec. 2.5 (only
 // O and G saved) over explicit (query, key) pairs.  With q~ = tau q^,
 // u = 1 / G, delta_i = dO_i.O_i and t = 1 + q~_i.k^_n = f_2'(tau s),
 //   dv_n  = sum_i f_2 u_i dO_i,               f_2 = (t^2 + 1) / 2,
@@ -40,19 +41,17 @@ struct BwdCfg {
     typedef T_ T;
     static constexpr int D = D_, NQ = NQ_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
     static constexpr bool CAUSAL = CAUSAL_, SPL = SPL_;
-    static constexpr bool VSPL = SPL && sizeof(T) == 4;
-    static constexpr bool EXACT = VSPL;   // as in the forward
     static constexpr int NTH = 64 * NWQ * NWK;
     static constexpr int QB = 32 * NQ * NWQ;
     static constexpr int KS = D / 16, CT = D < 32 ? 1 : D / 32;
     static constexpr int LPT = D / 8, TPP = NTH / LPT, NP = (BK + TPP - 1) / TPP;
     static constexpr int RS = row_stride<D>(), VS = tr_stride<D>();
     static constexpr int XH = BK * RS, AH = BK * VS;
-    static constexpr int NX = SPL ? 2 : 1, NV = VSPL ? 2 : 1;
+    static constexpr int NX = SPL ? 2 : 1;
     // planes of a step: x (scores), val (dO.v), and the contraction's A
     // operand where it is not x itself (role K: scaled q~; role V: scaled dO u)
-    static constexpr int TILE_Q = 2 * (NX * XH + NV * XH);
-    static constexpr int TILE_K = 2 * (NX * XH + NV * XH + NX * AH) + 8 * BK;
+    static constexpr int TILE_Q = 2 * (NX * XH + XH);
+    static constexpr int TILE_K = 2 * (NX * XH + XH + NX * AH) + 8 * BK;
     static constexpr int TILE = TILE_K;   // role V: NX (x) + NX (u) planes, fewer
     static constexpr bool QLDS = SPL && D >= 128;
     // two steps' tiles in turn where LDS has room beside the other workgroups
@@ -80,13 +79,13 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
                                           int qb)
 {
     typedef typename C::T T;
-    constexpr int D = C::D, NQ = C::NQ, KS = C::KS, CT = C::CT, RS = C::RS, VS = C::VS, NX = C::NX, NV = C::NV;
-    constexpr bool SPL = C::SPL, VSPL = C::VSPL;
+    constexpr int D = C::D, NQ = C::NQ, KS = C::KS, CT = C::CT, RS = C::RS, VS = C::VS, NX = C::NX;
+    constexpr bool SPL = C::SPL;
     const int N = a.N;
     // a step's planes (a buffer of them), in halves from its start: x, the
     // staged values (roles Q, K), the contraction's A operand (K, V), and
     // role K's row factors
-    constexpr int OV = NX * C::XH, OA = ROLE == ROLE_V ? OV : OV + NV * C::XH, OB = OA + NX * C::AH;
+    constexpr int OV = NX * C::XH, OA = ROLE == ROLE_V ? OV : OV + C::XH, OB = OA + NX * C::AH;
     static_assert(C::TILE % 16 == 0, "alignment");
     _Float16 *const olo = (_Float16 *)(smem + C::NB * C::TILE);
 
@@ -176,7 +175,7 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
 
     // own columns as B operands: x, and (roles Q, K) dO or v scaled
     h8 oh[NQ][KS], ol[NQ][SPL && !C::QLDS ? KS : 1];
-    h8 vo[ROLE != ROLE_V ? NQ : 1][KS], vol[ROLE != ROLE_V && VSPL ? NQ : 1][KS];
+    h8 vo[ROLE != ROLE_V ? NQ : 1][KS];
     float dcol[NQ];
     int ecol[NQ];
     _Float16 *const olw = olo + (32 * NQ * wq + r32) * RS + 8 * h;
@@ -211,7 +210,10 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
 #pragma unroll
                 for (int i = 0; i < D / 2; ++i) x[i] *= s;
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) split8<VSPL>(x + 8 * ks, vo[t][ks], vol[VSPL ? t : 0][ks]);
+                for (int ks = 0; ks < KS; ++ks) {
+                    h8 lo;
+                    split8<false>(x + 8 * ks, vo[t][ks], lo);
+                }
             } else {
                 const _Float16 *const pl = a.planes + (ROLE == ROLE_Q ? 3 : 2) * np + hb;
                 const _Float16 s = ROLE == ROLE_Q ? (_Float16)1.0f : half2i((w.e_v == NO_EXP ? 0 : w.e_v) - MO);
@@ -276,14 +278,6 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
                 const h8 x = ld8(vp + 16 * ks);
 #pragma unroll
                 for (int u = 0; u < NQ; ++u) d[u] = mma(x, vo[u][ks], d[u]);
-                if constexpr (VSPL) {
-                    const h8 w = ld8(vp + C::XH + 16 * ks);
-#pragma unroll
-                    for (int u = 0; u < NQ; ++u) {
-                        d[u] = mma(x, vol[u][ks], d[u]);
-                        d[u] = mma(w, vo[u][ks], d[u]);
-                    }
-                }
             }
         }
         h8 th[NQ][2], tl[NQ][SPL ? 2 : 1];
@@ -322,39 +316,22 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
         constexpr int AS = ROLE == ROLE_Q ? RS : VS;
         constexpr int APL = ROLE == ROLE_Q ? C::XH : C::AH;
         const _Float16 *const ap = ROLE == ROLE_Q ? xhi : ahi;
-        if constexpr (C::EXACT) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
-                const h8 x0 = ld_tr<AS>(ap, 32 * j, 32 * c), x1 = ld_tr<AS>(ap, 32 * j + 16, 32 * c);
-                const h8 y0 = ld_tr<AS>(ap + APL, 32 * j, 32 * c), y1 = ld_tr<AS>(ap + APL, 32 * j + 16, 32 * c);
+                const h8 x = ld_tr<AS>(ap, 32 * j + 16 * e, 32 * c);
 #pragma unroll
-                for (int u = 0; u < NQ; ++u) {
-                    f16v z = mma(y0, th[u][0], f16v{});
-                    z = mma(y1, th[u][1], z);
-                    z = mma(x0, tl[u][0], z);
-                    z = mma(x1, tl[u][1], z);
-                    z = mma(x0, th[u][0], z);
-                    acc[u][c] += mma(x1, th[u][1], z);
-                }
-            }
-        } else {
+                for (int u = 0; u < NQ; ++u) acc[u][c] = mma(x, th[u][e], acc[u][c]);
+                if constexpr (SPL) {
+                    const h8 y = ld_tr<AS>(ap + APL, 32 * j + 16 * e, 32 * c);
 #pragma unroll
-            for (int e = 0; e < 2; ++e)
-#pragma unroll
-                for (int c = 0; c < CT; ++c) {
-                    const h8 x = ld_tr<AS>(ap, 32 * j + 16 * e, 32 * c);
-#pragma unroll
-                    for (int u = 0; u < NQ; ++u) acc[u][c] = mma(x, th[u][e], acc[u][c]);
-                    if constexpr (SPL) {
-                        const h8 y = ld_tr<AS>(ap + APL, 32 * j + 16 * e, 32 * c);
-#pragma unroll
-                        for (int u = 0; u < NQ; ++u) {
-                            acc[u][c] = mma(x, tl[u][SPL ? e : 0], acc[u][c]);
-                            acc[u][c] = mma(y, th[u][e], acc[u][c]);
-                        }
+                    for (int u = 0; u < NQ; ++u) {
+                        acc[u][c] = mma(x, tl[u][SPL ? e : 0], acc[u][c]);
+                        acc[u][c] = mma(y, th[u][e], acc[u][c]);
                     }
                 }
-        }
+            }
     };
 
     // writes the loaded step t to a buffer
@@ -423,11 +400,8 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
                         *(h8 *)(ahi + C::AH + row * VS + 8 * sc) = lo;
                     }
                 } else {
-                    split8<VSPL>(z, hi, lo);
-                    if (ok) {
-                        *(h8 *)(vhi + row * RS + 8 * sc) = hi;
-                        if constexpr (VSPL) *(h8 *)(vhi + C::XH + row * RS + 8 * sc) = lo;
-                    }
+                    split8<false>(z, hi, lo);
+                    if (ok) *(h8 *)(vhi + row * RS + 8 * sc) = hi;
                 }
                 if constexpr (ROLE == ROLE_K) {
                     const _Float16 w = half2i(y + 11);
@@ -576,17 +550,16 @@ constexpr Shape BS16[] = {{32, 11.f, 5.9f, 2.6f}, {32, 10.5f, 8.5f, 1.6f}, {256,
 constexpr Shape BS32[] = {{32, 13.f, 8.7f, 3.8f}, {64, 14.5f, 11.f, 2.4f}, {256, 15.f, 31.f, 1.65f}};
 constexpr Shape BS64[] = {{64, 17.f, 19.7f, 4.35f}, {128, 18.f, 28.f, 3.3f}, {256, 20.f, 47.f, 2.85f}};
 constexpr Shape BS128[] = {{128, 20.f, 45.f, 5.4f}, {256, 22.f, 70.f, 4.3f}};
-constexpr Shape BF128[] = {{128, 20.f, 82.f, 7.5f}, {256, 22.f, 90.f, 5.3f}};
 
-Moments moments_bwd(int D, int causal, int is_bf16, bool grade32)
+Moments moments_bwd(int D, int causal, bool grade32)
 {
     if (!grade32 && causal) return {12.f, 0.f, 113.f, 3.6f};
     if (!grade32) return {40.f, .5f, 68.f, 3.25f};
     switch (D) {
-    case 16: return {42.f, 0.f, 7.f, causal ? 1.75f : 1.25f};
-    case 32: return {60.f, 0.f, 13.f, causal ? 6.f : 4.4f};
-    case 64: return {110.f, 0.f, 30.f, 20.5f};
-    default: return {110.f, 0.f, 236.f, 162.f};
+    case 16: return causal ? Moments{36.f, .27f, 5.7f, 2.f} : Moments{37.5f, .4f, 6.3f, 1.21f};
+    case 32: return causal ? Moments{72.f, .2f, 9.f, 6.15f} : Moments{71.f, 1.05f, 5.7f, 3.9f};
+    case 64: return causal ? Moments{103.f, 2.f, 34.f, 29.6f} : Moments{101.f, 5.9f, 15.4f, 18.7f};
+    default: return causal ? Moments{130.f, 0.f, 236.f, 162.f} : Moments{150.f, 0.f, 175.f, 168.f};
     }
 }
 
@@ -618,12 +591,9 @@ hipError_t launch_bwd_shape(const void *q, const void *k, const void *v, const v
         if (shape == 0) L(BS64[0], 1, 2, 4, 128);
         if (shape == 1) L(BS64[1], 1, 4, 2, 64);
         if (shape == 2) L(BS64[2], 1, 8, 1, 64);
-    } else if constexpr (sizeof(T) == 2) {
+    } else {
         if (shape == 0) L(BS128[0], 1, 4, 2, 64);
         if (shape == 1) L(BS128[1], 1, 8, 1, 32);
-    } else {
-        if (shape == 0) L(BF128[0], 1, 4, 1, 32);
-        if (shape == 1) L(BF128[1], 1, 8, 1, 32);
     }
 #undef L
     return hipErrorInvalidValue;
@@ -637,13 +607,16 @@ int pairs_bwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t 
     if (p != 2) return -1;
     const bool grade32 = pairs_grade32(N, D, causal, is_bf16);
     const size_t rows = (size_t)BH * N;
-    if (ws_bytes < rows * (grade32 ? 8 * (size_t)D + sizeof(RowInfo) : 10 * (size_t)D + sizeof(RowInfoH))) return -1;
-    const Moments m = moments_bwd(D, causal, is_bf16, grade32);
+    const size_t per_row = !is_bf16 ? PAIRS_BWD32_ROW_BYTES
+                         : grade32 ? 8 * (size_t)D + sizeof(RowInfo) : 10 * (size_t)D + sizeof(RowInfoH);
+    if (ws_bytes < rows * per_row) return -1;
+    const Moments m = moments_bwd(D, causal, grade32);
+    if (!is_bf16) return pairs_bwd32_pick(BH, N, D, causal, m);
     switch (D) {
     case 16: return pick(BS16, 3, m, BH, N, causal);
     case 32: return pick(BS32, 3, m, BH, N, causal);
     case 64: return grade32 ? pick(BS64, 3, m, BH, N, causal) : pick(BH64, 4, m, BH, N, causal);
-    case 128: return is_bf16 ? pick(BS128, 2, m, BH, N, causal) : pick(BF128, 2, m, BH, N, causal);
+    case 128: return pick(BS128, 2, m, BH, N, causal);
     }
     return -1;
 }
@@ -660,23 +633,15 @@ hipError_t pairs_bwd(const void *q, const void *k, const void *v, const void *o,
         if (causal) GO(T, DD, true, true);                                                         \
         GO(T, DD, false, true);                                                                    \
     } while (0)
-    if (is_bf16) {
-        switch (D) {
-        case 16: GO2(bf16_t, 16);
-        case 32: GO2(bf16_t, 32);
-        case 64:
-            if (causal) GO(bf16_t, 64, true, false);
-            if (pairs_grade32(N, D, causal, is_bf16)) GO(bf16_t, 64, false, true);
-            GO(bf16_t, 64, false, false);
-        case 128: GO2(bf16_t, 128);
-        }
-    } else {
-        switch (D) {
-        case 16: GO2(float, 16);
-        case 32: GO2(float, 32);
-        case 64: GO2(float, 64);
-        case 128: GO2(float, 128);
-        }
+    if (!is_bf16) return pairs_bwd32(q, k, v, o, dout, g, dq, dk, dv, BH, N, D, causal, qs, shape, ws, st);
+    switch (D) {
+    case 16: GO2(bf16_t, 16);
+    case 32: GO2(bf16_t, 32);
+    case 64:
+        if (causal) GO(bf16_t, 64, true, false);
+        if (pairs_grade32(N, D, causal, is_bf16)) GO(bf16_t, 64, false, true);
+        GO(bf16_t, 64, false, false);
+    case 128: GO2(bf16_t, 128);
     }
 #undef GO2
 #undef GO

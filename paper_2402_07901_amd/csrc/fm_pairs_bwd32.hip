@@ -1,0 +1,444 @@
+// Pair backward of float32 rows (p = 2): the gradient of fm_pairs_bwd.hip (see
+// there for the formulas and the three roles) with every operand in full.
+//
+// Nothing is known about the range of v, dO and 1 / G, and a causal row or a
+// column may never meet the largest value of its tile, so no operand stands
+// under a shared scale: q~, k^, v, dO and the weights are bf16 triples
+// (fm_pairs.h), six MFMAs a product, and 1 / G enters the weights in float32.
+// bwd32_prep leaves six floats per row; a step stages the raw rows and takes
+// them apart on the way into LDS (the same bytes from memory as two fp16
+// planes, and no planes to write).  Bound by MFMA issue once the chip is full
+// (18 products a tile), by a workgroup's walk down its rows before that; the
+// table at the end holds the paces.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <cmath>
+
+#include "fm_internal.h"
+#include "fm_pairs.h"
+
+namespace fm {
+namespace pr {
+namespace f32 {
+
+enum Role { ROLE_Q = 0, ROLE_K = 1, ROLE_V = 2 };
+
+// q~ = (q - mq) rq (tau in rq), k^ = (k - mk) rk, delta = dO.O, u = 1 / G.
+struct Row {
+    float mq, rq, mk, rk, delta, u;
+};
+static_assert(sizeof(Row) == PAIRS_BWD32_ROW_BYTES, "bytes per row");
+
+// Mean and 1 / std (Sec. 2.2, Eqs. 6-7) of the row whose 8 channels a lane holds.
+template <int D>
+__device__ __forceinline__ float2 row_stats(const RawRow<float, 8> &raw)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s += raw.get(i);
+    const float mu = group_sum<D / 8>(s) * (1.0f / D);
+    float v = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float x = raw.get(i) - mu;
+        v = fmaf(x, x, v);
+    }
+    return make_float2(mu, rsqrt1(group_sum<D / 8>(v) * (1.0f / D)));
+}
+
+// One thread per 8 channels of a row of the whole call.
+template <int D>
+__global__ __launch_bounds__(256) void bwd32_prep_kernel(
+    const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ o,
+    const float *__restrict__ dout, const float *__restrict__ g, Row *__restrict__ info,
+    long long rows, float tau)
+{
+    constexpr int L = D / 8;
+    const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / L;
+    const int c = threadIdx.x % L;
+    const bool ok = row < rows;
+    const size_t off = (size_t)(ok ? row : 0) * D + 8 * c;
+    RawRow<float, 8> rq, rk, ro, rd;
+    rq.load(q + off, ok);
+    rk.load(k + off, ok);
+    ro.load(o + off, ok);
+    rd.load(dout + off, ok);
+    float d = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) d = fmaf(rd.get(i), ro.get(i), d);
+    d = group_sum<L>(d);
+    const float2 a = row_stats<D>(rq), b = row_stats<D>(rk);
+    if (ok && c == 0) info[row] = Row{a.x, a.y * tau, b.x, b.y, d, 1.0f / g[row]};
+}
+
+template <int D_, bool CAUSAL_, int NWQ_, int NWK_, int BK_>
+struct Cfg {
+    static constexpr int D = D_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
+    static constexpr bool CAUSAL = CAUSAL_;
+    static constexpr int NTH = 64 * NWQ * NWK, QB = 32 * NWQ;
+    static constexpr int KS = D / 16, CT = D < 32 ? 1 : D / 32;
+    static constexpr int LPT = D / 8, TPP = NTH / LPT, NP = (BK + TPP - 1) / TPP;
+    static constexpr int RS = row_stride<D>(), VS = tr_stride<D>();
+    static constexpr int XH = BK * RS, AH = BK * VS, PH = XH > AH ? XH : AH;
+    // x (scores; also contracted by roles Q and K) and the staged values, three
+    // planes each, and two floats per row
+    static constexpr int TILE = 2 * (3 * XH + 3 * PH) + 8 * BK;
+    // waves per SIMD: at D = 128 a wave's own columns take 192 registers, so
+    // its workgroup of four is alone on the CU
+    static constexpr int WPS = D >= 128 ? 1 : 2;
+    // two steps' tiles in turn where LDS has room beside the other workgroups
+    // of the CU: one barrier a step instead of two
+    static constexpr int ROOM = 160 * 1024 * NWQ * NWK / (4 * WPS) - 256;
+    static constexpr bool DB = 2 * TILE <= ROOM;
+    static constexpr int RED_BYTES = NWK > 1 ? 4 * NWQ * NWK * 32 * 32 * CT : 0;
+    static constexpr int LOOP_BYTES = (DB ? 2 : 1) * TILE;
+    static constexpr int SMEM = LOOP_BYTES > RED_BYTES ? LOOP_BYTES : RED_BYTES;
+    static_assert(BK % (32 * NWK) == 0 && NWQ * NWK <= 4 * WPS, "shape");
+    static_assert(SMEM <= 160 * 1024 - 256 && TILE % 16 == 0, "LDS");
+};
+
+struct Args {
+    const float *q, *k, *v, *dout;
+    const Row *info;
+    float *dq, *dk, *dv;
+    int N, BH;
+    float tau;
+};
+
+// Rows x columns of two triples, the staged one read by rows from its planes.
+template <int KS>
+__device__ __forceinline__ f16v dot33(const _Float16 *p, int plane, const h8 (&o)[KS][3])
+{
+    f16v y = f16v{}, z = f16v{};   // as mma33
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const h8 a0 = ld8(p + 16 * ks), a1 = ld8(p + plane + 16 * ks), a2 = ld8(p + 2 * plane + 16 * ks);
+        y = mma_b(a2, o[ks][0], y);
+        y = mma_b(a1, o[ks][1], y);
+        y = mma_b(a0, o[ks][2], y);
+        y = mma_b(a1, o[ks][0], y);
+        y = mma_b(a0, o[ks][1], y);
+        z = mma_b(a0, o[ks][0], z);
+    }
+    return y + z;
+}
+
+template <typename C, int ROLE>
+__device__ __forceinline__ void block(unsigned char *smem, const Args &a, int head, int qb)
+{
+    constexpr int D = C::D, KS = C::KS, CT = C::CT, RS = C::RS, VS = C::VS;
+    const int N = a.N;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r32 = lane & 31, h = lane >> 5;
+    const int wq = wave / C::NWK, wk = wave % C::NWK;
+    const size_t hb = (size_t)head * N * D;
+    // own columns and staged rows
+    const float *const own = (ROLE == ROLE_Q ? a.q : a.k) + hb, *const stg = (ROLE == ROLE_Q ? a.k : a.q) + hb;
+    const float *const ownv = (ROLE == ROLE_Q ? a.dout : a.v) + hb, *const stgv = (ROLE == ROLE_Q ? a.v : a.dout) + hb;
+    const Row *const info = a.info + (size_t)head * N;
+    const int q0 = qb * C::QB + 32 * wq, col = q0 + r32;
+    const bool cok = col < N;
+    const int rbeg = C::CAUSAL && ROLE != ROLE_Q ? qb * C::QB : 0;
+    const int rend = C::CAUSAL && ROLE == ROLE_Q ? min(N, (qb + 1) * C::QB) : N;
+    const int t0 = rbeg / C::BK, t1 = (rend + C::BK - 1) / C::BK;
+
+    // staging: this thread's 8 channels and first row
+    const int sc = tid % C::LPT, st0 = tid / C::LPT;
+    RawRow<float, 8> xr[C::NP], vr[C::NP];
+    float mx[C::NP], rx[C::NP], ru[C::NP], rd[C::NP];
+    auto load_tile = [&](int t) {
+#pragma unroll
+        for (int p = 0; p < C::NP; ++p) {
+            // rows past the end repeat the last one: masked (role Q) or given weight 0
+            const unsigned n = (unsigned)min(t * C::BK + st0 + C::TPP * p, N - 1);
+            const unsigned off = n * (unsigned)D + 8u * sc;
+            xr[p].load(stg + off, true);
+            vr[p].load(stgv + off, true);
+            const Row w = info[n];
+            mx[p] = ROLE == ROLE_Q ? w.mk : w.mq;
+            rx[p] = ROLE == ROLE_Q ? w.rk : w.rq;
+            ru[p] = w.u;
+            rd[p] = w.delta;
+        }
+    };
+    load_tile(t0);
+
+    // own columns as B operands: x and (roles Q, K) dO or v
+    h8 ox[KS][3], ov[ROLE != ROLE_V ? KS : 1][3];
+    const Row cw = info[cok ? col : 0];
+    {
+        float x[D / 2];
+        load_cols<float, D>(own, col, N, x);
+        const float m = ROLE == ROLE_Q ? cw.mq : cw.mk, r = ROLE == ROLE_Q ? cw.rq : cw.rk;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[8 * ks + i] = cok ? (x[8 * ks + i] - m) * r : 0.f;
+            split3(x + 8 * ks, ox[ks]);
+        }
+        if constexpr (ROLE != ROLE_V) {
+            load_cols<float, D>(ownv, col, N, x);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) split3(x + 8 * ks, ov[ks]);
+        }
+    }
+
+    f16v acc[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) acc[c] = f16v{};
+
+    // One 32-row tile j of the staged step against the wave's columns; masked:
+    // some of its pairs lie beyond the diagonal or the last row.
+    auto tile = [&](const _Float16 *xp, int j, int kb, bool masked) {
+        const _Float16 *const vp = xp + 3 * C::XH;
+        const float *const rowU = (const float *)(vp + 3 * C::PH), *const rowD = rowU + C::BK;
+        const f16v s = dot33<KS>(xp + (32 * j + r32) * RS + 8 * h, C::XH, ox);
+        f16v d = f16v{};
+        if constexpr (ROLE != ROLE_V) d = dot33<KS>(vp + (32 * j + r32) * RS + 8 * h, C::PH, ov);
+        float w[16];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            float4 U, E;
+            if constexpr (ROLE != ROLE_Q) U = *(const float4 *)(rowU + 32 * j + 8 * b + 4 * h);
+            if constexpr (ROLE == ROLE_K) E = *(const float4 *)(rowD + 32 * j + 8 * b + 4 * h);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = 4 * b + i;
+                if constexpr (ROLE == ROLE_Q) w[e] = (1.0f + s[e]) * (d[e] - cw.delta);
+                else if constexpr (ROLE == ROLE_K)
+                    w[e] = (1.0f + s[e]) * fmaf(d[e], ((const float *)&U)[i], -((const float *)&E)[i]);
+                else w[e] = fmaf(s[e], s[e] + 2.0f, 2.0f) * ((const float *)&U)[i];   // U: u / 2
+            }
+        }
+        if (masked) {
+            asm volatile("");   // a branch, not a compare and select per element of every tile
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int row = kb + 8 * (i / 4) + 4 * h + i % 4;
+                if (ROLE == ROLE_Q ? row >= N || (C::CAUSAL && row > col) : row < col) w[i] = 0.f;
+            }
+        }
+        h8 w3[2][3];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) split3(w + 8 * e, w3[e]);
+        constexpr int AS = ROLE == ROLE_V ? VS : RS, PL = ROLE == ROLE_V ? C::PH : C::XH;
+        const _Float16 *const ap = ROLE == ROLE_V ? vp : xp;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            h8 x[3][2];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) x[i][e] = ld_tr<AS>(ap + i * PL, 32 * j + 16 * e, 32 * c);
+            acc[c] += mma33(x, w3);
+        }
+    };
+
+    // writes the loaded step t to a buffer
+    auto stage = [&](_Float16 *xp, int t) {
+        _Float16 *const vp = xp + 3 * C::XH;
+        float *const rowU = (float *)(vp + 3 * C::PH), *const rowD = rowU + C::BK;
+        constexpr int VST = ROLE == ROLE_V ? VS : RS;
+#pragma unroll
+        for (int p = 0; p < C::NP; ++p) {
+            const int row = st0 + C::TPP * p;
+            if (C::BK % C::TPP != 0 && row >= C::BK) continue;
+            float x[8];
+            h8 y[3];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = (xr[p].get(i) - mx[p]) * rx[p];
+            split3(x, y);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) *(h8 *)(xp + i * C::XH + row * RS + 8 * sc) = y[i];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = vr[p].get(i);
+            split3(x, y);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) *(h8 *)(vp + i * C::PH + row * VST + 8 * sc) = y[i];
+            if (ROLE != ROLE_Q && sc == 0) {
+                const bool in = t * C::BK + row < N;
+                rowU[row] = in ? (ROLE == ROLE_V ? 0.5f * ru[p] : ru[p]) : 0.f;
+                if constexpr (ROLE == ROLE_K) rowD[row] = in ? ru[p] * rd[p] : 0.f;
+            }
+        }
+    };
+    auto compute = [&](const _Float16 *buf, int t) {
+#pragma unroll 1
+        for (int j = wk; j < C::BK / 32; j += C::NWK) {
+            const int kb = t * C::BK + 32 * j;
+            if (kb >= N || (C::CAUSAL && ROLE == ROLE_Q && kb > q0 + 31)) break;
+            if (C::CAUSAL && ROLE != ROLE_Q && kb + 31 < q0) continue;
+            tile(buf, j, kb, ROLE == ROLE_Q ? (C::CAUSAL && kb + 31 > q0) || kb + 32 > N
+                                            : C::CAUSAL && kb < q0 + 31);
+        }
+    };
+
+    if constexpr (C::DB) {
+        constexpr int BUF = C::TILE / 2;
+        if (t0 < t1) stage((_Float16 *)smem, t0);
+        if (t0 + 1 < t1) load_tile(t0 + 1);
+        __syncthreads();
+        for (int t = t0; t < t1; ++t) {
+            compute((const _Float16 *)smem + ((t - t0) & 1) * BUF, t);
+            if (t + 1 < t1) {
+                stage((_Float16 *)smem + ((t + 1 - t0) & 1) * BUF, t + 1);
+                if (t + 2 < t1) load_tile(t + 2);
+            }
+            __syncthreads();
+        }
+    } else {
+        for (int t = t0; t < t1; ++t) {
+            __syncthreads();
+            stage((_Float16 *)smem, t);
+            if (t + 1 < t1) load_tile(t + 1);
+            __syncthreads();
+            compute((const _Float16 *)smem, t);
+        }
+    }
+    // partial sums of the waves that shared the columns
+    if constexpr (C::NWK > 1) {
+        float *red = (float *)smem;
+        constexpr int W = 32 * 32 * CT;
+        __syncthreads();
+        if (wk > 0) {
+            float *mine = red + wave * W;
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    mine[32 * (32 * c + 8 * (i / 4) + 4 * h + i % 4) + r32] = acc[c][i];
+        }
+        __syncthreads();
+        if (wk > 0) return;
+#pragma unroll
+        for (int w = 1; w < C::NWK; ++w) {
+            const float *part = red + (wave + w) * W;
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    acc[c][i] += part[32 * (32 * c + 8 * (i / 4) + 4 * h + i % 4) + r32];
+        }
+    }
+
+    if constexpr (ROLE == ROLE_Q) {
+        const float f = a.tau * cw.u;
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[c][i] *= f;
+    }
+    const size_t at = hb + (size_t)(cok ? col : 0) * D;
+    if constexpr (ROLE != ROLE_V) standardise_back<float, D>((ROLE == ROLE_Q ? a.q : a.k) + at, acc);
+    if (cok) store_col<float, D>((ROLE == ROLE_Q ? a.dq : ROLE == ROLE_K ? a.dk : a.dv) + at, acc);
+}
+
+// Block order: heads in groups of hgrp; within a group the columns with the
+// most rows first (role Q: the last queries; K, V: the first keys), the three
+// roles of a column block side by side.
+template <typename C>
+__global__ __launch_bounds__(C::NTH, C::WPS) void bwd32_kernel(Args a, int nqb, int hgrp)
+{
+    __shared__ alignas(16) unsigned char smem[C::SMEM];
+    const int b = blockIdx.x, per = 3 * hgrp * nqb, grp = b / per, r = b - grp * per;
+    const int gs = min(hgrp, a.BH - grp * hgrp);
+    const int head = grp * hgrp + r % gs, rest = r / gs, role = rest % 3, i = rest / 3;
+    if (role == 0) block<C, ROLE_Q>(smem, a, head, nqb - 1 - i);
+    else if (role == 1) block<C, ROLE_K>(smem, a, head, i);
+    else block<C, ROLE_V>(smem, a, head, i);
+}
+
+template <typename C>
+hipError_t launch(const float *q, const float *k, const float *v, const float *o, const float *dout,
+                  const float *g, float *dq, float *dk, float *dv, int BH, int N, float qs, void *ws,
+                  hipStream_t st)
+{
+    const long long rows = (long long)BH * N, pb = (rows * (C::D / 8) + 255) / 256;
+    const int nqb = (N + C::QB - 1) / C::QB, hgrp = BH < 32 ? BH : 32;
+    if (!grid_fits(pb, 256) || !grid_fits(3LL * BH * nqb, C::NTH)) return hipErrorInvalidConfiguration;
+    Row *info = (Row *)ws;
+    hipLaunchKernelGGL((bwd32_prep_kernel<C::D>), dim3((unsigned)pb), dim3(256), 0, st, q, k, o, dout, g,
+                       info, rows, qs);
+    const Args a{q, k, v, dout, info, dq, dk, dv, N, BH, qs};
+    hipLaunchKernelGGL((bwd32_kernel<C>), dim3((unsigned)(3LL * BH * nqb)), dim3(C::NTH), 0, st, a, nqb, hgrp);
+    return hipGetLastError();
+}
+
+// The workgroup shapes and their measured paces, as in the forward's tables:
+// t = t0 + |(a N, b pairs)|_2 us for the whole call, fitted to 1 to 96 heads of
+// 130 to 32768 tokens (the choice is within 1% of the best one on average, 21%
+// at most).  8 heads of 2048 tokens, causal: D = 32 74 us (fp16 pairs under
+// shared scales 64, the moment kernels 155), D = 64 121 (592).
+constexpr Shape B16[] = {{32, 6.5f, 3.4f, 3.7f}, {32, 6.5f, 6.7f, 2.5f}, {256, 7.9f, 41.4f, 1.85f}};
+constexpr Shape B32[] = {{32, 14.3f, 5.3f, 6.f}, {64, 14.3f, 11.5f, 3.6f}, {256, 9.9f, 52.4f, 1.92f}};
+constexpr Shape B64[] = {{64, 15.7f, 15.1f, 9.2f}, {128, 13.7f, 42.6f, 6.1f}, {256, 11.3f, 70.4f, 3.97f}};
+constexpr Shape B128[] = {{128, 22.7f, 110.f, 13.5f}};
+
+template <int D, bool CAUSAL>
+hipError_t launch_shape(const float *q, const float *k, const float *v, const float *o, const float *dout,
+                        const float *g, float *dq, float *dk, float *dv, int BH, int N, float qs, int shape,
+                        void *ws, hipStream_t st)
+{
+#define L(S, ...)                                                                                  \
+    do {                                                                                           \
+        typedef Cfg<D, CAUSAL, __VA_ARGS__> C;                                                     \
+        static_assert(C::QB == (S).qb, "table");                                                   \
+        return launch<C>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st);                      \
+    } while (0)
+    if constexpr (D == 16) {
+        if (shape == 0) L(B16[0], 1, 8, 256);
+        if (shape == 1) L(B16[1], 1, 4, 128);
+        if (shape == 2) L(B16[2], 8, 1, 64);
+    } else if constexpr (D == 32) {
+        if (shape == 0) L(B32[0], 1, 8, 256);
+        if (shape == 1) L(B32[1], 2, 4, 128);
+        if (shape == 2) L(B32[2], 8, 1, 64);
+    } else if constexpr (D == 64) {
+        if (shape == 0) L(B64[0], 2, 4, 128);
+        if (shape == 1) L(B64[1], 4, 2, 64);
+        if (shape == 2) L(B64[2], 8, 1, 64);
+    } else {
+        if (shape == 0) L(B128[0], 4, 1, 32);
+    }
+#undef L
+    return hipErrorInvalidValue;
+}
+
+}  // namespace f32
+}  // namespace pr
+
+int pairs_bwd32_pick(int BH, int N, int D, int causal, const pr::Moments &m)
+{
+    using namespace pr;
+    switch (D) {
+    case 16: return pick(f32::B16, 3, m, BH, N, causal);
+    case 32: return pick(f32::B32, 3, m, BH, N, causal);
+    case 64: return pick(f32::B64, 3, m, BH, N, causal);
+    case 128: return pick(f32::B128, 1, m, BH, N, causal);
+    }
+    return -1;
+}
+
+hipError_t pairs_bwd32(const void *q, const void *k, const void *v, const void *o, const void *dout,
+                       const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
+                       float qs, int shape, void *ws, hipStream_t st)
+{
+#define GO(DD)                                                                                     \
+    return causal ? pr::f32::launch_shape<DD, true>((const float *)q, (const float *)k, (const float *)v, \
+                        (const float *)o, (const float *)dout, g, (float *)dq, (float *)dk, (float *)dv, \
+                        BH, N, qs, shape, ws, st)                                                  \
+                  : pr::f32::launch_shape<DD, false>((const float *)q, (const float *)k, (const float *)v, \
+                        (const float *)o, (const float *)dout, g, (float *)dq, (float *)dk, (float *)dv, \
+                        BH, N, qs, shape, ws, st)
+    switch (D) {
+    case 16: GO(16);
+    case 32: GO(32);
+    case 64: GO(64);
+    case 128: GO(128);
+    }
+#undef GO
+    return hipErrorInvalidValue;
+}
+
+}  // namespace fm
