@@ -24,9 +24,8 @@
  *    (D fastest) in the I/O dtype `dt`; g is [B, H, N] float32.
  *    Statistics (standardisation, G) are float32 whatever `dt` is;
  *    contractions accumulate in float32.  float32 rows keep every bit at any
- *    magnitude (float32 MFMA, or three bf16 parts per operand), except in the
- *    first-order (p = 1) backward's block kernels, whose operands are fp16 hi
- *    + lo pairs under powers of two shared by a head.  bf16 rows enter the
+ *    magnitude (float32 MFMA, or three bf16 parts per operand; standardised
+ *    rows and weights also as fp16 hi + lo).  bf16 rows enter the
  *    fp16 MFMA kernels under powers of two shared by a group of columns, a row
  *    or a head: values down to 2^-20 of the largest one that shares the scale
  *    keep bf16's bits.  The causal bf16, D = 64, p = 2
@@ -52,7 +51,7 @@
  *  - Supported: D in {16, 32, 64, 128} (p = 2 below a length that depends on
  *    the shape: pair kernels on fp16 MFMA; longer: factorised fp16 MFMA
  *    kernels for D = 64, bf16, float32 MFMA kernels otherwise; p = 1: block
- *    kernels on fp16 MFMA where qk_scale D <= 1 and heads fill the GPU
+ *    kernels where qk_scale D <= 1 and heads fill the GPU
  *    (float32: the backward only), float32 MFMA kernels otherwise; the dropout
  *    calls: float32 VALU kernels);
  *    p in {1, 2}; causal in {0, 1};

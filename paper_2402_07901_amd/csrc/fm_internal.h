@@ -102,8 +102,9 @@ hipError_t pairs_bwd(const void *q, const void *k, const void *v, const void *o,
                      const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
                      int is_bf16, float qs, int shape, void *ws, hipStream_t st);
 
-// Its float32 rows (fm_pairs_bwd32.hip): six floats of ws per row.
-constexpr int PAIRS_BWD32_ROW_BYTES = 24;
+// Float32 rows (fm_pairs_bwd32.hip; first order fm_linear32.hip): six floats of
+// ws per row.
+constexpr int ROW32_BYTES = 24;
 namespace pr { struct Moments; }
 int pairs_bwd32_pick(int BH, int N, int D, int causal, const pr::Moments &m);
 hipError_t pairs_bwd32(const void *q, const void *k, const void *v, const void *o, const void *dout,
@@ -120,6 +121,9 @@ hipError_t linear_fwd(const void *q, const void *k, const void *v, void *out, fl
 hipError_t linear_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
                       const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
                       int is_bf16, float qs, void *ws, hipStream_t st);
+hipError_t linear_bwd32(const void *q, const void *k, const void *v, const void *o, const void *dout,
+                        const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
+                        float qs, void *ws, hipStream_t st);
 
 // Float32 MFMA kernels (v_mfma_f32_16x16x4_f32): p in {1, 2}, D in {16, 32,
 // 64, 128}, float32 or bf16 I/O, causal and non-causal (dispatch sends bf16

@@ -1,5 +1,6 @@
-// First order (p = 1, f = 1 + tau s) over blocks: forward and backward as
-// linear attention, float32-grade operands (fm_pairs.h).
+// First order (p = 1, f = 1 + tau s) over blocks: forward and backward of bf16
+// rows as linear attention, float32-grade operands (fm_pairs.h).  The backward
+// of float32 rows: fm_linear32.hip.
 //
 // Every pass is out_t = sum_r (alpha + X_r.Z_t) Y_r over the rows r that
 // column t sees (Sec. 2.4 at p = 1; Sec. 2.5's gradient with f' = 1):
@@ -47,7 +48,6 @@ struct Cfg {
     typedef T_ T;
     static constexpr int D = D_;
     static constexpr bool CAUSAL = CAUSAL_;
-    static constexpr bool VSPL = sizeof(T) == 4;
     static constexpr int NW = 8, NTH = 512, QB = 256, BK = 64;
     static constexpr int KS = D / 16, CT = D < 32 ? 1 : D / 32;
     static constexpr int LPT = D / 8, TPP = NTH / LPT, NP = (BK + TPP - 1) / TPP;
@@ -70,7 +70,7 @@ struct Cfg {
     static constexpr int SMEM = BODY + (ZLDS ? 2 * QB * RS : 0);
     static_assert(SMEM <= 158 * 1024, "LDS");
     // D <= 64: at most 128 registers in the backward, two workgroups a CU
-    static constexpr int BWD_WAVES = D <= 64 && !VSPL ? 4 : 2;
+    static constexpr int BWD_WAVES = D <= 64 ? 4 : 2;
 };
 
 template <typename C, int PASS>
@@ -79,9 +79,8 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
 {
     typedef typename C::T T;
     constexpr int D = C::D, KS = C::KS, CT = C::CT, RS = C::RS, VS = C::VS;
-    constexpr bool VSPL = C::VSPL;
-    constexpr bool XSPL = PASS == DQ ? VSPL : true, YSPL = PASS == FWD ? VSPL : true;
-    constexpr bool ZSPL = PASS == FWD || PASS == DV ? true : VSPL;
+    // operands with a lo part: bf16 rows need none
+    constexpr bool XSPL = PASS != DQ, YSPL = PASS != FWD, ZSPL = PASS == FWD || PASS == DV;
     constexpr bool UNIT = PASS == FWD || PASS == DV;   // alpha = 1
     const int N = a.N;
     _Float16 *const xp = (_Float16 *)smem, *const yp = xp + 2 * C::XH;
@@ -229,7 +228,7 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
                 }
                 standardise_group<D>(x, in);
                 split8<true>(x, xh, xl);
-                split8<VSPL>(y, yh, yl);
+                split8<false>(y, yh, yl);
             } else {
                 const h8 ah = __builtin_bit_cast(h8, *(uint4 *)ph[p].w), bl = __builtin_bit_cast(h8, *(uint4 *)pl[p].w);
                 const float f = !in ? 0.f : PASS == DQ ? exp2i(14 - M) : exp2i(14 - M) / gr[p];
@@ -237,7 +236,7 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
 #pragma unroll
                 for (int i = 0; i < 8; ++i) z[i] = in ? r0[p].get(i) * f : 0.f;
                 h8 zh8, zl8;
-                split8<PASS == DQ ? VSPL : true>(z, zh8, zl8);
+                split8<PASS != DQ>(z, zh8, zl8);
                 if constexpr (PASS == DV) {
                     xh = ah; xl = bl; yh = zh8; yl = zl8;
 #pragma unroll
@@ -336,33 +335,14 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
 #pragma unroll
                 for (int i = 0; i < C::TPW; ++i) {
                     const int yc = (tile0 + i) / CT, xc = (tile0 + i) % CT;
-                    if constexpr (C::VSPL) {
-                        // the step's products on their own, the ones with a lo part
-                        // first, then one rounded add (the matrix pipe's chained
-                        // sums round toward zero)
-                        f16v z = f16v{};
-                        h8 ya[(C::STEPS + C::GW - 1) / C::GW], xb[(C::STEPS + C::GW - 1) / C::GW];
 #pragma unroll
-                        for (int e0 = 0; e0 < C::STEPS; e0 += C::GW) {
-                            const int e = min(e0 + part, C::STEPS - 1);
-                            ya[e0 / C::GW] = ld_tr<VS>(yp, 16 * e, 32 * yc);
-                            xb[e0 / C::GW] = ld_tr<RS>(xp, 16 * e, 32 * xc);
-                            if constexpr (XSPL) z = mma(ya[e0 / C::GW], ld_tr<RS>(xp + C::XH, 16 * e, 32 * xc), z);
-                            if constexpr (YSPL) z = mma(ld_tr<VS>(yp + C::YH, 16 * e, 32 * yc), xb[e0 / C::GW], z);
-                        }
-#pragma unroll
-                        for (int e0 = 0; e0 < C::STEPS; e0 += C::GW) z = mma(ya[e0 / C::GW], xb[e0 / C::GW], z);
-                        if (C::STEPS % C::GW == 0 || part < C::STEPS) sh[i] += z;
-                    } else {
-#pragma unroll
-                        for (int e0 = 0; e0 < C::STEPS; e0 += C::GW) {
-                            const int e = e0 + part;
-                            if (C::STEPS % C::GW != 0 && e >= C::STEPS) break;
-                            const h8 ya = ld_tr<VS>(yp, 16 * e, 32 * yc), xb = ld_tr<RS>(xp, 16 * e, 32 * xc);
-                            sh[i] = mma(ya, xb, sh[i]);
-                            if constexpr (XSPL) sl[i] = mma(ya, ld_tr<RS>(xp + C::XH, 16 * e, 32 * xc), sl[i]);
-                            if constexpr (YSPL) sl[i] = mma(ld_tr<VS>(yp + C::YH, 16 * e, 32 * yc), xb, sl[i]);
-                        }
+                    for (int e0 = 0; e0 < C::STEPS; e0 += C::GW) {
+                        const int e = e0 + part;
+                        if (C::STEPS % C::GW != 0 && e >= C::STEPS) break;
+                        const h8 ya = ld_tr<VS>(yp, 16 * e, 32 * yc), xb = ld_tr<RS>(xp, 16 * e, 32 * xc);
+                        sh[i] = mma(ya, xb, sh[i]);
+                        if constexpr (XSPL) sl[i] = mma(ya, ld_tr<RS>(xp + C::XH, 16 * e, 32 * xc), sl[i]);
+                        if constexpr (YSPL) sl[i] = mma(ld_tr<VS>(yp + C::YH, 16 * e, 32 * yc), xb, sl[i]);
                     }
                 }
             }
@@ -504,7 +484,7 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
                     const h8 A0 = ld_tr<VS>(yp, 32 * j, 32 * c), A1 = ld_tr<VS>(yp, 32 * j + 16, 32 * c);
-                    f16v z = C::VSPL ? f16v{} : acc[c];
+                    f16v z = acc[c];
                     z = mma(A0, wl[0], z);
                     z = mma(A1, wl[1], z);
                     if constexpr (YSPL) {
@@ -513,7 +493,7 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
                     }
                     z = mma(A0, wh[0], z);
                     z = mma(A1, wh[1], z);
-                    acc[c] = C::VSPL ? acc[c] + z : z;
+                    acc[c] = z;
                 }
             }
         }
@@ -611,24 +591,25 @@ hipError_t run_bwd(const void *q, const void *k, const void *v, const void *o, c
 }
 
 // First-order calls that run here: scores with |tau s| <= 1 (tau D <= 1), so
-// that every weight is non-negative: G cannot nearly cancel, which would show
-// the operands' 22 bits (at tau = 1 the error of O was ten times the float32
-// scans', whose 24 bits those calls keep).  Float32 I/O: the backward only,
-// whose errors are the scans' (O 1.1e-7, dq, dk 1.8e-7, dv 1.3e-7); a float32
-// forward's G would go from 3.2e-8 to 4.6e-8.
+// that no weight is negative and G rarely comes close to cancelling, which
+// would show the bf16 rows' 22-bit operands (at tau = 1 the error of O was ten
+// times the float32 scans', whose 24 bits those calls keep).  Float32 rows: the
+// backward only (a float32 forward's G would go from 3.2e-8 to 4.6e-8).
 //
 // Paces, us: a workgroup takes w + a N rows / 1000 (half the rows under the
-// causal mask, on average), 256 run at once, float32 rows 1.25 times as long;
-// the scans take s + o heads N / 1000.  Measured, scans -> here (D = 64,
-// causal, tau = 1/64): 64 heads of 3001 tokens bf16 226 -> 118 forward,
-// 976 -> 313 backward, float32 backward 990 -> 440; 8 of 3001 51 -> 49
-// and 197 -> 73; 64 of 256 21 -> 17 and 91 -> 29; 1 of 8192 26 -> 103 (stays).
-// Float32 backward of 8 heads of 2048 tokens, D = 32: 71 -> 48.
+// causal mask, on average), 256 run at once; the scans take s + o heads N /
+// 1000.  Measured, scans -> here (D = 64, causal, tau = 1/64): 64 heads of 3001
+// tokens bf16 226 -> 118 forward, 976 -> 313 backward; 8 of 3001 51 -> 49 and
+// 197 -> 73; 64 of 256 21 -> 17 and 91 -> 29; 1 of 8192 26 -> 103 (stays).
+// Float32 backward, causal: 8 heads of 2048, D = 32 71 -> 42; 64 of 2048, D = 64
+// 677 -> 276; D = 128 1974 -> 683.
 struct Pace {
     float w, a, s, o;
 };
 constexpr Pace FP[] = {{13.f, 8.2f, 12.f, .21f}, {13.f, 10.6f, 12.f, .5f}, {13.f, 11.5f, 11.f, 1.1f}, {50.f, 33.f, 15.f, 2.9f}};
+// backward: bf16 rows, float32 rows
 constexpr Pace BP[] = {{13.f, 8.f, 37.f, 1.f}, {15.f, 11.f, 38.f, 2.2f}, {18.f, 14.f, 38.f, 4.8f}, {31.f, 39.f, 50.f, 14.5f}};
+constexpr Pace BF[] = {{5.6f, 7.8f, 37.f, 1.f}, {7.4f, 10.5f, 38.f, 2.2f}, {12.3f, 17.9f, 38.f, 4.8f}, {21.4f, 55.5f, 50.f, 14.5f}};
 
 }  // namespace lin
 
@@ -637,11 +618,11 @@ bool linear_plan(int BH, int N, int D, int p, int causal, int is_bf16, float qs,
     using namespace lin;
     if (p != 1 || qs * (float)D > 1.0f || (!is_bf16 && !backward)) return false;
     const size_t rows = (size_t)BH * N;
-    if (backward && ws_bytes < rows * (8 * (size_t)D + sizeof(RowInfo))) return false;
-    const Pace &x = (backward ? BP : FP)[D == 16 ? 0 : D == 32 ? 1 : D == 64 ? 2 : 3];
+    if (backward && ws_bytes < rows * (is_bf16 ? 8 * (size_t)D + sizeof(RowInfo) : ROW32_BYTES)) return false;
+    const Pace &x = (!backward ? FP : is_bf16 ? BP : BF)[D == 16 ? 0 : D == 32 ? 1 : D == 64 ? 2 : 3];
     const double n = 1e-3 * N, blocks = (double)BH * ((N + 255) / 256) * (backward ? 3 : 1) / 256;
     const double t = 5 + std::hypot(x.w + x.a * n, blocks * (x.w + x.a * n * (causal ? .5 : 1)));
-    return (is_bf16 ? t : 1.25 * t) < 0.9 * (x.s + x.o * BH * n);
+    return t < 0.9 * (x.s + x.o * BH * n);
 }
 
 hipError_t linear_fwd(const void *q, const void *k, const void *v, void *out, float *g, int BH,
@@ -664,10 +645,9 @@ hipError_t linear_bwd(const void *q, const void *k, const void *v, const void *o
                       const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
                       int is_bf16, float qs, void *ws, hipStream_t st)
 {
-#define GO2(T, DD)                                                                                 \
-    (causal ? lin::run_bwd<T, DD, true>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st)        \
-            : lin::run_bwd<T, DD, false>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st))
-#define GO(DD) return is_bf16 ? GO2(bf16_t, DD) : GO2(float, DD)
+    if (!is_bf16) return linear_bwd32(q, k, v, o, dout, g, dq, dk, dv, BH, N, D, causal, qs, ws, st);
+#define GO2(DD, CA) lin::run_bwd<bf16_t, DD, CA>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st)
+#define GO(DD) return causal ? GO2(DD, true) : GO2(DD, false)
     switch (D) {
     case 16: GO(16);
     case 32: GO(32);

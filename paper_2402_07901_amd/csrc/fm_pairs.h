@@ -176,6 +176,24 @@ __device__ __forceinline__ f16v mma33(const h8 (&a)[3][2], const h8 (&b)[2][3])
     return y + z;
 }
 
+// Rows x columns of two triples, the staged one read by rows from its planes.
+template <int KS>
+__device__ __forceinline__ f16v dot33(const _Float16 *p, int plane, const h8 (&o)[KS][3])
+{
+    f16v y = f16v{}, z = f16v{};   // as mma33
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const h8 a0 = ld8(p + 16 * ks), a1 = ld8(p + plane + 16 * ks), a2 = ld8(p + 2 * plane + 16 * ks);
+        y = mma_b(a2, o[ks][0], y);
+        y = mma_b(a1, o[ks][1], y);
+        y = mma_b(a0, o[ks][2], y);
+        y = mma_b(a1, o[ks][0], y);
+        y = mma_b(a0, o[ks][1], y);
+        z = mma_b(a0, o[ks][0], z);
+    }
+    return y + z;
+}
+
 // 1 / sqrt(v): the hardware's approximation (1 ulp) with one Newton step, so
 // that a row's scale is no larger an error than its elements' rounding.
 __device__ __forceinline__ float rsqrt1(float v)

@@ -607,7 +607,7 @@ int pairs_bwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t 
     if (p != 2) return -1;
     const bool grade32 = pairs_grade32(N, D, causal, is_bf16);
     const size_t rows = (size_t)BH * N;
-    const size_t per_row = !is_bf16 ? PAIRS_BWD32_ROW_BYTES
+    const size_t per_row = !is_bf16 ? ROW32_BYTES
                          : grade32 ? 8 * (size_t)D + sizeof(RowInfo) : 10 * (size_t)D + sizeof(RowInfoH);
     if (ws_bytes < rows * per_row) return -1;
     const Moments m = moments_bwd(D, causal, grade32);

@@ -17,60 +17,13 @@
 
 #include "fm_internal.h"
 #include "fm_pairs.h"
+#include "fm_pairs_rows.h"
 
 namespace fm {
 namespace pr {
 namespace f32 {
 
 enum Role { ROLE_Q = 0, ROLE_K = 1, ROLE_V = 2 };
-
-// q~ = (q - mq) rq (tau in rq), k^ = (k - mk) rk, delta = dO.O, u = 1 / G.
-struct Row {
-    float mq, rq, mk, rk, delta, u;
-};
-static_assert(sizeof(Row) == PAIRS_BWD32_ROW_BYTES, "bytes per row");
-
-// Mean and 1 / std (Sec. 2.2, Eqs. 6-7) of the row whose 8 channels a lane holds.
-template <int D>
-__device__ __forceinline__ float2 row_stats(const RawRow<float, 8> &raw)
-{
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s += raw.get(i);
-    const float mu = group_sum<D / 8>(s) * (1.0f / D);
-    float v = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float x = raw.get(i) - mu;
-        v = fmaf(x, x, v);
-    }
-    return make_float2(mu, rsqrt1(group_sum<D / 8>(v) * (1.0f / D)));
-}
-
-// One thread per 8 channels of a row of the whole call.
-template <int D>
-__global__ __launch_bounds__(256) void bwd32_prep_kernel(
-    const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ o,
-    const float *__restrict__ dout, const float *__restrict__ g, Row *__restrict__ info,
-    long long rows, float tau)
-{
-    constexpr int L = D / 8;
-    const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / L;
-    const int c = threadIdx.x % L;
-    const bool ok = row < rows;
-    const size_t off = (size_t)(ok ? row : 0) * D + 8 * c;
-    RawRow<float, 8> rq, rk, ro, rd;
-    rq.load(q + off, ok);
-    rk.load(k + off, ok);
-    ro.load(o + off, ok);
-    rd.load(dout + off, ok);
-    float d = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) d = fmaf(rd.get(i), ro.get(i), d);
-    d = group_sum<L>(d);
-    const float2 a = row_stats<D>(rq), b = row_stats<D>(rk);
-    if (ok && c == 0) info[row] = Row{a.x, a.y * tau, b.x, b.y, d, 1.0f / g[row]};
-}
 
 template <int D_, bool CAUSAL_, int NWQ_, int NWK_, int BK_>
 struct Cfg {
@@ -100,29 +53,11 @@ struct Cfg {
 
 struct Args {
     const float *q, *k, *v, *dout;
-    const Row *info;
+    const Row32 *info;
     float *dq, *dk, *dv;
     int N, BH;
     float tau;
 };
-
-// Rows x columns of two triples, the staged one read by rows from its planes.
-template <int KS>
-__device__ __forceinline__ f16v dot33(const _Float16 *p, int plane, const h8 (&o)[KS][3])
-{
-    f16v y = f16v{}, z = f16v{};   // as mma33
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const h8 a0 = ld8(p + 16 * ks), a1 = ld8(p + plane + 16 * ks), a2 = ld8(p + 2 * plane + 16 * ks);
-        y = mma_b(a2, o[ks][0], y);
-        y = mma_b(a1, o[ks][1], y);
-        y = mma_b(a0, o[ks][2], y);
-        y = mma_b(a1, o[ks][0], y);
-        y = mma_b(a0, o[ks][1], y);
-        z = mma_b(a0, o[ks][0], z);
-    }
-    return y + z;
-}
 
 template <typename C, int ROLE>
 __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int head, int qb)
@@ -136,7 +71,7 @@ __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int he
     // own columns and staged rows
     const float *const own = (ROLE == ROLE_Q ? a.q : a.k) + hb, *const stg = (ROLE == ROLE_Q ? a.k : a.q) + hb;
     const float *const ownv = (ROLE == ROLE_Q ? a.dout : a.v) + hb, *const stgv = (ROLE == ROLE_Q ? a.v : a.dout) + hb;
-    const Row *const info = a.info + (size_t)head * N;
+    const Row32 *const info = a.info + (size_t)head * N;
     const int q0 = qb * C::QB + 32 * wq, col = q0 + r32;
     const bool cok = col < N;
     const int rbeg = C::CAUSAL && ROLE != ROLE_Q ? qb * C::QB : 0;
@@ -155,7 +90,7 @@ __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int he
             const unsigned off = n * (unsigned)D + 8u * sc;
             xr[p].load(stg + off, true);
             vr[p].load(stgv + off, true);
-            const Row w = info[n];
+            const Row32 w = info[n];
             mx[p] = ROLE == ROLE_Q ? w.mk : w.mq;
             rx[p] = ROLE == ROLE_Q ? w.rk : w.rq;
             ru[p] = w.u;
@@ -166,7 +101,7 @@ __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int he
 
     // own columns as B operands: x and (roles Q, K) dO or v
     h8 ox[KS][3], ov[ROLE != ROLE_V ? KS : 1][3];
-    const Row cw = info[cok ? col : 0];
+    const Row32 cw = info[cok ? col : 0];
     {
         float x[D / 2];
         load_cols<float, D>(own, col, N, x);
@@ -357,7 +292,7 @@ hipError_t launch(const float *q, const float *k, const float *v, const float *o
     const long long rows = (long long)BH * N, pb = (rows * (C::D / 8) + 255) / 256;
     const int nqb = (N + C::QB - 1) / C::QB, hgrp = BH < 32 ? BH : 32;
     if (!grid_fits(pb, 256) || !grid_fits(3LL * BH * nqb, C::NTH)) return hipErrorInvalidConfiguration;
-    Row *info = (Row *)ws;
+    Row32 *info = (Row32 *)ws;
     hipLaunchKernelGGL((bwd32_prep_kernel<C::D>), dim3((unsigned)pb), dim3(256), 0, st, q, k, o, dout, g,
                        info, rows, qs);
     const Args a{q, k, v, dout, info, dq, dk, dv, N, BH, qs};

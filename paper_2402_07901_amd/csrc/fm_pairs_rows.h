@@ -5,6 +5,7 @@
 
 #include <type_traits>
 
+#include "fm_internal.h"
 #include "fm_pairs.h"
 
 namespace fm {
@@ -134,6 +135,55 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(
                 ((RowInfoH *)info)[row] = RowInfoH{d * fd, rho, (short)ed, (short)ev, ed == NO_EXP ? NO_EXP : ed - kx};
         }
     }
+}
+
+// What the backwards of float32 rows (fm_pairs_bwd32.hip, fm_linear32.hip) keep
+// per row: q~ = (q - mq) rq (tau in rq), k^ = (k - mk) rk, delta = dO.O, u = 1 / G.
+struct Row32 {
+    float mq, rq, mk, rk, delta, u;
+};
+static_assert(sizeof(Row32) == ROW32_BYTES, "bytes per row");
+
+// Mean and 1 / std (Sec. 2.2, Eqs. 6-7) of the row whose 8 channels a lane holds.
+template <int D>
+__device__ __forceinline__ float2 row_stats(const RawRow<float, 8> &raw)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s += raw.get(i);
+    const float mu = group_sum<D / 8>(s) * (1.0f / D);
+    float v = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float x = raw.get(i) - mu;
+        v = fmaf(x, x, v);
+    }
+    return make_float2(mu, rsqrt1(group_sum<D / 8>(v) * (1.0f / D)));
+}
+
+// One thread per 8 channels of a row of the whole call.
+template <int D>
+__global__ __launch_bounds__(256) void bwd32_prep_kernel(
+    const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ o,
+    const float *__restrict__ dout, const float *__restrict__ g, Row32 *__restrict__ info,
+    long long rows, float tau)
+{
+    constexpr int L = D / 8;
+    const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / L;
+    const int c = threadIdx.x % L;
+    const bool ok = row < rows;
+    const size_t off = (size_t)(ok ? row : 0) * D + 8 * c;
+    RawRow<float, 8> rq, rk, ro, rd;
+    rq.load(q + off, ok);
+    rk.load(k + off, ok);
+    ro.load(o + off, ok);
+    rd.load(dout + off, ok);
+    float d = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) d = fmaf(rd.get(i), ro.get(i), d);
+    d = group_sum<L>(d);
+    const float2 a = row_stats<D>(rq), b = row_stats<D>(rk);
+    if (ok && c == 0) info[row] = Row32{a.x, a.y * tau, b.x, b.y, d, 1.0f / g[row]};
 }
 
 }  // namespace pr

@@ -486,3 +486,32 @@ def test_linear_against_explicit_gradient(BH, N, D, causal, kind, dt):
             e = float(np.abs(to_f64(x).reshape(BH, N, D)[h] - r[0, 0]).max() / den)
             say(f"linear {kind} BH{BH} N{N} D{D} c{causal} head {h} {name}: {e:.2e}")
             assert e <= TOL[dt], (h, name, e)
+
+
+def gradient_bounds_p1(q64, k64, v64, d64, causal, scale):
+    """As gradient_bounds, first order: the weights' parts may cancel in w and in
+    G, so both count by magnitude."""
+    (qh, _, sq), (kh, _, sk) = oracle.standardize(q64), oracle.standardize(k64)
+    keep = np.tril(np.ones((len(q64),) * 2)) if causal else np.ones((len(q64),) * 2)
+    g = (keep * (1.0 + scale * qh @ kh.T)).sum(1)[:, None]
+    wa = keep * (1.0 + scale * np.abs(qh) @ np.abs(kh).T)
+    kappa = wa.sum(1)[:, None] / g
+    a = keep * kappa / g * (np.abs(d64) @ np.abs(v64).T
+                            + (np.abs(d64) * (wa @ np.abs(v64) / g)).sum(1)[:, None])
+
+    def back(b, xh, sd):
+        return (b + b.mean(1)[:, None] + np.abs(xh) * (b * np.abs(xh)).mean(1)[:, None]) / sd.reshape(-1, 1)
+
+    return (back(scale * a @ np.abs(kh), qh, sq), back(scale * a.T @ np.abs(qh), kh, sk),
+            wa.T @ (kappa * np.abs(d64) / g))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("kind", ["v row", "dout row", "columns", "plain"])
+@pytest.mark.parametrize("D,N", [(16, 600), (32, 600), (64, 600), (128, 600), (64, 33)])
+def test_float32_first_order_gradient_entries(D, N, kind, causal):
+    """The same for the float32 rows of the first-order block backward."""
+    assert linear_plan(8, N, D, causal, 1.0 / D, True, dt="f32")
+    check_gradient_entries(outlier_inputs(8, N, D, kind), 1, causal, 1.0 / D, gradient_bounds_p1,
+                           (D + N / 32 + 64) * 2.0 ** -24, f"p1 {kind} D{D} N{N} c{causal}")
