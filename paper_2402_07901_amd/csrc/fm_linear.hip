@@ -119,7 +119,10 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
             if (n < rbeg || n >= rend) continue;
             if constexpr (PASS == DQ) {
                 m = max(m, (int)x.e_v);
-            } else if (x.e_do != NO_EXP) {
+            } else if (x.e_do != NO_EXP && 1.0f / fabsf(g[n]) <= 3.4028235e38f) {
+                // (G may be zero at tau D = 1, where q^ = -k^ in the first row:
+                // such a row has no finite gradient, and no part in the scale of
+                // the rows that other columns see)
                 m = max(m, x.e_do - g_exp(g[n]));
                 if (PASS == DK) mc = max(mc, exp_above(fabsf(x.delta / g[n])));
             }

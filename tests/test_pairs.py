@@ -515,3 +515,22 @@ def test_float32_first_order_gradient_entries(D, N, kind, causal):
     assert linear_plan(8, N, D, causal, 1.0 / D, True, dt="f32")
     check_gradient_entries(outlier_inputs(8, N, D, kind), 1, causal, 1.0 / D, gradient_bounds_p1,
                            (D + N / 32 + 64) * 2.0 ** -24, f"p1 {kind} D{D} N{N} c{causal}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("D", [16, 64])
+def test_first_order_row_without_weight(D, dt):
+    """tau D = 1 and q^ = -k^ in the first row: its G is zero (here exactly), its
+    gradient not finite.  Keys past the 32-row tile that it shares do not see it
+    and keep theirs."""
+    BH, N = 48, 700
+    assert linear_plan(BH, N, D, True, 1.0 / D, True, dt=dt)
+    inp = make_inputs(1, BH, N, D, 7900, dt, with_dout=True)
+    q, k, v, do = (to_dev(inp[n], dt) for n in ("q", "k", "v", "dout"))
+    o, g = fm.fastmax_fwd(q, k, v, p=1, causal=True, scale=1.0 / D)
+    ref = fm.fastmax_bwd(q, k, v, o, do, g, p=1, causal=True, scale=1.0 / D)
+    g[:, :, 0] = 0.0
+    got = fm.fastmax_bwd(q, k, v, o, do, g, p=1, causal=True, scale=1.0 / D)
+    for name, a, b in zip(("dq", "dk", "dv"), got, ref):
+        assert row_rel(to_f64(a)[0, :, 32:], to_f64(b)[0, :, 32:]) <= TOL[dt], name
