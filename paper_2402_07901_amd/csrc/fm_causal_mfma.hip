@@ -193,7 +193,8 @@ size_t mfma_causal_fwd_workspace(int BH, int N)
 // Segments of the many-segment scan: as many as fill the CUs once, limited by
 // the summaries' room beside k^ in the workspace and to eight chunks at least;
 // fewer than three are not worth the build (a chunk's build takes about half
-// its scan's time).  Measured, us per forward, S segments against one or two:
+// its scan's time).  Its grids are a little larger than the plain scan's (heads
+// end in blocks of their own): a call that only the latter fit stays with it.  Measured, us per forward, S segments against one or two:
 // B1 H8 N65536 (S = 8) 3340 -> 712; B1 H16 N32768 (4) 1650 -> 708;
 // B1 H21 N32768 (3) 1650 -> 947.
 int causal_multi_segments(int BH, int N)
@@ -211,7 +212,8 @@ int causal_multi_segments(int BH, int N)
     if (S < 3) return 0;
     const int cseg = ((nch + (int)S - 1) / (int)S + 1) & ~1;
     S = (nch + cseg - 1) / cseg;
-    return S < 3 ? 0 : (int)S;
+    if (S < 3 || !grid_fits((long long)BH * ((N + 31) / 32), 256) || !grid_fits(items * S, NTH)) return 0;
+    return (int)S;
 }
 
 size_t mfma_causal_smem_bytes() { return sizeof(mfma_causal::Smem); }
@@ -235,8 +237,6 @@ hipError_t multi_fwd(const void *q, const void *k, const void *v, void *out, flo
     const size_t rows = (size_t)BH * N;
     const int items = BH * NSL, nch = (N + C - 1) / C, nvb = (N + 31) / 32;
     const int cseg = ((nch + S - 1) / S + 1) & ~1;
-    if (!grid_fits((long long)BH * nvb, 256) || !grid_fits((long long)items * S, NTH))
-        return hipErrorInvalidConfiguration;
     unsigned char *p = (unsigned char *)ws;
     _Float16 *kh = (_Float16 *)p;
     p += a256(rows * D * 2);

@@ -392,6 +392,21 @@ def test_many_segment_scan(BH, N):
     assert eo <= TOL["bf16"] and eg <= TOL["bf16"]
 
 
+def test_many_segments_refuse_no_size():
+    """At the dispatch limit (2^32 threads a launch) the many-segment scan's
+    blocks of 32 tokens per head can be one launch too many where the plain
+    scan's blocks of 32 rows fit: such a call is left to the latter."""
+    multi = getattr(fm.lib(), "_ZN2fm21causal_multi_segmentsEii")
+    fits = getattr(fm.lib(), "_ZN2fm25mfma_causal_fwd_grids_fitEii")
+    fits.restype = ctypes.c_bool
+    most = (2 ** 32 - 1) // 256             # workgroups of 256 threads
+    BH = 20
+    N = 32 * (most // BH) + 1
+    assert BH * -(-N // 32) > most >= -(-BH * N // 32)
+    assert fits(BH, N) and multi(BH, N) == 0
+    assert multi(BH, N - 33) >= 3
+
+
 @pytest.mark.gpu
 def test_scan_modes_agree_where_the_scan_serves():
     """The segment modes of the causal scan give the same bits at a size that
