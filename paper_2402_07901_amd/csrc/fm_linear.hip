@@ -621,6 +621,7 @@ bool linear_plan(int BH, int N, int D, int p, int causal, int is_bf16, float qs,
     using namespace lin;
     if (p != 1 || qs * (float)D > 1.0f || (!is_bf16 && !backward)) return false;
     const size_t rows = (size_t)BH * N;
+    if (!grid_fits((backward ? 3LL : 1LL) * BH * ((N + 255LL) / 256), 512)) return false;
     if (backward && ws_bytes < rows * (is_bf16 ? 8 * (size_t)D + sizeof(RowInfo) : ROW32_BYTES)) return false;
     const Pace &x = (!backward ? FP : is_bf16 ? BP : BF)[D == 16 ? 0 : D == 32 ? 1 : D == 64 ? 2 : 3];
     const double n = 1e-3 * N, blocks = (double)BH * ((N + 255) / 256) * (backward ? 3 : 1) / 256;

@@ -36,6 +36,7 @@
 #include <cmath>
 
 #include "fm_common.h"
+#include "fm_internal.h"
 #include "fm_f32_mfma.h"
 #include "fm_mfma.h"
 
@@ -349,16 +350,18 @@ struct Moments {
     float t0, h, a, b;
 };
 
-// The fastest shape, or -1 where the moment kernels are faster (by 3% at
-// least: near the line the rule stays with them).  skip: a shape left out.
-inline int pick(const Shape *s, int n, const Moments &m, int BH, int N, int causal, int skip = -1)
+// The fastest shape whose grid fits the dispatch limits (kinds workgroups of at
+// most 512 threads per block of queries), or -1 where the moment kernels are
+// faster (by 3% at least: near the line the rule stays with them) or no shape
+// fits.  skip: a shape left out.
+inline int pick(const Shape *s, int n, const Moments &m, int BH, int N, int causal, int kinds, int skip = -1)
 {
     const double tok = (double)N;
     const double mtok = std::max(tok, 128.0);   // their chunk
     double best = 0.97 * (m.t0 + m.h * BH + 1e-3 * std::max(m.a * mtok, m.b * mtok * BH));
     int shape = -1;
     for (int i = 0; i < n; ++i) {
-        if (i == skip) continue;
+        if (i == skip || !grid_fits((long long)kinds * BH * ((N + s[i].qb - 1LL) / s[i].qb), 512)) continue;
         const double pairs = causal ? 0.5 * BH * tok * (tok + s[i].qb) : 0.95 * BH * tok * tok;
         const double t = s[i].t0 + std::hypot(1e-3 * s[i].a * tok, 1e-6 * s[i].b * pairs);
         if (t < best) {

@@ -613,10 +613,10 @@ int pairs_bwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t 
     const Moments m = moments_bwd(D, causal, grade32);
     if (!is_bf16) return pairs_bwd32_pick(BH, N, D, causal, m);
     switch (D) {
-    case 16: return pick(BS16, 3, m, BH, N, causal);
-    case 32: return pick(BS32, 3, m, BH, N, causal);
-    case 64: return grade32 ? pick(BS64, 3, m, BH, N, causal) : pick(BH64, 4, m, BH, N, causal);
-    case 128: return pick(BS128, 2, m, BH, N, causal);
+    case 16: return pick(BS16, 3, m, BH, N, causal, 3);
+    case 32: return pick(BS32, 3, m, BH, N, causal, 3);
+    case 64: return grade32 ? pick(BS64, 3, m, BH, N, causal, 3) : pick(BH64, 4, m, BH, N, causal, 3);
+    case 128: return pick(BS128, 2, m, BH, N, causal, 3);
     }
     return -1;
 }

@@ -347,10 +347,10 @@ int pairs_bwd32_pick(int BH, int N, int D, int causal, const pr::Moments &m)
 {
     using namespace pr;
     switch (D) {
-    case 16: return pick(f32::B16, 3, m, BH, N, causal);
-    case 32: return pick(f32::B32, 3, m, BH, N, causal);
-    case 64: return pick(f32::B64, 3, m, BH, N, causal);
-    case 128: return pick(f32::B128, 1, m, BH, N, causal);
+    case 16: return pick(f32::B16, 3, m, BH, N, causal, 3);
+    case 32: return pick(f32::B32, 3, m, BH, N, causal, 3);
+    case 64: return pick(f32::B64, 3, m, BH, N, causal, 3);
+    case 128: return pick(f32::B128, 1, m, BH, N, causal, 3);
     }
     return -1;
 }

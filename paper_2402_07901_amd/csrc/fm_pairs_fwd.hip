@@ -569,13 +569,13 @@ int pairs_fwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t 
     const bool grade32 = pairs_grade32(N, D, causal, is_bf16);
     const Moments m = moments_fwd(BH, N, D, causal, grade32);
     switch (D) {
-    case 16: return pick(is_bf16 ? SS16 : SF16, 3, m, BH, N, causal);
-    case 32: return pick(is_bf16 ? SS32 : SF32, 3, m, BH, N, causal);
+    case 16: return pick(is_bf16 ? SS16 : SF16, 3, m, BH, N, causal, 1);
+    case 32: return pick(is_bf16 ? SS32 : SF32, 3, m, BH, N, causal, 1);
     case 64:
-        if (grade32) return pick(is_bf16 ? SS64 : SF64, 3, m, BH, N, causal);
+        if (grade32) return pick(is_bf16 ? SS64 : SF64, 3, m, BH, N, causal, 1);
         // shape 4 keeps k^ in the workspace
-        return pick(SH64, 6, m, BH, N, causal, ws_bytes < (size_t)BH * N * 128 ? 4 : -1);
-    case 128: return is_bf16 ? pick(SS128, 3, m, BH, N, causal) : pick(SF128, 3, m, BH, N, causal);
+        return pick(SH64, 6, m, BH, N, causal, 1, ws_bytes < (size_t)BH * N * 128 ? 4 : -1);
+    case 128: return is_bf16 ? pick(SS128, 3, m, BH, N, causal, 1) : pick(SF128, 3, m, BH, N, causal, 1);
     }
     return -1;
 }

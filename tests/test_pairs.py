@@ -392,6 +392,36 @@ def test_many_segment_scan(BH, N):
     assert eo <= TOL["bf16"] and eg <= TOL["bf16"]
 
 
+# queries (keys) per workgroup of each shape
+QB_FWD = {16: (32, 64, 256), 32: (32, 64, 256), 64: (64, 128, 256), 128: (64, 128, 256),
+          "half": (32, 64, 128, 128, 256, 512)}
+QB_BWD = {(16, "f32"): (32, 32, 256), (32, "f32"): (32, 64, 256), (64, "f32"): (64, 128, 256),
+          (128, "f32"): (128,), (16, "bf16"): (32, 32, 256), (32, "bf16"): (32, 64, 256),
+          (64, "bf16"): (64, 128, 256, 256), (128, "bf16"): (128, 256)}
+
+
+@pytest.mark.parametrize("D", [16, 32, 64, 128])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_plans_refuse_no_size(D, dt):
+    """A launch holds 2^32 threads at most: where a shape's grid is larger (many
+    short heads), the call goes to a shape or a kernel that fits."""
+    for BH in (1 << 17, 1 << 19, 700000, 1 << 20):
+        for N in (1, 33, 100, 161, 257, 300, 600, 1100, 2500):
+            for causal in (True, False):
+                half = dt == "bf16" and D == 64 and (causal or N >= 128)
+                s = plan(BH, N, D, causal, dt)
+                if s >= 0:
+                    qb = QB_FWD["half" if half else D][s]
+                    assert BH * -(-N // qb) * 512 < 2 ** 32, (BH, N, s)
+                s = plan(BH, N, D, causal, dt, True)
+                if s >= 0:
+                    qb = QB_BWD[(D, dt)][s]
+                    assert 3 * BH * -(-N // qb) * 512 < 2 ** 32, (BH, N, s)
+                for back in (False, True):
+                    if linear_plan(BH, N, D, causal, 1.0 / D, back, dt=dt):
+                        assert (3 if back else 1) * BH * -(-N // 256) * 512 < 2 ** 32, (BH, N, back)
+
+
 def test_many_segments_refuse_no_size():
     """At the dispatch limit (2^32 threads a launch) the many-segment scan's
     blocks of 32 tokens per head can be one launch too many where the plain
