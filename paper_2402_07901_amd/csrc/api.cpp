@@ -8,6 +8,10 @@
 #include "fm_common.h"
 #include "fm_internal.h"
 
+namespace fm {
+int code_of(hipError_t e);
+}
+
 namespace {
 
 // Head sizes served: 16, 32, 64 and 128 (the last the head size of Sec. 3.1's
@@ -73,8 +77,8 @@ bool mfma_causal(int D, int p, int causal, int dt)
 }
 
 // The float32 MFMA kernels (forward and backward) serve every case that no
-// plan and none of the factorised fp16 MFMA kernels takes (p = 1; p = 2 with float32 I/O, with D != 64, or
-// non-causal below 128 tokens).
+// plan and none of the factorised fp16 MFMA kernels takes (p = 1; p = 2 with
+// float32 I/O, with D != 64, or non-causal below 128 tokens).
 bool f32mfma(int D, int p, int causal, int dt, int N)
 {
     if (mfma_causal(D, p, causal, dt) || mfma_noncausal(N, D, p, causal, dt)) return false;
@@ -111,6 +115,81 @@ size_t bwd_ws(int B, int H, int N, int D, int p, int causal, int dt)
     if (mfma_noncausal(N, D, p, causal, dt)) return fm::mfma_nc_bwd_workspace(B * H, N);
     if (f32mfma(D, p, causal, dt, N)) return fm::f32mfma_bwd_workspace(B * H, N, D, p);
     return fm::generic_bwd_workspace(B, H, N, D, p);
+}
+
+// The kernels that serve a call; shape: the pair kernels' workgroup shape.
+struct Route {
+    fm::Kernels kernels;
+    int shape;
+};
+
+Route factorised_route(int N, int D, int p, int causal, int dt)
+{
+    if (mfma_causal(D, p, causal, dt)) return {fm::KERNELS_CAUSAL, 0};
+    if (mfma_noncausal(N, D, p, causal, dt)) return {fm::KERNELS_NONCAUSAL, 0};
+    return {f32mfma(D, p, causal, dt, N) ? fm::KERNELS_F32 : fm::KERNELS_GENERIC, 0};
+}
+
+Route fwd_route(int B, int H, int N, int D, int p, int causal, int dt, float qs)
+{
+    const int BH = B * H, bf = dt == FASTMAX_BF16;
+    if (fwd_grids_fit(BH, N, D, p, causal, dt)) {
+        if (fm::linear_plan(BH, N, D, p, causal, bf, qs, 0, 0)) return {fm::KERNELS_LINEAR, 0};
+        // short sequences: explicit pairs (the plan's tables hold both sides)
+        const int shape = fm::pairs_fwd_plan(BH, N, D, p, causal, bf, fwd_ws(B, H, N, D, p, causal, dt));
+        if (shape >= 0) return {fm::KERNELS_PAIRS, shape};
+    }
+    return factorised_route(N, D, p, causal, dt);
+}
+
+Route bwd_route(int B, int H, int N, int D, int p, int causal, int dt, float qs)
+{
+    const int BH = B * H, bf = dt == FASTMAX_BF16;
+    if (bwd_grids_fit(BH, N, D, p, causal, dt)) {
+        const size_t ws = bwd_ws(B, H, N, D, p, causal, dt);
+        if (fm::linear_plan(BH, N, D, p, causal, bf, qs, 1, ws)) return {fm::KERNELS_LINEAR, 0};
+        const int shape = fm::pairs_bwd_plan(BH, N, D, p, causal, bf, ws);
+        if (shape >= 0) return {fm::KERNELS_PAIRS, shape};
+    }
+    return factorised_route(N, D, p, causal, dt);
+}
+
+int fwd_launch(const Route &r, const void *q, const void *k, const void *v, void *out, float *g,
+               int BH, int N, int D, int p, int causal, float qs, int dt, void *ws, hipStream_t st)
+{
+    const int bf = dt == FASTMAX_BF16;
+    switch (r.kernels) {
+    case fm::KERNELS_LINEAR: return fm::code_of(fm::linear_fwd(q, k, v, out, g, BH, N, D, causal, qs, st));
+    case fm::KERNELS_PAIRS:
+        return fm::code_of(fm::pairs_fwd(q, k, v, out, g, BH, N, D, causal, bf, qs, r.shape, ws, st));
+    case fm::KERNELS_CAUSAL: return fm::code_of(fm::mfma_causal_fwd(q, k, v, out, g, BH, N, qs, ws, st));
+    case fm::KERNELS_NONCAUSAL: return fm::code_of(fm::mfma_nc_fwd(q, k, v, out, g, BH, N, qs, ws, st));
+    case fm::KERNELS_F32:
+        return fm::code_of(fm::f32mfma_fwd(q, k, v, out, g, BH, N, D, p, causal, bf, qs, ws, st));
+    default: return fm::code_of(fm::generic_fwd(q, k, v, out, g, BH, N, D, p, causal, bf, qs, ws, st));
+    }
+}
+
+int bwd_launch(const Route &r, const void *q, const void *k, const void *v, const void *out,
+               const void *dout, const float *g, void *dq, void *dk, void *dv, int BH, int N, int D,
+               int p, int causal, float qs, int dt, void *ws, hipStream_t st)
+{
+    const int bf = dt == FASTMAX_BF16;
+    switch (r.kernels) {
+    case fm::KERNELS_LINEAR:
+        return fm::code_of(fm::linear_bwd(q, k, v, out, dout, g, dq, dk, dv, BH, N, D, causal, bf, qs, ws, st));
+    case fm::KERNELS_PAIRS:
+        return fm::code_of(fm::pairs_bwd(q, k, v, out, dout, g, dq, dk, dv, BH, N, D, causal, bf, qs,
+                                         r.shape, ws, st));
+    case fm::KERNELS_CAUSAL:
+        return fm::code_of(fm::mfma_causal_bwd(q, k, v, out, dout, g, dq, dk, dv, BH, N, qs, ws, st));
+    case fm::KERNELS_NONCAUSAL:
+        return fm::code_of(fm::mfma_nc_bwd(q, k, v, out, dout, g, dq, dk, dv, BH, N, qs, ws, st));
+    case fm::KERNELS_F32:
+        return fm::code_of(fm::f32mfma_bwd(q, k, v, out, dout, g, dq, dk, dv, BH, N, D, p, causal, bf, qs, ws, st));
+    default:
+        return fm::code_of(fm::generic_bwd(q, k, v, out, dout, g, dq, dk, dv, BH, N, D, p, causal, bf, qs, ws, st));
+    }
 }
 
 }  // namespace
@@ -162,25 +241,8 @@ size_t fwd_workspace(int B, int H, int N, int D, int p, int causal, int dt)
 int fwd_run(const void *q, const void *k, const void *v, void *out, float *g, int B, int H, int N,
             int D, int p, int causal, float qk_scale, int dt, void *workspace, hipStream_t stream)
 {
-    hipError_t e;
-    const int bf = dt == FASTMAX_BF16;
-    // Short sequences: explicit pairs (the plan's tables hold both sides).
-    const int shape = pairs_fwd_plan(B * H, N, D, p, causal, bf, fwd_ws(B, H, N, D, p, causal, dt));
-    if (linear_plan(B * H, N, D, p, causal, bf, qk_scale, 0, 0) && fwd_grids_fit(B * H, N, D, p, causal, dt))
-        e = linear_fwd(q, k, v, out, g, B * H, N, D, causal, qk_scale, stream);
-    else if (shape >= 0 && fwd_grids_fit(B * H, N, D, p, causal, dt))
-        e = pairs_fwd(q, k, v, out, g, B * H, N, D, causal, bf, qk_scale, shape, workspace, stream);
-    else if (mfma_causal(D, p, causal, dt))
-        e = mfma_causal_fwd(q, k, v, out, g, B * H, N, qk_scale, workspace, stream);
-    else if (mfma_noncausal(N, D, p, causal, dt))
-        e = mfma_nc_fwd(q, k, v, out, g, B * H, N, qk_scale, workspace, stream);
-    else if (f32mfma(D, p, causal, dt, N))
-        e = f32mfma_fwd(q, k, v, out, g, B * H, N, D, p, causal, dt == FASTMAX_BF16, qk_scale,
-                        workspace, stream);
-    else
-        e = generic_fwd(q, k, v, out, g, B * H, N, D, p, causal, dt == FASTMAX_BF16, qk_scale,
-                        workspace, stream);
-    return fm::code_of(e);
+    return fwd_launch(fwd_route(B, H, N, D, p, causal, dt, qk_scale), q, k, v, out, g, B * H, N, D, p,
+                      causal, qk_scale, dt, workspace, stream);
 }
 
 }  // namespace fm
@@ -189,7 +251,7 @@ namespace {
 
 int fwd_impl(const void *q, const void *k, const void *v, void *out, float *g, int B, int H,
              int N, int D, int p, int causal, float qk_scale, int dt, void *workspace,
-             size_t workspace_bytes, hipStream_t stream)
+             size_t workspace_bytes, hipStream_t stream, bool factorised = false)
 {
     int rc = fm::fwd_validate(q, k, v, out, g, B, H, N, D, p, causal, qk_scale, dt);
     if (rc != FASTMAX_OK) return rc;
@@ -197,13 +259,15 @@ int fwd_impl(const void *q, const void *k, const void *v, void *out, float *g, i
     if (need > 0 && (!workspace || workspace_bytes < need)) return FASTMAX_EWORKSPACE;
     if (workspace && !aligned16(workspace)) return FASTMAX_EALIGN;
     if ((rc = fm::check_stream(stream)) != FASTMAX_OK) return rc;
-    return fm::fwd_run(q, k, v, out, g, B, H, N, D, p, causal, qk_scale, dt, workspace, stream);
+    return fwd_launch(factorised ? factorised_route(N, D, p, causal, dt)
+                                 : fwd_route(B, H, N, D, p, causal, dt, qk_scale),
+                      q, k, v, out, g, B * H, N, D, p, causal, qk_scale, dt, workspace, stream);
 }
 
 int bwd_impl(const void *q, const void *k, const void *v, const void *out, const void *dout,
              const float *g, void *dq, void *dk, void *dv, int B, int H, int N, int D, int p,
              int causal, float qk_scale, int dt, void *workspace, size_t workspace_bytes,
-             hipStream_t stream)
+             hipStream_t stream, bool factorised = false)
 {
     int rc = check_common(B, H, N, D, p, causal, dt);
     if (rc != FASTMAX_OK) return rc;
@@ -216,29 +280,10 @@ int bwd_impl(const void *q, const void *k, const void *v, const void *out, const
     if (need > 0 && (!workspace || workspace_bytes < need)) return FASTMAX_EWORKSPACE;
     if (workspace && !aligned16(workspace)) return FASTMAX_EALIGN;
     if ((rc = fm::check_stream(stream)) != FASTMAX_OK) return rc;
-    hipError_t e;
-    const int bf = dt == FASTMAX_BF16;
-    const int shape = fm::pairs_bwd_plan(B * H, N, D, p, causal, bf, need);
-    if (fm::linear_plan(B * H, N, D, p, causal, bf, qk_scale, 1, need) &&
-        bwd_grids_fit(B * H, N, D, p, causal, dt))
-        e = fm::linear_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, causal, bf, qk_scale,
-                           workspace, stream);
-    else if (shape >= 0 && bwd_grids_fit(B * H, N, D, p, causal, dt))
-        e = fm::pairs_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, causal, bf, qk_scale,
-                          shape, workspace, stream);
-    else if (mfma_causal(D, p, causal, dt))
-        e = fm::mfma_causal_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, qk_scale, workspace,
-                                stream);
-    else if (mfma_noncausal(N, D, p, causal, dt))
-        e = fm::mfma_nc_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, qk_scale, workspace,
-                            stream);
-    else if (f32mfma(D, p, causal, dt, N))
-        e = fm::f32mfma_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, p, causal,
-                            dt == FASTMAX_BF16, qk_scale, workspace, stream);
-    else
-        e = fm::generic_bwd(q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, p, causal,
-                            dt == FASTMAX_BF16, qk_scale, workspace, stream);
-    return fm::code_of(e);
+    return bwd_launch(factorised ? factorised_route(N, D, p, causal, dt)
+                                 : bwd_route(B, H, N, D, p, causal, dt, qk_scale),
+                      q, k, v, out, dout, g, dq, dk, dv, B * H, N, D, p, causal, qk_scale, dt,
+                      workspace, stream);
 }
 
 }  // namespace
@@ -388,5 +433,32 @@ const char *fastmax_strerror(int code)
 }
 
 const char *fastmax_version(void) { return "0.1.0"; }
+
+int fm_route(int BH, int N, int D, int p, int causal, float qk_scale, int dt, int backward)
+{
+    if (check_common(1, BH, N, D, p, causal, dt) != FASTMAX_OK) return FASTMAX_EINVAL;
+    const Route r = backward ? bwd_route(1, BH, N, D, p, causal, dt, qk_scale)
+                             : fwd_route(1, BH, N, D, p, causal, dt, qk_scale);
+    return 16 * r.kernels + r.shape;
+}
+
+int fm_scan_segments(int BH, int N) { return fm::causal_multi_segments(BH, N); }
+
+int fm_factorised_fwd(const void *q, const void *k, const void *v, void *out, float *g, int B, int H,
+                      int N, int D, int p, int causal, float qk_scale, int dt, void *workspace,
+                      size_t workspace_bytes, hipStream_t stream)
+{
+    return fwd_impl(q, k, v, out, g, B, H, N, D, p, causal, qk_scale, dt, workspace, workspace_bytes,
+                    stream, true);
+}
+
+int fm_factorised_bwd(const void *q, const void *k, const void *v, const void *out, const void *dout,
+                      const float *g, void *dq, void *dk, void *dv, int B, int H, int N, int D, int p,
+                      int causal, float qk_scale, int dt, void *workspace, size_t workspace_bytes,
+                      hipStream_t stream)
+{
+    return bwd_impl(q, k, v, out, dout, g, dq, dk, dv, B, H, N, D, p, causal, qk_scale, dt, workspace,
+                    workspace_bytes, stream, true);
+}
 
 }  // extern "C"

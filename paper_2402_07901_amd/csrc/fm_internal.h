@@ -184,4 +184,34 @@ size_t mfma_nc_workspace(int BH, int N);
 hipError_t mfma_nc_dv(const void *qh, const void *kh, const void *dout, const float *rg, void *dv,
                       int BH, int N, void *ws, hipStream_t st);
 
+// The kernel families, in the order that api.cpp offers a call to them.
+enum Kernels {
+    KERNELS_LINEAR = 0,      // first order over blocks (fm_linear*.hip)
+    KERNELS_PAIRS = 1,       // explicit pairs (fm_pairs_*.hip)
+    KERNELS_CAUSAL = 2,      // factorised fp16 MFMA scans
+    KERNELS_NONCAUSAL = 3,   // factorised fp16 MFMA moments
+    KERNELS_F32 = 4,         // factorised float32 MFMA
+    KERNELS_GENERIC = 5,     // float32 VALU
+};
+
+}  // namespace fm
+
+// For the tests, not part of the ABI: which kernels serve a call (16 * Kernels
+// + the pair kernels' shape), the many-segment scan's segments (0: none), and
+// the calls on the factorised kernels whatever the plans say, with the
+// arguments, checks and workspace of fastmax_fwd_scaled and fastmax_bwd_scaled.
+extern "C" {
+int fm_route(int BH, int N, int D, int p, int causal, float qk_scale, int dt, int backward);
+int fm_scan_segments(int BH, int N);
+int fm_factorised_fwd(const void *q, const void *k, const void *v, void *out, float *g, int B, int H,
+                      int N, int D, int p, int causal, float qk_scale, int dt, void *workspace,
+                      size_t workspace_bytes, hipStream_t stream);
+int fm_factorised_bwd(const void *q, const void *k, const void *v, const void *out, const void *dout,
+                      const float *g, void *dq, void *dk, void *dv, int B, int H, int N, int D, int p,
+                      int causal, float qk_scale, int dt, void *workspace, size_t workspace_bytes,
+                      hipStream_t stream);
+}
+
+namespace fm {
+
 }  // namespace fm

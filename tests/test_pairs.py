@@ -22,13 +22,27 @@ from paper_2402_07901_amd.inputs import bf16_bits_to_f64, f32_to_bf16_bits, make
 from gpu_util import TOL, max_rel, say, to_dev, to_f64
 
 
+LINEAR, PAIRS, CAUSAL, NONCAUSAL, FLOAT32 = range(5)     # enum Kernels of fm_internal.h
+
+
+def route(BH, N, D, causal, dt, backward=False, p=2, scale=1.0):
+    """(kernels, shape) that the library picks for a call."""
+    f = fm.lib().fm_route
+    f.argtypes = [ctypes.c_int] * 5 + [ctypes.c_float] + [ctypes.c_int] * 2
+    r = f(BH, N, D, p, int(causal), scale, fm.BF16 if dt == "bf16" else fm.F32, int(backward))
+    assert r >= 0
+    return divmod(r, 16)
+
+
 def plan(BH, N, D, causal, dt, backward=False):
-    """The shape the library picks (-1: the moment kernels)."""
-    f = getattr(fm.lib(), f"_ZN2fm14pairs_{'bwd' if backward else 'fwd'}_planEiiiiiim")
-    f.restype = ctypes.c_int
-    code = fm.BF16 if dt == "bf16" else fm.F32
-    ws = fm.workspace_bytes(1, BH, N, D, 2, causal, code, backward)
-    return f(BH, N, D, 2, int(causal), int(dt == "bf16"), ctypes.c_size_t(ws))
+    """The pair kernels' shape for a call of order 2 (-1: other kernels)."""
+    kernels, shape = route(BH, N, D, causal, dt, backward)
+    return shape if kernels == PAIRS else -1
+
+
+def segments(BH, N):
+    """Segments of the many-segment scan (0: not cut so)."""
+    return fm.lib().fm_scan_segments(BH, N)
 
 
 # (heads, N, D, dtype): sizes around the edges of each shape's tiles
@@ -373,8 +387,7 @@ def test_many_segment_scan(BH, N):
     """Few heads over a long sequence: the causal scan cut into many segments
     (a ragged last one among them) against the oracle's sampled rows, every
     segment's edge rows included."""
-    f = getattr(fm.lib(), "_ZN2fm21causal_multi_segmentsEii")
-    S = f(BH, N)
+    S = segments(BH, N)
     assert S >= 3 and plan(BH, N, 64, True, "bf16") == -1
     inp = make_inputs(1, BH, N, 64, 7600 + BH, "bf16")
     q, k, v = (to_dev(inp[n], "bf16") for n in ("q", "k", "v"))
@@ -426,15 +439,11 @@ def test_many_segments_refuse_no_size():
     """At the dispatch limit (2^32 threads a launch) the many-segment scan's
     blocks of 32 tokens per head can be one launch too many where the plain
     scan's blocks of 32 rows fit: such a call is left to the latter."""
-    multi = getattr(fm.lib(), "_ZN2fm21causal_multi_segmentsEii")
-    fits = getattr(fm.lib(), "_ZN2fm25mfma_causal_fwd_grids_fitEii")
-    fits.restype = ctypes.c_bool
     most = (2 ** 32 - 1) // 256             # workgroups of 256 threads
     BH = 20
     N = 32 * (most // BH) + 1
     assert BH * -(-N // 32) > most >= -(-BH * N // 32)
-    assert fits(BH, N) and multi(BH, N) == 0
-    assert multi(BH, N - 33) >= 3
+    assert segments(BH, N) == 0 and segments(BH, N - 33) >= 3
 
 
 @pytest.mark.gpu
@@ -462,11 +471,7 @@ def test_scan_modes_agree_where_the_scan_serves():
 # forward and backward, float32 backward
 # ---------------------------------------------------------------------------
 def linear_plan(BH, N, D, causal, scale, backward, dt="bf16", p=1):
-    f = getattr(fm.lib(), "_ZN2fm11linear_planEiiiiiifim")
-    f.restype = ctypes.c_bool
-    ws = fm.workspace_bytes(1, BH, N, D, p, causal, fm.BF16 if dt == "bf16" else fm.F32, backward)
-    return f(BH, N, D, p, int(causal), int(dt == "bf16"), ctypes.c_float(scale), int(backward),
-             ctypes.c_size_t(ws))
+    return route(BH, N, D, causal, dt, backward, p, scale)[0] == LINEAR
 
 
 LINEAR_CASES = [(64, 1, 64), (48, 255, 64), (32, 257, 64), (24, 1281, 64), (64, 900, 32),

@@ -9,8 +9,11 @@ perform the unsplit scan's operations in the same order, so every mode must
 give bit-identical O, G, dq, dk, dv; the split results are also held to the
 fp64 oracle (explicit N x N definition, Sec. 2.2) at the bf16 bar.  Shapes
 cover 2, 3 (odd: split after 1 chunk), 4, 6 and 8 chunks with ragged last
-chunks, a single chunk (never split), and the B8 H12 N4096 shape where the
-automatic plan splits (384 scans on 256 CUs).
+chunks, a single chunk (never split), and the B8 H12 N4096 shape.  All of them
+are short enough for the pair kernels, which have no segments: through the
+public calls these tests show that the modes change nothing there;
+test_factorised.py runs them on the scans (where B8 H12 N4096 is split
+automatically: 384 scans on 256 CUs) and adds longer ones.
 """
 import numpy as np
 import pytest
@@ -111,8 +114,8 @@ def test_backward_modes_bit_identical(shape):
 
 
 def test_full_shape_auto_split_matches_unsplit():
-    """B8 H12 N4096 (the forward+backward workload's shape): the automatic
-    plan splits the forward's scans (384 on 256 CUs); forward and backward
+    """B8 H12 N4096 (the forward+backward workload's shape): where the scans
+    serve it, the automatic plan splits the forward's; forward and backward
     (its dv scan split under ON) are bit-identical to the unsplit scans, and
     the rebuilt prefixes give the same forward."""
     import torch
