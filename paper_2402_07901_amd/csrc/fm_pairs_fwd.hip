@@ -458,18 +458,19 @@ __global__ __launch_bounds__(256) void khat_kernel(const T *__restrict__ k, _Flo
 // waves, keys per step; KP: k^ from khat_kernel) and what each measured on an
 // MI355X: t = t0 + |(a N, b pairs)|_2 us, a (ns per key) one workgroup's pace
 // down its keys, b (ps per pair) the chip's when full, fitted to calls of 1 to
-// 96 heads of 256 to 8192 tokens (float32 rows: 130 to 100000), causal (pairs =
-// heads N (N + queries per workgroup) / 2; without the mask b is 0.85 to 0.95 of
-// it).  Waves that split the keys shorten a, waves that share a staged tile
-// lower b.  Beyond the fit, to 100000 tokens of bf16 rows, the choice was within
-// 7% of the better side of the line between pairs and moments but for 1.31 (8
-// heads of 12000, D = 64) and 1.19.
+// 96 heads of 256 to 8192 tokens (D = 16, 32 and float32 rows: 33 to 100000),
+// causal (pairs = heads N (N + queries per workgroup) / 2; without the mask b is
+// 0.85 to 0.95 of it).  Waves that split the keys shorten a, waves that share a
+// staged tile lower b.  Against every shape and the moment kernels timed at 766
+// sizes, up to 100000 tokens, the choice takes 1.01 to 1.06 times the best one's
+// time on average; where it is on the wrong side of the line between pairs and
+// moments, at most 1.34 times (1.42 at 22 us).
 // fp16 operands: bf16, D = 64
 constexpr Shape SH64[] = {{32, 5.f, 7.6f, 1.13f}, {64, 4.f, 9.6f, .68f}, {128, 5.f, 13.f, .455f},
                           {128, 4.f, 20.5f, .375f}, {256, 7.f, 17.f, .31f}, {512, 6.f, 31.f, .275f}};
 // float32-grade operands, bf16 rows
-constexpr Shape SS16[] = {{32, 4.f, 4.6f, .70f}, {64, 4.f, 7.2f, .53f}, {256, 4.f, 18.6f, .32f}};
-constexpr Shape SS32[] = {{32, 4.f, 6.7f, 1.02f}, {64, 4.f, 9.f, .66f}, {256, 4.f, 21.5f, .40f}};
+constexpr Shape SS16[] = {{32, 4.3f, 2.8f, .47f}, {64, 4.4f, 4.1f, .29f}, {256, 4.4f, 14.4f, .225f}};
+constexpr Shape SS32[] = {{32, 5.f, 3.15f, .72f}, {64, 4.8f, 6.f, .42f}, {256, 5.9f, 18.f, .295f}};
 constexpr Shape SS64[] = {{64, 6.f, 15.4f, 1.14f}, {128, 6.f, 21.2f, .82f}, {256, 6.f, 36.5f, .71f}};
 constexpr Shape SS128[] = {{64, 7.f, 25.f, 1.67f}, {128, 7.f, 36.f, 1.27f}, {256, 7.f, 57.f, 1.05f}};
 // float32 rows (bf16 triples for the values: 1.0 to 1.5 of the time that fp16
