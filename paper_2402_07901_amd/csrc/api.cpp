@@ -133,24 +133,28 @@ Route factorised_route(int N, int D, int p, int causal, int dt)
 Route fwd_route(int B, int H, int N, int D, int p, int causal, int dt, float qs)
 {
     const int BH = B * H, bf = dt == FASTMAX_BF16;
-    if (fwd_grids_fit(BH, N, D, p, causal, dt)) {
-        if (fm::linear_plan(BH, N, D, p, causal, bf, qs, 0, 0)) return {fm::KERNELS_LINEAR, 0};
+    Route r{fm::KERNELS_GENERIC, -1};
+    if (p == 1) {
+        if (fm::linear_plan(BH, N, D, p, causal, bf, qs, 0, 0)) r = {fm::KERNELS_LINEAR, 0};
+    } else {
         // short sequences: explicit pairs (the plan's tables hold both sides)
-        const int shape = fm::pairs_fwd_plan(BH, N, D, p, causal, bf, fwd_ws(B, H, N, D, p, causal, dt));
-        if (shape >= 0) return {fm::KERNELS_PAIRS, shape};
+        r = {fm::KERNELS_PAIRS, fm::pairs_fwd_plan(BH, N, D, p, causal, bf, fwd_ws(B, H, N, D, p, causal, dt))};
     }
+    if (r.shape >= 0 && fwd_grids_fit(BH, N, D, p, causal, dt)) return r;
     return factorised_route(N, D, p, causal, dt);
 }
 
 Route bwd_route(int B, int H, int N, int D, int p, int causal, int dt, float qs)
 {
     const int BH = B * H, bf = dt == FASTMAX_BF16;
-    if (bwd_grids_fit(BH, N, D, p, causal, dt)) {
-        const size_t ws = bwd_ws(B, H, N, D, p, causal, dt);
-        if (fm::linear_plan(BH, N, D, p, causal, bf, qs, 1, ws)) return {fm::KERNELS_LINEAR, 0};
-        const int shape = fm::pairs_bwd_plan(BH, N, D, p, causal, bf, ws);
-        if (shape >= 0) return {fm::KERNELS_PAIRS, shape};
+    const size_t ws = bwd_ws(B, H, N, D, p, causal, dt);
+    Route r{fm::KERNELS_GENERIC, -1};
+    if (p == 1) {
+        if (fm::linear_plan(BH, N, D, p, causal, bf, qs, 1, ws)) r = {fm::KERNELS_LINEAR, 0};
+    } else {
+        r = {fm::KERNELS_PAIRS, fm::pairs_bwd_plan(BH, N, D, p, causal, bf, ws)};
     }
+    if (r.shape >= 0 && bwd_grids_fit(BH, N, D, p, causal, dt)) return r;
     return factorised_route(N, D, p, causal, dt);
 }
 

@@ -275,11 +275,10 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
 
     f16v acc[CT];
     float rs = 0.f;
-    bool rescan = false;
     if constexpr (PASS == FWD) {
-        // value scale of the head: the first step read, with headroom; where
-        // that step is all zeros (a padded prefix), or a later value outgrows
-        // the headroom, the largest finite value of all the rows read
+        // value scale of the head: the first step read, with headroom (below; a
+        // step of zeros, e.g. a padded prefix, takes the largest scale there is,
+        // which any later value outgrows)
         load(p0 < s0 ? p0 : s0);
 #pragma unroll
         for (int p = 0; p < C::NP; ++p)
@@ -294,29 +293,8 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
         __syncthreads();
         vscale = pow2_scale(__int_as_float(sred[0]), 7);
         vmax = 0.f;
-        rescan = sred[0] == 0 && rend > C::BK;
     }
-    for (;;) {
-        if constexpr (PASS == FWD) {
-            if (rescan) {
-                float m = 0.f;
-                for (int n = st0; n < rend; n += C::TPP) {
-                    RawRow<T, 8> x;
-                    x.load(vr + (size_t)n * D + 8 * sc, true);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const float y = fabsf(x.get(i));
-                        if (y <= 3.4028235e38f) m = fmaxf(m, y);
-                    }
-                }
-                __syncthreads();   // sred[0] has been read
-                if (tid == 0) sred[0] = 0;
-                __syncthreads();
-                atomicMax(&sred[0], __float_as_int(m));
-                __syncthreads();
-                vscale = pow2_scale(__int_as_float(sred[0]), 14);
-            }
-        }
+    for (int attempt = 0;; ++attempt) {
 #pragma unroll
         for (int c = 0; c < CT; ++c) acc[c] = f16v{};
         rs = 0.f;
@@ -501,8 +479,24 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
             }
         }
         if constexpr (PASS != FWD) break;
-        if (rescan || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
-        rescan = true;
+        if (attempt || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
+        // a value outgrew the first step's scale: the largest finite one of
+        // the rows read
+        float m = 0.f;
+        for (int n = st0; n < rend; n += C::TPP) {
+            RawRow<T, 8> x;
+            x.load(vr + (size_t)n * D + 8 * sc, true);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float y = fabsf(x.get(i));
+                if (y <= 3.4028235e38f) m = fmaxf(m, y);
+            }
+        }
+        if (tid == 0) sred[0] = 0;
+        __syncthreads();
+        atomicMax(&sred[0], __float_as_int(m));
+        __syncthreads();
+        vscale = pow2_scale(__int_as_float(sred[0]), 14);
     }
 
     // out of the scales

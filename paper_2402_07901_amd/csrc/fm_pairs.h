@@ -329,10 +329,9 @@ __device__ __forceinline__ void store_col(T *__restrict__ out, const f16v (&acc)
 
 // Power of two 2^(top - e), 2^e the least power of two above m (m finite,
 // >= 0): values up to m scaled by it stay below 2^top.  The result and its
-// inverse are normal numbers.
+// inverse are normal numbers; for m = 0 it is the largest, 2^126.
 __device__ __forceinline__ float pow2_scale(float m, int top)
 {
-    if (m == 0.0f) return 1.0f;
     int e = (int)(__float_as_uint(m) >> 23) - 126;   // m < 2^e
     int x = top - e + 127;
     x = x < 1 ? 1 : (x > 253 ? 253 : x);
@@ -361,7 +360,7 @@ inline int pick(const Shape *s, int n, const Moments &m, int BH, int N, int caus
     double best = 0.97 * (m.t0 + m.h * BH + 1e-3 * std::max(m.a * mtok, m.b * mtok * BH));
     int shape = -1;
     for (int i = 0; i < n; ++i) {
-        if (i == skip || !grid_fits((long long)kinds * BH * ((N + s[i].qb - 1LL) / s[i].qb), 512)) continue;
+        if (i == skip || !grid_fits((long long)kinds * BH * ((N - 1) / s[i].qb + 1), 512)) continue;
         const double pairs = causal ? 0.5 * BH * tok * (tok + s[i].qb) : 0.95 * BH * tok * tok;
         const double t = s[i].t0 + std::hypot(1e-3 * s[i].a * tok, 1e-6 * s[i].b * pairs);
         if (t < best) {

@@ -14,8 +14,8 @@
 // overflowed the headroom (a later token more than 2^8 times the first tile's
 // largest) the workgroup finds the true maximum and runs its keys again.  A
 // group that is zero over the whole first tile (a padded or zeroed prefix)
-// says nothing about the later values, however small: the workgroup finds the
-// true maximum first.
+// says nothing about the later values: its scale is the largest there is, which
+// any value outgrows.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -159,11 +159,9 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
 
     load_tile(0);
     float vscale = 1.0f;
-    bool rescan = false;
     if constexpr (!V3) {
         raw_max();
         vscale = set_scale(vmax <= 3e38f ? vmax : 0.f, 7);
-        rescan = __syncthreads_or(smax[sc] == 0u) && nt > 1;
     }
 
     f16v acc[NQ][CT];
@@ -284,22 +282,7 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
         }
     };
 
-    for (;;) {
-        if (rescan) {
-            // the largest finite magnitude of the column group over the keys read
-            float m = 0.f;
-            for (int n = st0; n < kend; n += C::TPP) {
-                RawRow<T, 8> x;
-                x.load(v + (size_t)n * D + 8 * sc, true);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float y = fabsf(x.get(i));
-                    if (y <= 3.4028235e38f) m = fmaxf(m, y);
-                }
-            }
-            vscale = set_scale(m, 14);
-            load_tile(0);
-        }
+    for (int attempt = 0;; ++attempt) {
 #pragma unroll
         for (int t = 0; t < NQ; ++t) {
             rs[t] = 0.f;
@@ -355,8 +338,20 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
                 tile(j, kb, (C::CAUSAL && kb + 31 > q0) || kb + 32 > N);
             }
         }
-        if (V3 || rescan || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
-        rescan = true;
+        if (V3 || attempt || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
+        // the largest finite magnitude of the column group over the keys read
+        float m = 0.f;
+        for (int n = st0; n < kend; n += C::TPP) {
+            RawRow<T, 8> x;
+            x.load(v + (size_t)n * D + 8 * sc, true);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float y = fabsf(x.get(i));
+                if (y <= 3.4028235e38f) m = fmaxf(m, y);
+            }
+        }
+        vscale = set_scale(m, 14);
+        load_tile(0);
     }
 
     auto keys_of = [&](int n) { return C::CAUSAL ? n + 1 : N; };
