@@ -482,16 +482,7 @@ __device__ __forceinline__ void block(unsigned char *smem, int *sred, float *ssu
         if (attempt || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
         // a value outgrew the first step's scale: the largest finite one of
         // the rows read
-        float m = 0.f;
-        for (int n = st0; n < rend; n += C::TPP) {
-            RawRow<T, 8> x;
-            x.load(vr + (size_t)n * D + 8 * sc, true);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float y = fabsf(x.get(i));
-                if (y <= 3.4028235e38f) m = fmaxf(m, y);
-            }
-        }
+        const float m = largest_finite<T, D>(vr, sc, st0, C::TPP, rend);
         if (tid == 0) sred[0] = 0;
         __syncthreads();
         atomicMax(&sred[0], __float_as_int(m));
@@ -603,7 +594,7 @@ hipError_t run_bwd(const void *q, const void *k, const void *v, const void *o, c
 struct Pace {
     float w, a, s, o;
 };
-constexpr Pace FP[] = {{13.f, 8.2f, 12.f, .21f}, {13.f, 10.6f, 12.f, .5f}, {13.f, 11.5f, 11.f, 1.1f}, {50.f, 33.f, 15.f, 2.9f}};
+constexpr Pace FP[] = {{}, {13.f, 10.6f, 12.f, .5f}, {13.f, 11.5f, 11.f, 1.1f}, {50.f, 33.f, 15.f, 2.9f}};
 // backward: bf16 rows, float32 rows
 constexpr Pace BP[] = {{13.f, 8.f, 37.f, 1.f}, {15.f, 11.f, 38.f, 2.2f}, {18.f, 14.f, 38.f, 4.8f}, {31.f, 39.f, 50.f, 14.5f}};
 constexpr Pace BF[] = {{5.6f, 7.8f, 37.f, 1.f}, {7.4f, 10.5f, 38.f, 2.2f}, {12.3f, 17.9f, 38.f, 4.8f}, {21.4f, 55.5f, 50.f, 14.5f}};
@@ -613,7 +604,8 @@ constexpr Pace BF[] = {{5.6f, 7.8f, 37.f, 1.f}, {7.4f, 10.5f, 38.f, 2.2f}, {12.3
 bool linear_plan(int BH, int N, int D, int p, int causal, int is_bf16, float qs, int backward, size_t ws_bytes)
 {
     using namespace lin;
-    if (p != 1 || qs * (float)D > 1.0f || (!is_bf16 && !backward)) return false;
+    // (at D = 16 the forward's scans are the faster ones at every size)
+    if (p != 1 || qs * (float)D > 1.0f || (!backward && (!is_bf16 || D == 16))) return false;
     const size_t rows = (size_t)BH * N;
     if (!grid_fits((backward ? 3LL : 1LL) * BH * ((N + 255LL) / 256), 512)) return false;
     if (backward && ws_bytes < rows * (is_bf16 ? 8 * (size_t)D + sizeof(RowInfo) : ROW32_BYTES)) return false;
@@ -630,7 +622,6 @@ hipError_t linear_fwd(const void *q, const void *k, const void *v, void *out, fl
     return causal ? lin::run_fwd<bf16_t, DD, true>(q, k, v, out, g, BH, N, qs, st)                 \
                   : lin::run_fwd<bf16_t, DD, false>(q, k, v, out, g, BH, N, qs, st)
     switch (D) {
-    case 16: GO(16);
     case 32: GO(32);
     case 64: GO(64);
     case 128: GO(128);

@@ -338,6 +338,24 @@ __device__ __forceinline__ float pow2_scale(float m, int top)
     return __uint_as_float((uint32_t)x << 23);
 }
 
+// The largest finite magnitude of 8 channels (the c-th group) of rows n0, n0 +
+// step, .. below end: a value scale's second attempt.
+template <typename T, int D>
+__device__ __forceinline__ float largest_finite(const T *__restrict__ rows, int c, int n0, int step, int end)
+{
+    float m = 0.f;
+    for (int n = n0; n < end; n += step) {
+        RawRow<T, 8> x;
+        x.load(rows + (size_t)n * D + 8 * c, true);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float y = fabsf(x.get(i));
+            if (y <= 3.4028235e38f) m = fmaxf(m, y);
+        }
+    }
+    return m;
+}
+
 // A workgroup shape: queries (keys) per workgroup and its paces, and the
 // moment kernels' t = t0 + h heads + max(a N, b heads N) us (a and b in ns per
 // token).

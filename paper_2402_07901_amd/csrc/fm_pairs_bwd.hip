@@ -543,7 +543,7 @@ hipError_t launch_bwd(const void *q, const void *k, const void *v, const void *o
 
 // The workgroup shapes and their measured paces, as in the forward's tables:
 // t = t0 + |(a N, b pairs)|_2 us for the whole call, fitted to 1 to 96 heads
-// of 33 to 4096 tokens.  Against every shape and the moment kernels at 300
+// of 33 to 4096 tokens.  Against every shape and the moment kernels at 507
 // sizes, up to 200000 tokens, the choice takes 1.00 to 1.03 times the best one's
 // time on average, and at most 1.36 on the wrong side of the line.
 constexpr Shape BH64[] = {{64, 13.5f, 10.f, 2.15f}, {128, 13.5f, 14.f, 1.5f}, {256, 13.f, 23.f, 1.22f},

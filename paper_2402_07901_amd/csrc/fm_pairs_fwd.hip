@@ -339,18 +339,7 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
             }
         }
         if (V3 || attempt || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
-        // the largest finite magnitude of the column group over the keys read
-        float m = 0.f;
-        for (int n = st0; n < kend; n += C::TPP) {
-            RawRow<T, 8> x;
-            x.load(v + (size_t)n * D + 8 * sc, true);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float y = fabsf(x.get(i));
-                if (y <= 3.4028235e38f) m = fmaxf(m, y);
-            }
-        }
-        vscale = set_scale(m, 14);
+        vscale = set_scale(largest_finite<T, D>(v, sc, st0, C::TPP, kend), 14);
         load_tile(0);
     }
 
@@ -456,7 +445,7 @@ __global__ __launch_bounds__(256) void khat_kernel(const T *__restrict__ k, _Flo
 // 96 heads of 256 to 8192 tokens (D = 16, 32 and float32 rows: 33 to 100000),
 // causal (pairs = heads N (N + queries per workgroup) / 2; without the mask b is
 // 0.85 to 0.95 of it).  Waves that split the keys shorten a, waves that share a
-// staged tile lower b.  Against every shape and the moment kernels timed at 766
+// staged tile lower b.  Against every shape and the moment kernels timed at 801
 // sizes, up to 100000 tokens, the choice takes 1.01 to 1.06 times the best one's
 // time on average; where it is on the wrong side of the line between pairs and
 // moments, at most 1.34 times (1.42 at 22 us).

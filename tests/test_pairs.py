@@ -488,8 +488,12 @@ def test_linear_plan():
     assert not linear_plan(1, 65536, 64, True, 1.0 / 64, False)
     for back in (False, True):
         for D in (16, 32, 64, 128):
-            assert any(linear_plan(BH, N, D, c, 1.0 / D, back) for BH, N, d in LINEAR_CASES if d == D
-                       for c in (True, False)) or (D == 16 and not back)
+            took = any(linear_plan(BH, N, D, c, 1.0 / D, back) for BH, N, d in LINEAR_CASES if d == D
+                       for c in (True, False))
+            assert took == (back or D > 16)
+    # the scans are faster at D = 16 whatever the size
+    assert not any(linear_plan(BH, N, 16, c, 1.0 / 16, False) for BH in (1, 16, 256, 4096, 1 << 20)
+                   for N in (1, 256, 2048, 60000) for c in (True, False))
 
 
 @pytest.mark.gpu
