@@ -102,7 +102,7 @@ hipError_t pairs_bwd(const void *q, const void *k, const void *v, const void *o,
                      const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
                      int is_bf16, float qs, int shape, void *ws, hipStream_t st);
 
-// Float32 rows (fm_pairs_bwd32.hip; first order fm_linear32.hip): six floats of
+// Float32 rows (fm_pairs_bwd32.hip; first order, all rows: fm_linear.hip): six floats of
 // ws per row.
 constexpr int ROW32_BYTES = 24;
 namespace pr { struct Moments; }
@@ -112,8 +112,8 @@ hipError_t pairs_bwd32(const void *q, const void *k, const void *v, const void *
                        float qs, int shape, void *ws, hipStream_t st);
 
 // First order over blocks with linear states (tau D <= 1; forward: bf16 I/O):
-// whether a call runs there, and the calls (the backward's ws: 8 D + 8 bytes
-// per row).
+// whether a call runs there, and the calls (the backward's ws: ROW32_BYTES per
+// row).
 bool linear_plan(int BH, int N, int D, int p, int causal, int is_bf16, float qs, int backward,
                  size_t ws_bytes);
 hipError_t linear_fwd(const void *q, const void *k, const void *v, void *out, float *g, int BH,
@@ -121,9 +121,6 @@ hipError_t linear_fwd(const void *q, const void *k, const void *v, void *out, fl
 hipError_t linear_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
                       const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
                       int is_bf16, float qs, void *ws, hipStream_t st);
-hipError_t linear_bwd32(const void *q, const void *k, const void *v, const void *o, const void *dout,
-                        const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
-                        float qs, void *ws, hipStream_t st);
 
 // Float32 MFMA kernels (v_mfma_f32_16x16x4_f32): p in {1, 2}, D in {16, 32,
 // 64, 128}, float32 or bf16 I/O, causal and non-causal (dispatch sends bf16
@@ -186,7 +183,7 @@ hipError_t mfma_nc_dv(const void *qh, const void *kh, const void *dout, const fl
 
 // The kernel families, in the order that api.cpp offers a call to them.
 enum Kernels {
-    KERNELS_LINEAR = 0,      // first order over blocks (fm_linear*.hip)
+    KERNELS_LINEAR = 0,      // first order over blocks (fm_linear.hip)
     KERNELS_PAIRS = 1,       // explicit pairs (fm_pairs_*.hip)
     KERNELS_CAUSAL = 2,      // factorised fp16 MFMA scans
     KERNELS_NONCAUSAL = 3,   // factorised fp16 MFMA moments

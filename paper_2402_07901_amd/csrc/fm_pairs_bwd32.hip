@@ -293,7 +293,7 @@ hipError_t launch(const float *q, const float *k, const float *v, const float *o
     const int nqb = (N + C::QB - 1) / C::QB, hgrp = BH < 32 ? BH : 32;
     if (!grid_fits(pb, 256) || !grid_fits(3LL * BH * nqb, C::NTH)) return hipErrorInvalidConfiguration;
     Row32 *info = (Row32 *)ws;
-    hipLaunchKernelGGL((bwd32_prep_kernel<C::D>), dim3((unsigned)pb), dim3(256), 0, st, q, k, o, dout, g,
+    hipLaunchKernelGGL((bwd32_prep_kernel<float, C::D>), dim3((unsigned)pb), dim3(256), 0, st, q, k, o, dout, g,
                        info, rows, qs);
     const Args a{q, k, v, dout, info, dq, dk, dv, N, BH, qs};
     hipLaunchKernelGGL((bwd32_kernel<C>), dim3((unsigned)(3LL * BH * nqb)), dim3(C::NTH), 0, st, a, nqb, hgrp);

@@ -1,6 +1,6 @@
-// What the backwards over explicit pairs (fm_pairs_bwd.hip) and over blocks
-// with linear states (fm_linear.hip) prepare per row: the planes of q~ and k^,
-// delta = dO.O, and the powers of two of dO, v and dO / G.
+// What the backwards prepare per row.  Over explicit pairs, bf16 rows
+// (fm_pairs_bwd.hip): the planes of q~ and k^, delta = dO.O, and the powers of
+// two of dO, v and dO / G.  The others: at the end.
 #pragma once
 
 #include <type_traits>
@@ -137,16 +137,16 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(
     }
 }
 
-// What the backwards of float32 rows (fm_pairs_bwd32.hip, fm_linear32.hip) keep
-// per row: q~ = (q - mq) rq (tau in rq), k^ = (k - mk) rk, delta = dO.O, u = 1 / G.
+// What the backwards without shared scales (float32 rows by pairs:
+// fm_pairs_bwd32.hip; first order: fm_linear.hip) keep per row: q~ = (q - mq) rq (tau in rq), k^ = (k - mk) rk, delta = dO.O, u = 1 / G.
 struct Row32 {
     float mq, rq, mk, rk, delta, u;
 };
 static_assert(sizeof(Row32) == ROW32_BYTES, "bytes per row");
 
 // Mean and 1 / std (Sec. 2.2, Eqs. 6-7) of the row whose 8 channels a lane holds.
-template <int D>
-__device__ __forceinline__ float2 row_stats(const RawRow<float, 8> &raw)
+template <typename T, int D>
+__device__ __forceinline__ float2 row_stats(const RawRow<T, 8> &raw)
 {
     float s = 0.f;
 #pragma unroll
@@ -162,10 +162,10 @@ __device__ __forceinline__ float2 row_stats(const RawRow<float, 8> &raw)
 }
 
 // One thread per 8 channels of a row of the whole call.
-template <int D>
+template <typename T, int D>
 __global__ __launch_bounds__(256) void bwd32_prep_kernel(
-    const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ o,
-    const float *__restrict__ dout, const float *__restrict__ g, Row32 *__restrict__ info,
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ o,
+    const T *__restrict__ dout, const float *__restrict__ g, Row32 *__restrict__ info,
     long long rows, float tau)
 {
     constexpr int L = D / 8;
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void bwd32_prep_kernel(
     const int c = threadIdx.x % L;
     const bool ok = row < rows;
     const size_t off = (size_t)(ok ? row : 0) * D + 8 * c;
-    RawRow<float, 8> rq, rk, ro, rd;
+    RawRow<T, 8> rq, rk, ro, rd;
     rq.load(q + off, ok);
     rk.load(k + off, ok);
     ro.load(o + off, ok);
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(256) void bwd32_prep_kernel(
 #pragma unroll
     for (int i = 0; i < 8; ++i) d = fmaf(rd.get(i), ro.get(i), d);
     d = group_sum<L>(d);
-    const float2 a = row_stats<D>(rq), b = row_stats<D>(rk);
+    const float2 a = row_stats<T, D>(rq), b = row_stats<T, D>(rk);
     if (ok && c == 0) info[row] = Row32{a.x, a.y * tau, b.x, b.y, d, 1.0f / g[row]};
 }
 

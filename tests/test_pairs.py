@@ -156,7 +156,18 @@ def test_shapes_against_explicit_matrix(BH, N, D, dt, causal):
     check(inp, dt, causal, f"BH{BH} N{N} D{D} {dt} c{causal} shape {plan(BH, N, D, causal, dt)}")
 
 
-def check_bwd(inp, dt, causal, scale, label):
+def group_rel(x, ref, edges):
+    """The largest error of a group of rows (between edges) over the largest entry
+    of that group."""
+    out = 0.0
+    for a, b in zip((0, *edges), (*edges, len(ref))):
+        den = np.abs(ref[a:b]).max()
+        err = np.abs(x[a:b] - ref[a:b]).max()
+        out = max(out, float(err / den) if den > 0 else float(err))
+    return out
+
+
+def check_bwd(inp, dt, causal, scale, label, edges=()):
     BH, N, D = inp["q64"].shape[1:]
     q, k, v, do = (to_dev(inp[n], dt) for n in ("q", "k", "v", "dout"))
     o, g = fm.fastmax_fwd(q, k, v, p=2, causal=causal, scale=scale)
@@ -177,6 +188,8 @@ def check_bwd(inp, dt, causal, scale, label):
         for name, x, r in zip(("dq", "dk", "dv"), grads, ref):
             den = max(np.abs(r).max(), floor if name != "dv" else 0.0)
             e = float(np.abs(x[h] - r[0, 0]).max() / den)
+            if edges:
+                e = max(e, group_rel(x[h], r[0, 0], edges))
             say(f"{label} head {h} {name}: {e:.2e}")
             assert e <= TOL[dt], (label, h, name, e)
 
@@ -196,7 +209,8 @@ def test_backward_shapes_against_explicit_gradient(BH, N, D, dt, causal):
 @pytest.mark.parametrize("kind", ["late", "zeros", "tau", "huge", "tiny"])
 def test_backward_scales(D, dt, causal, kind):
     """Rows of v and dO that differ by large powers of two, rows of zeros, a
-    small score scale, and values near the ends of the range."""
+    small score scale, and values near the ends of the range.  Rows on either
+    side of a jump are held to the largest entry of their own."""
     N = 300
     f = np.ones(N)
     if kind == "late":
@@ -207,7 +221,8 @@ def test_backward_scales(D, dt, causal, kind):
         f[:] = 2.0 ** (55 if kind == "huge" else -55)
     inp = scale_values(make_inputs(1, 3, N, D, 7500, dt, with_dout=True), dt, f)
     inp = scale_values(inp, dt, f[::-1] if kind == "late" else f, "dout")
-    check_bwd(inp, dt, causal, 1.0 / D if kind == "tau" else 1.0, f"bwd {kind} D{D} {dt} c{causal}")
+    check_bwd(inp, dt, causal, 1.0 / D if kind == "tau" else 1.0, f"bwd {kind} D{D} {dt} c{causal}",
+              edges=(100, 200) if kind == "late" else (150,) if kind == "zeros" else ())
 
 
 def scale_values(inp, dt, factor, name="v"):
@@ -500,13 +515,14 @@ def test_linear_plan():
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("BH,N,D", LINEAR_CASES)
 @pytest.mark.parametrize("kind,dt", [("plain", "bf16"), ("late", "bf16"), ("zeros", "bf16"),
-                                     ("prefix", "bf16"), ("plain", "f32"), ("late", "f32"),
-                                     ("prefix", "f32")])
+                                     ("prefix", "bf16"), ("far", "bf16"), ("plain", "f32"),
+                                     ("late", "f32"), ("prefix", "f32"), ("far", "f32")])
 def test_linear_against_explicit_gradient(BH, N, D, causal, kind, dt):
     """O, G and the gradients against the oracle (the suite's bars; G, whose weights
     are non-negative sums of operands good to 2^-22, to 1e-5), with rows of v
-    and dO that jump by 2^12, and rows of zeros before values of 1 and (prefix)
-    of 2^-24."""
+    and dO that jump by 2^12, rows of zeros before values of 1 and (prefix) of
+    2^-24, and (far) one row each of v and dO at 2^40.  Rows between the jumps are
+    held to the largest entry of their own."""
     scale = 1.0 / D
     inp = make_inputs(1, BH, N, D, 7700 + N, dt, with_dout=True)
     if kind != "plain":
@@ -514,10 +530,14 @@ def test_linear_against_explicit_gradient(BH, N, D, causal, kind, dt):
             pytest.skip("one step of rows")
         f = np.ones(N)
         f[2 * N // 3:] = 2.0 ** 12 if kind == "late" else 1.0
+        edges = (N - 2 * N // 3, 2 * N // 3)
+        if kind == "far":
+            f[N // 2] = 2.0 ** 40
+            edges = tuple(sorted({N - 1 - N // 2, N - N // 2, N // 2, N // 2 + 1}))
         if kind in ("zeros", "prefix"):
             f[:N // 3] = 0.0
             f[N // 3:] *= 1.0 if kind == "zeros" else 2.0 ** -24
-        inp = scale_values(scale_values(inp, dt, f), dt, f[::-1] if kind == "late" else f, "dout")
+        inp = scale_values(scale_values(inp, dt, f), dt, f[::-1] if kind in ("late", "far") else f, "dout")
     q, k, v, do = (to_dev(inp[n], dt) for n in ("q", "k", "v", "dout"))
     o, g = fm.fastmax_fwd(q, k, v, p=1, causal=causal, scale=scale)
     grads = fm.fastmax_bwd(q, k, v, o, do, g, p=1, causal=causal, scale=scale)
@@ -529,7 +549,8 @@ def test_linear_against_explicit_gradient(BH, N, D, causal, kind, dt):
         d64 = inp["dout64"].reshape(BH, N, D)[h]
         four = [x[None, None] for x in (q64, k64, v64)]
         ro, rg = oracle.fwd_brute(*four, 1, causal, scale=scale)
-        eo = max_rel(to_f64(o).reshape(BH, N, D)[h], ro[0, 0])
+        eo = max(max_rel(to_f64(o).reshape(BH, N, D)[h], ro[0, 0]),
+                 group_rel(to_f64(o).reshape(BH, N, D)[h], ro[0, 0], edges) if kind != "plain" else 0.0)
         gg = g.cpu().numpy().astype(np.float64).reshape(BH, N)[h]
         eg = float((np.abs(gg - rg[0, 0]) / np.abs(rg[0, 0]).max()).max())
         assert eo <= TOL[dt] and eg <= 1e-5, (h, eo, eg)
@@ -538,8 +559,12 @@ def test_linear_against_explicit_gradient(BH, N, D, causal, kind, dt):
         for name, x, r in zip(("dq", "dk", "dv"), grads, ref):
             den = max(np.abs(r).max(), floor if name != "dv" else 0.0)
             e = float(np.abs(to_f64(x).reshape(BH, N, D)[h] - r[0, 0]).max() / den)
+            if kind in ("late", "far"):
+                e = max(e, group_rel(to_f64(x).reshape(BH, N, D)[h], r[0, 0], edges))
             say(f"linear {kind} BH{BH} N{N} D{D} c{causal} head {h} {name}: {e:.2e}")
-            assert e <= TOL[dt], (h, name, e)
+            # far: dk is a sum of dO.O times q^ that nearly cancels, and O is rounded
+            # to bf16 (the float32 scans show the same 2.9e-2)
+            assert e <= TOL[dt] * (2 if kind == "far" and dt == "bf16" else 1), (h, name, e)
 
 
 def gradient_bounds_p1(q64, k64, v64, d64, causal, scale):
