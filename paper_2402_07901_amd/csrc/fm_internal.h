@@ -102,8 +102,8 @@ hipError_t pairs_bwd(const void *q, const void *k, const void *v, const void *o,
                      const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
                      int is_bf16, float qs, int shape, void *ws, hipStream_t st);
 
-// Float32 rows (fm_pairs_bwd32.hip; first order, all rows: fm_linear.hip): six floats of
-// ws per row.
+// Float32 rows (fm_pairs_bwd32.hip; first order, all rows: fm_linear.hip): six
+// floats of ws per row.
 constexpr int ROW32_BYTES = 24;
 namespace pr { struct Moments; }
 int pairs_bwd32_pick(int BH, int N, int D, int causal, const pr::Moments &m);

@@ -1,4 +1,5 @@
-// Shared pieces of the pair kernels (fm_pairs_fwd.hip, fm_pairs_bwd.hip):
+// Shared pieces of the pair kernels (fm_pairs_fwd.hip, fm_pairs_bwd.hip,
+// fm_pairs_bwd32.hip):
 // Fastmax evaluated over explicit (query, key) pairs, 32 x 32 at a time in
 // registers, for sequences short enough that a pair costs less than its share
 // of the moments (Sec. 2.4's factorisation pays once N exceeds about D^2; the
@@ -17,9 +18,9 @@
 //
 // float32-grade operands.  The standardised q^ and k^ and the weights, whose
 // range is known, are held as two fp16 numbers hi + lo, a product takes three
-// MFMAs (hi hi, lo hi, hi lo); q^ and k^ are multiplied by 2^8 each, which
-// keeps lo out of fp16's subnormals (24 bits, not 22; the scores' 2^16 goes
-// into the factor that they are read with).  bf16 values have one fp16 plane
+// MFMAs (hi hi, lo hi, hi lo); the forward multiplies q^ and k^ by 2^8 each,
+// which keeps lo out of fp16's subnormals (24 bits, not 22; the scores' 2^16
+// goes into the factor that they are read with).  bf16 values have one fp16 plane
 // with a power-of-two scale per 8-column group.  float32 values have no known
 // range: an fp16 pair under a shared scale loses what lies far below the
 // scale's largest value, even if a row or column never meets that value.  They

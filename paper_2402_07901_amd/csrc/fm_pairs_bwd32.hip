@@ -7,9 +7,10 @@
 // (fm_pairs.h), six MFMAs a product, and 1 / G enters the weights in float32.
 // bwd32_prep leaves six floats per row; a step stages the raw rows and takes
 // them apart on the way into LDS (the same bytes from memory as two fp16
-// planes, and no planes to write).  Bound by MFMA issue once the chip is full
-// (18 products a tile), by a workgroup's walk down its rows before that; the
-// table at the end holds the paces.
+// planes, and no planes to write).  Bound by vector issue beside the MFMAs once
+// the chip is full (11 other instructions an MFMA, taking floats apart for the
+// most part; MFMAs busy 32%), by a workgroup's walk down its rows before that;
+// the table at the end holds the paces.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
