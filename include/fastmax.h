@@ -25,10 +25,12 @@
  *    Statistics (standardisation, G) are float32 whatever `dt` is;
  *    contractions accumulate in float32.  float32 rows keep every bit at any
  *    magnitude (float32 MFMA, or three bf16 parts per operand; standardised
- *    rows and weights also as fp16 hi + lo), and so do bf16 rows at p = 1.  At
- *    p = 2 bf16 rows enter the fp16 MFMA kernels under powers of two shared by a
- *    group of columns, a row or a head: values down to 2^-20 of the largest one
- *    that shares the scale keep bf16's bits.  The causal bf16, D = 64, p = 2
+ *    rows and weights also as fp16 hi + lo), and so do bf16 rows, but for
+ *    p = 2 at D = 64 (causal, or 128 tokens and more): those enter fp16 MFMA
+ *    kernels under powers of two shared by a group of columns, a row or a head.
+ *    Outputs keep bf16's accuracy beside values up to 2^20 larger, gradients
+ *    beside rows of v and dout up to 2^12 larger (2^20: dk up to 5e-2 off).
+ *    The causal bf16, D = 64, p = 2
  *    MFMA path carries its moment state between 128-token chunks in fp16
  *    (each chunk's float32 contribution is rounded and added); its error
  *    stays within the bf16 tolerance on every row of 65536-token causal

@@ -95,21 +95,21 @@ int pairs_fwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t 
 hipError_t pairs_fwd(const void *q, const void *k, const void *v, void *out, float *g, int BH,
                      int N, int D, int causal, int is_bf16, float qs, int shape, void *ws,
                      hipStream_t st);
-// The backward likewise: at most 8 D + 8 bytes of ws per row (bf16, D = 64:
+// The backward likewise: ROW32_BYTES of ws per row (fp16 operands, D = 64:
 // 656), which the plan holds against ws_bytes.
 int pairs_bwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t ws_bytes);
 hipError_t pairs_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
                      const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
                      int is_bf16, float qs, int shape, void *ws, hipStream_t st);
 
-// Float32 rows (fm_pairs_bwd32.hip; first order, all rows: fm_linear.hip): six
+// The backwards without shared scales (fm_pairs_bwd32.hip, fm_linear.hip): six
 // floats of ws per row.
 constexpr int ROW32_BYTES = 24;
 namespace pr { struct Moments; }
-int pairs_bwd32_pick(int BH, int N, int D, int causal, const pr::Moments &m);
+int pairs_bwd32_pick(int BH, int N, int D, int causal, int is_bf16, const pr::Moments &m);
 hipError_t pairs_bwd32(const void *q, const void *k, const void *v, const void *o, const void *dout,
                        const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
-                       float qs, int shape, void *ws, hipStream_t st);
+                       int is_bf16, float qs, int shape, void *ws, hipStream_t st);
 
 // First order over blocks with linear states (tau D <= 1; forward: bf16 I/O):
 // whether a call runs there, and the calls (the backward's ws: ROW32_BYTES per

@@ -20,14 +20,16 @@
 // range is known, are held as two fp16 numbers hi + lo, a product takes three
 // MFMAs (hi hi, lo hi, hi lo); the forward multiplies q^ and k^ by 2^8 each,
 // which keeps lo out of fp16's subnormals (24 bits, not 22; the scores' 2^16
-// goes into the factor that they are read with).  bf16 values have one fp16 plane
-// with a power-of-two scale per 8-column group.  float32 values have no known
-// range: an fp16 pair under a shared scale loses what lies far below the
-// scale's largest value, even if a row or column never meets that value.  They
-// are held as three bf16 numbers, which take a float32 apart into 8 + 8 + 8
-// bits: every bit of every exponent, no scale; the weights meet them in the
-// same form and a product takes six MFMAs (the other three of nine are 2^-26 of
-// it and less).
+// goes into the factor that they are read with).  Values have no known
+// range: fp16 numbers under a shared scale lose what lies far below the
+// scale's largest value, even if a row or column never meets that value.
+// float32 values are held as three bf16 numbers, which take a float32 apart
+// into 8 + 8 + 8 bits: every bit of every exponent, no scale; the weights meet
+// them in the same form and a product takes six MFMAs (the other three of nine
+// are 2^-26 of it and less).  bf16 values are one such plane: three MFMAs.
+//
+// fp16 operands (bf16 rows, D = 64, causal or at least 128 tokens): one plane
+// each, the values under a power-of-two scale per 8-column group.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -179,10 +181,11 @@ __device__ __forceinline__ f16v mma33(const h8 (&a)[3][2], const h8 (&b)[2][3])
 }
 
 // Rows x columns of two triples, the staged one read by rows from its planes.
-template <int KS>
+// SEP: the leading products apart, as mma33; else one chain.
+template <int KS, bool SEP = true>
 __device__ __forceinline__ f16v dot33(const _Float16 *p, int plane, const h8 (&o)[KS][3])
 {
-    f16v y = f16v{}, z = f16v{};   // as mma33
+    f16v y = f16v{}, z = f16v{};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         const h8 a0 = ld8(p + 16 * ks), a1 = ld8(p + plane + 16 * ks), a2 = ld8(p + 2 * plane + 16 * ks);
@@ -191,9 +194,11 @@ __device__ __forceinline__ f16v dot33(const _Float16 *p, int plane, const h8 (&o
         y = mma_b(a0, o[ks][2], y);
         y = mma_b(a1, o[ks][0], y);
         y = mma_b(a0, o[ks][1], y);
-        z = mma_b(a0, o[ks][0], z);
+        if constexpr (SEP) z = mma_b(a0, o[ks][0], z);
+        else y = mma_b(a0, o[ks][0], y);
     }
-    return y + z;
+    if constexpr (SEP) return y + z;
+    return y;
 }
 
 // 1 / sqrt(v): the hardware's approximation (1 ulp) with one Newton step, so

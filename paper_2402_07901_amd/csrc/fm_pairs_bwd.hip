@@ -1,4 +1,5 @@
-// Pair backward of bf16 rows (see fm_pairs.h; p = 2; float32 rows:
+// Pair backward of fp16 operands (see fm_pairs.h; p = 2, bf16 rows of D = 64,
+// causal or at least 128 tokens; the others:
 // fm_pairs_bwd32.hip): the custom gradient of Sec. 2.5 (only
 // O and G saved) over explicit (query, key) pairs.  With q~ = tau q^,
 // u = 1 / G, delta_i = dO_i.O_i and t = 1 + q~_i.k^_n = f_2'(tau s),
@@ -6,8 +7,8 @@
 //   dq~_i = sum_n T_in k^_n,  dk^_n = sum_i T_in q~_i,
 //   T_in  = t u_i (dO_i.v_n - delta_i)
 // (Sec. 2.3, Eq. "bound"), then the standardisation backward (Eqs. 6-7) of the
-// finished rows.  bwd_prep writes q~ and k^ as fp16 planes (and their lo
-// parts) and one word pair per row; bwd_kernel holds three kinds of workgroups
+// finished rows.  bwd_prep writes q~, k^, v and dO as fp16 planes
+// and four words per row; bwd_kernel holds three kinds of workgroups
 // in one launch, each with 32 columns per wave in registers and the other side
 // staged in steps of BK rows: role Q (columns queries, out dq), role K (columns
 // keys, out dk) and role V (columns keys, out dv).  No atomics: every output
@@ -36,42 +37,40 @@ namespace pr {
 
 enum Role { ROLE_Q = 0, ROLE_K = 1, ROLE_V = 2 };
 
-template <typename T_, int D_, bool CAUSAL_, bool SPL_, int NQ_, int NWQ_, int NWK_, int BK_>
+template <typename T_, int D_, bool CAUSAL_, int NQ_, int NWQ_, int NWK_, int BK_>
 struct BwdCfg {
     typedef T_ T;
     static constexpr int D = D_, NQ = NQ_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
-    static constexpr bool CAUSAL = CAUSAL_, SPL = SPL_;
+    static constexpr bool CAUSAL = CAUSAL_;
     static constexpr int NTH = 64 * NWQ * NWK;
     static constexpr int QB = 32 * NQ * NWQ;
     static constexpr int KS = D / 16, CT = D < 32 ? 1 : D / 32;
     static constexpr int LPT = D / 8, TPP = NTH / LPT, NP = (BK + TPP - 1) / TPP;
     static constexpr int RS = row_stride<D>(), VS = tr_stride<D>();
     static constexpr int XH = BK * RS, AH = BK * VS;
-    static constexpr int NX = SPL ? 2 : 1;
     // planes of a step: x (scores), val (dO.v), and the contraction's A
     // operand where it is not x itself (role K: scaled q~; role V: scaled dO u)
-    static constexpr int TILE_Q = 2 * (NX * XH + XH);
-    static constexpr int TILE_K = 2 * (NX * XH + XH + NX * AH) + 8 * BK;
-    static constexpr int TILE = TILE_K;   // role V: NX (x) + NX (u) planes, fewer
-    static constexpr bool QLDS = SPL && D >= 128;
+    static constexpr int TILE_Q = 2 * 2 * XH;
+    static constexpr int TILE_K = 2 * (2 * XH + AH) + 8 * BK;
+    static constexpr int TILE = TILE_K;   // role V: fewer planes
     // two steps' tiles in turn where LDS has room beside the other workgroups
     // of the CU (eight waves in all): one barrier a step instead of two
-    static constexpr bool DB = 2 * TILE + (QLDS ? 2 * QB * RS : 0) <= 160 * 1024 * NWQ * NWK / 8 - 256;
+    static constexpr bool DB = 2 * TILE <= 160 * 1024 * NWQ * NWK / 8 - 256;
     static constexpr int NB = DB ? 2 : 1;
-    static constexpr int LOOP_BYTES = NB * TILE + (QLDS ? 2 * QB * RS : 0);
+    static constexpr int LOOP_BYTES = NB * TILE;
     static constexpr int RED_BYTES = NWK > 1 ? 4 * NWQ * NWK * 32 * 32 * CT : 0;
     static constexpr int SMEM = LOOP_BYTES > RED_BYTES ? LOOP_BYTES : RED_BYTES;
     static_assert(BK % (32 * NWK) == 0 && (NWK == 1 || NQ == 1) && TILE_K >= TILE_Q, "shape");
 };
 
 struct BwdArgs {
-    const void *q, *k, *v, *dout;
+    const void *q, *k;
     const float *g;
     const _Float16 *planes;
-    const void *info;
+    const RowInfoH *info;
     void *dq, *dk, *dv;
     int N, BH;
-    float qs, sc;   // tau, and the power of two the planes of q~ lack
+    float qs;   // tau
 };
 
 template <typename C, int ROLE>
@@ -79,27 +78,23 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
                                           int qb)
 {
     typedef typename C::T T;
-    constexpr int D = C::D, NQ = C::NQ, KS = C::KS, CT = C::CT, RS = C::RS, VS = C::VS, NX = C::NX;
-    constexpr bool SPL = C::SPL;
+    constexpr int D = C::D, NQ = C::NQ, KS = C::KS, CT = C::CT, RS = C::RS, VS = C::VS;
     const int N = a.N;
     // a step's planes (a buffer of them), in halves from its start: x, the
     // staged values (roles Q, K), the contraction's A operand (K, V), and
     // role K's row factors
-    constexpr int OV = NX * C::XH, OA = ROLE == ROLE_V ? OV : OV + C::XH, OB = OA + NX * C::AH;
+    constexpr int OV = C::XH, OA = ROLE == ROLE_V ? OV : OV + C::XH, OB = OA + C::AH;
     static_assert(C::TILE % 16 == 0, "alignment");
-    _Float16 *const olo = (_Float16 *)(smem + C::NB * C::TILE);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, h = lane >> 5;
     const int wq = wave / C::NWK, wk = wave % C::NWK;
     const size_t hb = (size_t)head * N * D, np = (size_t)a.BH * N * D;
     // own columns and staged rows
-    const _Float16 *const qpl = a.planes + hb, *const kpl = a.planes + (size_t)NX * np + hb;
+    const _Float16 *const qpl = a.planes + hb, *const kpl = a.planes + np + hb;
     const _Float16 *const own = ROLE == ROLE_Q ? qpl : kpl, *const stg = ROLE == ROLE_Q ? kpl : qpl;
-    const T *const val = (const T *)(ROLE == ROLE_Q ? a.v : a.dout) + hb;   // staged
-    typedef typename std::conditional<SPL, RowInfo, RowInfoH>::type Info;
-    const Info *const info = (const Info *)a.info + (size_t)head * N;
-    // fp16 planes of v, dO and dO rho (unsplit operands only)
+    const RowInfoH *const info = a.info + (size_t)head * N;
+    // fp16 planes of v, dO and dO rho
     const _Float16 *const hpl = a.planes + (ROLE == ROLE_Q ? 2 : ROLE == ROLE_K ? 3 : 4) * np + hb;
     const float *const g = a.g + (size_t)head * N;
     const int q0 = qb * C::QB + 32 * NQ * wq;
@@ -109,11 +104,8 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
 
     // staging: this thread's 8 channels and first row
     const int sc = tid % C::LPT, st0 = tid / C::LPT;
-    RawRow<bf16_t, 8> xr[C::NP], xl[SPL ? C::NP : 1];   // fp16 words
-    RawRow<T, 8> vr[SPL ? C::NP : 1];
-    RawRow<bf16_t, 8> hr[SPL ? 1 : C::NP];              // fp16 words
-    Info ri[C::NP];
-    float gr[C::NP];
+    RawRow<bf16_t, 8> xr[C::NP], hr[C::NP];   // fp16 words
+    RowInfoH ri[C::NP];
     // rows past the end repeat the last one: masked (role Q) or given weight 0
     auto load_tile = [&](int t) {
 #pragma unroll
@@ -121,17 +113,8 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
             const unsigned n = (unsigned)min(t * C::BK + st0 + C::TPP * p, N - 1);
             const unsigned off = n * (unsigned)D + 8u * sc;
             xr[p].load((const bf16_t *)stg + off, true);
-            if constexpr (SPL) {
-                xl[p].load((const bf16_t *)stg + np + off, true);
-                vr[p].load(val + off, true);
-                if constexpr (ROLE != ROLE_Q) {
-                    ri[p] = info[n];
-                    gr[p] = g[n];
-                }
-            } else {
-                hr[p].load((const bf16_t *)hpl + off, true);
-                ri[p] = info[n];
-            }
+            hr[p].load((const bf16_t *)hpl + off, true);
+            ri[p] = info[n];
         }
     };
     load_tile(t0);
@@ -149,21 +132,15 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
         MO = sred[1] == NO_EXP ? 0 : sred[1];
     }
     // h - e of a row of dO
-    auto row_h = [&](const Info &x) {
-        if constexpr (SPL) return max(LD + MO, exp_above(fabsf(x.delta)) - x.e_do);
-        else return max(LD + MO, exp_above(fabsf(x.delta)) - 10);
-    };
+    auto row_h = [&](const RowInfoH &x) { return max(LD + MO, exp_above(fabsf(x.delta)) - 10); };
     {
         int m = NO_EXP;
         for (int n = rbeg + tid; n < rend; n += C::NTH) {
-            const Info x = info[n];
+            const RowInfoH x = info[n];
             if constexpr (ROLE == ROLE_Q) {
                 m = max(m, (int)x.e_v);
             } else if (x.e_do != NO_EXP) {
-                int e;
-                if constexpr (SPL) e = x.e_do - g_exp(g[n]);
-                else e = x.eg;
-                m = max(m, ROLE == ROLE_K ? e + row_h(x) : e);
+                m = max(m, ROLE == ROLE_K ? x.eg + row_h(x) : x.eg);
             }
         }
         if (m > NO_EXP) atomicMax(&sred[0], m);
@@ -174,11 +151,10 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
     constexpr int X = -10 - 2 * LD;
 
     // own columns as B operands: x, and (roles Q, K) dO or v scaled
-    h8 oh[NQ][KS], ol[NQ][SPL && !C::QLDS ? KS : 1];
+    h8 oh[NQ][KS];
     h8 vo[ROLE != ROLE_V ? NQ : 1][KS];
     float dcol[NQ];
     int ecol[NQ];
-    _Float16 *const olw = olo + (32 * NQ * wq + r32) * RS + 8 * h;
 #pragma unroll
     for (int t = 0; t < NQ; ++t) {
         const int n = q0 + 32 * t + r32;
@@ -186,41 +162,17 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
         const size_t off = (size_t)(ok ? n : 0) * D + 8 * h;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            h8 x = *(const h8 *)(own + off + 16 * ks);
+            const h8 x = *(const h8 *)(own + off + 16 * ks);
             oh[t][ks] = ok ? x : h8{};
-            if constexpr (SPL) {
-                x = *(const h8 *)(own + np + off + 16 * ks);
-                x = ok ? x : h8{};
-                if constexpr (C::QLDS) {
-                    if (wk == 0) *(h8 *)(olw + 32 * t * RS + 16 * ks) = x;
-                } else {
-                    ol[t][ks] = x;
-                }
-            }
         }
         if constexpr (ROLE != ROLE_V) {
-            const Info w = info[ok ? n : 0];
+            const RowInfoH w = info[ok ? n : 0];
+            const _Float16 *const pl = a.planes + (ROLE == ROLE_Q ? 3 : 2) * np + hb;
+            const _Float16 s = ROLE == ROLE_Q ? (_Float16)1.0f : half2i((w.e_v == NO_EXP ? 0 : w.e_v) - MO);
             ecol[t] = ROLE == ROLE_Q ? (w.e_do == NO_EXP ? 0 : w.e_do) : MO;
-            if constexpr (SPL) {
-                float x[D / 2];
-                load_cols<T, D>((const T *)(ROLE == ROLE_Q ? a.dout : a.v) + hb, n, N, x);
-                const float s = exp2i(10 - ecol[t]);
-                // role Q: delta in the scale of dP, times the scale of T
-                dcol[t] = ROLE == ROLE_Q ? (ok ? w.delta : 0.f) * s * exp2i(14 - M) * exp2i(X) : 0.f;
+            dcol[t] = ROLE == ROLE_Q ? w.delta * exp2i(14 - M) * exp2i(X) : 0.f;
 #pragma unroll
-                for (int i = 0; i < D / 2; ++i) x[i] *= s;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    h8 lo;
-                    split8<false>(x + 8 * ks, vo[t][ks], lo);
-                }
-            } else {
-                const _Float16 *const pl = a.planes + (ROLE == ROLE_Q ? 3 : 2) * np + hb;
-                const _Float16 s = ROLE == ROLE_Q ? (_Float16)1.0f : half2i((w.e_v == NO_EXP ? 0 : w.e_v) - MO);
-                dcol[t] = ROLE == ROLE_Q ? w.delta * exp2i(14 - M) * exp2i(X) : 0.f;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) vo[t][ks] = *(const h8 *)(pl + off + 16 * ks) * s;
-            }
+            for (int ks = 0; ks < KS; ++ks) vo[t][ks] = *(const h8 *)(pl + off + 16 * ks) * s;
         }
     }
 
@@ -242,32 +194,13 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
         for (int u = 0; u < NQ; ++u)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                s[u][i] = SPL ? 0.0f : 1.0f;
+                s[u][i] = 1.0f;   // 1 + tau s
                 if constexpr (ROLE != ROLE_V) d[u][i] = 0.0f;
             }
         const _Float16 *xp = xhi + (32 * j + r32) * RS + 8 * h;
-        if constexpr (SPL && D < 128) {
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const h8 x = ld8(xp + 16 * ks), w = ld8(xp + C::XH + 16 * ks);
-#pragma unroll
-                for (int u = 0; u < NQ; ++u) {
-                    s[u] = mma(x, ol[u][C::QLDS ? 0 : ks], s[u]);
-                    s[u] = mma(w, oh[u][ks], s[u]);
-                }
-            }
-        }
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const h8 x = ld8(xp + 16 * ks);
-            if constexpr (SPL && D >= 128) {
-                const h8 w = ld8(xp + C::XH + 16 * ks);
-#pragma unroll
-                for (int u = 0; u < NQ; ++u) {
-                    s[u] = mma(x, ld8(olw + 32 * u * RS + 16 * ks), s[u]);
-                    s[u] = mma(w, oh[u][ks], s[u]);
-                }
-            }
 #pragma unroll
             for (int u = 0; u < NQ; ++u) s[u] = mma(x, oh[u][ks], s[u]);
         }
@@ -280,7 +213,7 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
                 for (int u = 0; u < NQ; ++u) d[u] = mma(x, vo[u][ks], d[u]);
             }
         }
-        h8 th[NQ][2], tl[NQ][SPL ? 2 : 1];
+        h8 th[NQ][2], lo;
 #pragma unroll
         for (int u = 0; u < NQ; ++u) {
             const int col = q0 + 32 * u + r32, last = C::CAUSAL ? min(col, N - 1) : N - 1;
@@ -294,7 +227,7 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float st = SPL ? fmaf(s[u][4 * b + i], a.sc, 1.0f) : s[u][4 * b + i];   // 1 + tau s
+                    const float st = s[u][4 * b + i];
                     if constexpr (ROLE == ROLE_V) w[4 * b + i] = fmaf(st, st, 1.0f);
                     else if constexpr (ROLE == ROLE_Q)
                         w[4 * b + i] = st * fmaf(d[u][4 * b + i], exp2i(X), -dcol[u]);
@@ -311,10 +244,9 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
                 }
             }
 #pragma unroll
-            for (int e = 0; e < 2; ++e) split8<SPL>(w + 8 * e, th[u][e], tl[u][SPL ? e : 0]);
+            for (int e = 0; e < 2; ++e) split8<false>(w + 8 * e, th[u][e], lo);
         }
         constexpr int AS = ROLE == ROLE_Q ? RS : VS;
-        constexpr int APL = ROLE == ROLE_Q ? C::XH : C::AH;
         const _Float16 *const ap = ROLE == ROLE_Q ? xhi : ahi;
 #pragma unroll
         for (int e = 0; e < 2; ++e)
@@ -323,14 +255,6 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
                 const h8 x = ld_tr<AS>(ap, 32 * j + 16 * e, 32 * c);
 #pragma unroll
                 for (int u = 0; u < NQ; ++u) acc[u][c] = mma(x, th[u][e], acc[u][c]);
-                if constexpr (SPL) {
-                    const h8 y = ld_tr<AS>(ap + APL, 32 * j + 16 * e, 32 * c);
-#pragma unroll
-                    for (int u = 0; u < NQ; ++u) {
-                        acc[u][c] = mma(x, tl[u][SPL ? e : 0], acc[u][c]);
-                        acc[u][c] = mma(y, th[u][e], acc[u][c]);
-                    }
-                }
             }
     };
 
@@ -346,68 +270,21 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
             const bool in = n < N && n >= rbeg;   // the others weigh nothing
             const h8 x0 = __builtin_bit_cast(h8, *(uint4 *)xr[p].w);
             if (ok) *(h8 *)(xhi + row * RS + 8 * sc) = x0;
-            if constexpr (!SPL) {
-                const h8 z = __builtin_bit_cast(h8, *(uint4 *)hr[p].w);
-                if constexpr (ROLE == ROLE_Q) {
-                    if (ok) *(h8 *)(vhi + row * RS + 8 * sc) = z * half2i(4 + ri[p].e_v - M);
-                } else if constexpr (ROLE == ROLE_V) {
-                    if (ok) *(h8 *)(ahi + row * VS + 8 * sc) = z * (in ? half2i(4 + ri[p].eg - M) : (_Float16)0.0f);
-                } else {
-                    const int hm = row_h(ri[p]), y = in ? min(max(ri[p].eg + hm - M, -40), 0) : -40;
-                    if (ok) {
-                        *(h8 *)(vhi + row * RS + 8 * sc) = z;
-                        *(h8 *)(ahi + row * VS + 8 * sc) = x0 * half2i(11 + y);
-                        if (sc == 0) {
-                            // the scales of dO.v (values below 2^10) and delta in T
-                            const float B = in ? ri[p].rho * exp2i(MO - 8 - LD - hm) : 0.f;
-                            rowB[row] = B;
-                            rowD[row] = in ? ri[p].rho * exp2i(2 - LD - hm) * ri[p].delta : 0.f;
-                        }
-                    }
-                }
+            const h8 z = __builtin_bit_cast(h8, *(uint4 *)hr[p].w);
+            if constexpr (ROLE == ROLE_Q) {
+                if (ok) *(h8 *)(vhi + row * RS + 8 * sc) = z * half2i(4 + ri[p].e_v - M);
+            } else if constexpr (ROLE == ROLE_V) {
+                if (ok) *(h8 *)(ahi + row * VS + 8 * sc) = z * (in ? half2i(4 + ri[p].eg - M) : (_Float16)0.0f);
             } else {
-                float f;            // the staged values' scale
-                int y = 0;          // role K: the row's share of the scale of q~
-                if constexpr (ROLE == ROLE_Q) {
-                    f = exp2i(14 - M);
-                } else {
-                    const int kx = g_exp(gr[p]), e = ri[p].e_do == NO_EXP ? 0 : ri[p].e_do;
-                    if constexpr (ROLE == ROLE_K) {
-                        const int hm = row_h(ri[p]);
-                        const bool live = in && ri[p].e_do != NO_EXP;
-                        y = live ? min(max(e + hm - kx - M, -40), 0) : -40;
-                        f = exp2i(14 - e);
-                        if (ok && sc == 0) {
-                            // the scales of dO.v (below 2^14, 2^10) and delta in T
-                            const float rho = live ? exp2i(kx) / gr[p] : 0.f;
-                            rowB[row] = rho * exp2i(MO - 12 - LD - hm);
-                            rowD[row] = live ? rho * exp2i(12 - LD - hm - e) * ri[p].delta : 0.f;
-                        }
-                    } else {
-                        f = in ? exp2i(14 - M) / gr[p] : 0.f;
-                    }
-                }
-                float z[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) z[i] = vr[p].get(i) * f;
-                h8 hi, lo;
-                const h8 x1 = __builtin_bit_cast(h8, *(uint4 *)xl[p].w);
-                if (ok) *(h8 *)(xhi + C::XH + row * RS + 8 * sc) = x1;
-                if constexpr (ROLE == ROLE_V) {
-                    split8<true>(z, hi, lo);
-                    if (ok) {
-                        *(h8 *)(ahi + row * VS + 8 * sc) = hi;
-                        *(h8 *)(ahi + C::AH + row * VS + 8 * sc) = lo;
-                    }
-                } else {
-                    split8<false>(z, hi, lo);
-                    if (ok) *(h8 *)(vhi + row * RS + 8 * sc) = hi;
-                }
-                if constexpr (ROLE == ROLE_K) {
-                    const _Float16 w = half2i(y + 11);
-                    if (ok) {
-                        *(h8 *)(ahi + row * VS + 8 * sc) = x0 * w;
-                        *(h8 *)(ahi + C::AH + row * VS + 8 * sc) = x1 * w;
+                const int hm = row_h(ri[p]), y = in ? min(max(ri[p].eg + hm - M, -40), 0) : -40;
+                if (ok) {
+                    *(h8 *)(vhi + row * RS + 8 * sc) = z;
+                    *(h8 *)(ahi + row * VS + 8 * sc) = x0 * half2i(11 + y);
+                    if (sc == 0) {
+                        // the scales of dO.v (values below 2^10) and delta in T
+                        const float B = in ? ri[p].rho * exp2i(MO - 8 - LD - hm) : 0.f;
+                        rowB[row] = B;
+                        rowD[row] = in ? ri[p].rho * exp2i(2 - LD - hm) * ri[p].delta : 0.f;
                     }
                 }
             }
@@ -485,7 +362,7 @@ __device__ __forceinline__ void bwd_block(unsigned char *smem, int *sred, const 
             f0 = 0.5f * exp2i(-14);
             f1 = exp2i(M);
         } else if constexpr (ROLE == ROLE_K) {
-            f0 = exp2i(LD - 23) * a.sc;
+            f0 = exp2i(LD - 23);
             f1 = exp2i(M);
         } else {
             f0 = tau / g[ok ? n : 0] * exp2i(-X - 24);
@@ -526,17 +403,12 @@ hipError_t launch_bwd(const void *q, const void *k, const void *v, const void *o
     const long long rows = (long long)BH * N, pb = (rows * (C::D / 8) + 255) / 256;
     const int nqb = (N + C::QB - 1) / C::QB, hgrp = BH < 32 ? BH : 32;
     if (!grid_fits(pb, 256) || !grid_fits(3LL * BH * nqb, C::NTH)) return hipErrorInvalidConfiguration;
-    // the planes hold q^ scaled by tau's mantissa: a small tau would push their
-    // lo parts below fp16's range
-    int e = 0;
-    if (C::SPL) frexpf(qs, &e);
-    const float sc = C::SPL ? ldexpf(1.0f, e - 1) : 1.0f;
     _Float16 *planes = (_Float16 *)ws;
-    void *info = planes + (C::SPL ? 4 : 5) * (size_t)rows * C::D;
-    hipLaunchKernelGGL((bwd_prep_kernel<T, C::D, C::SPL>), dim3((unsigned)pb), dim3(256), 0, st,
+    RowInfoH *info = (RowInfoH *)(planes + 5 * (size_t)rows * C::D);
+    hipLaunchKernelGGL((bwd_prep_kernel<T, C::D>), dim3((unsigned)pb), dim3(256), 0, st,
                        (const T *)q, (const T *)k, (const T *)v, (const T *)o, (const T *)dout, g,
-                       planes, info, rows, qs / sc);
-    const BwdArgs a{q, k, v, dout, g, planes, info, dq, dk, dv, N, BH, qs, sc};
+                       planes, info, rows, qs);
+    const BwdArgs a{q, k, g, planes, info, dq, dk, dv, N, BH, qs};
     hipLaunchKernelGGL((bwd_kernel<C>), dim3((unsigned)(3LL * BH * nqb)), dim3(C::NTH), 0, st, a, nqb, hgrp);
     return hipGetLastError();
 }
@@ -548,10 +420,6 @@ hipError_t launch_bwd(const void *q, const void *k, const void *v, const void *o
 // time on average, and at most 1.36 on the wrong side of the line.
 constexpr Shape BH64[] = {{64, 13.5f, 10.f, 2.15f}, {128, 13.5f, 14.f, 1.5f}, {256, 13.f, 23.f, 1.22f},
                           {256, 15.f, 36.f, 1.1f}};
-constexpr Shape BS16[] = {{32, 11.f, 2.f, 2.5f}, {32, 9.6f, 5.6f, 2.f}, {256, 8.3f, 19.9f, .88f}};
-constexpr Shape BS32[] = {{32, 11.1f, 4.f, 4.65f}, {64, 11.f, 8.1f, 3.2f}, {256, 9.f, 27.f, 1.31f}};
-constexpr Shape BS64[] = {{64, 17.f, 19.7f, 4.35f}, {128, 18.f, 28.f, 3.3f}, {256, 20.f, 47.f, 2.85f}};
-constexpr Shape BS128[] = {{128, 20.f, 45.f, 5.4f}, {256, 22.f, 70.f, 4.3f}};
 
 Moments moments_bwd(int D, int causal, bool grade32)
 {
@@ -565,38 +433,21 @@ Moments moments_bwd(int D, int causal, bool grade32)
     }
 }
 
-template <typename T, int D, bool CAUSAL, bool SPL>
+template <bool CAUSAL>
 hipError_t launch_bwd_shape(const void *q, const void *k, const void *v, const void *o,
                             const void *dout, const float *g, void *dq, void *dk, void *dv, int BH,
                             int N, float qs, int shape, void *ws, hipStream_t st)
 {
 #define L(S, ...)                                                                                  \
     do {                                                                                           \
-        typedef BwdCfg<T, D, CAUSAL, SPL, __VA_ARGS__> C;                                          \
+        typedef BwdCfg<bf16_t, 64, CAUSAL, __VA_ARGS__> C;                                         \
         static_assert(C::QB == (S).qb, "table");                                                   \
         return launch_bwd<C>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st);                  \
     } while (0)
-    if constexpr (D == 16) {
-        if (shape == 0) L(BS16[0], 1, 1, 8, 256);
-        if (shape == 1) L(BS16[1], 1, 1, 4, 128);
-        if (shape == 2) L(BS16[2], 1, 8, 1, 64);
-    } else if constexpr (D == 32) {
-        if (shape == 0) L(BS32[0], 1, 1, 8, 256);
-        if (shape == 1) L(BS32[1], 1, 2, 4, 128);
-        if (shape == 2) L(BS32[2], 1, 8, 1, 64);
-    } else if constexpr (D == 64 && !SPL) {
-        if (shape == 0) L(BH64[0], 1, 2, 4, 128);
-        if (shape == 1) L(BH64[1], 1, 4, 2, 128);
-        if (shape == 2) L(BH64[2], 1, 8, 1, 64);
-        if (shape == 3) L(BH64[3], 2, 4, 1, 32);
-    } else if constexpr (D == 64) {
-        if (shape == 0) L(BS64[0], 1, 2, 4, 128);
-        if (shape == 1) L(BS64[1], 1, 4, 2, 64);
-        if (shape == 2) L(BS64[2], 1, 8, 1, 64);
-    } else {
-        if (shape == 0) L(BS128[0], 1, 4, 2, 64);
-        if (shape == 1) L(BS128[1], 1, 8, 1, 32);
-    }
+    if (shape == 0) L(BH64[0], 1, 2, 4, 128);
+    if (shape == 1) L(BH64[1], 1, 4, 2, 128);
+    if (shape == 2) L(BH64[2], 1, 8, 1, 64);
+    if (shape == 3) L(BH64[3], 2, 4, 1, 32);
 #undef L
     return hipErrorInvalidValue;
 }
@@ -609,45 +460,21 @@ int pairs_bwd_plan(int BH, int N, int D, int p, int causal, int is_bf16, size_t 
     if (p != 2) return -1;
     const bool grade32 = pairs_grade32(N, D, causal, is_bf16);
     const size_t rows = (size_t)BH * N;
-    const size_t per_row = !is_bf16 ? ROW32_BYTES
-                         : grade32 ? 8 * (size_t)D + sizeof(RowInfo) : 10 * (size_t)D + sizeof(RowInfoH);
+    const size_t per_row = grade32 ? (size_t)ROW32_BYTES : 10 * (size_t)D + sizeof(RowInfoH);
     if (ws_bytes < rows * per_row) return -1;
     const Moments m = moments_bwd(D, causal, grade32);
-    if (!is_bf16) return pairs_bwd32_pick(BH, N, D, causal, m);
-    switch (D) {
-    case 16: return pick(BS16, 3, m, BH, N, causal, 3);
-    case 32: return pick(BS32, 3, m, BH, N, causal, 3);
-    case 64: return grade32 ? pick(BS64, 3, m, BH, N, causal, 3) : pick(BH64, 4, m, BH, N, causal, 3);
-    case 128: return pick(BS128, 2, m, BH, N, causal, 3);
-    }
-    return -1;
+    if (grade32) return pairs_bwd32_pick(BH, N, D, causal, is_bf16, m);
+    return pick(BH64, 4, m, BH, N, causal, 3);
 }
 
 hipError_t pairs_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
                      const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
                      int is_bf16, float qs, int shape, void *ws, hipStream_t st)
 {
-#define GO(T, DD, CA, SPL)                                                                         \
-    return pr::launch_bwd_shape<T, DD, CA, SPL>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, shape, \
-                                                ws, st)
-#define GO2(T, DD)                                                                                 \
-    do {                                                                                           \
-        if (causal) GO(T, DD, true, true);                                                         \
-        GO(T, DD, false, true);                                                                    \
-    } while (0)
-    if (!is_bf16) return pairs_bwd32(q, k, v, o, dout, g, dq, dk, dv, BH, N, D, causal, qs, shape, ws, st);
-    switch (D) {
-    case 16: GO2(bf16_t, 16);
-    case 32: GO2(bf16_t, 32);
-    case 64:
-        if (causal) GO(bf16_t, 64, true, false);
-        if (pairs_grade32(N, D, causal, is_bf16)) GO(bf16_t, 64, false, true);
-        GO(bf16_t, 64, false, false);
-    case 128: GO2(bf16_t, 128);
-    }
-#undef GO2
-#undef GO
-    return hipErrorInvalidValue;
+    if (pairs_grade32(N, D, causal, is_bf16))
+        return pairs_bwd32(q, k, v, o, dout, g, dq, dk, dv, BH, N, D, causal, is_bf16, qs, shape, ws, st);
+    return causal ? pr::launch_bwd_shape<true>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, shape, ws, st)
+                  : pr::launch_bwd_shape<false>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, shape, ws, st);
 }
 
 }  // namespace fm

@@ -1,14 +1,16 @@
-// Pair backward of float32 rows (p = 2): the gradient of fm_pairs_bwd.hip (see
-// there for the formulas and the three roles) with every operand in full.
+// Pair backward without shared scales (p = 2; all calls but bf16 rows at D = 64,
+// see pairs_grade32): the gradient of fm_pairs_bwd.hip (see there for the
+// formulas and the three roles) with every operand in full.
 //
 // Nothing is known about the range of v, dO and 1 / G, and a causal row or a
 // column may never meet the largest value of its tile, so no operand stands
 // under a shared scale: q~, k^, v, dO and the weights are bf16 triples
-// (fm_pairs.h), six MFMAs a product, and 1 / G enters the weights in float32.
+// (fm_pairs.h), six MFMAs a product (bf16 rows of v and dO as they are, one or
+// three MFMAs), and 1 / G enters the weights in float32.
 // bwd32_prep leaves six floats per row; a step stages the raw rows and takes
 // them apart on the way into LDS (the same bytes from memory as two fp16
 // planes, and no planes to write).  Bound by vector issue beside the MFMAs once
-// the chip is full (11 other instructions an MFMA, taking floats apart for the
+// the chip is full (float32 rows: 11 other instructions an MFMA, taking floats apart for the
 // most part; MFMAs busy 32%), by a workgroup's walk down its rows before that;
 // the table at the end holds the paces.
 #include <hip/hip_runtime.h>
@@ -26,8 +28,11 @@ namespace f32 {
 
 enum Role { ROLE_Q = 0, ROLE_K = 1, ROLE_V = 2 };
 
-template <int D_, bool CAUSAL_, int NWQ_, int NWK_, int BK_>
+template <typename T_, int D_, bool CAUSAL_, int NWQ_, int NWK_, int BK_>
 struct Cfg {
+    typedef T_ T;
+    static constexpr bool F32 = sizeof(T) == 4;
+    static constexpr int RP = F32 ? 3 : 1;   // parts of a row of v or dO
     static constexpr int D = D_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
     static constexpr bool CAUSAL = CAUSAL_;
     static constexpr int NTH = 64 * NWQ * NWK, QB = 32 * NWQ;
@@ -37,25 +42,28 @@ struct Cfg {
     static constexpr int XH = BK * RS, AH = BK * VS, PH = XH > AH ? XH : AH;
     // x (scores; also contracted by roles Q and K) and the staged values, three
     // planes each, and two floats per row
-    static constexpr int TILE = 2 * (3 * XH + 3 * PH) + 8 * BK;
-    // waves per SIMD: at D = 128 a wave's own columns take 192 registers, so
-    // its workgroup of four is alone on the CU
-    static constexpr int WPS = D >= 128 ? 1 : 2;
+    static constexpr int TILE = 2 * (3 * XH + RP * PH) + 8 * BK;
+    // waves per SIMD: at D = 128, float32 rows, a wave's own columns take 192
+    // registers, so its workgroup of four is alone on the CU
+    static constexpr int WPS = D >= 128 && F32 ? 1 : 2;
     // two steps' tiles in turn where LDS has room beside the other workgroups
     // of the CU: one barrier a step instead of two
     static constexpr int ROOM = 160 * 1024 * NWQ * NWK / (4 * WPS) - 256;
-    static constexpr bool DB = 2 * TILE <= ROOM;
+    // bf16 rows at D = 128: the own columns' last part waits in LDS
+    static constexpr bool OLDS = D >= 128 && !F32;
+    static constexpr int OB = OLDS ? 2 * QB * RS : 0;
+    static constexpr bool DB = 2 * TILE + OB <= ROOM;
     static constexpr int RED_BYTES = NWK > 1 ? 4 * NWQ * NWK * 32 * 32 * CT : 0;
-    static constexpr int LOOP_BYTES = (DB ? 2 : 1) * TILE;
+    static constexpr int LOOP_BYTES = (DB ? 2 : 1) * TILE + OB;
     static constexpr int SMEM = LOOP_BYTES > RED_BYTES ? LOOP_BYTES : RED_BYTES;
     static_assert(BK % (32 * NWK) == 0 && NWQ * NWK <= 4 * WPS, "shape");
     static_assert(SMEM <= 160 * 1024 - 256 && TILE % 16 == 0, "LDS");
 };
 
 struct Args {
-    const float *q, *k, *v, *dout;
+    const void *q, *k, *v, *dout;
     const Row32 *info;
-    float *dq, *dk, *dv;
+    void *dq, *dk, *dv;
     int N, BH;
     float tau;
 };
@@ -63,15 +71,16 @@ struct Args {
 template <typename C, int ROLE>
 __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int head, int qb)
 {
-    constexpr int D = C::D, KS = C::KS, CT = C::CT, RS = C::RS, VS = C::VS;
+    typedef typename C::T T;
+    constexpr int D = C::D, KS = C::KS, CT = C::CT, RS = C::RS, VS = C::VS, RP = C::RP;
     const int N = a.N;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, h = lane >> 5;
     const int wq = wave / C::NWK, wk = wave % C::NWK;
     const size_t hb = (size_t)head * N * D;
     // own columns and staged rows
-    const float *const own = (ROLE == ROLE_Q ? a.q : a.k) + hb, *const stg = (ROLE == ROLE_Q ? a.k : a.q) + hb;
-    const float *const ownv = (ROLE == ROLE_Q ? a.dout : a.v) + hb, *const stgv = (ROLE == ROLE_Q ? a.v : a.dout) + hb;
+    const T *const own = (const T *)(ROLE == ROLE_Q ? a.q : a.k) + hb, *const stg = (const T *)(ROLE == ROLE_Q ? a.k : a.q) + hb;
+    const T *const ownv = (const T *)(ROLE == ROLE_Q ? a.dout : a.v) + hb, *const stgv = (const T *)(ROLE == ROLE_Q ? a.v : a.dout) + hb;
     const Row32 *const info = a.info + (size_t)head * N;
     const int q0 = qb * C::QB + 32 * wq, col = q0 + r32;
     const bool cok = col < N;
@@ -81,7 +90,7 @@ __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int he
 
     // staging: this thread's 8 channels and first row
     const int sc = tid % C::LPT, st0 = tid / C::LPT;
-    RawRow<float, 8> xr[C::NP], vr[C::NP];
+    RawRow<T, 8> xr[C::NP], vr[C::NP];
     float mx[C::NP], rx[C::NP], ru[C::NP], rd[C::NP];
     auto load_tile = [&](int t) {
 #pragma unroll
@@ -101,22 +110,33 @@ __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int he
     load_tile(t0);
 
     // own columns as B operands: x and (roles Q, K) dO or v
-    h8 ox[KS][3], ov[ROLE != ROLE_V ? KS : 1][3];
+    constexpr int OP = C::OLDS ? 2 : 3;
+    _Float16 *const olw = (_Float16 *)(smem + (C::DB ? 2 : 1) * C::TILE) + (32 * wq + r32) * RS + 8 * h;
+    h8 ox[KS][OP], ov[ROLE != ROLE_V ? KS : 1][RP];
     const Row32 cw = info[cok ? col : 0];
     {
         float x[D / 2];
-        load_cols<float, D>(own, col, N, x);
+        load_cols<T, D>(own, col, N, x);
         const float m = ROLE == ROLE_Q ? cw.mq : cw.mk, r = ROLE == ROLE_Q ? cw.rq : cw.rk;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) x[8 * ks + i] = cok ? (x[8 * ks + i] - m) * r : 0.f;
-            split3(x + 8 * ks, ox[ks]);
+            h8 w[3];
+            split3(x + 8 * ks, w);
+#pragma unroll
+            for (int i = 0; i < OP; ++i) ox[ks][i] = w[i];
+            if (C::OLDS && wk == 0) *(h8 *)(olw + 16 * ks) = w[2];
         }
         if constexpr (ROLE != ROLE_V) {
-            load_cols<float, D>(ownv, col, N, x);
+            load_cols<T, D>(ownv, col, N, x);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) split3(x + 8 * ks, ov[ks]);
+            for (int ks = 0; ks < KS; ++ks) {
+                h8 w[3];
+                split3(x + 8 * ks, w);
+#pragma unroll
+                for (int i = 0; i < RP; ++i) ov[ks][i] = w[i];   // (a bf16 row is its own first part)
+            }
         }
     }
 
@@ -128,10 +148,30 @@ __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int he
     // some of its pairs lie beyond the diagonal or the last row.
     auto tile = [&](const _Float16 *xp, int j, int kb, bool masked) {
         const _Float16 *const vp = xp + 3 * C::XH;
-        const float *const rowU = (const float *)(vp + 3 * C::PH), *const rowD = rowU + C::BK;
-        const f16v s = dot33<KS>(xp + (32 * j + r32) * RS + 8 * h, C::XH, ox);
+        const float *const rowU = (const float *)(vp + RP * C::PH), *const rowD = rowU + C::BK;
+        f16v s = f16v{};
+        if constexpr (C::OLDS) {
+            const _Float16 *const q = xp + (32 * j + r32) * RS + 8 * h;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const h8 a0 = ld8(q + 16 * ks), a1 = ld8(q + C::XH + 16 * ks), a2 = ld8(q + 2 * C::XH + 16 * ks);
+                s = mma_b(a2, ox[ks][0], s);
+                s = mma_b(a1, ox[ks][1], s);
+                s = mma_b(a0, ld8(olw + 16 * ks), s);
+                s = mma_b(a1, ox[ks][0], s);
+                s = mma_b(a0, ox[ks][1], s);
+                s = mma_b(a0, ox[ks][0], s);
+            }
+        } else {
+            s = dot33<KS, C::F32>(xp + (32 * j + r32) * RS + 8 * h, C::XH, ox);
+        }
         f16v d = f16v{};
-        if constexpr (ROLE != ROLE_V) d = dot33<KS>(vp + (32 * j + r32) * RS + 8 * h, C::PH, ov);
+        if constexpr (ROLE != ROLE_V && RP == 3) d = dot33<KS>(vp + (32 * j + r32) * RS + 8 * h, C::PH, ov);
+        else if constexpr (ROLE != ROLE_V) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                d = mma_b(ld8(vp + (32 * j + r32) * RS + 8 * h + 16 * ks), ov[ks][0], d);
+        }
         float w[16];
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
@@ -162,19 +202,29 @@ __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int he
         const _Float16 *const ap = ROLE == ROLE_V ? vp : xp;
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-            h8 x[3][2];
+            constexpr int AP = ROLE == ROLE_V ? RP : 3;
+            h8 x[AP][2];
 #pragma unroll
-            for (int i = 0; i < 3; ++i)
+            for (int i = 0; i < AP; ++i)
 #pragma unroll
                 for (int e = 0; e < 2; ++e) x[i][e] = ld_tr<AS>(ap + i * PL, 32 * j + 16 * e, 32 * c);
-            acc[c] += mma33(x, w3);
+            if constexpr (C::F32) {
+                acc[c] += mma33(x, w3);
+            } else {   // one chain, smallest first: bf16 shows no more
+#pragma unroll
+                for (int o = 2; o >= 0; --o)
+#pragma unroll
+                    for (int i = 0; i < AP && i <= o; ++i)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) acc[c] = mma_b(x[i][e], w3[e][o - i], acc[c]);
+            }
         }
     };
 
     // writes the loaded step t to a buffer
     auto stage = [&](_Float16 *xp, int t) {
         _Float16 *const vp = xp + 3 * C::XH;
-        float *const rowU = (float *)(vp + 3 * C::PH), *const rowD = rowU + C::BK;
+        float *const rowU = (float *)(vp + RP * C::PH), *const rowD = rowU + C::BK;
         constexpr int VST = ROLE == ROLE_V ? VS : RS;
 #pragma unroll
         for (int p = 0; p < C::NP; ++p) {
@@ -187,11 +237,15 @@ __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int he
             split3(x, y);
 #pragma unroll
             for (int i = 0; i < 3; ++i) *(h8 *)(xp + i * C::XH + row * RS + 8 * sc) = y[i];
+            if constexpr (RP == 1) {
+                *(uint4 *)(vp + row * VST + 8 * sc) = *(uint4 *)vr[p].w;
+            } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) x[i] = vr[p].get(i);
-            split3(x, y);
+                for (int i = 0; i < 8; ++i) x[i] = vr[p].get(i);
+                split3(x, y);
 #pragma unroll
-            for (int i = 0; i < 3; ++i) *(h8 *)(vp + i * C::PH + row * VST + 8 * sc) = y[i];
+                for (int i = 0; i < 3; ++i) *(h8 *)(vp + i * C::PH + row * VST + 8 * sc) = y[i];
+            }
             if (ROLE != ROLE_Q && sc == 0) {
                 const bool in = t * C::BK + row < N;
                 rowU[row] = in ? (ROLE == ROLE_V ? 0.5f * ru[p] : ru[p]) : 0.f;
@@ -266,8 +320,8 @@ __device__ __forceinline__ void block(unsigned char *smem, const Args &a, int he
             for (int i = 0; i < 16; ++i) acc[c][i] *= f;
     }
     const size_t at = hb + (size_t)(cok ? col : 0) * D;
-    if constexpr (ROLE != ROLE_V) standardise_back<float, D>((ROLE == ROLE_Q ? a.q : a.k) + at, acc);
-    if (cok) store_col<float, D>((ROLE == ROLE_Q ? a.dq : ROLE == ROLE_K ? a.dk : a.dv) + at, acc);
+    if constexpr (ROLE != ROLE_V) standardise_back<T, D>((const T *)(ROLE == ROLE_Q ? a.q : a.k) + at, acc);
+    if (cok) store_col<T, D>((T *)(ROLE == ROLE_Q ? a.dq : ROLE == ROLE_K ? a.dk : a.dv) + at, acc);
 }
 
 // Block order: heads in groups of hgrp; within a group the columns with the
@@ -286,16 +340,17 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void bwd32_kernel(Args a, int nqb, 
 }
 
 template <typename C>
-hipError_t launch(const float *q, const float *k, const float *v, const float *o, const float *dout,
-                  const float *g, float *dq, float *dk, float *dv, int BH, int N, float qs, void *ws,
+hipError_t launch(const void *q, const void *k, const void *v, const void *o, const void *dout,
+                  const float *g, void *dq, void *dk, void *dv, int BH, int N, float qs, void *ws,
                   hipStream_t st)
 {
     const long long rows = (long long)BH * N, pb = (rows * (C::D / 8) + 255) / 256;
     const int nqb = (N + C::QB - 1) / C::QB, hgrp = BH < 32 ? BH : 32;
     if (!grid_fits(pb, 256) || !grid_fits(3LL * BH * nqb, C::NTH)) return hipErrorInvalidConfiguration;
     Row32 *info = (Row32 *)ws;
-    hipLaunchKernelGGL((bwd32_prep_kernel<float, C::D>), dim3((unsigned)pb), dim3(256), 0, st, q, k, o, dout, g,
-                       info, rows, qs);
+    typedef typename C::T T;
+    hipLaunchKernelGGL((bwd32_prep_kernel<T, C::D>), dim3((unsigned)pb), dim3(256), 0, st, (const T *)q,
+                       (const T *)k, (const T *)o, (const T *)dout, g, info, rows, qs);
     const Args a{q, k, v, dout, info, dq, dk, dv, N, BH, qs};
     hipLaunchKernelGGL((bwd32_kernel<C>), dim3((unsigned)(3LL * BH * nqb)), dim3(C::NTH), 0, st, a, nqb, hgrp);
     return hipGetLastError();
@@ -304,24 +359,34 @@ hipError_t launch(const float *q, const float *k, const float *v, const float *o
 // The workgroup shapes and their measured paces, as in the forward's tables:
 // t = t0 + |(a N, b pairs)|_2 us for the whole call, fitted to 1 to 96 heads of
 // 130 to 32768 tokens (the choice is within 1% of the best one on average, 21%
-// at most).  8 heads of 2048 tokens, causal: D = 32 74 us (fp16 pairs under
+// at most).  Float32 rows, 8 heads of 2048 tokens, causal: D = 32 74 us (fp16 pairs under
 // shared scales 64, the moment kernels 155), D = 64 121 (592).
 constexpr Shape B16[] = {{32, 6.5f, 3.4f, 3.7f}, {32, 6.5f, 6.7f, 2.5f}, {256, 7.9f, 41.4f, 1.85f}};
 constexpr Shape B32[] = {{32, 14.3f, 5.3f, 6.f}, {64, 14.3f, 11.5f, 3.6f}, {256, 9.9f, 52.4f, 1.92f}};
 constexpr Shape B64[] = {{64, 15.7f, 15.1f, 9.2f}, {128, 13.7f, 42.6f, 6.1f}, {256, 11.3f, 70.4f, 3.97f}};
 constexpr Shape B128[] = {{128, 22.7f, 110.f, 13.5f}};
+// bf16 rows, fitted likewise (against 280 sizes the choice takes 1.00 to 1.03
+// times the best one's time on average, 1.34 at most; H64, whose calls have fewer
+// than 128 tokens, by estimate).  8 heads of 4096 tokens, causal, D = 128: 593 us
+// (fp16 pairs under shared scales about 410, the moment kernels 5290); with rows
+// of v and dO 2^20 larger than the others dk was off by 6e-2 there, 3e-3 here.
+constexpr Shape H16[] = {{32, 6.35f, 2.8f, 2.7f}, {32, 6.3f, 4.8f, 2.2f}, {256, 8.2f, 32.f, 1.24f}};
+constexpr Shape H32[] = {{32, 9.f, 3.6f, 5.2f}, {64, 8.75f, 11.f, 2.8f}, {256, 6.1f, 35.f, 1.63f}};
+constexpr Shape H64[] = {{64, 15.7f, 15.1f, 8.f}, {128, 13.7f, 38.f, 5.f}, {256, 11.3f, 60.f, 3.4f}};
+constexpr Shape H128[] = {{128, 15.4f, 72.5f, 9.7f}, {256, 13.8f, 129.f, 5.24f}};
 
-template <int D, bool CAUSAL>
-hipError_t launch_shape(const float *q, const float *k, const float *v, const float *o, const float *dout,
-                        const float *g, float *dq, float *dk, float *dv, int BH, int N, float qs, int shape,
+template <typename T, int D, bool CAUSAL>
+hipError_t launch_shape(const void *q, const void *k, const void *v, const void *o, const void *dout,
+                        const float *g, void *dq, void *dk, void *dv, int BH, int N, float qs, int shape,
                         void *ws, hipStream_t st)
 {
 #define L(S, ...)                                                                                  \
     do {                                                                                           \
-        typedef Cfg<D, CAUSAL, __VA_ARGS__> C;                                                     \
+        typedef Cfg<T, D, CAUSAL, __VA_ARGS__> C;                                                  \
         static_assert(C::QB == (S).qb, "table");                                                   \
         return launch<C>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, ws, st);                      \
     } while (0)
+    constexpr bool F32 = sizeof(T) == 4;
     if constexpr (D == 16) {
         if (shape == 0) L(B16[0], 1, 8, 256);
         if (shape == 1) L(B16[1], 1, 4, 128);
@@ -334,8 +399,11 @@ hipError_t launch_shape(const float *q, const float *k, const float *v, const fl
         if (shape == 0) L(B64[0], 2, 4, 128);
         if (shape == 1) L(B64[1], 4, 2, 64);
         if (shape == 2) L(B64[2], 8, 1, 64);
-    } else {
+    } else if constexpr (F32) {
         if (shape == 0) L(B128[0], 4, 1, 32);
+    } else {
+        if (shape == 0) L(H128[0], 4, 2, 64);
+        if (shape == 1) L(H128[1], 8, 1, 32);
     }
 #undef L
     return hipErrorInvalidValue;
@@ -344,29 +412,27 @@ hipError_t launch_shape(const float *q, const float *k, const float *v, const fl
 }  // namespace f32
 }  // namespace pr
 
-int pairs_bwd32_pick(int BH, int N, int D, int causal, const pr::Moments &m)
+int pairs_bwd32_pick(int BH, int N, int D, int causal, int is_bf16, const pr::Moments &m)
 {
     using namespace pr;
+    using namespace pr::f32;
     switch (D) {
-    case 16: return pick(f32::B16, 3, m, BH, N, causal, 3);
-    case 32: return pick(f32::B32, 3, m, BH, N, causal, 3);
-    case 64: return pick(f32::B64, 3, m, BH, N, causal, 3);
-    case 128: return pick(f32::B128, 1, m, BH, N, causal, 3);
+    case 16: return pick(is_bf16 ? H16 : B16, 3, m, BH, N, causal, 3);
+    case 32: return pick(is_bf16 ? H32 : B32, 3, m, BH, N, causal, 3);
+    case 64: return pick(is_bf16 ? H64 : B64, 3, m, BH, N, causal, 3);
+    case 128: return is_bf16 ? pick(H128, 2, m, BH, N, causal, 3) : pick(B128, 1, m, BH, N, causal, 3);
     }
     return -1;
 }
 
 hipError_t pairs_bwd32(const void *q, const void *k, const void *v, const void *o, const void *dout,
                        const float *g, void *dq, void *dk, void *dv, int BH, int N, int D, int causal,
-                       float qs, int shape, void *ws, hipStream_t st)
+                       int is_bf16, float qs, int shape, void *ws, hipStream_t st)
 {
-#define GO(DD)                                                                                     \
-    return causal ? pr::f32::launch_shape<DD, true>((const float *)q, (const float *)k, (const float *)v, \
-                        (const float *)o, (const float *)dout, g, (float *)dq, (float *)dk, (float *)dv, \
-                        BH, N, qs, shape, ws, st)                                                  \
-                  : pr::f32::launch_shape<DD, false>((const float *)q, (const float *)k, (const float *)v, \
-                        (const float *)o, (const float *)dout, g, (float *)dq, (float *)dk, (float *)dv, \
-                        BH, N, qs, shape, ws, st)
+#define GO3(T, DD, CA)                                                                             \
+    pr::f32::launch_shape<T, DD, CA>(q, k, v, o, dout, g, dq, dk, dv, BH, N, qs, shape, ws, st)
+#define GO2(T, DD) (causal ? GO3(T, DD, true) : GO3(T, DD, false))
+#define GO(DD) return is_bf16 ? GO2(bf16_t, DD) : GO2(float, DD)
     switch (D) {
     case 16: GO(16);
     case 32: GO(32);
@@ -374,6 +440,8 @@ hipError_t pairs_bwd32(const void *q, const void *k, const void *v, const void *
     case 128: GO(128);
     }
 #undef GO
+#undef GO2
+#undef GO3
     return hipErrorInvalidValue;
 }
 

@@ -7,9 +7,9 @@
 // BK keys (standardised on the way, Sec. 2.2) and their values in LDS, the
 // next step's rows already on their way into registers.
 //
-// Value scale.  bf16 values go to fp16 under a power-of-two scale per 8-column
-// group (float32 values are bf16 triples and need none).  It
-// is taken from the first staged tile with 8 binary digits of headroom; each
+// Value scale.  At D = 64 bf16 values go to fp16 under a power-of-two scale per
+// 8-column group (the float32-grade calls hold values as bf16 parts and need
+// none).  It is taken from the first staged tile with 8 binary digits of headroom; each
 // thread keeps the largest magnitude that it stages, and only if that
 // overflowed the headroom (a later token more than 2^8 times the first tile's
 // largest) the workgroup finds the true maximum and runs its keys again.  A
@@ -18,7 +18,6 @@
 // any value outgrows.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-
 
 #include "fm_internal.h"
 #include "fm_pairs.h"
@@ -31,11 +30,12 @@ struct FwdCfg {
     typedef T_ T;
     static constexpr int D = D_, NQ = NQ_, NWQ = NWQ_, NWK = NWK_, BK = BK_;
     static constexpr bool CAUSAL = CAUSAL_, SPL = SPL_, KP = KP_;
-    // float32 values: three bf16 parts.  A tile's contribution is summed on its
-    // own, the small products first, and added with a rounded float32 add (the
-    // matrix pipe's own chained sums round toward zero).
-    static constexpr bool V3 = SPL && sizeof(T) == 4;
-    static constexpr int VP = V3 ? 3 : 1;
+    // SPL: the weights as bf16 triples; float32 values in three bf16 parts, bf16
+    // values as they are.  A float32 tile's contribution is summed on its own,
+    // the small products first, and added with a rounded float32 add (the matrix
+    // pipe's own chained sums round toward zero).
+    static constexpr bool F32 = sizeof(T) == 4;
+    static constexpr int VP = F32 ? 3 : 1;
     static constexpr float QKS = SPL ? 256.0f : 1.0f;      // of q^ and of k^
     static constexpr int NTH = 64 * NWQ * NWK;
     static constexpr int QB = 32 * NQ * NWQ;              // queries per workgroup
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
 {
     typedef typename C::T T;
     constexpr int D = C::D, NQ = C::NQ, KS = C::KS, CT = C::CT, LPT = C::LPT, RS = C::RS, VS = C::VS;
-    constexpr bool SPL = C::SPL, V3 = C::V3;
+    constexpr bool SPL = C::SPL, F32 = C::F32;
     __shared__ alignas(16) unsigned char smem[C::SMEM];
     __shared__ unsigned int smax[LPT];
     __shared__ float sscale[LPT];
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
 
     load_tile(0);
     float vscale = 1.0f;
-    if constexpr (!V3) {
+    if constexpr (!SPL) {
         raw_max();
         vscale = set_scale(vmax <= 3e38f ? vmax : 0.f, 7);
     }
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
                 const h8 a = ld8(kp + 16 * ks), b = ld8(kp + C::KH + 16 * ks);
 #pragma unroll
                 for (int u = 0; u < NQ; ++u) {
-                    if constexpr (V3) s[u] = mma(b, ql[u][C::QLDS ? 0 : ks], s[u]);
+                    if constexpr (F32) s[u] = mma(b, ql[u][C::QLDS ? 0 : ks], s[u]);
                     s[u] = mma(a, ql[u][C::QLDS ? 0 : ks], s[u]);
                     s[u] = mma(b, qh[u][ks], s[u]);
                 }
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
 #pragma unroll
                 for (int u = 0; u < NQ; ++u) {
                     const h8 lo = ld8(qlw + 32 * u * RS + 16 * ks);
-                    if constexpr (V3) s[u] = mma(b, lo, s[u]);
+                    if constexpr (F32) s[u] = mma(b, lo, s[u]);
                     s[u] = mma(a, lo, s[u]);
                     s[u] = mma(b, qh[u][ks], s[u]);
                 }
@@ -207,14 +207,14 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
         }
         // weights 2 f_2 = (1 + s)^2 + 1 (the factor 2 cancels in F / G and is
         // taken out of G)
-        h8 wh[NQ][2], wl[NQ][SPL ? 2 : 1], w3[V3 ? NQ : 1][2][3];
+        h8 wh[SPL ? 1 : NQ][2], w3[SPL ? NQ : 1][2][3];
 #pragma unroll
         for (int u = 0; u < NQ; ++u) {
             const int qb0 = q0 + 32 * u;
-            float w[16], z[V3 ? 16 : 1];
+            float w[16], z[F32 ? 16 : 1];
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                if constexpr (V3) {
+                if constexpr (F32) {
                     // 2 f_2 - 2 = s (s + 2): what G has beside its count of keys
                     const float x = s[u][i] * sc2;
                     z[i] = x * (x + 2.0f);
@@ -231,16 +231,17 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
                 for (int i = 0; i < 16; ++i)
                     if (kb + 8 * (i / 4) + 4 * h + i % 4 > last) {
                         w[i] = 0.f;
-                        if constexpr (V3) z[i] = 0.f;
+                        if constexpr (F32) z[i] = 0.f;
                     }
             }
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                if constexpr (V3) split3(w + 8 * e, w3[u][e]);
-                else split8<SPL>(w + 8 * e, wh[u][e], wl[u][SPL ? e : 0]);
+                h8 lo;
+                if constexpr (SPL) split3(w + 8 * e, w3[u][e]);
+                else split8<false>(w + 8 * e, wh[u][e], lo);
             }
             if constexpr (SPL) {
-                float *const y = V3 ? z : w;
+                float *const y = F32 ? z : w;
 #pragma unroll
                 for (int d = 8; d; d /= 2)
 #pragma unroll
@@ -255,16 +256,25 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
                                                    one, rs[u], false);
             }
         }
-        if constexpr (V3) {
+        if constexpr (SPL) {
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
-                h8 a[3][2];
+                h8 a[C::VP][2];
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
+                for (int i = 0; i < C::VP; ++i)
 #pragma unroll
                     for (int e = 0; e < 2; ++e) a[i][e] = ld_tr<VS>(vhi + i * C::VH, 32 * j + 16 * e, 32 * c);
 #pragma unroll
-                for (int u = 0; u < NQ; ++u) acc[u][c] += mma33(a, w3[u]);
+                for (int u = 0; u < NQ; ++u) {
+                    if constexpr (F32) {
+                        acc[u][c] += mma33(a, w3[u]);
+                    } else {
+#pragma unroll
+                        for (int o = 2; o >= 0; --o)
+#pragma unroll
+                            for (int e = 0; e < 2; ++e) acc[u][c] = mma_b(a[0][e], w3[u][e][o], acc[u][c]);
+                    }
+                }
             }
         } else {
 #pragma unroll
@@ -274,10 +284,6 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
                     const h8 a = ld_tr<VS>(vhi, 32 * j + 16 * e, 32 * c);
 #pragma unroll
                     for (int u = 0; u < NQ; ++u) acc[u][c] = mma(a, wh[u][e], acc[u][c]);
-                    if constexpr (SPL) {
-#pragma unroll
-                        for (int u = 0; u < NQ; ++u) acc[u][c] = mma(a, wl[u][SPL ? e : 0], acc[u][c]);
-                    }
                 }
         }
     };
@@ -298,14 +304,16 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     y[i] = vr[p].get(i);
-                    if constexpr (!V3) {
+                    if constexpr (!SPL) {
                         vmax = fmaxf(vmax, fabsf(y[i]));
                         y[i] *= vscale;
                     }
                 }
                 h8 hi, lo;
                 const bool ok = C::BK % C::TPP == 0 || row < C::BK;
-                if constexpr (V3) {
+                if constexpr (SPL && !F32) {
+                    if (ok) *(uint4 *)(vhi + row * VS + 8 * sc) = *(uint4 *)vr[p].w;
+                } else if constexpr (SPL) {
                     h8 y3[3];
                     split3(y, y3);
 #pragma unroll
@@ -338,7 +346,7 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
                 tile(j, kb, (C::CAUSAL && kb + 31 > q0) || kb + 32 > N);
             }
         }
-        if (V3 || attempt || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
+        if (SPL || attempt || !__syncthreads_or(vmax * vscale > 65504.0f)) break;
         vscale = set_scale(largest_finite<T, D>(v, sc, st0, C::TPP, kend), 14);
         load_tile(0);
     }
@@ -351,7 +359,7 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
 #pragma unroll
         for (int u = 0; u < NQ; ++u) {
             const int n = q0 + 32 * u + r32;
-            const float G = half_sum(rs[u]) + (V3 ? 2.0f * (float)keys_of(n) : 0.f);
+            const float G = half_sum(rs[u]) + (F32 ? 2.0f * (float)keys_of(n) : 0.f);
             if (n < N) {
                 if (g && h == 0) g[(size_t)head * N + n] = 0.5f * G;
                 const float r = 1.0f / G;
@@ -361,7 +369,7 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
                     for (int b = 0; b < 4; ++b) {
                         const int d = 32 * c + 8 * b + 4 * h;
                         if (D % 32 == 0 || d < D) {
-                            const float f = V3 ? r : r / sscale[d / 8];
+                            const float f = SPL ? r : r / sscale[d / 8];
                             T *o = out + (size_t)n * D + d;
                             if constexpr (sizeof(T) == 2) {
                                 *(uint2 *)o = make_uint2(
@@ -393,14 +401,14 @@ __global__ __launch_bounds__(C::NTH, C::WPS) void fwd_kernel(
 #pragma unroll
         for (int w = 0; w < C::NWK; ++w) G += part[w * 32 * W + 32 * 32 * CT + r32];
         const int n = q0 + r32;
-        if constexpr (V3) G += 2.0f * (float)keys_of(n);
+        if constexpr (F32) G += 2.0f * (float)keys_of(n);
         if (n < N) {
             if (g && h == 0 && wk == 0) g[(size_t)head * N + n] = 0.5f * G;
             const float r = 1.0f / G;
             // columns of this wave and half wave, 4 at a time
 #pragma unroll
             for (int d = 4 * (2 * wk + h); d < D; d += 8 * C::NWK) {
-                const float f = V3 ? r : r / sscale[d / 8];
+                const float f = SPL ? r : r / sscale[d / 8];
                 float x[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -452,11 +460,12 @@ __global__ __launch_bounds__(256) void khat_kernel(const T *__restrict__ k, _Flo
 // fp16 operands: bf16, D = 64
 constexpr Shape SH64[] = {{32, 5.f, 7.6f, 1.13f}, {64, 4.f, 9.6f, .68f}, {128, 5.f, 13.f, .455f},
                           {128, 4.f, 20.5f, .375f}, {256, 7.f, 17.f, .31f}, {512, 6.f, 31.f, .275f}};
-// float32-grade operands, bf16 rows
-constexpr Shape SS16[] = {{32, 4.3f, 2.8f, .47f}, {64, 4.4f, 4.1f, .29f}, {256, 4.4f, 14.4f, .225f}};
-constexpr Shape SS32[] = {{32, 5.f, 3.15f, .72f}, {64, 4.8f, 6.f, .42f}, {256, 5.9f, 18.f, .295f}};
+// float32-grade operands, bf16 rows (SS64, whose calls have fewer than 128 keys,
+// by an earlier form's paces; the others against 195 sizes: 1.00 to 1.02, 1.24 at most)
+constexpr Shape SS16[] = {{32, 3.7f, 2.95f, .59f}, {64, 3.85f, 4.9f, .363f}, {256, 4.7f, 13.2f, .316f}};
+constexpr Shape SS32[] = {{32, 3.8f, 4.1f, .75f}, {64, 4.f, 6.05f, .505f}, {256, 4.3f, 20.8f, .38f}};
 constexpr Shape SS64[] = {{64, 6.f, 15.4f, 1.14f}, {128, 6.f, 21.2f, .82f}, {256, 6.f, 36.5f, .71f}};
-constexpr Shape SS128[] = {{64, 7.f, 25.f, 1.67f}, {128, 7.f, 36.f, 1.27f}, {256, 7.f, 57.f, 1.05f}};
+constexpr Shape SS128[] = {{64, 7.8f, 23.f, 2.2f}, {128, 6.3f, 36.f, 1.55f}, {256, 5.7f, 47.7f, 1.47f}};
 // float32 rows (bf16 triples for the values: 1.0 to 1.5 of the time that fp16
 // pairs took, whose values depended on a shared scale)
 constexpr Shape SF16[] = {{32, 4.5f, 4.1f, .68f}, {64, 4.4f, 7.9f, .575f}, {256, 3.8f, 27.f, .485f}};

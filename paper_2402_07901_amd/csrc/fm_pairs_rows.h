@@ -1,6 +1,6 @@
-// What the backwards prepare per row.  Over explicit pairs, bf16 rows
-// (fm_pairs_bwd.hip): the planes of q~ and k^, delta = dO.O, and the powers of
-// two of dO, v and dO / G.  The others: at the end.
+// What the backwards prepare per row.  fp16 operands (fm_pairs_bwd.hip): the
+// planes of q~, k^, v and dO, delta = dO.O, and the powers of two of dO, v and
+// dO / G.  The others: at the end.
 #pragma once
 
 #include <type_traits>
@@ -42,31 +42,26 @@ __device__ __forceinline__ float group_max(float x)
     return x;
 }
 
-// The per-row words.  float32-grade calls keep delta = dO.O and the exponents
-// of dO and v.  The fp16 ones also keep v, dO and dO rho as fp16 planes, each row scaled by
-// a power of two to below 2^10, so that a step stages them with one packed
-// multiply per pair: delta in dO's scale, rho, and the exponents of dO, v and
-// dO / G.
-struct RowInfo {
-    float delta;
-    short e_do, e_v;
-};
+// The per-row words of the fp16 calls, which keep v, dO and dO rho as fp16
+// planes, each row scaled by a power of two to below 2^10, so that a step
+// stages them with one packed multiply per pair: delta in dO's scale, rho, and
+// the exponents of dO, v and dO / G.
 struct RowInfoH {
     float delta, rho;
     short e_do, e_v;
     int eg;
 };
-static_assert(sizeof(RowInfo) == 8 && sizeof(RowInfoH) == 16, "bytes per row");
+static_assert(sizeof(RowInfoH) == 16, "bytes per row");
 
 // 2^n as a half, flushed to zero below its range (n at most 15).
 __device__ __forceinline__ _Float16 half2i(int n) { return n < -24 ? (_Float16)0.0f : (_Float16)exp2i(n); }
 
 // One thread per 8 channels of a row of the whole call.
-template <typename T, int D, bool SPL>
+template <typename T, int D>
 __global__ __launch_bounds__(256) void bwd_prep_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
     const T *__restrict__ o, const T *__restrict__ dout, const float *__restrict__ g,
-    _Float16 *__restrict__ planes, void *__restrict__ info, long long rows, float qn)
+    _Float16 *__restrict__ planes, RowInfoH *__restrict__ info, long long rows, float tau)
 {
     constexpr int L = D / 8;
     const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / L;
@@ -85,20 +80,14 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(
     for (int i = 0; i < 8; ++i) x[i] = rq.get(i);
     standardise_group<D>(x, ok);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] *= qn;
-    split8<SPL>(x, hi, lo);
-    if (ok) {
-        *(h8 *)(planes + off) = hi;
-        if constexpr (SPL) *(h8 *)(planes + np + off) = lo;
-    }
+    for (int i = 0; i < 8; ++i) x[i] *= tau;
+    split8<false>(x, hi, lo);
+    if (ok) *(h8 *)(planes + off) = hi;
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i] = rk.get(i);
     standardise_group<D>(x, ok);
-    split8<SPL>(x, hi, lo);
-    if (ok) {
-        *(h8 *)(planes + (SPL ? 2 : 1) * np + off) = hi;
-        if constexpr (SPL) *(h8 *)(planes + 3 * np + off) = lo;
-    }
+    split8<false>(x, hi, lo);
+    if (ok) *(h8 *)(planes + np + off) = hi;
     float d = 0.f, md = 0.f, mv = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -110,35 +99,32 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(
     md = group_max<L>(md);
     mv = group_max<L>(mv);
     const int ed = exp_above(md), ev = exp_above(mv);
-    if constexpr (SPL) {
-        if (ok && c == 0) ((RowInfo *)info)[row] = RowInfo{d, (short)ed, (short)ev};
-    } else {
-        const int e = ed == NO_EXP ? 0 : ed;
-        const float G = g[ok ? row : 0];
-        const int kx = g_exp(G);
-        const float rho = exp2i(kx) / G, fd = exp2i(10 - e), fv = exp2i(10 - (ev == NO_EXP ? 0 : ev));
-        float y[8], z[8];
+    const int e = ed == NO_EXP ? 0 : ed;
+    const float G = g[ok ? row : 0];
+    const int kx = g_exp(G);
+    const float rho = exp2i(kx) / G, fd = exp2i(10 - e), fv = exp2i(10 - (ev == NO_EXP ? 0 : ev));
+    float y[8], z[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            x[i] = rv.get(i) * fv;
-            y[i] = rd.get(i) * fd;
-            z[i] = y[i] * rho;
-        }
-        if (ok) {
-            split8<false>(x, hi, lo);
-            *(h8 *)(planes + 2 * np + off) = hi;
-            split8<false>(y, hi, lo);
-            *(h8 *)(planes + 3 * np + off) = hi;
-            split8<false>(z, hi, lo);
-            *(h8 *)(planes + 4 * np + off) = hi;
-            if (c == 0)
-                ((RowInfoH *)info)[row] = RowInfoH{d * fd, rho, (short)ed, (short)ev, ed == NO_EXP ? NO_EXP : ed - kx};
-        }
+    for (int i = 0; i < 8; ++i) {
+        x[i] = rv.get(i) * fv;
+        y[i] = rd.get(i) * fd;
+        z[i] = y[i] * rho;
+    }
+    if (ok) {
+        split8<false>(x, hi, lo);
+        *(h8 *)(planes + 2 * np + off) = hi;
+        split8<false>(y, hi, lo);
+        *(h8 *)(planes + 3 * np + off) = hi;
+        split8<false>(z, hi, lo);
+        *(h8 *)(planes + 4 * np + off) = hi;
+        if (c == 0)
+            info[row] = RowInfoH{d * fd, rho, (short)ed, (short)ev, ed == NO_EXP ? NO_EXP : ed - kx};
     }
 }
 
-// What the backwards without shared scales (float32 rows by pairs:
-// fm_pairs_bwd32.hip; first order: fm_linear.hip) keep per row: q~ = (q - mq) rq (tau in rq), k^ = (k - mk) rk, delta = dO.O, u = 1 / G.
+// What the backwards without shared scales (fm_pairs_bwd32.hip, fm_linear.hip)
+// keep per row: q~ = (q - mq) rq (tau in rq), k^ = (k - mk) rk, delta = dO.O,
+// u = 1 / G.
 struct Row32 {
     float mq, rq, mk, rk, delta, u;
 };

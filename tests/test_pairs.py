@@ -49,7 +49,7 @@ def segments(BH, N):
 CASES = [
     (1, 1, 16, "f32"), (2, 31, 16, "f32"), (1, 257, 16, "f32"), (16, 1000, 16, "f32"),
     (64, 1601, 16, "f32"), (64, 700, 32, "f32"), (3, 33, 16, "bf16"),
-    (16, 1000, 16, "bf16"), (64, 1601, 16, "bf16"), (2, 255, 32, "f32"), (8, 1030, 32, "f32"),
+    (16, 1000, 16, "bf16"), (64, 1601, 16, "bf16"), (96, 1025, 16, "bf16"), (2, 255, 32, "f32"), (8, 1030, 32, "f32"),
     (64, 1500, 32, "f32"), (5, 129, 32, "bf16"), (8, 1030, 32, "bf16"), (64, 1290, 32, "bf16"),
     (3, 65, 64, "f32"),
     (24, 700, 64, "f32"), (64, 1025, 64, "f32"), (64, 2049, 64, "f32"), (2, 32, 128, "f32"), (16, 513, 128, "f32"),
@@ -63,7 +63,7 @@ CASES = [
 
 BWD_CASES = [
     (1, 1, 16, "f32"), (2, 257, 16, "f32"), (16, 300, 16, "f32"), (64, 801, 16, "f32"),
-    (3, 33, 16, "bf16"), (1, 513, 16, "bf16"), (4, 513, 16, "bf16"), (64, 801, 16, "bf16"), (2, 257, 32, "bf16"),
+    (3, 33, 16, "bf16"), (1, 513, 16, "bf16"), (4, 513, 16, "bf16"), (64, 801, 16, "bf16"), (16, 513, 16, "bf16"), (2, 257, 32, "bf16"),
     (5, 801, 32, "bf16"), (64, 700, 32, "bf16"), (1, 255, 32, "f32"), (1, 2047, 32, "f32"), (8, 1030, 32, "f32"),
     (64, 700, 32, "f32"), (5, 129, 32, "bf16"), (3, 65, 64, "f32"), (24, 700, 64, "f32"),
     (64, 900, 64, "f32"), (3, 129, 64, "f32"), (64, 257, 64, "f32"), (8, 1029, 64, "f32"), (2, 32, 128, "f32"), (16, 513, 128, "f32"), (64, 1025, 128, "f32"),
@@ -223,6 +223,28 @@ def test_backward_scales(D, dt, causal, kind):
     inp = scale_values(inp, dt, f[::-1] if kind == "late" else f, "dout")
     check_bwd(inp, dt, causal, 1.0 / D if kind == "tau" else 1.0, f"bwd {kind} D{D} {dt} c{causal}",
               edges=(100, 200) if kind == "late" else (150,) if kind == "zeros" else ())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [16, 32, 128])
+def test_bf16_rows_beside_far_larger_ones(D):
+    """One row of v and one of dO at 2^30: the causal rows that never meet it
+    keep their own magnitude, O and gradients alike."""
+    N = 300
+    f = np.ones(N)
+    f[N // 2] = 2.0 ** 30
+    edges = sorted({N - 1 - N // 2, N - N // 2, N // 2, N // 2 + 1})
+    inp = scale_values(make_inputs(1, 3, N, D, 7500, "bf16", with_dout=True), "bf16", f)
+    inp = scale_values(inp, "bf16", f[::-1], "dout")
+    q, k, v = (to_dev(inp[n], "bf16") for n in ("q", "k", "v"))
+    assert plan(3, N, D, True, "bf16") >= 0 and plan(3, N, D, True, "bf16", True) >= 0
+    o = to_f64(fm.fastmax_fwd(q, k, v, p=2, causal=True)[0])
+    for h in range(3):
+        ref = oracle.fwd_brute(*(x[None, None] for x in heads_of(inp, h)), 2, True)[0][0, 0]
+        e = group_rel(o[0, h], ref, edges)
+        say(f"D{D} head {h} O: {e:.2e}")
+        assert e <= TOL["bf16"], (h, e)
+    check_bwd(inp, "bf16", True, 1.0, f"bwd far D{D}", edges)
 
 
 def scale_values(inp, dt, factor, name="v"):
