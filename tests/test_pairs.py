@@ -1,4 +1,4 @@
-"""The pair kernels (fm_pairs_fwd.hip, fm_pairs_bwd.hip): explicit 32 x 32
+"""The pair kernels (fm_pairs_fwd.hip, fm_pairs_bwd*.hip): explicit 32 x 32
 weight tiles for short sequences.
 
 Every workgroup shape of the plan, at sizes that straddle its tiles (32 keys,
